@@ -8,12 +8,16 @@
 // layout is the operand layout: no unpacking, no widening, the block scales are applied inside the MFMA (measured on
 // the device: the result equals the fp64 sum for random operands whose partial sums fit fp32).
 //
-// Workgroup and data movement as in the INT4 product (fq_gemm.hip): 4 waves, C tile 128 tokens x 128 output channels,
-// 64 x 64 per wave with the weights as the MFMA's first operand; K advances by 256 codes per iteration through
-// double-buffered LDS tiles filled by global-to-LDS loads (unpadded rows, 16-byte chunks swizzled), one barrier per
-// iteration.  The exponents (8 bytes per row and iteration, stored in tile order) travel the same way.
-// (A ring of four 128-code stages with three in flight measured slower: 64-byte row pieces multiply the number of
-// L2 requests.)
+// Tiled kernel (many tokens): every operand byte goes from global memory straight into LDS (global-to-LDS loads, unpadded
+// 128-byte rows, 16-byte chunks swizzled), NST iterations of 256 codes deep, one barrier per iteration, persistent
+// workgroups whose loads run on from one output tile into the next.  What bounds it, measured at 16384 x 8192 x 8192 (zero
+// codes in brackets): MFMAs and barriers alone 381 us (269: the chip keeps 1.5 GHz under FP4 MFMAs on random operands,
+// 22 ns per 32x32x64 instead of 13.5), with the output tiles 396 (289), with the operand reads from LDS 421 (306), with
+// the loads 504 (408).  Beside the power limit it is the operand traffic, so the tile per wave is as large as the register
+// file allows: 128 x 128 (4 waves, one per SIMD, 256 accumulators) moves half as many bytes per product term through LDS
+// and L2 as the 64 x 64 wave tiles of 128 x 128 workgroups.  Against the two-stage kernel that was here (128 x 128, exponents
+// one iteration ahead, MFMAs bunched behind the barrier; same box): 16384 x 8192 x 8192 678 -> 505 us, 2048 x 4096 x
+// 11008 56.8 -> 49.6, 4096 x 4096 x 4096 45.9 -> 37.0, 777 x 5120 x 5120 25.4 -> 20.5.
 #include "fq_internal.h"
 
 namespace fq {
@@ -25,11 +29,6 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int XT = 128;               // tile edge, tokens and output channels
 constexpr int XKB = 128;              // packed bytes of K per row and iteration (256 codes, 8 blocks)
-constexpr int X_NT = 256;
-constexpr int X_TILE_BYTES = XT * XKB;
-constexpr int X_EXP_BYTES = 2 * XT * 8;         // exponents of both tiles for one iteration: 8 bytes per row
-constexpr int X_LDS_BYTES = 4 * X_TILE_BYTES + 2 * X_EXP_BYTES;   // A and B, two buffers each (the output tile reuses them), + exponents
-
 struct MxGemmDev {
     const uint8_t* xc;
     const uint8_t* xe;
@@ -41,175 +40,280 @@ struct MxGemmDev {
     int m, n;
 };
 
-__global__ __launch_bounds__(X_NT) __attribute__((amdgpu_waves_per_eu(2))) void mxfp4_gemm_kernel(MxGemmDev p) {
+// TI x TJ: MFMA tiles per wave (tokens x channels), WM x WN: waves, NST: LDS stages, LA: K steps that an operand is read
+// from LDS ahead of its MFMAs.
+template <int TI, int TJ, int WM, int WN, int NST>
+struct MxTile {
+    static constexpr int NW = WM * WN;
+    static constexpr int TOK = 32 * TI * WM, CH = 32 * TJ * WN, ROWS = TOK + CH;
+    static constexpr int CODES = ROWS * XKB;                        // code tiles of one K iteration, then its exponents
+    static constexpr int STAGE = CODES + 8 * ROWS;
+    static constexpr int OPITCH = 64 * TJ + 16;                     // output staging: 32 tokens of a wave's channels
+    static constexpr int LDS = NST * STAGE;
+    static_assert(NW * 32 * OPITCH <= STAGE && LDS <= 160 * 1024 && NST >= 2, "LDS budget");
+};
+
+template <int TI, int TJ, int WM, int WN, int NST, int LA>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI * TJ > 4 ? 1 : 2, TI * TJ > 4 ? 1 : 2))) void mxfp4_gemm_kernel(MxGemmDev p) {
+    using L = MxTile<TI, TJ, WM, WN, NST>;
+    constexpr int NW = L::NW, TOK = L::TOK, CH = L::CH, STAGE = L::STAGE, A_TILE = TOK * XKB, NOP = TI + TJ;
+    constexpr int NLA = TOK / 8 / NW, NLB = CH / 8 / NW, NL = 1 + NLA + NLB;   // load instructions per wave and iteration
+    constexpr int NPC = L::ROWS / 128;                              // 1 KB pieces of exponents per iteration
+    constexpr int NKP = XKB / 32;                                   // K steps (64 codes) per iteration
+    static_assert(NKP == 4 && (LA == 1 || LA == 2), "exponent bytes and the operand ring below");
+    constexpr int KB = NKP - LA;                                    // the steps before the iteration's barrier
+    constexpr int RING = LA == 1 ? 2 : 4;
+    constexpr int NQ = TI * TJ, RPS = NQ > 4 ? 2 : 1;               // MFMAs per step; LDS reads behind each of the first ones
+    constexpr int LSTEPS = NST == 2 ? 2 : NKP;                      // steps over which an iteration's loads are spread
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x;
     const int l = tid & 63, c = l & 31, h = l >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = w & 1, wn = w >> 1;
-    const int64_t t0 = (int64_t)blockIdx.x * XT;
-    const int o0 = blockIdx.y * XT;
+    const int wm = w % WM, wn = w / WM;
     const int64_t kbytes = p.n / 2;
     const int nk = p.n / (2 * XKB);
+    const int64_t tile_e = (int64_t)nk * 1024;                      // bytes of exponents per tile of 128 rows
+    const int ntx = (int)((p.T + TOK - 1) / TOK), nty = (p.m + CH - 1) / CH;
+    const int64_t ntiles = (int64_t)ntx * nty;
 
-    // code tiles: one instruction fills 8 rows of 128 bytes; wave w owns rows 32 w .. 32 w + 31 of both tiles.  LDS slot
-    // j of row r holds the row's chunk j ^ ((r >> 1) & 7).  Rows past the end re-read the last row.
-    constexpr int NLD = 4;
-    const unsigned char* asrc[NLD];
-    const unsigned char* bsrc[NLD];
+    // Tiles of this workgroup.  Workgroup b runs on XCD b % 8: every XCD takes a contiguous eighth of a tile order that
+    // goes through panels of PW token tiles, so that the tiles in flight on an XCD share rows of both operands in its L2
+    // (32 workgroups that stream 256 + 256 rows each: 100 KB per us and CU arrive in LDS with 4 x 8 tiles per XCD, 55 with
+    // a token tile per XCD and all the channels).
+    constexpr int PW = 4;
+    const int64_t per_xcd = (ntiles + 7) / 8;
+    const int xcd = blockIdx.x & 7;
+    const int64_t first = xcd * per_xcd, left = ntiles - first;
+    const int64_t mine = left < per_xcd ? left : per_xcd;           // tiles of this XCD (<= 0: none)
+    const int64_t qstep = gridDim.x >> 3;
+    int64_t q = blockIdx.x >> 3;
+    if (q >= mine) return;
+    struct Pos { int64_t t0; int o0; };
+    auto tile_pos = [&](int64_t qq) -> Pos {
+        const int pos = (int)(first + qq), panel = pos / (PW * nty), r = pos - panel * (PW * nty);
+        const int width = ntx - panel * PW < PW ? ntx - panel * PW : PW;
+        const int ty = r / width;
+        return Pos{(int64_t)(panel * PW + r - ty * width) * TOK, ty * CH};
+    };
+
+    // ---- loads: one instruction fills 8 rows of 128 bytes of codes; LDS slot j of row r holds the row's chunk
+    // j ^ ((r >> 1) & 7).  Rows past the end re-read the last row.  The exponents (8 bytes per row and iteration, in tile
+    // order: per 128-row tile and iteration 1 KB in one piece) take one instruction per 128 rows; wave w brings piece w,
+    // waves past the last piece repeat it, so that every wave counts the same number of loads.
+    const unsigned char *abase, *bbase, *ebase;
+    uint32_t aoff[NLA], boff[NLB];
+    const int pc = w < NPC ? w : NPC - 1;
+    auto set_source = [&](const Pos& t) {
+        abase = p.xc + t.t0 * kbytes;
+        bbase = p.wc + (int64_t)t.o0 * kbytes;
+        const int arows = (int)(p.T - t.t0 < TOK ? p.T - t.t0 : TOK), brows = p.m - t.o0 < CH ? p.m - t.o0 : CH;
 #pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-        const int row = 8 * (4 * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-        int64_t tr = t0 + row;
-        if (tr >= p.T) tr = p.T - 1;
-        int orow = o0 + row;
-        if (orow >= p.m) orow = p.m - 1;
-        asrc[k] = p.xc + tr * kbytes + 16 * ch;
-        bsrc[k] = p.wc + (int64_t)orow * kbytes + 16 * ch;
-    }
+        for (int k = 0; k < NLA; ++k) {
+            const int row = 8 * (NLA * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
+            aoff[k] = (uint32_t)(row < arows ? row : arows - 1) * (uint32_t)kbytes + 16 * ch;
+        }
+#pragma unroll
+        for (int k = 0; k < NLB; ++k) {
+            const int row = 8 * (NLB * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
+            boff[k] = (uint32_t)(row < brows ? row : brows - 1) * (uint32_t)kbytes + 16 * ch;
+        }
+        const bool tok = pc < TOK / 128;
+        const int64_t tile = tok ? (t.t0 >> 7) + pc : (int64_t)(t.o0 >> 7) + pc - TOK / 128;
+        const int64_t last = tok ? (p.T - 1) >> 7 : (int64_t)(p.m - 1) >> 7;   // tiles past the end do not exist
+        ebase = (tok ? p.xe : p.we) + (tile < last ? tile : last) * tile_e + 16 * l;
+    };
     typedef const __attribute__((address_space(1))) void* gptr;
     typedef __attribute__((address_space(3))) void* lptr;
-    auto issue = [&](int it, int buf) {   // past the last tile the last one is re-read (nobody uses it)
+    // loads k0 .. k1 - 1 of the NL that bring iteration `it` (past the last one it is re-read; nobody uses it)
+    auto issue = [&](int it, int stage, int k0, int k1) {
         const int itc = it < nk ? it : nk - 1;
-        unsigned char* A = smem + buf * X_TILE_BYTES + w * (32 * XKB);
-        unsigned char* B = smem + (2 + buf) * X_TILE_BYTES + w * (32 * XKB);
 #pragma unroll
-        for (int k = 0; k < NLD; ++k) {
-            __builtin_amdgcn_global_load_lds((gptr)(asrc[k] + (int64_t)itc * XKB), (lptr)(A + k * 8 * XKB), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((gptr)(bsrc[k] + (int64_t)itc * XKB), (lptr)(B + k * 8 * XKB), 16, 0, 0);
+        for (int k = k0; k < k1; ++k) {
+            if (k == 0) __builtin_amdgcn_global_load_lds((gptr)(ebase + (int64_t)itc * 1024), (lptr)(smem + stage + L::CODES + pc * 1024), 16, 0, 0);
+            else if (k <= NLA) __builtin_amdgcn_global_load_lds((gptr)(abase + (int64_t)itc * XKB + aoff[k - 1]), (lptr)(smem + stage + (NLA * w + k - 1) * 8 * XKB), 16, 0, 0);
+            else __builtin_amdgcn_global_load_lds((gptr)(bbase + (int64_t)itc * XKB + boff[k - 1 - NLA]), (lptr)(smem + stage + A_TILE + (NLB * w + k - 1 - NLA) * 8 * XKB), 16, 0, 0);
         }
     };
-    auto tile_ready = [&]() {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-    };
 
-    // Exponents: 8 bytes per row and iteration, stored in tile order (rows in tiles of 128; per tile and iteration the
-    // 128 rows' 8 bytes are contiguous), so one iteration's exponents of a tile are 1 KB in one piece: one global-to-LDS
-    // instruction per operand, issued with the code tiles (wave 0: tokens, wave 1: channels).  Measured on the way: with
-    // row-major exponents fetched into registers (8 bytes per lane, row and iteration: four times as many cache lines
-    // touched per iteration as the code tiles) the exponents took 45 % of the kernel's time; fetched through LDS 32
-    // bytes per row at a time, still 25 %.
-    const int64_t tile_e = (int64_t)nk * 1024;   // bytes of exponents per tile of 128 rows
-    const unsigned char* xsrc = (w == 0 ? p.xe + (int64_t)blockIdx.x * tile_e : p.we + (int64_t)blockIdx.y * tile_e) + 16 * l;
-    unsigned char* ebuf = smem + 4 * X_TILE_BYTES;
-    auto issue_exps = [&](int it, int buf) {   // past the last iteration the last one is re-read (nobody uses it)
-        const int itc = it < nk ? it : nk - 1;
-        if (w < 2) __builtin_amdgcn_global_load_lds((gptr)(xsrc + (int64_t)itc * 1024), (lptr)(ebuf + buf * X_EXP_BYTES + w * 1024), 16, 0, 0);
+    // ---- operands.  x < TI: tokens 32 (TI wm + x) + c; else channels 32 (TJ wn + x - TI) + c
+    const int hs = h ^ ((c >> 1) & 7);   // chunk 2 kp + h of row 32 x + c sits in slot (2 kp) ^ hs
+    const int abyte = (32 * TI * wm + c) * XKB, bbyte = A_TILE + (32 * TJ * wn + c) * XKB;
+    auto lds_chunk = [&](int stage, int kp, int x) -> u32x4 {
+        const int a = stage + (x < TI ? abyte + 32 * x * XKB : bbyte + 32 * (x - TI) * XKB) + 16 * ((2 * kp) ^ hs);
+        return *reinterpret_cast<const u32x4*>(smem + a);
     };
-    // this lane's four operand rows (x = 0, 1: tokens 64 wm + 32 x + c; x = 2, 3: channels 64 wn + 32 (x - 2) + c).  K
-    // step kp (64 codes) uses block 2 kp + h; the MFMA picks a byte of a register by an immediate, the same for every
+    // K step kp (64 codes) uses block 2 kp + h; the MFMA picks a byte of a register by an immediate, the same for every
     // lane, so the half-wave h = 1 shifts its bytes down by one: byte 2 (kp & 1) of dword kp / 2 then is the block of
     // this lane.
-    const int eoff[4] = {(64 * wm + c) * 8, (64 * wm + 32 + c) * 8, (XT + 64 * wn + c) * 8, (XT + 64 * wn + 32 + c) * 8};
-    auto lds_exps = [&](int buf, u32x2 (&e)[4]) {
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const u32x2 v = *reinterpret_cast<const u32x2*>(ebuf + buf * X_EXP_BYTES + eoff[x]);
-            e[x] = u32x2{v[0] >> (8 * h), v[1] >> (8 * h)};
-        }
+    auto lds_exps = [&](int stage, int x) -> u32x2 {
+        const int row = (x < TI ? 32 * (TI * wm + x) : TOK + 32 * (TJ * wn + x - TI)) + c;
+        return *reinterpret_cast<const u32x2*>(smem + stage + L::CODES + 8 * row);
     };
-
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    const int aoff = (64 * wm + c) * XKB;
-    const int boff = (64 * wn + c) * XKB;
-    const int hs = h ^ ((c >> 1) & 7);   // chunk 2 kp + h of row 32 x + c sits in slot (2 kp) ^ hs
-    constexpr int NKP = XKB / 32;        // K steps (64 codes) per tile
-    static_assert(NKP == 4, "exponent bytes and the barrier position below");
-    auto lds_chunk = [&](int buf, int kp, int x) -> u32x4 {
-        const unsigned char* base = smem + ((x >> 1) * 2 + buf) * X_TILE_BYTES + ((x >> 1) ? boff : aoff);
-        return *reinterpret_cast<const u32x4*>(base + 32 * (x & 1) * XKB + 16 * ((2 * kp) ^ hs));
-    };
-    auto mfma = [&](const u32x4& wv, const u32x4& xv, f32x16& cacc, int kp, const u32x2& ew, const u32x2& ex) {
+    f32x16 acc[TI][TJ];
+    u32x4 P[RING][NOP];
+    u32x2 ec[NOP], en[NOP];              // exponents of the current iteration, and of the next one as they are stored
+    auto mfma = [&](int i, int j, int kp) {
+        const u32x4 &wv = P[kp % RING][TI + j], &xv = P[kp % RING][i];
         const i32x8 a = {(int)wv[0], (int)wv[1], (int)wv[2], (int)wv[3], 0, 0, 0, 0};
         const i32x8 b = {(int)xv[0], (int)xv[1], (int)xv[2], (int)xv[3], 0, 0, 0, 0};
         // formats: 4 = FP4 (E2M1) for both operands; byte 2 (kp & 1) of the exponent registers
-        if (kp & 1) cacc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, cacc, 4, 4, 2, (int)ew[kp >> 1], 2, (int)ex[kp >> 1]);
-        else cacc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, cacc, 4, 4, 0, (int)ew[kp >> 1], 0, (int)ex[kp >> 1]);
+        if (kp & 1) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i][j], 4, 4, 2, (int)ec[TI + j][kp >> 1], 2, (int)ec[i][kp >> 1]);
+        else acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i][j], 4, 4, 0, (int)ec[TI + j][kp >> 1], 0, (int)ec[i][kp >> 1]);
     };
-
-    // Two-stage pipeline over K steps g = it * NKP + kp: while the MFMAs of step g run on P[g & 1], step g + 1 is read
-    // from LDS into P[(g + 1) & 1].  Step NKP - 1 reads the first step of the next tile, so that tile is published
-    // (loads waited for, barrier) after step NKP - 2; the buffer of the current tile is not read after that and
-    // takes tile it + 2 behind the same barrier.
-    u32x4 P[2][4];
-    u32x2 E[2][4];   // exponents of the current and of the next tile
-    issue(0, 0);
-    issue_exps(0, 0);
-    tile_ready();
-    issue(1, 1);
-    issue_exps(1, 1);
+    // K step kp: its MFMAs, between them the operands of the step LA further on (of `stage_ahead`) and a share of the
+    // loads of iteration `lit` into `stage_load`.  Steps KB .. NKP - 1 of an iteration, then 0 .. KB - 1 of the next one, lie
+    // between two barriers: s is the step's place in that sequence, which the loads are spread over.
+    auto step = [&](int kp, int stage_ahead, int lit, int stage_load, int s, int s0, int nsteps) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x) P[0][x] = lds_chunk(0, 0, x);
-    lds_exps(0, E[0]);
-    auto iteration = [&](int it, int buf, u32x2 (&ec)[4], u32x2 (&en)[4]) {
+        for (int m = 0; m < NQ; ++m) {
+            mfma(m / TJ, m % TJ, kp);
 #pragma unroll
-        for (int kp = 0; kp < NKP; ++kp) {
-            const int cur = kp & 1, nxt = cur ^ 1;
-            const int fkp = (kp + 1) % NKP;
-            const int fbuf = (kp + 1 < NKP) ? buf : buf ^ 1;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = q >> 1, j = q & 1;
-                mfma(P[cur][2 + j], P[cur][i], acc[i][j], kp, ec[2 + j], ec[i]);
-                P[nxt][q] = lds_chunk(fbuf, fkp, q);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (kp == NKP - 2) {
-                tile_ready();          // tile it + 1 and its exponents are in LDS; buffer `buf` is free
-                lds_exps(buf ^ 1, en);
-                issue(it + 2, buf);
-                issue_exps(it + 2, buf);
-            }
+            for (int x = m * RPS; x < (m + 1) * RPS && x < NOP; ++x) P[(kp + LA) % RING][x] = lds_chunk(stage_ahead, (kp + LA) % NKP, x);
+            if (s >= s0 && s < s0 + nsteps) issue(lit, stage_load, ((s - s0) * NQ + m) * NL / (nsteps * NQ), ((s - s0) * NQ + m + 1) * NL / (nsteps * NQ));
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
-    for (int it = 0; it < nk; it += 2) {
-        iteration(it, 0, E[0], E[1]);
-        if (it + 1 < nk) iteration(it + 1, 1, E[1], E[0]);
-    }
-    tile_ready();   // no load is still writing, every wave is done with the K tiles: the epilogue reuses their space
+    // the next iteration has arrived (this wave's part, then everybody's) and nobody reads the current one's stage any more
+    auto arrive = [&](int pending) {
+        if (pending) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NST - 2) * NL) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto read_exps = [&](int stage) {
+#pragma unroll
+        for (int x = 0; x < NOP; ++x) en[x] = lds_exps(stage, x);
+    };
+    auto next_exps = [&]() {
+#pragma unroll
+        for (int x = 0; x < NOP; ++x) ec[x] = u32x2{en[x][0] >> (8 * h), en[x][1] >> (8 * h)};
+    };
 
-    // epilogue: in acc[i][j] a lane holds, for token 64 wm + 32 i + c, the output channels 64 wn + 32 j + 8 (r / 4) + 4 h
-    // + r % 4.  Rounded to fp16 and staged in LDS as a [128 tokens][128 channels] tile, which leaves in 16-byte pieces.
-    typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-    constexpr int OPITCH = 2 * XT + 16;
-    unsigned char* otile = smem;
+    Pos cur = tile_pos(q);
+    set_source(cur);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int s = 0; s + 1 < NST; ++s) issue(s, s * STAGE, 0, NL);
+    arrive(1);
+    int st = 0, stl = (NST - 1) * STAGE;     // stage of the current iteration, and the one to be loaded next
+    auto advance = [&](int stage) { return stage + STAGE == NST * STAGE ? 0 : stage + STAGE; };
+    read_exps(0);
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+    for (int d = 0; d < LA; ++d)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int oc = 64 * wn + 32 * j + 8 * g + 4 * h;
-                const half4 v = {(_Float16)acc[i][j][4 * g], (_Float16)acc[i][j][4 * g + 1], (_Float16)acc[i][j][4 * g + 2], (_Float16)acc[i][j][4 * g + 3]};
-                *reinterpret_cast<half4*>(otile + (64 * wm + 32 * i + c) * OPITCH + 2 * oc) = v;
+        for (int x = 0; x < NOP; ++x) P[d][x] = lds_chunk(0, d, x);
+
+    // Loads run NST - 1 iterations ahead of the steps 0 .. KB - 1 and go on into the next tile: the last NST - 1 iterations
+    // of a tile load the first ones of the next.
+    const bool flow = nk >= NST;
+    while (true) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        next_exps();
+        // steps 0 .. KB - 1 of iteration 0; loads of iteration NST - 1
+#pragma unroll
+        for (int kp = 0; kp < KB; ++kp) step(kp, st, NST - 1, stl, kp, 0, LSTEPS < KB ? LSTEPS : KB);
+        arrive(1);
+        int lit = NST;                       // iteration to be loaded next
+        auto body = [&]() {
+            const int stn = advance(st);
+            read_exps(stn);
+            stl = advance(stl);
+#pragma unroll
+            for (int kp = KB; kp < NKP; ++kp) step(kp, stn, lit, stl, kp - KB, 0, LSTEPS);
+            next_exps();
+#pragma unroll
+            for (int kp = 0; kp < KB; ++kp) step(kp, stn, lit, stl, kp + LA, 0, LSTEPS);
+            arrive(1);
+            st = stn;
+            ++lit;
+        };
+        int it = 0;
+        for (; it < nk - 1 && lit < nk; ++it) body();
+        const int64_t qn = q + qstep;
+        const bool more = qn < mine;
+        Pos nxt = cur;
+        if (more) nxt = tile_pos(qn);
+        if (more && flow) { set_source(nxt); lit = 0; }
+        for (; it < nk - 1; ++it) body();
+        // the last steps of the tile: nothing is loaded, the current stage takes the output tile
+        {
+            const int stn = advance(st);
+            read_exps(stn);
+#pragma unroll
+            for (int kp = KB; kp < NKP; ++kp) step(kp, stn, 0, 0, 0, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+
+        // epilogue: in acc[i][j] a lane holds, for token 32 (TI wm + i) + c, the output channels 32 (TJ wn + j) + 8 (r / 4) +
+        // 4 h + r % 4.  Rounded to fp16 and turned, 32 tokens at a time, through a part of LDS that belongs to the wave
+        // alone (no barrier), from where they leave in 16-byte pieces of whole rows.
+        typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+        constexpr int OPITCH = L::OPITCH, CPR = 4 * TJ;              // 16-byte pieces per token
+        unsigned char* ot = smem + st + w * (32 * OPITCH);
+        const uintptr_t pitch_bits = reinterpret_cast<uintptr_t>(p.out) | (uintptr_t)(2 * p.out_stride);
+        const bool wide = (pitch_bits & 15) == 0, pairs = (pitch_bits & 3) == 0;   // whole pieces, dwords, or halves
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const half4 v = {(_Float16)acc[i][j][4 * g], (_Float16)acc[i][j][4 * g + 1], (_Float16)acc[i][j][4 * g + 2], (_Float16)acc[i][j][4 * g + 3]};
+                    *reinterpret_cast<half4*>(ot + c * OPITCH + 64 * j + 16 * g + 8 * h) = v;
+                }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < 32 * CPR / 64; ++k) {
+                const int e = l + 64 * k, row = e / CPR, ch = e % CPR;
+                const int64_t t = cur.t0 + 32 * (TI * wm + i) + row;
+                const int o = cur.o0 + 32 * TJ * wn + 8 * ch;
+                const u32x4 v = *reinterpret_cast<const u32x4*>(ot + row * OPITCH + 16 * ch);
+                if (t < p.T && o < p.m) {
+                    _Float16* dst = p.out + t * p.out_stride + o;
+                    if (wide && o + 8 <= p.m) {
+                        *reinterpret_cast<u32x4*>(dst) = v;
+                    } else if (pairs && o + 8 <= p.m) {
+                        for (int x = 0; x < 4; ++x) reinterpret_cast<uint32_t*>(dst)[x] = v[x];
+                    } else {
+                        const _Float16* ev = reinterpret_cast<const _Float16*>(&v);
+                        for (int x = 0; x < 8; ++x)
+                            if (o + x < p.m) dst[x] = ev[x];
+                    }
+                }
             }
-    __syncthreads();
-    const bool wide = ((reinterpret_cast<uintptr_t>(p.out) & 15) == 0) && (p.out_stride % 8 == 0);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (!more) break;
+        q = qn;
+        cur = nxt;
+        if (flow) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();    // every wave is done with the output stage: it takes the next loads
+            stl = st;
+            st = advance(st);
+        } else {                             // fewer iterations than stages: start over
+            wait_vm_pending<0>();
+            __syncthreads();
+            set_source(cur);
 #pragma unroll
-    for (int k = 0; k < XT * 16 / X_NT; ++k) {
-        const int q = tid + X_NT * k, row = q >> 4, ch = q & 15;
-        const int64_t t = t0 + row;
-        const int o = o0 + 8 * ch;
-        if (t < p.T && o < p.m) {
-            const u32x4 v = *reinterpret_cast<const u32x4*>(otile + row * OPITCH + 16 * ch);
-            _Float16* dst = p.out + t * p.out_stride + o;
-            if (wide && o + 8 <= p.m) {
-                *reinterpret_cast<u32x4*>(dst) = v;
-            } else {
-                const _Float16* e = reinterpret_cast<const _Float16*>(&v);
-                for (int x = 0; x < 8; ++x)
-                    if (o + x < p.m) dst[x] = e[x];
-            }
+            for (int s = 0; s + 1 < NST; ++s) issue(s, s * STAGE, 0, NL);
+            arrive(1);
+            st = 0;
+            stl = (NST - 1) * STAGE;
+            read_exps(0);
+#pragma unroll
+            for (int d = 0; d < LA; ++d)
+#pragma unroll
+                for (int x = 0; x < NOP; ++x) P[d][x] = lds_chunk(0, d, x);
         }
     }
+    wait_vm_pending<0>();                    // nothing may still be on its way into LDS when the workgroup ends
 }
 
 // ---- few tokens (decode, short prefill chunks; tiles of up to 64 tokens): the weights are read once per tile and the kernel is bound by how fast a CU takes them in.  A
@@ -394,6 +498,35 @@ static hipError_t mx_skinny_launch(const MxGemmDev& d, hipStream_t stream, int t
     return hipErrorInvalidValue;
 }
 
+template <int TI, int TJ, int WM, int WN, int NST, int LA>
+static hipError_t mx_tile_launch(const MxGemmDev& d, hipStream_t stream) {
+    using L = MxTile<TI, TJ, WM, WN, NST>;
+    static OccCache cache;
+    int occ = 0;
+    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA>), 64 * L::NW, L::LDS, cache, occ);
+    if (e != hipSuccess) return e;
+    // persistent: every XCD (eight of them) gets as many workgroups as it holds at once, or as it has tiles
+    const int64_t tiles = ((d.T + L::TOK - 1) / L::TOK) * ((d.m + L::CH - 1) / L::CH);
+    const int64_t per_xcd = (tiles + 7) / 8, resident = (int64_t)occ * cu_count() / 8;
+    const unsigned grid = 8 * (unsigned)(per_xcd < resident ? per_xcd : resident);
+    return launch((mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA>), dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
+}
+
+// Tile form: 0 = 128 x 128 (two workgroups per CU), 1 = 256 x 128, 2 = 256 x 256 (one per CU).  The time of a launch goes
+// in rounds of what is resident at once; the cost of a round, full / at most half full, is what 8192 channels take in us:
+// 39 / 24, 35 / 26 and 64 / 45.  (Measured, us for forms 0 / 1 / 2: 1024 x 4096 x 4096 15.8 / 17.0 / 26.5, 2048 x 4096 x
+// 4096 23.5 / 22.7 / 29.9, 3000 x 4096 x 4096 35.2 / 35.6 / 32.4, 4096 x 4096 x 4096 43.3 / 40.8 / 37.1, 2048 x 4096 x
+// 11008 53.2 / 49.6 / 60.3, 1024 x 11008 x 4096 34.4 / 35.2 / 31.3, 16384 x 8192 x 8192 635 / 567 / 510.)
+static int mx_tile_form(const MxGemmDev& d) {
+    const int64_t cu = cu_count();
+    auto cost = [&](int64_t tok, int64_t ch, int64_t slots, int64_t full, int64_t half) {
+        const int64_t tiles = ((d.T + tok - 1) / tok) * ((d.m + ch - 1) / ch);
+        return 2 * tiles <= slots ? half : (tiles + slots - 1) / slots * full;
+    };
+    const int64_t c0 = cost(128, 128, 2 * cu, 39, 24), c1 = cost(256, 128, cu, 35, 26), c2 = cost(256, 256, cu, 64, 45);
+    return c2 <= c0 && c2 <= c1 ? 2 : c1 <= c0 ? 1 : 0;
+}
+
 hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
     MxGemmDev d;
     d.xc = a.x_codes; d.xe = a.x_exps; d.wc = a.w_codes; d.we = a.w_exps; d.out = a.out;
@@ -412,12 +545,11 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
         if (ring_max >= 0 ? a.T <= ring_max : (2 * tiled_wgs <= cu_count() && a.T <= 4096))
             return mx_skinny_launch<8>(d, stream, (int)((a.T + 63) / 64));
     }
-    static OccCache cache;
-    int unused = 0;
-    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(mxfp4_gemm_kernel), X_NT, X_LDS_BYTES, cache, unused);
-    if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)((a.T + XT - 1) / XT), (unsigned)((a.m + XT - 1) / XT));
-    return launch(mxfp4_gemm_kernel, grid, dim3(X_NT), X_LDS_BYTES, stream, d);
+    switch (env_int("FLATQUANT_GEMM_WIDE", mx_tile_form(d))) {
+        case 1: return mx_tile_launch<4, 2, 2, 2, 3, 2>(d, stream);
+        case 2: return mx_tile_launch<4, 4, 2, 2, 2, 1>(d, stream);
+        default: return mx_tile_launch<2, 2, 2, 2, 2, 1>(d, stream);
+    }
 }
 
 }  // namespace fq

@@ -713,6 +713,16 @@ def test_mxfp4_gemm(T, m, n):
     _mxfp4_gemm_case(T, m, n)
 
 
+@pytest.mark.parametrize("form", [0, 1, 2])
+@pytest.mark.parametrize("T,m,n", [(300, 260, 256), (257, 385, 512), (130, 511, 768), (513, 129, 1280), (4400, 4500, 512), (4353, 4105, 1024)])
+def test_mxfp4_gemm_every_tile_form(tuning, form, T, m, n):
+    """128 x 128, 256 x 128 and 256 x 256 tiles: fewer K iterations than LDS stages (one to three), ragged tiles on both
+    sides, and more tiles than workgroups are resident, where the loads of a tile's last iterations belong to the next."""
+    tuning("FLATQUANT_GEMM_TILED", 1)
+    tuning("FLATQUANT_GEMM_WIDE", form)
+    _mxfp4_gemm_case(T, m, n)
+
+
 @pytest.mark.parametrize("waves,depth,rows,T,m,n", [(16, 1, 32, 5, 100, 4096), (16, 2, 16, 64, 70, 2304), (4, 3, 32, 20, 330, 11008), (8, 8, 16, 40, 64, 4096),
                                                     (4, 1, 16, 1, 33, 256), (8, 2, 32, 9, 8200, 512), (8, 2, 16, 12, 8200, 512), (4, 2, 32, 64, 4096, 1024), (16, 3, 32, 120, 200, 2304), (4, 2, 16, 90, 100, 1024)])
 @pytest.mark.parametrize("kind", ["int4", "mxfp4"])
