@@ -7,7 +7,8 @@
 // extension: for a packed dword w, (w << 4) & 0xF0F0F0F0 holds 16 q of the even channels and w & 0xF0F0F0F0 holds 16 q
 // of the odd channels, as signed bytes.  Both operands are widened the same way, so the K order inside an MFMA is
 // the same permutation for both and every product carries a factor 256 that the epilogue divides out exactly.
-// v_mfma_i32_32x32x32_i8 accumulates in int32 (|sum| <= 128 * 128 * n < 2^31 for n <= 65536).
+// v_mfma_i32_32x32x32_i8 accumulates in int32 (|sum| <= 128 * 128 * n < 2^31 for n <= 65536).  Large launches widen to FP6
+// instead (w4a4_fp6_kernel, further down).
 //
 // Workgroup: 4 waves, C tile 128 tokens x 128 output channels (or 8 waves, 256 x 128, when the launch has enough such
 // tiles for every CU), each wave 64 x 64 (2 x 2 MFMA tiles; the weights are
@@ -21,7 +22,9 @@
 namespace fq {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int GT = 128;               // tile edge, tokens and output channels
@@ -222,6 +225,323 @@ __global__ __launch_bounds__(128 * TW) __attribute__((amdgpu_waves_per_eu(2))) v
     }
 }
 
+// ---- many tokens.  A chunk of 32 codes becomes an FP6 operand (E2M3) in registers: the code q offset to q + 8 = 0 .. 15 IS
+// the E2M3 bit pattern of (q + 8) / 8 (subnormal up to 7 / 8, the first binade up to 15 / 8), so the codes need only be
+// spread from 4-bit to 6-bit fields, 8 vector instructions per 16 codes.  Their order inside a lane is free as long as both
+// operands share it.  The sums are exact: every product is an integer / 64 and the total at most 225 n / 64 with
+// n <= 65536, which fits 24 bits.  The offset leaves in the epilogue,
+//   sum q_x q_w = sum (q_x + 8)(q_w + 8) - 8 sum q_x - 8 sum q_w - 64 n,
+// with the row sums of the codes (one v_dot8 per dword) taken on the way.
+// FP6 MFMAs have twice the rate of int8 ones and are held back less by the power limit: alone, for the 2.2e12 operations of
+// 16384 x 8192 x 8192 on random codes, they take 303 us (328 with sign and magnitude in place of the offset), int8 ones 531.
+// What bounds the kernel there (615 - 672 us; 888 with the int8 kernel above): one wave per SIMD issues in order, and its
+// slots are busy 62 % of the time (some 200 instructions per 16 MFMAs; the MFMA pipe 37 %), 25 % go to waits for the tiles.
+// Without the row sums 554, without loads as well 483.  Two waves per SIMD (eight of 128 x 64) spread every weight row
+// four times: 697.  Row sums by one of the two waves that share a row: the same time, twice the code.
+constexpr unsigned kSpreadA0 = 0x0F00F00Fu, kSpreadA1 = 0xF00F00F0u, kSpreadA2 = 0x00F00F00u;   // fields that do not move
+constexpr unsigned kSpreadM0 = 0xCF3CF3CFu, kSpreadM1 = 0xF3CF3CF3u, kSpreadM2 = 0x3CF3CF3Cu;   // the low 4 bits of all fields
+constexpr unsigned kSpreadX0 = 0x08208208u, kSpreadX1 = 0x82082082u, kSpreadX2 = 0x20820820u;   // bit 3 of all fields
+__device__ __forceinline__ unsigned pick_bits(unsigned mask, unsigned a, unsigned b) { return __builtin_amdgcn_bitop3_b32(mask, a, b, 0xCA); }   // mask ? a : b
+__device__ __forceinline__ unsigned and_xor(unsigned v, unsigned m, unsigned x) { return __builtin_amdgcn_bitop3_b32(v, m, x, 0x6A); }           // (v & m) ^ x
+// 16 codes -> 16 fields of 6 bits in three dwords.  Every nibble stays or moves up by 2 bits, into the next dword where it
+// straddles the end (fields in order: nibbles 0 1 3 4 6 7 of lo, 1 2 4 5 7 0 of hi, 2 of lo, 3 of hi, 5 of lo, 6 of hi).
+__device__ __forceinline__ void spread16(unsigned lo, unsigned hi, unsigned* o) {
+    const unsigned t = lo << 2, u = __builtin_amdgcn_alignbit(hi, lo, 30);      // u = hi << 2 | lo >> 30
+    o[0] = and_xor(pick_bits(kSpreadA0, lo, t), kSpreadM0, kSpreadX0);
+    o[1] = and_xor(pick_bits(kSpreadA1, hi, u), kSpreadM1, kSpreadX1);
+    o[2] = and_xor(pick_bits(kSpreadA2, lo, u), kSpreadM2, kSpreadX2);
+}
+
+struct Fp6Tile {
+    // MFMA tiles of 32 x 32 per wave (tokens x channels), waves, LDS stages: 256 x 256 with a wave on each SIMD, as large as
+    // the register file allows, so that every code is spread by two waves only and crosses LDS and L2 least often
+    static constexpr int TI = 4, TJ = 4, WM = 2, WN = 2, NST = 2;
+    static constexpr int NW = WM * WN;
+    static constexpr int TOK = 32 * TI * WM, CH = 32 * TJ * WN, ROWS = TOK + CH;
+    static constexpr int STAGE = ROWS * GKB;                        // code tiles of one K iteration
+    static constexpr int OPITCH = 64 * TJ + 16;                     // output staging: 32 tokens of a wave's channels
+    static constexpr int WCOL = 32 * TJ * 8;                        // step and row sum of a wave's channels
+    static constexpr int LDS = NST * STAGE + NW * WCOL;
+    static_assert(NW * 32 * OPITCH <= STAGE && LDS <= 160 * 1024 && NST >= 2, "LDS budget");
+};
+
+// Every operand byte goes from global memory straight into LDS (global-to-LDS loads, unpadded 128-byte rows, 16-byte chunks
+// swizzled), NST iterations of 256 codes deep, one barrier per iteration; persistent workgroups whose loads run on from one
+// output tile into the next.
+__global__ __launch_bounds__(64 * Fp6Tile::NW) __attribute__((amdgpu_waves_per_eu(1, 1))) void w4a4_fp6_kernel(GemmDev p) {
+    using L = Fp6Tile;
+    constexpr int TI = L::TI, TJ = L::TJ, WM = L::WM, NST = L::NST;
+    constexpr int NW = L::NW, TOK = L::TOK, CH = L::CH, STAGE = L::STAGE, A_TILE = TOK * GKB, NOP = TI + TJ;
+    constexpr int NLA = TOK / 8 / NW, NLB = CH / 8 / NW, NL = NLA + NLB;   // load instructions per wave and iteration
+    constexpr int NKP = GKB / 32;                                   // K steps (64 codes) per iteration
+    constexpr int LA = 2, KB = NKP - LA;                            // operands are read LA steps ahead; the steps before the barrier
+    constexpr int NQ = TI * TJ;                                     // MFMAs per step
+    constexpr int LSTEPS = 2;                                       // steps over which an iteration's loads are spread
+    static_assert(NKP == 4, "register stages below");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x;
+    const int l = tid & 63, c = l & 31, h = l >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = w % WM, wn = w / WM;
+    const int64_t kbytes = p.n / 2;
+    const int nk = p.n / (2 * GKB);
+    const int ntx = (int)((p.T + TOK - 1) / TOK), nty = (p.m + CH - 1) / CH;
+    const int64_t ntiles = (int64_t)ntx * nty;
+
+    // Tiles of this workgroup.  Workgroup b runs on XCD b % 8: every XCD takes a contiguous eighth of a tile order that
+    // goes through panels of PW token tiles, so that the tiles in flight on an XCD share rows of both operands in its L2.
+    constexpr int PW = 4;
+    const int64_t per_xcd = (ntiles + 7) / 8;
+    const int xcd = blockIdx.x & 7;
+    const int64_t first = xcd * per_xcd, left = ntiles - first;
+    const int64_t mine = left < per_xcd ? left : per_xcd;           // tiles of this XCD (<= 0: none)
+    const int64_t qstep = gridDim.x >> 3;
+    int64_t q = blockIdx.x >> 3;
+    if (q >= mine) return;
+    struct Pos { int64_t t0; int o0; };
+    auto tile_pos = [&](int64_t qq) -> Pos {
+        const int64_t pos = first + qq, panel = pos / ((int64_t)PW * nty);
+        const int r = (int)(pos - panel * ((int64_t)PW * nty));
+        const int width = ntx - panel * PW < PW ? (int)(ntx - panel * PW) : PW;
+        const int ty = r / width;
+        return Pos{(panel * PW + r - ty * width) * TOK, ty * CH};
+    };
+
+    // ---- loads: one instruction fills 8 rows of 128 bytes; LDS slot j of row r holds the row's chunk j ^ ((r >> 1) & 7).
+    // Rows past the end re-read the last row.
+    __amdgpu_buffer_rsrc_t abuf, bbuf;
+    uint32_t aoff[NLA], boff[NLB];
+    auto set_source = [&](const Pos& t) {
+        const int arows = (int)(p.T - t.t0 < TOK ? p.T - t.t0 : TOK), brows = p.m - t.o0 < CH ? p.m - t.o0 : CH;
+        abuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.xc) + t.t0 * kbytes, 0, arows * (int)kbytes, 0x00020000);
+        bbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.wc) + (int64_t)t.o0 * kbytes, 0, brows * (int)kbytes, 0x00020000);
+#pragma unroll
+        for (int k = 0; k < NLA; ++k) {
+            const int row = 8 * (NLA * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
+            aoff[k] = (uint32_t)(row < arows ? row : arows - 1) * (uint32_t)kbytes + 16 * ch;
+        }
+#pragma unroll
+        for (int k = 0; k < NLB; ++k) {
+            const int row = 8 * (NLB * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
+            boff[k] = (uint32_t)(row < brows ? row : brows - 1) * (uint32_t)kbytes + 16 * ch;
+        }
+    };
+    typedef __attribute__((address_space(3))) void* lptr;
+    // loads k0 .. k1 - 1 of the NL that bring iteration `it` (past the last one it is re-read; nobody uses it)
+    auto issue = [&](int it, int stage, int k0, int k1) {
+        const int itc = it < nk ? it : nk - 1;
+#pragma unroll
+        for (int k = k0; k < k1; ++k) {
+            if (k < NLA) __builtin_amdgcn_raw_ptr_buffer_load_lds(abuf, (lptr)(smem + stage + (NLA * w + k) * 8 * GKB), 16, (int)aoff[k], itc * GKB, 0, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(bbuf, (lptr)(smem + stage + A_TILE + (NLB * w + k - NLA) * 8 * GKB), 16, (int)boff[k - NLA], itc * GKB, 0, 0);
+        }
+    };
+
+    // ---- operands.  x < TI: tokens 32 (TI wm + x) + c; else channels 32 (TJ wn + x - TI) + c
+    const int hs = h ^ ((c >> 1) & 7);   // chunk 2 kp + h of row 32 x + c sits in slot (2 kp) ^ hs
+    const int abyte = (32 * TI * wm + c) * GKB, bbyte = A_TILE + (32 * TJ * wn + c) * GKB;
+    auto lds_chunk = [&](int stage, int kp, int x) -> u32x4 {
+        const int a = stage + (x < TI ? abyte + 32 * x * GKB : bbyte + 32 * (x - TI) * GKB) + 16 * ((2 * kp) ^ hs);
+        return *reinterpret_cast<const u32x4*>(smem + a);
+    };
+    // Three register stages: while the MFMAs of step kp run on the FP6 operands W[kp & 1], the packed codes P of step kp + 1
+    // are spread into W[(kp + 1) & 1], and as each operand has been spread its registers take the codes of step kp + 2 from
+    // LDS.  A wave issues in order, so the vector work stands between the MFMAs, a share behind each.
+    f32x16 acc[TI][TJ];
+    u32x4 P[NOP];
+    unsigned W[2][NOP][6];
+    int rsum[NOP];                       // sums of this lane's codes, per operand row
+    auto mfma = [&](int i, int j, int st) {
+        const unsigned *wv = W[st][TI + j], *xv = W[st][i];
+        const i32x8 a = {(int)wv[0], (int)wv[1], (int)wv[2], (int)wv[3], (int)wv[4], (int)wv[5], 0, 0};
+        const i32x8 b = {(int)xv[0], (int)xv[1], (int)xv[2], (int)xv[3], (int)xv[4], (int)xv[5], 0, 0};
+        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i][j], 2, 2, 0, 0, 0, 0);   // FP6 E2M3 for both, no scale
+    };
+    auto spread = [&](int st, int u) {   // half u & 1 of operand u / 2: 16 codes
+        const int x = u >> 1, s = u & 1;
+        const unsigned lo = P[x][2 * s], hi = P[x][2 * s + 1];
+        spread16(lo, hi, &W[st][x][3 * s]);
+        rsum[x] = __builtin_amdgcn_sdot8((int)hi, 0x11111111, __builtin_amdgcn_sdot8((int)lo, 0x11111111, rsum[x], false), false);
+    };
+    // K step kp and a share of the loads of iteration `lit` into `stage_load`.  Steps KB .. NKP - 1 of an iteration, then
+    // 0 .. KB - 1 of the next one, lie between two barriers: s is the step's place in that sequence, which the loads are
+    // spread over.  `next`: there is a next step in this tile.
+    auto step = [&](int kp, int stage_ahead, int lit, int stage_load, int s, int s0, int nsteps, bool next) {
+#pragma unroll
+        for (int m = 0; m < NQ; ++m) {
+            mfma(m / TJ, m % TJ, kp & 1);
+#pragma unroll
+            for (int u = m * 2 * NOP / NQ; next && u < (m + 1) * 2 * NOP / NQ; ++u) {
+                spread((kp + 1) & 1, u);
+                if (u & 1) P[u >> 1] = lds_chunk(stage_ahead, (kp + LA) % NKP, u >> 1);
+            }
+            if (s >= s0 && s < s0 + nsteps) issue(lit, stage_load, ((s - s0) * NQ + m) * NL / (nsteps * NQ), ((s - s0) * NQ + m + 1) * NL / (nsteps * NQ));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // the next iteration has arrived (this wave's part, then everybody's) and nobody reads the current one's stage any more
+    auto arrive = [&]() {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NST - 2) * NL) : "memory");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto read_step = [&](int stage, int kp) {
+#pragma unroll
+        for (int x = 0; x < NOP; ++x) P[x] = lds_chunk(stage, kp, x);
+    };
+
+    Pos cur = tile_pos(q);
+    set_source(cur);
+#pragma unroll
+    for (int s = 0; s + 1 < NST; ++s) issue(s, s * STAGE, 0, NL);
+    arrive();
+    int st = 0, stl = (NST - 1) * STAGE;     // stage of the current iteration, and the one to be loaded next
+    auto advance = [&](int stage) { return stage + STAGE == NST * STAGE ? 0 : stage + STAGE; };
+    read_step(0, 0);
+
+    // Loads run NST - 1 iterations ahead of the steps 0 .. KB - 1 and go on into the next tile: the last NST - 1 iterations
+    // of a tile load the first ones of the next.
+    const bool flow = nk >= NST;
+    while (true) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+#pragma unroll
+        for (int x = 0; x < NOP; ++x) rsum[x] = 0;
+#pragma unroll
+        for (int u = 0; u < 2 * NOP; ++u) spread(0, u);
+        read_step(st, 1);
+        // steps 0 .. KB - 1 of iteration 0; loads of iteration NST - 1
+#pragma unroll
+        for (int kp = 0; kp < KB; ++kp) step(kp, st, NST - 1, stl, kp, 0, LSTEPS, true);
+        arrive();
+        int lit = NST;                       // iteration to be loaded next
+        auto body = [&]() {
+            const int stn = advance(st);
+            stl = advance(stl);
+#pragma unroll
+            for (int kp = KB; kp < NKP; ++kp) step(kp, stn, lit, stl, kp - KB, 0, LSTEPS, true);
+#pragma unroll
+            for (int kp = 0; kp < KB; ++kp) step(kp, stn, lit, stl, kp + LA, 0, LSTEPS, true);
+            arrive();
+            st = stn;
+            ++lit;
+        };
+        int it = 0;
+        for (; it < nk - 1 && lit < nk; ++it) body();
+        const int64_t qn = q + qstep;
+        const bool more = qn < mine;
+        Pos nxt = cur;
+        if (more) nxt = tile_pos(qn);
+        if (more && flow) { set_source(nxt); lit = 0; }
+        for (; it < nk - 1; ++it) body();
+        // the quantization steps of this tile's rows and channels, requested ahead of the epilogue (raw bits: nothing waits here)
+        const uint16_t* xs_bits = reinterpret_cast<const uint16_t*>(p.xs);
+        const uint16_t* ws_bits = reinterpret_cast<const uint16_t*>(p.ws);
+        unsigned esx[TI], esw[TJ];
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+            const int64_t t = cur.t0 + 32 * (TI * wm + i) + c;
+            esx[i] = xs_bits[t < p.T ? t : p.T - 1];
+        }
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+            const int o = cur.o0 + 32 * (TJ * wn + j) + c;
+            esw[j] = ws_bits[o < p.m ? o : p.m - 1];
+        }
+        // the last steps of the tile: nothing is loaded, the current stage takes the output tile
+        {
+            const int stn = advance(st);
+#pragma unroll
+            for (int kp = KB; kp < NKP; ++kp) step(kp, stn, 0, 0, 0, 1, 0, kp + 1 < NKP);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+
+        // epilogue: in acc[i][j] a lane holds, for token 32 (TI wm + i) + c, the output channels 32 (TJ wn + j) + 8 (r / 4) +
+        // 4 h + r % 4.  Rounded to fp16 and turned, 32 tokens at a time, through a part of LDS that belongs to the wave
+        // alone (no barrier), from where they leave in 16-byte pieces of whole rows.  All corrections are integers below
+        // 2^24, so their fp32 sums are exact.
+        typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+        constexpr int OPITCH = L::OPITCH, CPR = 4 * TJ;              // 16-byte pieces per token
+        unsigned char* ot = smem + st + w * (32 * OPITCH);
+        float* wcol = reinterpret_cast<float*>(smem + NST * STAGE + w * L::WCOL);   // [32 TJ] steps, [32 TJ] corrections
+#pragma unroll
+        for (int x = 0; x < NOP; ++x) rsum[x] += __shfl_xor(rsum[x], 32);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+            wcol[32 * j + c] = (float)__builtin_bit_cast(_Float16, (uint16_t)esw[j]);   // both halves of the wave store the same
+            wcol[32 * TJ + 32 * j + c] = (float)(-8 * rsum[TI + j]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const uintptr_t pitch_bits = reinterpret_cast<uintptr_t>(p.out) | (uintptr_t)(2 * p.out_stride);
+        const bool wide = (pitch_bits & 15) == 0, pairs = (pitch_bits & 3) == 0;   // whole pieces, dwords, or halves
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+            const float sx = (float)__builtin_bit_cast(_Float16, (uint16_t)esx[i]);
+            const float cx = (float)(-8 * rsum[i] - 64 * p.n);
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float4 sw = *reinterpret_cast<const float4*>(wcol + 32 * j + 8 * g + 4 * h);
+                    const float4 cw = *reinterpret_cast<const float4*>(wcol + 32 * TJ + 32 * j + 8 * g + 4 * h);
+                    const half4 v = {(_Float16)(fmaf(acc[i][j][4 * g], 64.0f, cx + cw.x) * sx * sw.x),
+                                     (_Float16)(fmaf(acc[i][j][4 * g + 1], 64.0f, cx + cw.y) * sx * sw.y),
+                                     (_Float16)(fmaf(acc[i][j][4 * g + 2], 64.0f, cx + cw.z) * sx * sw.z),
+                                     (_Float16)(fmaf(acc[i][j][4 * g + 3], 64.0f, cx + cw.w) * sx * sw.w)};
+                    *reinterpret_cast<half4*>(ot + c * OPITCH + 64 * j + 16 * g + 8 * h) = v;
+                }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < 32 * CPR / 64; ++k) {
+                const int e = l + 64 * k, row = e / CPR, ch = e % CPR;
+                const int64_t t = cur.t0 + 32 * (TI * wm + i) + row;
+                const int o = cur.o0 + 32 * TJ * wn + 8 * ch;
+                const u32x4 v = *reinterpret_cast<const u32x4*>(ot + row * OPITCH + 16 * ch);
+                if (t < p.T && o < p.m) {
+                    _Float16* dst = p.out + t * p.out_stride + o;
+                    if (wide && o + 8 <= p.m) {
+                        *reinterpret_cast<u32x4*>(dst) = v;
+                    } else if (pairs && o + 8 <= p.m) {
+                        for (int x = 0; x < 4; ++x) reinterpret_cast<uint32_t*>(dst)[x] = v[x];
+                    } else {
+                        const _Float16* ev = reinterpret_cast<const _Float16*>(&v);
+                        for (int x = 0; x < 8; ++x)
+                            if (o + x < p.m) dst[x] = ev[x];
+                    }
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (!more) break;
+        q = qn;
+        cur = nxt;
+        if (flow) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();    // every wave is done with the output stage: it takes the next loads
+            stl = st;
+            st = advance(st);
+        } else {                             // fewer iterations than stages: start over
+            wait_vm_pending<0>();
+            __syncthreads();
+            set_source(cur);
+#pragma unroll
+            for (int s = 0; s + 1 < NST; ++s) issue(s, s * STAGE, 0, NL);
+            arrive();
+            st = 0;
+            stl = (NST - 1) * STAGE;
+            read_step(0, 0);
+        }
+    }
+    wait_vm_pending<0>();                    // nothing may still be on its way into LDS when the workgroup ends
+}
+
 // ---- few tokens (decode, short prefill chunks): the weights are read once (per tile of 64 tokens), and what bounds the kernel is how fast the CUs take
 // them in.  A workgroup owns 32 (or 16) output channels for all tokens.  Every operand byte goes from global memory
 // straight into LDS, a whole cache line per row at a time: a wave owns every nwv-th 128-byte line of K (256 codes) of
@@ -418,6 +738,19 @@ static hipError_t skinny_launch(const GemmDev& d, hipStream_t stream, int token_
     return hipErrorInvalidValue;
 }
 
+static hipError_t fp6_launch(const GemmDev& d, hipStream_t stream) {
+    using L = Fp6Tile;
+    static OccCache cache;
+    int occ = 0;
+    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_fp6_kernel), 64 * L::NW, L::LDS, cache, occ);
+    if (e != hipSuccess) return e;
+    // persistent: every XCD (eight of them) gets as many workgroups as it holds at once, or as it has tiles
+    const int64_t tiles = ((d.T + L::TOK - 1) / L::TOK) * ((d.m + L::CH - 1) / L::CH);
+    const int64_t per_xcd = (tiles + 7) / 8, resident = (int64_t)occ * cu_count() / 8;
+    const unsigned grid = 8 * (unsigned)(per_xcd < resident ? per_xcd : resident);
+    return launch(w4a4_fp6_kernel, dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
+}
+
 hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
     int unused = 0;
     GemmDev d;
@@ -438,9 +771,19 @@ hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
             return skinny_launch<8>(d, stream, (int)((a.T + 63) / 64));
     }
     static OccCache ct, ctw;
-    // 256-token tiles when they still give every CU a workgroup (FLATQUANT_GEMM_WIDE = 0 / 1 forces a form)
-    const int64_t wide_wgs = ((a.T + 255) / 256) * ((a.m + GT - 1) / GT);
-    const int wide = env_int("FLATQUANT_GEMM_WIDE", wide_wgs >= cu_count() ? 1 : 0);
+    // Tile form (FLATQUANT_GEMM_WIDE forces one): int8 with 128 x 128 tiles, with 256 x 128 tiles when these still give every
+    // CU a workgroup (1), or FP6 with 256 x 256 tiles (2).  A launch takes rounds of one tile per CU, measured at n = 4096: 5 + 29 us
+    // per round of 256 x 128 int8 tiles, 9 + 43 us per round of FP6 tiles of twice the size, whose first pass over its
+    // code costs more.  (int8 / FP6, us: 2048 x 4096 x 4096 33.3 / 46.6, 3000 x 4096 x 4096 56.4 / 47.8, 4096 x 4096 x 4096
+    // 64.5 / 49.7, 1024 x 11008 x 4096 54.6 / 47.3, 2048 x 11008 x 4096 93.2 / 88.2, 777 x 5120 x 5120 34.7 / 52.8, 2048 x
+    // 4096 x 11008 77.0 / 95.4, 16384 x 8192 x 8192 888 / 615 - 672.  FP6 with 256 x 128 and 128 x 128 tiles is bound by the
+    // vector work and gains nothing over int8: 30.0 and 32.9 at 2048 x 4096 x 4096 with everything in the caches, but 41
+    // against 39 for the whole layer on fresh data.)
+    const int64_t cu = cu_count();
+    const int64_t wide_wgs = ((a.T + 255) / 256) * ((a.m + GT - 1) / GT), fp6_wgs = ((a.T + 255) / 256) * ((a.m + 255) / 256);
+    const int64_t int8_cost = 5 + (wide_wgs + cu - 1) / cu * 29, fp6_cost = 9 + (fp6_wgs + cu - 1) / cu * 43;
+    const int wide = env_int("FLATQUANT_GEMM_WIDE", wide_wgs < cu ? 0 : fp6_cost < int8_cost ? 2 : 1);
+    if (wide == 2) return fp6_launch(d, stream);
     if (wide) {
         hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_kernel<4>), 512, G_LDS_BYTES_WIDE, ctw, unused);
         if (e != hipSuccess) return e;

@@ -1012,6 +1012,24 @@ def test_w4a4_gemm(T, m, n, pad):
     _w4a4_case(T, m, n, pad)
 
 
+@pytest.mark.parametrize("T,m,n", [(1, 1, 256), (513, 129, 256), (257, 513, 512), (1030, 2051, 1280), (5000, 8192, 256)])
+@pytest.mark.parametrize("form", [0, 1, 2])
+def test_w4a4_gemm_tiles_are_exact(tuning, form, T, m, n):
+    """Every tile form, whole range of codes (-8 included), tiles and pipeline stages with remainders: the integer sums (below
+    64 n < 2^24) are exact in fp32 on both sides and the scaling takes the same roundings, so the fp16 outputs are equal."""
+    tuning("FLATQUANT_GEMM_TILED", 1)
+    tuning("FLATQUANT_GEMM_WIDE", form)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + m)
+    q = [torch.randint(-8, 8, (r, n), generator=g, device="cuda", dtype=torch.int8) for r in (T, m)]
+    packed = [((c[:, 0::2] & 15) | (c[:, 1::2] << 4)).view(torch.uint8) for c in q]
+    xs, ws = (torch.rand(r, generator=g, device="cuda").half() for r in (T, m))
+    out = torch.full((T, m), float("nan"), dtype=torch.float16, device="cuda")
+    fq.flatquant_w4a4_gemm(packed[0], xs, packed[1], ws, T, m, n, out, m, stream=torch.cuda.current_stream())
+    sums = q[0].float() @ q[1].float().t()
+    assert torch.equal(out, (sums * xs.float()[:, None] * ws.float()[None, :]).half())
+
+
 @pytest.mark.parametrize("knob,value,T,m,n", [("FLATQUANT_GEMM_WIDE", 1, 300, 260, 768), ("FLATQUANT_GEMM_WIDE", 1, 513, 129, 256),
                                               ("FLATQUANT_GEMM_WIDE", 0, 2048, 4224, 512), ("FLATQUANT_GEMM_TILED", 1, 33, 96, 768),
                                               ("FLATQUANT_GEMM_TILED", 1, 100, 200, 1024)])
