@@ -67,7 +67,7 @@ __device__ __forceinline__ uint32_t nibble(float y, float inv) {
 // consecutive channels straddles rows of X~ and column slabs): the token's Y is staged in LDS as fp32 in channel order,
 // then one thread per block takes its 32 values, forms the shared exponent and converts.
 template <int A, int B, bool P1LDS, bool MX = false>
-__global__ __launch_bounds__(64 * B) void tq_kernel(TqDev p) {
+__global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(A <= 2 ? 2 : 1))) void tq_kernel(TqDev p) {
     constexpr int NT = 64 * B;
     constexpr int PITCH = 32 * B + kLdsPad;      // halves per LDS row of the token tile
     constexpr int XS_HALVES = 32 * A * PITCH;
@@ -90,31 +90,54 @@ __global__ __launch_bounds__(64 * B) void tq_kernel(TqDev p) {
     // ---- one-off: zero the tile (pad rows/columns stay zero for the whole kernel)
     for (int q = tid; q < XS_HALVES / 8; q += NT) reinterpret_cast<u32x4*>(Xs)[q] = u32x4{0u, 0u, 0u, 0u};
 
-    // ---- one-off: this wave's P2 slab as B-operand fragments (lane <-> j', 8 k-values <-> j)
+    // ---- one-off: the constant factors.  Every element is a 2-byte load of its own (any n1, n2 and alignment), and all of
+    // them are requested before the first one is used: bounds are the buffer descriptor's (rows past the end, and columns
+    // past it through an offset that is out of range, read as zero, and so does all of a left-out factor), so nothing branches around a load.  (With a test around
+    // each load, and around each request of a token's chunks, every one of them cost its own latency.  Before / now, us: 64 x 80
+    // one token 12.9 / 6.2, 777 tokens 28.9 / 11.6, 16384 tokens 328 / 98; 64 x 172 14.8 / 9.3, 31.4 / 25.6, 389 / 319;
+    // 30 x 34 6.1 / 4.6, 7.3 / 6.2, 30.8 / 26.6; 128 x 250 27.4 / 19.8, 148 / 112, 8192 tokens 1186 / 934.)
+    constexpr int kOut = 0x40000000;             // byte offset past any factor
+    const __amdgpu_buffer_rsrc_t p1buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(p.P1), 0, p.P1 ? n1 * n1 * 2 : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t p2buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(p.P2), 0, p.P2 ? n2 * n2 * 2 : 0, 0x00020000);
+    auto element = [](__amdgpu_buffer_rsrc_t buf, int off) -> _Float16 {
+        return __builtin_bit_cast(_Float16, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(buf, off, 0, 0));
+    };
+
+    // ---- this wave's P2 slab as B-operand fragments (lane <-> j', 8 k-values <-> j)
     half8 p2f[KB2];
-#pragma unroll
-    for (int kb = 0; kb < KB2; ++kb) {
+    {
         const int jp = 32 * w + c;
+        const int base = jp < n2 ? 2 * (8 * h * n2 + jp) : kOut;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const int j = 16 * kb + 8 * h + s;
-            p2f[kb][s] = (j < n2 && jp < n2) ? (p.P2 ? p.P2[j * n2 + jp] : (_Float16)(j == jp ? 1.0f : 0.0f)) : (_Float16)0;
+        for (int kb = 0; kb < KB2; ++kb)
+#pragma unroll
+            for (int s = 0; s < 8; ++s) p2f[kb][s] = element(p2buf, base + 2 * (16 * kb + s) * n2);
+        if (!p.P2) {                             // a left-out factor: identity
+#pragma unroll
+            for (int kb = 0; kb < KB2; ++kb)
+#pragma unroll
+                for (int s = 0; s < 8; ++s) p2f[kb][s] = (_Float16)(16 * kb + 8 * h + s == jp && jp < n2 ? 1.0f : 0.0f);
         }
     }
-    // ---- one-off: P1 as B-operand fragments of the second contraction (lane <-> i'),
+    // ---- P1 as B-operand fragments of the second contraction (lane <-> i'),
     // gathered with the k-permutation that the accumulator layout of the first one imposes:
     // K block kk, slot s of half-wave h  <->  i = 32(kk/2) + 8(2(kk%2) + s/4) + 4h + s%4.
     half8 p1f[P1LDS ? 1 : A][P1LDS ? 1 : KB1];
     if constexpr (P1LDS) {
-        for (int e = tid; e < A * KB1 * 64; e += NT) {
+#pragma unroll
+        for (int e0 = 0; e0 < A * KB1 * 64; e0 += NT) {
+            const int e = e0 + tid;
+            if (A * KB1 % B != 0 && e >= A * KB1 * 64) break;
             const int ln = e & 63, kk = (e >> 6) % KB1, It = (e >> 6) / KB1;
             const int cc = ln & 31, hh = ln >> 5;
             const int ip = 32 * It + cc;
+            const int i0 = 16 * kk + 4 * hh, base = ip < n1 ? 2 * (i0 * n1 + ip) : kOut;
             half8 f;
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
-                const int i = 32 * (kk >> 1) + 8 * (2 * (kk & 1) + (s >> 2)) + 4 * hh + (s & 3);
-                f[s] = (i < n1 && ip < n1) ? (p.P1 ? p.P1[i * n1 + ip] : (_Float16)(i == ip ? 1.0f : 0.0f)) : (_Float16)0;
+                const int i = 8 * (s >> 2) + (s & 3);
+                const _Float16 v = element(p1buf, base + 2 * i * n1);
+                f[s] = !p.P1 && i0 + i == ip && ip < n1 ? (_Float16)1.0f : v;
             }
             *reinterpret_cast<half8*>(&P1s[e]) = f;
         }
@@ -124,10 +147,12 @@ __global__ __launch_bounds__(64 * B) void tq_kernel(TqDev p) {
 #pragma unroll
             for (int kk = 0; kk < KB1; ++kk) {
                 const int ip = 32 * It + c;
+                const int i0 = 16 * kk + 4 * h, base = ip < n1 ? 2 * (i0 * n1 + ip) : kOut;
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {
-                    const int i = 32 * (kk >> 1) + 8 * (2 * (kk & 1) + (s >> 2)) + 4 * h + (s & 3);
-                    p1f[It][kk][s] = (i < n1 && ip < n1) ? (p.P1 ? p.P1[i * n1 + ip] : (_Float16)(i == ip ? 1.0f : 0.0f)) : (_Float16)0;
+                    const int i = 8 * (s >> 2) + (s & 3);
+                    const _Float16 v = element(p1buf, base + 2 * i * n1);
+                    p1f[It][kk][s] = !p.P1 && i0 + i == ip && ip < n1 ? (_Float16)1.0f : v;
                 }
             }
     }
@@ -147,7 +172,7 @@ __global__ __launch_bounds__(64 * B) void tq_kernel(TqDev p) {
         const u32x4* src = reinterpret_cast<const u32x4*>(p.x + t * p.x_stride);
 #pragma unroll
         for (int k = 0; k < NPRE; ++k)
-            if (xoff[k] >= 0) pre[k] = __builtin_nontemporal_load(src + tid + k * NT);
+            pre[k] = __builtin_nontemporal_load(src + (tid + k * NT < nchunks ? tid + k * NT : nchunks - 1));   // past the end the last chunk again: no branch
     };
     auto commit = [&](const u32x4 (&pre)[NPRE]) {
 #pragma unroll
@@ -158,22 +183,22 @@ __global__ __launch_bounds__(64 * B) void tq_kernel(TqDev p) {
     // into registers before the MFMA work like the chunks above (n / 2 pairs over the workgroup: at most 8 A per thread);
     // a pair never straddles a row (n2 is even), and its row is umulhi(2 u, magic) with the magic divisor from the host
     constexpr int NPS = 8 * A;
-    uint32_t pres[NPS];
-    auto issue_slow = [&](int64_t t) {
+    static_assert(NPS == 4 * NPRE, "the pairs use the registers of the chunks");
+    auto issue_slow = [&](int64_t t, u32x4 (&pre)[NPRE]) {
         const uint32_t* src = reinterpret_cast<const uint32_t*>(p.x + t * p.x_stride);
 #pragma unroll
         for (int k = 0; k < NPS; ++k) {
             const int u = tid + k * NT;
-            if (u < (n >> 1)) pres[k] = src[u];
+            pre[k >> 2][k & 3] = src[u < (n >> 1) ? u : (n >> 1) - 1];
         }
     };
-    auto commit_slow = [&]() {
+    auto commit_slow = [&](const u32x4 (&pre)[NPRE]) {
 #pragma unroll
         for (int k = 0; k < NPS; ++k) {
             const int u = tid + k * NT;
             if (u < (n >> 1)) {
                 const int e = 2 * u, i = (int)__umulhi((uint32_t)e, p.n2_magic);
-                *reinterpret_cast<uint32_t*>(Xs + i * PITCH + (e - i * n2)) = pres[k];
+                *reinterpret_cast<uint32_t*>(Xs + i * PITCH + (e - i * n2)) = pre[k >> 2][k & 3];
             }
         }
     };
@@ -182,7 +207,7 @@ __global__ __launch_bounds__(64 * B) void tq_kernel(TqDev p) {
     u32x4 pre[NPRE];
     int64_t t = blockIdx.x;
     if (t < p.T) {
-        if (p.vec8) { issue(t, pre); commit(pre); } else { issue_slow(t); commit_slow(); }
+        if (p.vec8) { issue(t, pre); commit(pre); } else { issue_slow(t, pre); commit_slow(pre); }
     }
     __syncthreads();
 
@@ -190,7 +215,7 @@ __global__ __launch_bounds__(64 * B) void tq_kernel(TqDev p) {
         const int64_t tn = t + gridDim.x;
         const bool have_next = tn < p.T;
         if (have_next) {
-            if (p.vec8) issue(tn, pre); else issue_slow(tn);
+            if (p.vec8) issue(tn, pre); else issue_slow(tn, pre);
         }
 
         f32x16 acc2[A];
@@ -292,7 +317,7 @@ __global__ __launch_bounds__(64 * B) void tq_kernel(TqDev p) {
         }
         // ---- next token tile into LDS (its loads were issued before the MFMA work)
         if (have_next) {
-            if (p.vec8) commit(pre); else commit_slow();
+            if (p.vec8) commit(pre); else commit_slow(pre);
         }
         __syncthreads();   // (B) staged codes and next tile visible
 
