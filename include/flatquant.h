@@ -179,7 +179,7 @@ fq_status flatquant_weight_transform_quant(const void* w, const void* A1, const 
 /*
  * W4A4 matrix product of the two quantized factors (Sec. 3.2: low-bit matrix multiplications for all linear layers;
  * Eq. (1)-(2)):   out[t, o] = fp16( s_x[t] * s_w[o] * sum_k q_x[t, k] * q_w[o, k] ),
- * exact integer accumulation (int8 MFMA on the widened codes), two fp32 multiplications, one rounding to fp16.
+ * exact integer accumulation (int8 MFMA on the widened codes; FP6 MFMA, exact as well, in large launches), two fp32 multiplications, one rounding to fp16.
  *   x_codes  u8 [T, n/2], x_scales fp16 [T]   : outputs of flatquant_transform_quant
  *   w_codes  u8 [m, n/2], w_scales fp16 [m]   : outputs of flatquant_weight_transform_quant
  *   out      fp16 [T, m], row t at out + t*out_stride halves, out_stride >= m.
