@@ -1030,6 +1030,23 @@ def test_w4a4_gemm_tiles_are_exact(tuning, form, T, m, n):
     assert torch.equal(out, (sums * xs.float()[:, None] * ws.float()[None, :]).half())
 
 
+@pytest.mark.parametrize("low", [-8, 4, 7])
+def test_w4a4_gemm_fp6_longest_rows(tuning, low):
+    """The largest n: with codes of 7 throughout the offset sums reach 225 n = 14.7e6, just below 2^24, and are still exact."""
+    T, m, n = 70, 130, 65536
+    tuning("FLATQUANT_GEMM_TILED", 1)
+    tuning("FLATQUANT_GEMM_WIDE", 2)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(low + 8)
+    q = [torch.randint(low, 8, (r, n), generator=g, device="cuda", dtype=torch.int8) for r in (T, m)]
+    packed = [((c[:, 0::2] & 15) | (c[:, 1::2] << 4)).view(torch.uint8) for c in q]
+    xs, ws = (torch.rand(r, generator=g, device="cuda").half() * 0.01 for r in (T, m))
+    out = torch.full((T, m), float("nan"), dtype=torch.float16, device="cuda")
+    fq.flatquant_w4a4_gemm(packed[0], xs, packed[1], ws, T, m, n, out, m, stream=torch.cuda.current_stream())
+    sums = (q[0].double() @ q[1].double().t()).float()      # integers below 2^22
+    assert torch.equal(out, (sums * xs.float()[:, None] * ws.float()[None, :]).half())
+
+
 @pytest.mark.parametrize("knob,value,T,m,n", [("FLATQUANT_GEMM_WIDE", 1, 300, 260, 768), ("FLATQUANT_GEMM_WIDE", 1, 513, 129, 256),
                                               ("FLATQUANT_GEMM_WIDE", 0, 2048, 4224, 512), ("FLATQUANT_GEMM_TILED", 1, 33, 96, 768),
                                               ("FLATQUANT_GEMM_TILED", 1, 100, 200, 1024)])
