@@ -41,7 +41,9 @@ struct MxGemmDev {
 };
 
 // TI x TJ: MFMA tiles per wave (tokens x channels), WM x WN: waves, NST: LDS stages, LA: K steps that an operand is read
-// from LDS ahead of its MFMAs.
+// from LDS ahead of its MFMAs.  Off: offsets of a tile's rows from its first one.  32 bits hold 256 rows of n / 2 bytes up
+// to n = 2^25 (kOff32MaxN); longer rows take 64.
+constexpr int kOff32MaxN = 1 << 25;
 template <int TI, int TJ, int WM, int WN, int NST>
 struct MxTile {
     static constexpr int NW = WM * WN;
@@ -53,7 +55,7 @@ struct MxTile {
     static_assert(NW * 32 * OPITCH <= STAGE && LDS <= 160 * 1024 && NST >= 2, "LDS budget");
 };
 
-template <int TI, int TJ, int WM, int WN, int NST, int LA>
+template <int TI, int TJ, int WM, int WN, int NST, int LA, typename Off>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI * TJ > 4 ? 1 : 2, TI * TJ > 4 ? 1 : 2))) void mxfp4_gemm_kernel(MxGemmDev p) {
     using L = MxTile<TI, TJ, WM, WN, NST>;
     constexpr int NW = L::NW, TOK = L::TOK, CH = L::CH, STAGE = L::STAGE, A_TILE = TOK * XKB, NOP = TI + TJ;
@@ -61,6 +63,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
     constexpr int NPC = L::ROWS / 128;                              // 1 KB pieces of exponents per iteration
     constexpr int NKP = XKB / 32;                                   // K steps (64 codes) per iteration
     static_assert(NKP == 4 && (LA == 1 || LA == 2), "exponent bytes and the operand ring below");
+    static_assert(TOK <= 256 && CH <= 256, "kOff32MaxN");
     constexpr int KB = NKP - LA;                                    // the steps before the iteration's barrier
     constexpr int RING = LA == 1 ? 2 : 4;
     constexpr int NQ = TI * TJ, RPS = NQ > 4 ? 2 : 1;               // MFMAs per step; LDS reads behind each of the first ones
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
     // order: per 128-row tile and iteration 1 KB in one piece) take one instruction per 128 rows; wave w brings piece w,
     // waves past the last piece repeat it, so that every wave counts the same number of loads.
     const unsigned char *abase, *bbase, *ebase;
-    uint32_t aoff[NLA], boff[NLB];
+    Off aoff[NLA], boff[NLB];
     const int pc = w < NPC ? w : NPC - 1;
     auto set_source = [&](const Pos& t) {
         abase = p.xc + t.t0 * kbytes;
@@ -110,12 +113,12 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
 #pragma unroll
         for (int k = 0; k < NLA; ++k) {
             const int row = 8 * (NLA * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-            aoff[k] = (uint32_t)(row < arows ? row : arows - 1) * (uint32_t)kbytes + 16 * ch;
+            aoff[k] = (Off)(row < arows ? row : arows - 1) * (Off)kbytes + 16 * ch;
         }
 #pragma unroll
         for (int k = 0; k < NLB; ++k) {
             const int row = 8 * (NLB * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-            boff[k] = (uint32_t)(row < brows ? row : brows - 1) * (uint32_t)kbytes + 16 * ch;
+            boff[k] = (Off)(row < brows ? row : brows - 1) * (Off)kbytes + 16 * ch;
         }
         const bool tok = pc < TOK / 128;
         const int64_t tile = tok ? (t.t0 >> 7) + pc : (int64_t)(t.o0 >> 7) + pc - TOK / 128;
@@ -498,18 +501,18 @@ static hipError_t mx_skinny_launch(const MxGemmDev& d, hipStream_t stream, int t
     return hipErrorInvalidValue;
 }
 
-template <int TI, int TJ, int WM, int WN, int NST, int LA>
+template <int TI, int TJ, int WM, int WN, int NST, int LA, typename Off = uint32_t>
 static hipError_t mx_tile_launch(const MxGemmDev& d, hipStream_t stream) {
     using L = MxTile<TI, TJ, WM, WN, NST>;
     static OccCache cache;
     int occ = 0;
-    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA>), 64 * L::NW, L::LDS, cache, occ);
+    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA, Off>), 64 * L::NW, L::LDS, cache, occ);
     if (e != hipSuccess) return e;
     // persistent: every XCD (eight of them) gets as many workgroups as it holds at once, or as it has tiles
     const int64_t tiles = ((d.T + L::TOK - 1) / L::TOK) * ((d.m + L::CH - 1) / L::CH);
     const int64_t per_xcd = (tiles + 7) / 8, resident = (int64_t)occ * cu_count() / 8;
     const unsigned grid = 8 * (unsigned)(per_xcd < resident ? per_xcd : resident);
-    return launch((mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA>), dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
+    return launch((mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA, Off>), dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
 }
 
 // Tile form: 0 = 128 x 128 (two workgroups per CU), 1 = 256 x 128, 2 = 256 x 256 (one per CU).  The time of a launch goes
@@ -545,6 +548,10 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
         if (ring_max >= 0 ? a.T <= ring_max : (2 * tiled_wgs <= cu_count() && a.T <= 4096))
             return mx_skinny_launch<8>(d, stream, (int)((a.T + 63) / 64));
     }
+    // Rows whose offsets inside a tile need 64 bits: the smallest tile, whatever the form asked for.  They are far beyond
+    // what the transform produces (n <= 32768), so there is one instance for them (1024 x 2304 x 33686272: 142.8 ms; 143.8
+    // with the two-stage kernel mentioned at the top, all 64-bit addresses).
+    if (d.n > kOff32MaxN) return mx_tile_launch<2, 2, 2, 2, 2, 1, uint64_t>(d, stream);
     switch (env_int("FLATQUANT_GEMM_WIDE", mx_tile_form(d))) {
         case 1: return mx_tile_launch<4, 2, 2, 2, 3, 2>(d, stream);
         case 2: return mx_tile_launch<4, 4, 2, 2, 2, 1>(d, stream);

@@ -1,8 +1,9 @@
-"""Maximum sizes: tensors past 2^31 elements and 2^32 bytes.  Every kernel forms its row addresses in 64 bits; these
-cases put token rows, code rows and output rows on both sides of the 2^31- and 2^32-byte marks and compare sampled
-rows (the first, the last, the ones around each mark, a random handful) with the oracle.  The inputs are seeded
-normal deviates drawn on the device (several GB: too large to build on the host); the sampled rows are copied back and
-the oracle gets exactly those bytes."""
+"""Maximum sizes: tensors past 2^31 elements and 2^32 bytes.  Every kernel forms its row addresses in 64 bits (inside a
+tile, 32-bit offsets from a 64-bit base where they cannot wrap); these cases put token rows, code rows and output rows
+on both sides of the 2^31- and 2^32-byte marks and compare sampled rows (the first, the last, the ones around each
+mark, a random handful) with the oracle.  The inputs are seeded normal deviates drawn on the device (several GB: too
+large to build on the host); the sampled rows are copied back and the oracle gets exactly those bytes.  The last case
+has a closed form instead."""
 import numpy as np
 import pytest
 import torch
@@ -117,3 +118,30 @@ def test_product_output_past_4_gib(kind):
         tol = 2.0 ** -11 * np.abs(y) * (1 + 2.0 ** -9) + n * 2.0 ** -24 * ab + 2.0 ** -25
         assert np.all(np.isfinite(got)) and np.all(np.abs(got - y) <= tol)
     print(f"[parity] rows {rows.tolist()} agree with the oracle", flush=True)
+
+
+@pytest.mark.parametrize("form", [0, 1, 2])
+@pytest.mark.parametrize("side", ["tokens", "channels"])
+def test_mxfp4_product_tile_of_rows_past_4_gib(tuning, side, form):
+    """Rows so long that the 256 rows of one tile span more than 2^32 bytes (n = 33,686,272: row 255 starts 32,384 bytes
+    past the mark).  One operand is all ones, the other has a code of its own in the first and in the last byte of every
+    row and zeros between, so a row read anywhere else has another sum.  Values of the FP4 grid, sums exact."""
+    rows, few, n = 256, 2, 33_686_272
+    tuning("FLATQUANT_GEMM_TILED", 1)
+    tuning("FLATQUANT_GEMM_WIDE", form)
+    grid = torch.tensor([0.0, 0.5, 1.0, 1.5, 2.0, 3.0, 4.0, 6.0], device="cuda")
+    r = torch.arange(rows, device="cuda")
+    first, last = 1 + r % 7, 1 + (r // 7) % 7
+    long = torch.zeros((rows, n // 2), dtype=torch.uint8, device="cuda")
+    long[:, 0], long[:, -1] = first.to(torch.uint8), last.to(torch.uint8)
+    ones = torch.full((few, n // 2), 0x22, dtype=torch.uint8, device="cuda")
+    exps = {k: torch.full((fq.fq_mxfp4_tiled_scale_bytes(k, n),), 127, dtype=torch.uint8, device="cuda") for k in (rows, few)}
+    print(f"[case] mxfp4 product, {rows} long rows as {side}, form={form} n={n}", flush=True)
+    want = (grid[first] + grid[last]).half()
+    a, b = (long, exps[rows]), (ones, exps[few])
+    T, m = (rows, few) if side == "tokens" else (few, rows)
+    out = torch.full((T, m), float("nan"), dtype=torch.float16, device="cuda")
+    x, w = (a, b) if side == "tokens" else (b, a)
+    fq.flatquant_mxfp4_gemm(*x, *w, T, m, n, out, m, stream=torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert torch.equal(out, want[:, None].expand(T, m) if side == "tokens" else want[None, :].expand(T, m))
