@@ -1030,6 +1030,32 @@ def test_w4a4_gemm_tiles_are_exact(tuning, form, T, m, n):
     assert torch.equal(out, (sums * xs.float()[:, None] * ws.float()[None, :]).half())
 
 
+@pytest.mark.parametrize("form,T,m,n,pad", [(2, 4400, 4500, 512, 0), (2, 4353, 4105, 768, 7), (2, 4353, 4105, 1024, 1), (2, 4353, 4105, 1280, 0),
+                                            (0, 4353, 4105, 768, 7), (1, 4353, 4105, 768, 7), (None, 8000, 8100, 2304, 4)])
+def test_w4a4_gemm_tiles_follow_each_other(tuning, form, T, m, n, pad):
+    """More 256 x 256 tiles than workgroups are resident (306 and more for 256) and at least two K iterations: the loads of a
+    tile's last iteration belong to the next tile, its output leaves through a stage that then takes loads again, and the
+    row sums start over.  Ragged on both sides; the output leaves in 16-byte pieces (row strides 4112 and 8104), dwords
+    (4500 and 4106) and halves (4105); the last case goes through the library's own choice of form.
+    Equal to the integer product as above (64 n < 2^24), twice: the second launch starts with what the first one left in LDS."""
+    if form is not None:
+        tuning("FLATQUANT_GEMM_TILED", 1)
+        tuning("FLATQUANT_GEMM_WIDE", form)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + m + n)
+    q = [torch.randint(-8, 8, (r, n), generator=g, device="cuda", dtype=torch.int8) for r in (T, m)]
+    packed = [((c[:, 0::2] & 15) | (c[:, 1::2] << 4)).view(torch.uint8) for c in q]
+    xs, ws = (torch.rand(r, generator=g, device="cuda").half() for r in (T, m))
+    sums = q[0].float() @ q[1].float().t()
+    want = (sums * xs.float()[:, None] * ws.float()[None, :]).half()
+    print(f"[case] w4a4 tiles in a row: form={form} T={T} m={m} n={n} pad={pad}", flush=True)
+    for _ in range(2):
+        out = torch.full((T, m + pad), float("nan"), dtype=torch.float16, device="cuda")
+        fq.flatquant_w4a4_gemm(packed[0], xs, packed[1], ws, T, m, n, out, m + pad, stream=torch.cuda.current_stream())
+        assert torch.equal(out[:, :m], want)
+        assert bool(torch.isnan(out[:, m:]).all())
+
+
 @pytest.mark.parametrize("low", [-8, 4, 7])
 def test_w4a4_gemm_fp6_longest_rows(tuning, low):
     """The largest n: with codes of 7 throughout the offset sums reach 225 n = 14.7e6, just below 2^24, and are still exact."""
