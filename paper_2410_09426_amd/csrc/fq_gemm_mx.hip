@@ -520,6 +520,9 @@ static hipError_t mx_tile_launch(const MxGemmDev& d, hipStream_t stream) {
 // 39 / 24, 35 / 26 and 64 / 45.  (Measured, us for forms 0 / 1 / 2: 1024 x 4096 x 4096 15.8 / 17.0 / 26.5, 2048 x 4096 x
 // 4096 23.5 / 22.7 / 29.9, 3000 x 4096 x 4096 35.2 / 35.6 / 32.4, 4096 x 4096 x 4096 43.3 / 40.8 / 37.1, 2048 x 4096 x
 // 11008 53.2 / 49.6 / 60.3, 1024 x 11008 x 4096 34.4 / 35.2 / 31.3, 16384 x 8192 x 8192 635 / 567 / 510.)
+// Form 1 has three LDS stages: with fewer iterations than that (n < 768) its loads cannot run on into the next tile and it
+// is behind form 0 at every size (forms 0 / 1: 777 x 5120 x 256 5.6 / 6.4, 2048 x 4096 x 512 8.1 / 8.5, 4096 x 14336 x 512
+// 31.2 / 39.2, 15069 x 2510 x 256 22.3 / 27.0; at n = 768 2048 x 4096 12.1 / 10.0).
 static int mx_tile_form(const MxGemmDev& d) {
     const int64_t cu = cu_count();
     auto cost = [&](int64_t tok, int64_t ch, int64_t slots, int64_t full, int64_t half) {
@@ -527,7 +530,7 @@ static int mx_tile_form(const MxGemmDev& d) {
         return 2 * tiles <= slots ? half : (tiles + slots - 1) / slots * full;
     };
     const int64_t c0 = cost(128, 128, 2 * cu, 39, 24), c1 = cost(256, 128, cu, 35, 26), c2 = cost(256, 256, cu, 64, 45);
-    return c2 <= c0 && c2 <= c1 ? 2 : c1 <= c0 ? 1 : 0;
+    return c2 <= c0 && c2 <= c1 ? 2 : c1 <= c0 && d.n >= 3 * 2 * XKB ? 1 : 0;
 }
 
 hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
