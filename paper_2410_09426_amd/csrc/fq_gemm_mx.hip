@@ -515,9 +515,9 @@ static hipError_t mx_tile_launch(const MxGemmDev& d, hipStream_t stream) {
     return launch((mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA, Off>), dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
 }
 
-// Tile form: 0 = 128 x 128 (two workgroups per CU), 1 = 256 x 128, 2 = 256 x 256 (one per CU).  The time of a launch goes
+// Tile form: 0 = 128 x 128 (two workgroups per CU, or one with three stages), 1 = 256 x 128, 2 = 256 x 256 (one per CU).  The time of a launch goes
 // in rounds of what is resident at once; the cost of a round, full / at most half full, is what 8192 channels take in us:
-// 39 / 24, 35 / 26 and 64 / 45.  (Measured, us for forms 0 / 1 / 2: 1024 x 4096 x 4096 15.8 / 17.0 / 26.5, 2048 x 4096 x
+// 39 / 23, 35 / 26 and 64 / 45.  (Measured, us for forms 0 / 1 / 2: 1024 x 4096 x 4096 13.9 / 17.0 / 26.5, 2048 x 4096 x
 // 4096 23.5 / 22.7 / 29.9, 3000 x 4096 x 4096 35.2 / 35.6 / 32.4, 4096 x 4096 x 4096 43.3 / 40.8 / 37.1, 2048 x 4096 x
 // 11008 53.2 / 49.6 / 60.3, 1024 x 11008 x 4096 34.4 / 35.2 / 31.3, 16384 x 8192 x 8192 635 / 567 / 510.)
 // Form 1 has three LDS stages: with fewer iterations than that (n < 768) its loads cannot run on into the next tile and it
@@ -529,7 +529,7 @@ static int mx_tile_form(const MxGemmDev& d) {
         const int64_t tiles = ((d.T + tok - 1) / tok) * ((d.m + ch - 1) / ch);
         return 2 * tiles <= slots ? half : (tiles + slots - 1) / slots * full;
     };
-    const int64_t c0 = cost(128, 128, 2 * cu, 39, 24), c1 = cost(256, 128, cu, 35, 26), c2 = cost(256, 256, cu, 64, 45);
+    const int64_t c0 = cost(128, 128, 2 * cu, 39, 23), c1 = cost(256, 128, cu, 35, 26), c2 = cost(256, 256, cu, 64, 45);
     return c2 <= c0 && c2 <= c1 ? 2 : c1 <= c0 && d.n >= 3 * 2 * XKB ? 1 : 0;
 }
 
@@ -558,7 +558,13 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
     switch (env_int("FLATQUANT_GEMM_WIDE", mx_tile_form(d))) {
         case 1: return mx_tile_launch<4, 2, 2, 2, 3, 2>(d, stream);
         case 2: return mx_tile_launch<4, 4, 2, 2, 2, 1>(d, stream);
-        default: return mx_tile_launch<2, 2, 2, 2, 2, 1>(d, stream);
+        default:
+            // At most one 128 x 128 tile per CU: nobody else covers a workgroup's wait for its tiles, so a third stage takes the
+            // place of the second workgroup (us with two / three stages: 160 x 8896 x 2048 9.1 / 7.5, 4060 x 632 x 7168 22.7 /
+            // 16.3, 1024 x 4096 x 4096 15.6 / 12.7, 1024 x 4096 x 28672 85.6 / 63.9; a fourth one gains nothing: 7.7, 16.6,
+            // 12.9, 63.8).
+            if (((d.T + XT - 1) / XT) * ((d.m + XT - 1) / XT) <= cu_count()) return mx_tile_launch<2, 2, 2, 2, 3, 2>(d, stream);
+            return mx_tile_launch<2, 2, 2, 2, 2, 1>(d, stream);
     }
 }
 

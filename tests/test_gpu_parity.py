@@ -723,6 +723,14 @@ def test_mxfp4_gemm_every_tile_form(tuning, form, T, m, n):
     _mxfp4_gemm_case(T, m, n)
 
 
+@pytest.mark.parametrize("T,m,n", [(130, 1030, 512), (300, 260, 1024), (2048, 2048, 1280), (2049, 2040, 768)])
+def test_mxfp4_gemm_few_tiles(tuning, T, m, n):
+    """128 x 128 tiles, at most one per CU (three LDS stages; fewer iterations than stages, as many, more) and just above."""
+    tuning("FLATQUANT_GEMM_TILED", 1)
+    tuning("FLATQUANT_GEMM_WIDE", 0)
+    _mxfp4_gemm_case(T, m, n)
+
+
 @pytest.mark.parametrize("waves,depth,rows,T,m,n", [(16, 1, 32, 5, 100, 4096), (16, 2, 16, 64, 70, 2304), (4, 3, 32, 20, 330, 11008), (8, 8, 16, 40, 64, 4096),
                                                     (4, 1, 16, 1, 33, 256), (8, 2, 32, 9, 8200, 512), (8, 2, 16, 12, 8200, 512), (4, 2, 32, 64, 4096, 1024), (16, 3, 32, 120, 200, 2304), (4, 2, 16, 90, 100, 1024)])
 @pytest.mark.parametrize("kind", ["int4", "mxfp4"])
