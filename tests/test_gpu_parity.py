@@ -731,6 +731,37 @@ def test_mxfp4_gemm_few_tiles(tuning, T, m, n):
     _mxfp4_gemm_case(T, m, n)
 
 
+@pytest.mark.parametrize("form", [0, 1, 2])
+@pytest.mark.parametrize("T,m,n", [(300, 388, 1280), (2200, 2100, 512)])
+@pytest.mark.parametrize("kind", ["int4", "mxfp4"])
+def test_tiled_products_at_every_output_alignment(tuning, kind, T, m, n, form):
+    """Output rows that start on halves, dwords or 16-byte pieces, by their address and by their stride, leave the tiled kernels
+    by different stores: the same bits as into 16-byte aligned rows, and nothing beside them."""
+    tuning("FLATQUANT_GEMM_TILED", 1)
+    tuning("FLATQUANT_GEMM_WIDE", form)
+    g = torch.Generator(device="cuda").manual_seed(T + m + n)
+    codes = [torch.randint(0, 256, (r, n // 2), generator=g, device="cuda", dtype=torch.uint8) for r in (T, m)]
+    if kind == "int4":
+        product = fq.flatquant_w4a4_gemm
+        steps = [torch.rand(r, generator=g, device="cuda").half() * 0.1 for r in (T, m)]
+    else:
+        product = fq.flatquant_mxfp4_gemm
+        steps = [torch.randint(118, 126, (fq.fq_mxfp4_tiled_scale_bytes(r, n),), generator=g, device="cuda", dtype=torch.uint8) for r in (T, m)]
+
+    def run(offset, stride):
+        buf = torch.full((offset + T * stride + 16,), float("nan"), dtype=torch.float16, device="cuda")
+        product(codes[0], steps[0], codes[1], steps[1], T, m, n, buf[offset:], stride, stream=torch.cuda.current_stream())
+        rows = buf[offset:offset + T * stride].view(T, stride)
+        assert bool(torch.isnan(buf[:offset]).all()) and bool(torch.isnan(rows[:, m:]).all()) and bool(torch.isnan(buf[offset + T * stride:]).all())
+        return rows[:, :m]
+
+    want = run(0, 8 * (m // 8 + 1))
+    assert bool(torch.isfinite(want).all())
+    print(f"[case] output alignment {kind} form={form} T={T} m={m} n={n}", flush=True)
+    for offset, stride in ((0, m), (0, m + 1), (0, m + 2), (1, m), (1, m + 4), (2, m + 4), (8, m + 4), (4, m + 7)):
+        assert torch.equal(run(offset, stride), want), (offset, stride)
+
+
 @pytest.mark.parametrize("waves,depth,rows,T,m,n", [(16, 1, 32, 5, 100, 4096), (16, 2, 16, 64, 70, 2304), (4, 3, 32, 20, 330, 11008), (8, 8, 16, 40, 64, 4096),
                                                     (4, 1, 16, 1, 33, 256), (8, 2, 32, 9, 8200, 512), (8, 2, 16, 12, 8200, 512), (4, 2, 32, 64, 4096, 1024), (16, 3, 32, 120, 200, 2304), (4, 2, 16, 90, 100, 1024)])
 @pytest.mark.parametrize("kind", ["int4", "mxfp4"])
