@@ -794,17 +794,33 @@ hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
     }
     static OccCache ct, ctw;
     // Tile form (FLATQUANT_GEMM_WIDE forces one): int8 with 128 x 128 tiles, with 256 x 128 tiles when these still give every
-    // CU a workgroup (1), or FP6 with 256 x 256 tiles (2).  A launch takes rounds of one tile per CU, measured at n = 4096: 5 + 29 us
-    // per round of 256 x 128 int8 tiles, 9 + 43 us per round of FP6 tiles of twice the size, whose first pass over its
-    // code costs more.  (int8 / FP6, us: 2048 x 4096 x 4096 33.3 / 46.6, 3000 x 4096 x 4096 56.4 / 47.8, 4096 x 4096 x 4096
-    // 64.5 / 49.7, 1024 x 11008 x 4096 54.6 / 47.3, 2048 x 11008 x 4096 93.2 / 88.2, 777 x 5120 x 5120 34.7 / 52.8, 2048 x
-    // 4096 x 11008 77.0 / 95.4, 16384 x 8192 x 8192 888 / 615 - 672.  FP6 with 256 x 128 and 128 x 128 tiles is bound by the
-    // vector work and gains nothing over int8: 30.0 and 32.9 at 2048 x 4096 x 4096 with everything in the caches, but 41
-    // against 39 for the whole layer on fresh data.)
+    // CU a workgroup (1), or FP6 with 256 x 256 tiles (2).  A launch takes rounds of one tile per CU, measured at n = 4096: 5 + 29
+    // us per round of 256 x 128 int8 tiles, 9 + 43 us per round of FP6 tiles of twice the size, whose first pass over its
+    // code costs more.  Both parts grow with n, so their order holds from n = 1024 on.  (int8 / FP6, us: 2048 x 4096 x 4096 33.5 /
+    // 46.4, 3000 x 4096 x 4096 58.7 / 49.3, 4096 x 4096 x 4096 64.1 / 52.6, 1024 x 11008 x 4096 57.1 / 48.9, 2048 x 11008 x 4096
+    // 91.0 / 93.5, 2048 x 8192 x 14336 193 / 147, 8192 x 8192 x 1024 87.4 / 73.1, 777 x 5120 x 5120 33.2 / 49.8, 16384 x 8192 x
+    // 8192 835 - 857 / 613 - 646.  FP6 with 256 x 128 and 128 x 128 tiles is bound by the vector work and gains nothing over
+    // int8: 30.0 and 32.9 at 2048 x 4096 x 4096 with everything in the caches, but 41 against 39 for the whole layer on
+    // fresh data.)
+    // Shorter rows are one or two iterations, and output more than product: a round of FP6 tiles takes 11 us at n = 256 and 13 at
+    // n = 512, one of int8 tiles 6 and 7.5, and an int8 round on a part x of the CUs takes 0.6 + 0.4 x of that.  FP6 stays
+    // where its last round is nearly full (there the formula is not sharp enough) or comes out shorter all the same.  (int8 /
+    // FP6: 4230 x 8320 x 256, 2.2 rounds of FP6, 32.6 / 36.7; 10622 x 8576 x 256, 5.6, 64.1 / 69.1; 13407 x 8192 x 256, 6.6, 84.7 /
+    // 80.1; 4096 x 4096 x 256, 1, 16.2 / 15.2; 1429 x 8000 x 512, 0.75, 16.2 / 16.9; 9882 x 2496 x 512, 1.5, 32.3 / 29.5; 5144 x
+    // 5440 x 512, 1.8, 33.3 / 29.5.)  This is for rows of whole 128-byte lines; into others the int8 kernel's output costs
+    // more (1659 x 5716 x 256 29.7 / 20.0).
     const int64_t cu = cu_count();
     const int64_t wide_wgs = ((a.T + 255) / 256) * ((a.m + GT - 1) / GT), fp6_wgs = ((a.T + 255) / 256) * ((a.m + 255) / 256);
-    const int64_t int8_cost = 5 + (wide_wgs + cu - 1) / cu * 29, fp6_cost = 9 + (fp6_wgs + cu - 1) / cu * 43;
-    const int wide = env_int("FLATQUANT_GEMM_WIDE", wide_wgs < cu ? 0 : fp6_cost < int8_cost ? 2 : 1);
+    const int64_t int8_rounds = (wide_wgs + cu - 1) / cu, fp6_rounds = (fp6_wgs + cu - 1) / cu;
+    bool fp6 = wide_wgs >= cu && 9 + fp6_rounds * 43 < 5 + int8_rounds * 29;
+    if (fp6 && a.n <= 512 && ((reinterpret_cast<uintptr_t>(a.out) | (uintptr_t)(2 * a.out_stride)) & 127) == 0) {
+        const int64_t part = wide_wgs % cu;
+        const double int8_us = 3.2 + (wide_wgs / cu + (part ? 0.6 + 0.4 * part / cu : 0.0)) * (4.4 + 0.0061 * a.n);
+        const double fp6_us = 3.7 + fp6_rounds * (8.6 + 0.009 * a.n);
+        const bool full = 16 * fp6_wgs >= (a.n <= 256 ? 15 : 13) * fp6_rounds * cu;
+        fp6 = full || fp6_us < int8_us;
+    }
+    const int wide = env_int("FLATQUANT_GEMM_WIDE", fp6 ? 2 : wide_wgs >= cu ? 1 : 0);
     if (wide == 2) return fp6_launch(d, stream);
     if (wide) {
         hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_kernel<4>), 512, G_LDS_BYTES_WIDE, ctw, unused);
