@@ -183,7 +183,7 @@ fq_status flatquant_weight_transform_quant(const void* w, const void* A1, const 
  *   x_codes  u8 [T, n/2], x_scales fp16 [T]   : outputs of flatquant_transform_quant
  *   w_codes  u8 [m, n/2], w_scales fp16 [m]   : outputs of flatquant_weight_transform_quant
  *   out      fp16 [T, m], row t at out + t*out_stride halves, out_stride >= m.
- * n must be a multiple of 256 (and <= 65536, so that the int32 sums cannot overflow); code tensors 16-byte aligned.  T == 0 or m == 0 returns FQ_OK.
+ * n must be a multiple of 256 (and <= 65536, so that the sums are exact: below 2^31 in int32, below 2^24 on FP6 MFMA); code tensors 16-byte aligned.  T == 0 or m == 0 returns FQ_OK.
  * Values beyond the fp16 range come out as infinities.
  */
 fq_status flatquant_w4a4_gemm(const uint8_t* x_codes, const void* x_scales, const uint8_t* w_codes, const void* w_scales,
@@ -277,7 +277,8 @@ int fq_abi_version(void);
  * shot / persistent; 5 also forces the wave-per-token kernel of the left-factor-only case), FLATQUANT_WAVE_TPW (2 / 4 / 8 waves per workgroup of that kernel), FLATQUANT_PROBE_SHAPE (0..2: launch
  * shape of flatquant_stream_probe), FLATQUANT_WG_PER_CU, FLATQUANT_KV_WG_PER_CU (cap on resident
  * workgroups), FLATQUANT_FORCE_GENERIC (1: general kernel on shapes the specialised ones would take),
- * FLATQUANT_GEMM_TILED (1: tiled product for any T), FLATQUANT_GEMM_WIDE (0 / 1 / 2: 128 x 128, 256 x 128 or, MXFP4, 256 x 256 tiles),
+ * FLATQUANT_GEMM_TILED (1: tiled product for any T), FLATQUANT_GEMM_WIDE (0 / 1 / 2: 128 x 128, 256 x 128 or 256 x 256
+ * tiles, the last ones on FP6 MFMA for W4A4; any other value leaves the choice to the library),
  * FLATQUANT_GEMM_ROWS (16 / 32 output channels per workgroup), FLATQUANT_GEMM_WAVES (4 / 8 / 16) and
  * FLATQUANT_GEMM_DEPTH (1..8 line slots per wave) of the few-token products, FLATQUANT_GEMM_RING_MAX_T (token count up to
  * which the few-token kernel is used), FLATQUANT_KV_FOLD_HEADS (0: a shared P_h is applied head by head like separate

@@ -820,7 +820,8 @@ hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
         const bool full = 16 * fp6_wgs >= (a.n <= 256 ? 15 : 13) * fp6_rounds * cu;
         fp6 = full || fp6_us < int8_us;
     }
-    const int wide = env_int("FLATQUANT_GEMM_WIDE", fp6 ? 2 : wide_wgs >= cu ? 1 : 0);
+    const int rule = fp6 ? 2 : wide_wgs >= cu ? 1 : 0, asked = env_int("FLATQUANT_GEMM_WIDE", rule);
+    const int wide = asked >= 0 && asked <= 2 ? asked : rule;
     if (wide == 2) return fp6_launch(d, stream);
     if (wide) {
         hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_kernel<4>), 512, G_LDS_BYTES_WIDE, ctw, unused);

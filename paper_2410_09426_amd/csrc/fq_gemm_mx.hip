@@ -180,9 +180,8 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
         }
     };
     // the next iteration has arrived (this wave's part, then everybody's) and nobody reads the current one's stage any more
-    auto arrive = [&](int pending) {
-        if (pending) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NST - 2) * NL) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    auto arrive = [&]() {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NST - 2) * NL) : "memory");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -199,7 +198,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
     set_source(cur);
 #pragma unroll
     for (int s = 0; s + 1 < NST; ++s) issue(s, s * STAGE, 0, NL);
-    arrive(1);
+    arrive();
     int st = 0, stl = (NST - 1) * STAGE;     // stage of the current iteration, and the one to be loaded next
     auto advance = [&](int stage) { return stage + STAGE == NST * STAGE ? 0 : stage + STAGE; };
     read_exps(0);
@@ -222,7 +221,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
         // steps 0 .. KB - 1 of iteration 0; loads of iteration NST - 1
 #pragma unroll
         for (int kp = 0; kp < KB; ++kp) step(kp, st, NST - 1, stl, kp, 0, LSTEPS < KB ? LSTEPS : KB);
-        arrive(1);
+        arrive();
         int lit = NST;                       // iteration to be loaded next
         auto body = [&]() {
             const int stn = advance(st);
@@ -233,7 +232,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
             next_exps();
 #pragma unroll
             for (int kp = 0; kp < KB; ++kp) step(kp, stn, lit, stl, kp + LA, 0, LSTEPS);
-            arrive(1);
+            arrive();
             st = stn;
             ++lit;
         };
@@ -322,7 +321,7 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
             set_source(cur);
 #pragma unroll
             for (int s = 0; s + 1 < NST; ++s) issue(s, s * STAGE, 0, NL);
-            arrive(1);
+            arrive();
             st = 0;
             stl = (NST - 1) * STAGE;
             read_exps(0);
@@ -578,7 +577,8 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
     // what the transform produces (n <= 32768), so there is one instance for them (1024 x 2304 x 33686272: 142.8 ms; 143.8
     // with the two-stage kernel mentioned at the top, all 64-bit addresses).
     if (d.n > kOff32MaxN) return mx_tile_launch<2, 2, 2, 2, 2, 1, uint64_t>(d, stream);
-    switch (env_int("FLATQUANT_GEMM_WIDE", mx_tile_form(d))) {
+    const int rule = mx_tile_form(d), asked = env_int("FLATQUANT_GEMM_WIDE", rule);
+    switch (asked >= 0 && asked <= 2 ? asked : rule) {
         case 1: return mx_tile_launch<4, 2, 2, 2, 3, 2>(d, stream);
         case 2: return mx_tile_launch<4, 4, 2, 2, 2, 1>(d, stream);
         default:

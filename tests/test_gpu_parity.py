@@ -843,6 +843,18 @@ def test_ring_kernel_overrides_out_of_range_are_launch_errors(tuning, knob, valu
     assert bool(torch.isnan(out).all())
 
 
+@pytest.mark.parametrize("value", [-1, 3])
+@pytest.mark.parametrize("kind", ["int4", "mxfp4"])
+def test_tile_form_override_out_of_range_leaves_the_choice_to_the_library(tuning, kind, value):
+    """Values that name no tile form are accepted by both products and change nothing."""
+    tuning("FLATQUANT_GEMM_TILED", 1)
+    tuning("FLATQUANT_GEMM_WIDE", value)
+    if kind == "int4":
+        _w4a4_case(300, 388, 512, 0)
+    else:
+        _mxfp4_gemm_case(300, 388, 512)
+
+
 def test_int4_product_rows_do_not_depend_on_the_launch(tuning):
     """Integer sums and one fixed order of the two fp32 multiplications: a token's output row has the same bits whether it
     is computed alone, among 40 tokens (ring kernel), among 700 (tiled kernel) or by any forced form."""
