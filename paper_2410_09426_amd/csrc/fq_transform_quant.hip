@@ -66,6 +66,10 @@ __device__ __forceinline__ uint32_t nibble(float y, float inv) {
 // MX: MXFP4 output for the shapes the specialised kernels do not take (n2 not a multiple of 32, where a block of 32
 // consecutive channels straddles rows of X~ and column slabs): the token's Y is staged in LDS as fp32 in channel order,
 // then one thread per block takes its 32 values, forms the shared exponent and converts.
+// Up to 64 rows two waves per SIMD are asked for: in workgroups of up to four waves the compiler otherwise takes the registers
+// of the second one (accumulation registers beside 256 others), and a CU holds half as many tokens.  Without / with the
+// request, us: 60 x 88 4096 tokens 53.0 / 30.5, 60 x 120 57.4 / 33.6, 56 x 92 MXFP4 54.4 / 33.0, 60 x 24 at one to 4096 tokens
+// 5 - 9 % (up to 32 rows -7 .. +18 %, larger workgroups the same code).  With more than 64 rows one wave per SIMD has to do.
 template <int A, int B, bool P1LDS, bool MX = false>
 __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(A <= 2 ? 2 : 1))) void tq_kernel(TqDev p) {
     constexpr int NT = 64 * B;
@@ -92,10 +96,11 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(A <= 2 ?
 
     // ---- one-off: the constant factors.  Every element is a 2-byte load of its own (any n1, n2 and alignment), and all of
     // them are requested before the first one is used: bounds are the buffer descriptor's (rows past the end, and columns
-    // past it through an offset that is out of range, read as zero, and so does all of a left-out factor), so nothing branches around a load.  (With a test around
-    // each load, and around each request of a token's chunks, every one of them cost its own latency.  Before / now, us: 64 x 80
-    // one token 12.9 / 6.2, 777 tokens 28.9 / 11.6, 16384 tokens 328 / 98; 64 x 172 14.8 / 9.3, 31.4 / 25.6, 389 / 319;
-    // 30 x 34 6.1 / 4.6, 7.3 / 6.2, 30.8 / 26.6; 128 x 250 27.4 / 19.8, 148 / 112, 8192 tokens 1186 / 934.)
+    // past it through an offset that is out of range, read as zero, and so does all of a left-out factor), so nothing branches
+    // around a load.  (With a test around each load, and around each request of a token's chunks, every one of them cost its
+    // own latency.  Before / now, us: 64 x 80 one token 12.9 / 6.2, 777 tokens 28.9 / 11.6, 16384 tokens 328 / 98, the last two
+    // with the second wave per SIMD above; 64 x 172 14.8 / 9.3, 31.4 / 25.6, 389 / 319; 30 x 34 6.1 / 4.6, 7.3 / 6.2, 30.8 /
+    // 26.6; 128 x 250 27.4 / 19.8, 148 / 112, 8192 tokens 1186 / 934.)
     constexpr int kOut = 0x40000000;             // byte offset past any factor
     const __amdgpu_buffer_rsrc_t p1buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(p.P1), 0, p.P1 ? n1 * n1 * 2 : 0, 0x00020000);
     const __amdgpu_buffer_rsrc_t p2buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(p.P2), 0, p.P2 ? n2 * n2 * 2 : 0, 0x00020000);
