@@ -234,10 +234,11 @@ __global__ __launch_bounds__(128 * TW) __attribute__((amdgpu_waves_per_eu(2))) v
 // with the row sums of the codes (one v_dot8 per dword) taken on the way.
 // FP6 MFMAs have twice the rate of int8 ones and are held back less by the power limit: alone, for the 2.2e12 operations of
 // 16384 x 8192 x 8192 on random codes, they take 303 us (328 with sign and magnitude in place of the offset), int8 ones 531.
-// What bounds the kernel there (615 - 672 us; 888 with the int8 kernel above): one wave per SIMD issues in order, and its
-// slots are busy 62 % of the time (some 200 instructions per 16 MFMAs; the MFMA pipe 37 %), 25 % go to waits for the tiles.
-// Without the row sums 554, without loads as well 483.  Two waves per SIMD (eight of 128 x 64) spread every weight row
-// four times: 697.  Row sums by one of the two waves that share a row: the same time, twice the code.
+// What bounds the kernel there (613 - 672 us from box to box; 835 - 888 with the int8 kernel above): one wave per SIMD issues in
+// order, and it issues in 68 % of its cycles (12.0 vector instructions per MFMA, the MFMA among them: spreading and row
+// sums); waits for the tiles take 13 %, the MFMA pipe is busy 37 % of the time, at 2.0 GHz.  Without the row sums 554, without
+// loads as well 483.  Two waves per SIMD (eight of 128 x 64) spread every weight row four times: 697.  Row sums by one of
+// the two waves that share a row: the same time, twice the code.
 constexpr unsigned kSpreadA0 = 0x0F00F00Fu, kSpreadA1 = 0xF00F00F0u, kSpreadA2 = 0x00F00F00u;   // fields that do not move
 constexpr unsigned kSpreadM0 = 0xCF3CF3CFu, kSpreadM1 = 0xF3CF3CF3u, kSpreadM2 = 0x3CF3CF3Cu;   // the low 4 bits of all fields
 constexpr unsigned kSpreadX0 = 0x08208208u, kSpreadX1 = 0x82082082u, kSpreadX2 = 0x20820820u;   // bit 3 of all fields

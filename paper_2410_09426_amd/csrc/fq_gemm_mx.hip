@@ -537,11 +537,11 @@ static hipError_t mx_tile_launch(const MxGemmDev& d, hipStream_t stream) {
                : mx_tile_launch_rows<TI, TJ, WM, WN, NST, LA, Off, false>(d, stream);
 }
 
-// Tile form: 0 = 128 x 128 (two workgroups per CU, or one with three stages), 1 = 256 x 128, 2 = 256 x 256 (one per CU).  The time of a launch goes
-// in rounds of what is resident at once; the cost of a round, full / at most half full, is what 8192 channels take in us:
-// 39 / 23, 35 / 26 and 64 / 45.  (Measured, us for forms 0 / 1 / 2: 1024 x 4096 x 4096 13.9 / 17.0 / 26.5, 2048 x 4096 x
-// 4096 23.5 / 22.7 / 29.9, 3000 x 4096 x 4096 35.2 / 35.6 / 32.4, 4096 x 4096 x 4096 43.3 / 40.8 / 37.1, 2048 x 4096 x
-// 11008 53.2 / 49.6 / 60.3, 1024 x 11008 x 4096 34.4 / 35.2 / 31.3, 16384 x 8192 x 8192 635 / 567 / 510.)
+// Tile form: 0 = 128 x 128 (two workgroups per CU, or one with three stages), 1 = 256 x 128, 2 = 256 x 256 (one per CU).  The
+// time of a launch goes in rounds of what is resident at once; the cost of a round, full / at most half full, is what 8192
+// channels take in us: 39 / 23, 35 / 26 and 64 / 45.  (Measured, us for forms 0 / 1 / 2: 1024 x 4096 x 4096 13.9 / 17.0 / 26.5,
+// 2048 x 4096 x 4096 23.5 / 22.7 / 29.9, 3000 x 4096 x 4096 35.2 / 35.6 / 32.4, 4096 x 4096 x 4096 43.3 / 40.8 / 37.1, 2048 x
+// 4096 x 11008 53.2 / 49.6 / 60.3, 1024 x 11008 x 4096 34.4 / 35.2 / 31.3, 16384 x 8192 x 8192 635 / 567 / 510.)
 // Form 1 has three LDS stages: with fewer iterations than that (n < 768) its loads cannot run on into the next tile and it
 // is behind form 0 at every size (forms 0 / 1: 777 x 5120 x 256 5.6 / 6.4, 2048 x 4096 x 512 8.1 / 8.5, 4096 x 14336 x 512
 // 31.2 / 39.2, 15069 x 2510 x 256 22.3 / 27.0; at n = 768 2048 x 4096 12.1 / 10.0).
