@@ -126,7 +126,7 @@ def test_mxfp4_product_tile_of_rows_past_4_gib(tuning, side, form):
     """Rows so long that the 256 rows of one tile span more than 2^32 bytes (n = 33,686,272: row 255 starts 32,384 bytes
     past the mark).  One operand is all ones, the other has a code of its own in the first and in the last byte of every
     row and zeros between, so a row read anywhere else has another sum.  Values of the FP4 grid, sums exact."""
-    rows, few, n = 256, 2, 33_686_272
+    rows, few, n = 256, 3, 33_686_272            # three output channels: rows that leave in halves
     tuning("FLATQUANT_GEMM_TILED", 1)
     tuning("FLATQUANT_GEMM_WIDE", form)
     grid = torch.tensor([0.0, 0.5, 1.0, 1.5, 2.0, 3.0, 4.0, 6.0], device="cuda")
