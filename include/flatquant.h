@@ -278,7 +278,7 @@ int fq_abi_version(void);
  * shape of flatquant_stream_probe), FLATQUANT_WG_PER_CU, FLATQUANT_KV_WG_PER_CU (cap on resident
  * workgroups), FLATQUANT_FORCE_GENERIC (1: general kernel on shapes the specialised ones would take),
  * FLATQUANT_GEMM_TILED (1: tiled product for any T), FLATQUANT_GEMM_WIDE (0 / 1 / 2: 128 x 128, 256 x 128 or 256 x 256
- * tiles, the last ones on FP6 MFMA for W4A4; any other value leaves the choice to the library),
+ * tiles, the last two on FP6 MFMA for W4A4; W4A4 only, 4: 160 x 128; any other value leaves the choice to the library),
  * FLATQUANT_GEMM_ROWS (16 / 32 output channels per workgroup), FLATQUANT_GEMM_WAVES (4 / 8 / 16) and
  * FLATQUANT_GEMM_DEPTH (1..8 line slots per wave) of the few-token products, FLATQUANT_GEMM_RING_MAX_T (token count up to
  * which the few-token kernel is used), FLATQUANT_KV_FOLD_HEADS (0: a shared P_h is applied head by head like separate

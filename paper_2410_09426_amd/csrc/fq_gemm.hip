@@ -3,20 +3,20 @@
 // linear layers; Sec. 3.3: the transform + quantization kernel feeds an INT4 GEMM).
 //
 // Both operands arrive as packed 4-bit two's-complement codes, K contiguous (activations [T, n/2], weights [m, n/2]),
-// which is the operand order of an MFMA for C = A B^T.  The codes are widened to int8 on the fly without a sign
-// extension: for a packed dword w, (w << 4) & 0xF0F0F0F0 holds 16 q of the even channels and w & 0xF0F0F0F0 holds 16 q
-// of the odd channels, as signed bytes.  Both operands are widened the same way, so the K order inside an MFMA is
-// the same permutation for both and every product carries a factor 256 that the epilogue divides out exactly.
-// v_mfma_i32_32x32x32_i8 accumulates in int32 (|sum| <= 128 * 128 * n < 2^31 for n <= 65536).  Large launches widen to FP6
-// instead (w4a4_fp6_kernel, further down).
-//
-// Workgroup: 4 waves, C tile 128 tokens x 128 output channels (or 8 waves, 256 x 128, when the launch has enough such
-// tiles for every CU), each wave 64 x 64 (2 x 2 MFMA tiles; the weights are
-// the MFMA's first operand so that a lane ends up with runs of 4 consecutive output channels of one token).  K advances by
-// 256 codes (128 bytes = one cache line per row) per iteration through double-buffered LDS tiles, one barrier per
-// iteration; the tiles go from global memory straight into LDS, a whole iteration before they are read.
-// Launches whose 128 x 128 tiles would reach at most half of the CUs (decode, short prefill chunks) take the few-token
-// kernel further down instead.
+// which is the operand order of an MFMA for C = A B^T.  The codes become MFMA operands in registers, both sides in the same way,
+// so that the K order inside an MFMA is the same permutation for both:
+//  * int8: for a packed dword w, (w << 4) & 0xF0F0F0F0 holds 16 q of the even channels and w & 0xF0F0F0F0 holds 16 q of the odd
+//    channels, as signed bytes; every product carries a factor 256.  v_mfma_i32_32x32x32_i8 accumulates in int32 (|sum| <= 128 *
+//    128 * n < 2^31 for n <= 65536).
+//  * FP6 (E2M3): the code offset to q + 8 = 0 .. 15 IS the bit pattern of (q + 8) / 8 (subnormal up to 7 / 8, the first binade up to
+//    15 / 8), so the codes need only be spread from 4-bit to 6-bit fields.  The sums are exact: every product is an integer / 64
+//    and the total at most 225 n / 64, which fits 24 bits.  The offset leaves in the epilogue, with the row sums of the codes (one
+//    v_dot8 per dword) taken on the way.
+// The weights are the MFMA's first operand, so that a lane ends up with runs of 4 consecutive output channels of one token.
+// Many tokens take the tiled kernel; launches whose 128 x 128 tiles would reach at most half of the CUs (decode, short prefill
+// chunks) take the few-token kernel further down.
+#include <type_traits>
+
 #include "fq_internal.h"
 
 namespace fq {
@@ -24,17 +24,12 @@ namespace fq {
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
-constexpr int GT = 128;               // tile edge, tokens and output channels
 constexpr int GKB = 128;              // packed bytes of K per row and iteration (256 codes)
-constexpr int GPITCH = GKB;           // LDS row pitch: rows are written by global-to-LDS loads, 8 whole rows per wave and
-                                      // instruction, so there is no padding; the 16-byte chunks of a row are swizzled instead
-constexpr int G_NT = 256;
-constexpr int G_TILE_BYTES = GT * GPITCH;
-constexpr int G_LDS_BYTES = 4 * G_TILE_BYTES + GT * 4;   // A and B, two buffers each, + the weight steps of the tile
-constexpr int G_LDS_BYTES_WIDE = 6 * G_TILE_BYTES + GT * 4;   // 256-token tile: A twice the size
 
 struct GemmDev {
     const uint8_t* xc;
@@ -54,239 +49,83 @@ __device__ __forceinline__ void widen(const u32x4 w, i32x4& s0, i32x4& s1) {
     s1 = i32x4{(int)((w[2] << 4) & M), (int)(w[2] & M), (int)((w[3] << 4) & M), (int)(w[3] & M)};
 }
 
-// TW = waves along the token axis: 2 -> C tile 128 tokens x 128 channels (4 waves), 4 -> 256 x 128 (8 waves): a quarter
-// less operand traffic from L2 per product term, for launches with enough 256-token tiles to fill the chip.
-template <int TW>
-__global__ __launch_bounds__(128 * TW) __attribute__((amdgpu_waves_per_eu(2))) void w4a4_kernel(GemmDev p) {
-    constexpr int GTM = 64 * TW;                       // tokens per tile
-    constexpr int NW = 2 * TW;                         // waves
-    constexpr int A_TILE = GTM * GPITCH, B_TILE = GT * GPITCH, STAGE = A_TILE + B_TILE;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int tid = threadIdx.x;
-    const int l = tid & 63, c = l & 31, h = l >> 5;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = w % TW, wn = w / TW;
-    const int64_t t0 = (int64_t)blockIdx.x * GTM;
-    const int o0 = blockIdx.y * GT;
-    const int64_t kbytes = p.n / 2;
-    const int nk = p.n / (2 * GKB);
-
-    // Tile loads go from global memory straight into LDS (global_load_lds_dwordx4: lane i of a wave writes 16 bytes at
-    // the wave's LDS base + 16 i, from any global address).  One instruction fills 8 rows of 128 bytes; wave w owns rows
-    // 32 w .. 32 w + 31 of both tiles (4 instructions per operand and iteration).  LDS slot j of row r holds the row's
-    // chunk j ^ ((r >> 1) & 7): with that swizzle the 16-byte operand reads of 32 consecutive rows (same chunk) spread
-    // over all banks although the pitch is a multiple of the bank width.  Rows past the end re-read the last row.
-    static_assert(GKB == 128 && GT == 128, "load mapping below");
-    constexpr int NLA = GTM / 8 / NW, NLB = GT / 8 / NW;   // 8-row instructions per wave: 4 and 4 (4 waves), 4 and 2 (8 waves)
-    const unsigned char* asrc[NLA];
-    const unsigned char* bsrc[NLB];
-#pragma unroll
-    for (int k = 0; k < NLA; ++k) {
-        const int row = 8 * (NLA * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-        int64_t tr = t0 + row;
-        if (tr >= p.T) tr = p.T - 1;
-        asrc[k] = p.xc + tr * kbytes + 16 * ch;
-    }
-#pragma unroll
-    for (int k = 0; k < NLB; ++k) {
-        const int row = 8 * (NLB * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-        int orow = o0 + row;
-        if (orow >= p.m) orow = p.m - 1;
-        bsrc[k] = p.wc + (int64_t)orow * kbytes + 16 * ch;
-    }
-    typedef const __attribute__((address_space(1))) void* gptr;
-    typedef __attribute__((address_space(3))) void* lptr;
-    auto issue = [&](int it, int buf) {   // past the last tile the last one is re-read (nobody uses it): no branch in the loop body
-        const int itc = it < nk ? it : nk - 1;
-        unsigned char* A = smem + buf * STAGE + w * (8 * NLA * GPITCH);
-        unsigned char* B = smem + buf * STAGE + A_TILE + w * (8 * NLB * GPITCH);
-#pragma unroll
-        for (int k = 0; k < NLA; ++k) __builtin_amdgcn_global_load_lds((gptr)(asrc[k] + (int64_t)itc * GKB), (lptr)(A + k * 8 * GPITCH), 16, 0, 0);
-#pragma unroll
-        for (int k = 0; k < NLB; ++k) __builtin_amdgcn_global_load_lds((gptr)(bsrc[k] + (int64_t)itc * GKB), (lptr)(B + k * 8 * GPITCH), 16, 0, 0);
-    };
-    // the tile requested last has arrived in LDS (this wave's part), then every wave's part has
-    auto tile_ready = [&]() {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-    };
-
-    i32x16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
-
-    if (tid < GT) {
-        const int o = o0 + tid;
-        reinterpret_cast<float*>(smem + 2 * STAGE)[tid] = (o < p.m) ? (float)p.ws[o] : 0.0f;
-    }
-    const int aoff = (64 * wm + c) * GPITCH;
-    const int boff = (64 * wn + c) * GPITCH;
-    const int hs = h ^ ((c >> 1) & 7);   // chunk 2 kp + h of row 32 x + c sits in slot (2 kp) ^ hs (the row's swizzle is that of c)
-    constexpr int NKP = GKB / 32;   // K step pairs (64 codes) per tile
-    static_assert(NKP >= 4 && NKP % 2 == 0, "the pipeline below reads two step pairs ahead and alternates two register stages");
-    // packed operands of one K step pair: x = 0, 1: tokens 32 x + c (A); x = 2, 3: output channels 32 (x - 2) + c (B)
-    auto lds_chunk = [&](int buf, int kp, int x) -> u32x4 {
-        const unsigned char* base = smem + buf * STAGE + ((x >> 1) ? A_TILE + boff : aoff);
-        return *reinterpret_cast<const u32x4*>(base + 32 * (x & 1) * GPITCH + 16 * ((2 * kp) ^ hs));
-    };
-    // Software pipeline over K step pairs g = it * NKP + kp, three stages deep: while the MFMAs of pair g run on the
-    // widened operands W[g & 1], pair g + 1 is widened from its packed registers P[(g + 1) & 1] into W[(g + 1) & 1] and
-    // pair g + 2 is read from LDS into P[g & 1].  The work is cut into 8 slices per pair, one MFMA followed by one
-    // slice of widening (6 vector instructions, shorter than the MFMA) and at most one LDS read, in this order in
-    // the instruction stream: a wave issues in order, so only vector work that sits between two MFMAs can run in
-    // the shadow of the first.
-    u32x4 P[2][4];
-    i32x4 W[2][4][2];   // [stage][operand x][K step s]
-    issue(0, 0);
-    tile_ready();
-    issue(1, 1);
-#pragma unroll
-    for (int x = 0; x < 4; ++x) { P[0][x] = lds_chunk(0, 0, x); P[1][x] = lds_chunk(0, 1, x); }
-    constexpr unsigned M = 0xF0F0F0F0u;
-    auto widen_slice = [&](const u32x4& w, int s) -> i32x4 {
-        return i32x4{(int)((w[2 * s] << 4) & M), (int)(w[2 * s] & M), (int)((w[2 * s + 1] << 4) & M), (int)(w[2 * s + 1] & M)};
-    };
-#pragma unroll
-    for (int x = 0; x < 4; ++x) { W[0][x][0] = widen_slice(P[0][x], 0); W[0][x][1] = widen_slice(P[0][x], 1); }
-    // one iteration: tile `it` (LDS buffer `buf`) through the MFMAs.  After pair NKP - 3 nobody reads that buffer any
-    // more (the later pairs were read ahead), so behind the barrier that publishes tile it + 1 it takes tile it + 2.
-    auto iteration = [&](int it, int buf) {
-#pragma unroll
-        for (int kp = 0; kp < NKP; ++kp) {
-            const int cur = kp & 1, nxt = cur ^ 1;           // NKP is even: the stage parity of pair g is that of kp
-            const int fkp = (kp + 2) % NKP;                   // pair g + 2: in this tile, or the first pairs of the next one
-            const int fbuf = (kp + 2 < NKP) ? buf : buf ^ 1;
-#pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                const int s = m >> 2, i = (m >> 1) & 1, j = m & 1;
-                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(W[cur][2 + j][s], W[cur][i][s], acc[i][j], 0, 0, 0);
-                W[nxt][m >> 1][m & 1] = widen_slice(P[nxt][m >> 1], m & 1);
-                // P[cur] was widened during the previous pair: its registers take pair g + 2
-                if (m >= 4) P[cur][m - 4] = lds_chunk(fbuf, fkp, m - 4);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (kp == NKP - 3) {
-                tile_ready();
-                issue(it + 2, buf);
-            }
-        }
-    };
-    for (int it = 0; it < nk; it += 2) {
-        iteration(it, 0);
-        if (it + 1 < nk) iteration(it + 1, 1);
-    }
-    tile_ready();   // no load is still writing, every wave is done with the K tiles: the epilogue reuses their space
-
-    // epilogue.  The weights are the MFMA's first operand, so in acc[i][j] a lane holds, for token 64 wm + 32 i + c,
-    // the output channels 64 wn + 32 j + 8 (r / 4) + 4 h + r % 4: runs of 4 consecutive channels.  They are scaled,
-    // rounded to fp16 and staged in LDS (the K tiles are dead by now) as a [128 tokens][128 channels] tile, which then
-    // leaves in whole 16-byte pieces.  Every sum is a multiple of 256 (both operands carry a factor 16).
-    typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-    constexpr int OPITCH = 2 * GT + 16;
-    unsigned char* otile = smem;
-    float* sws = reinterpret_cast<float*>(smem + 2 * STAGE);          // [128] weight steps of this tile
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int64_t t = t0 + 64 * wm + 32 * i + c;
-        const float sx = (float)p.xs[t < p.T ? t : p.T - 1];
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int oc = 64 * wn + 32 * j + 8 * g + 4 * h;
-                const float4 sw = *reinterpret_cast<const float4*>(sws + oc);
-                const half4 v = {(_Float16)((float)(acc[i][j][4 * g] >> 8) * sx * sw.x), (_Float16)((float)(acc[i][j][4 * g + 1] >> 8) * sx * sw.y),
-                                 (_Float16)((float)(acc[i][j][4 * g + 2] >> 8) * sx * sw.z), (_Float16)((float)(acc[i][j][4 * g + 3] >> 8) * sx * sw.w)};
-                *reinterpret_cast<half4*>(otile + (64 * wm + 32 * i + c) * OPITCH + 2 * oc) = v;
-            }
-    }
-    __syncthreads();
-    const bool wide = ((reinterpret_cast<uintptr_t>(p.out) & 15) == 0) && (p.out_stride % 8 == 0);
-#pragma unroll
-    for (int k = 0; k < GTM * 16 / (64 * NW); ++k) {
-        const int q = tid + 64 * NW * k, row = q >> 4, ch = q & 15;
-        const int64_t t = t0 + row;
-        const int o = o0 + 8 * ch;
-        if (t < p.T && o < p.m) {
-            const u32x4 v = *reinterpret_cast<const u32x4*>(otile + row * OPITCH + 16 * ch);
-            _Float16* dst = p.out + t * p.out_stride + o;
-            if (wide && o + 8 <= p.m) {
-                *reinterpret_cast<u32x4*>(dst) = v;
-            } else {
-                const _Float16* e = reinterpret_cast<const _Float16*>(&v);
-                for (int x = 0; x < 8; ++x)
-                    if (o + x < p.m) dst[x] = e[x];
-            }
-        }
-    }
-}
-
-// ---- many tokens.  A chunk of 32 codes becomes an FP6 operand (E2M3) in registers: the code q offset to q + 8 = 0 .. 15 IS
-// the E2M3 bit pattern of (q + 8) / 8 (subnormal up to 7 / 8, the first binade up to 15 / 8), so the codes need only be
-// spread from 4-bit to 6-bit fields, 8 vector instructions per 16 codes.  Their order inside a lane is free as long as both
-// operands share it.  The sums are exact: every product is an integer / 64 and the total at most 225 n / 64 with
-// n <= 65536, which fits 24 bits.  The offset leaves in the epilogue,
-//   sum q_x q_w = sum (q_x + 8)(q_w + 8) - 8 sum q_x - 8 sum q_w - 64 n,
-// with the row sums of the codes (one v_dot8 per dword) taken on the way.
-// FP6 MFMAs have twice the rate of int8 ones and are held back less by the power limit: alone, for the 2.2e12 operations of
-// 16384 x 8192 x 8192 on random codes, they take 303 us (328 with sign and magnitude in place of the offset), int8 ones 531.
-// What bounds the kernel there (613 - 672 us from box to box; 835 - 888 with the int8 kernel above): one wave per SIMD issues in
-// order, and it issues in 68 % of its cycles (12.0 vector instructions per MFMA, the MFMA among them: spreading and row
-// sums); waits for the tiles take 13 %, the MFMA pipe is busy 37 % of the time, at 2.0 GHz.  Without the row sums 554, without
-// loads as well 483.  Two waves per SIMD (eight of 128 x 64) spread every weight row four times: 697.  Row sums by one of
-// the two waves that share a row: the same time, twice the code.
+// ---- many tokens.  What bounds this kernel: a SIMD issues one instruction per 4 clocks (an MFMA takes two such slots), whether it
+// holds one wave or two, so that behind a 32-clock MFMA there is room for 6 others; and the power limit, which holds the chip at
+// 1.7 GHz under a full load of MFMAs (2.2 and more with half of the CUs busy).  FP6 MFMAs do twice the work of int8 ones in the same 32
+// clocks, and for less power: alone, for the 2.2e12 operations of 16384 x 8192 x 8192 on random codes, 303 us, int8 531.
+// Spreading the codes costs 7 instructions per 16 codes and is what an FP6 tile must save on: a wave that owns 128 x 128
+// (16 MFMAs per 8 operands of 32 rows and 64 codes) spreads 7 instructions per MFMA, a 64 x 64 one 14, where int8, 6 per MFMA, is
+// the faster one.  So the FP6 forms have waves of 128 x 128, one per SIMD, as large as the register file allows: 2 x 2 waves
+// (256 x 256), and 2 x 1 waves with K in two parts (256 x 128, every weight row spread twice instead of the four times of 64 x 64 tiles),
+// whose partial sums meet in LDS.  A row that two waves read is summed by one of them, half of the rows each: a dot product
+// does not overlap with the MFMA before it (measured: two of them behind an MFMA, 54 clocks instead of 33), so those of a step stand
+// together.
+// 16384 x 8192 x 8192 650 -> 568 us, 4096 x 4096 x 4096 47.7 -> 41.3, 16384 x 8192 x 1024 142 -> 112 (one box; before: 8 instructions per 16
+// codes, row sums by both waves and between the MFMAs, and an epilogue whose hoisted offsets went through scratch); 2048 x 4096 x 8192
+// 55.5 -> 43.8 in 256 x 128 tiles.
 constexpr unsigned kSpreadA0 = 0x0F00F00Fu, kSpreadA1 = 0xF00F00F0u, kSpreadA2 = 0x00F00F00u;   // fields that do not move
 constexpr unsigned kSpreadM0 = 0xCF3CF3CFu, kSpreadM1 = 0xF3CF3CF3u, kSpreadM2 = 0x3CF3CF3Cu;   // the low 4 bits of all fields
 constexpr unsigned kSpreadX0 = 0x08208208u, kSpreadX1 = 0x82082082u, kSpreadX2 = 0x20820820u;   // bit 3 of all fields
-__device__ __forceinline__ unsigned pick_bits(unsigned mask, unsigned a, unsigned b) { return __builtin_amdgcn_bitop3_b32(mask, a, b, 0xCA); }   // mask ? a : b
-__device__ __forceinline__ unsigned and_xor(unsigned v, unsigned m, unsigned x) { return __builtin_amdgcn_bitop3_b32(v, m, x, 0x6A); }           // (v & m) ^ x
 // 16 codes -> 16 fields of 6 bits in three dwords.  Every nibble stays or moves up by 2 bits, into the next dword where it
-// straddles the end (fields in order: nibbles 0 1 3 4 6 7 of lo, 1 2 4 5 7 0 of hi, 2 of lo, 3 of hi, 5 of lo, 6 of hi).
+// straddles the end (fields in order: nibbles 0 1 3 4 6 7 of lo, 1 2 4 5 7 0 of hi, 2 of lo, 3 of hi, 5 of lo, 6 of hi).  One 64-bit
+// shift serves all that move; then mask ? stay : moved (0xca) and (v & fields) ^ bit 3 (0x6a) per dword: 7 instructions of 4
+// clocks.  One block, because the compiler takes the shift apart into five.
 __device__ __forceinline__ void spread16(unsigned lo, unsigned hi, unsigned* o) {
-    const unsigned t = lo << 2, u = __builtin_amdgcn_alignbit(hi, lo, 30);      // u = hi << 2 | lo >> 30
-    o[0] = and_xor(pick_bits(kSpreadA0, lo, t), kSpreadM0, kSpreadX0);
-    o[1] = and_xor(pick_bits(kSpreadA1, hi, u), kSpreadM1, kSpreadX1);
-    o[2] = and_xor(pick_bits(kSpreadA2, lo, u), kSpreadM2, kSpreadX2);
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    asm("v_lshlrev_b64 v[254:255], 2, %3\n\t"
+        "v_bitop3_b32 %0, %6, %4, v254 bitop3:0xca\n\t"
+        "v_bitop3_b32 %1, %7, %5, v255 bitop3:0xca\n\t"
+        "v_bitop3_b32 %2, %8, %4, v255 bitop3:0xca\n\t"
+        "v_bitop3_b32 %0, %0, %9, %12 bitop3:0x6a\n\t"
+        "v_bitop3_b32 %1, %1, %10, %13 bitop3:0x6a\n\t"
+        "v_bitop3_b32 %2, %2, %11, %14 bitop3:0x6a"
+        : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2])
+        : "v"(u32x2{lo, hi}), "v"(lo), "v"(hi), "s"(kSpreadA0), "s"(kSpreadA1), "s"(kSpreadA2), "s"(kSpreadM0), "s"(kSpreadM1), "s"(kSpreadM2),
+          "v"(kSpreadX0), "v"(kSpreadX1), "v"(kSpreadX2)
+        : "v254", "v255");
 }
 
-struct Fp6Tile {
-    // MFMA tiles of 32 x 32 per wave (tokens x channels), waves, LDS stages: 256 x 256 with a wave on each SIMD, as large as
-    // the register file allows, so that every code is spread by two waves only and crosses LDS and L2 least often
-    static constexpr int TI = 4, TJ = 4, WM = 2, WN = 2, NST = 2;
-    static constexpr int NW = WM * WN;
+// A tile form: MFMA tiles of 32 x 32 per wave (tokens x channels), waves (tokens x channels x parts of K), LDS stages, waves
+// per SIMD.
+template <bool FP6_, int TI_, int TJ_, int WM_, int WN_, int KS_, int NST_, int WPE_>
+struct Tile {
+    static constexpr bool FP6 = FP6_;
+    static constexpr int TI = TI_, TJ = TJ_, WM = WM_, WN = WN_, KS = KS_, NST = NST_, WPE = WPE_;
+    static constexpr int NW = WM * WN * KS;
     static constexpr int TOK = 32 * TI * WM, CH = 32 * TJ * WN, ROWS = TOK + CH;
     static constexpr int STAGE = ROWS * GKB;                        // code tiles of one K iteration
     static constexpr int OPITCH = 64 * TJ + 16;                     // output staging: 32 tokens of a wave's channels
-    static constexpr int WCOL = 32 * TJ * 8;                        // step and row sum of a wave's channels
-    static constexpr int LDS = NST * STAGE + NW * WCOL;
+    static constexpr int WCOL = 32 * TJ * 4;                        // steps of a wave's channels
+    static constexpr int SUMS = NST * STAGE + NW * WCOL;            // row sums of the tile, for each part of K
+    static constexpr int LDS = SUMS + (FP6 ? 4 * KS * ROWS : 0);
     static_assert(NW * 32 * OPITCH <= STAGE && LDS <= 160 * 1024 && NST >= 2, "LDS budget");
+    static_assert(TOK / 8 % NW == 0 && CH / 8 % NW == 0, "loads are whole groups of 8 rows per wave");
+    static_assert(!FP6 || (TI == 4 && TJ == 4), "a spread block and the MFMA that reads it: see the steps");
+    static_assert(KS == 1 || (KS == 2 && FP6 && TI % 2 == 0 && WN == 1 && NST >= 3), "the two waves that share a tile finish half of its tokens each");
 };
 
 // Every operand byte goes from global memory straight into LDS (global-to-LDS loads, unpadded 128-byte rows, 16-byte chunks
 // swizzled), NST iterations of 256 codes deep, one barrier per iteration; persistent workgroups whose loads run on from one
-// output tile into the next.  ODD: the output's rows are not all dword-aligned and leave in halves, by a loop that only such
-// launches carry (6486 x 5705 x 256 82 us with the halves of 16-byte pieces stored one by one, now 69; int8 78; 2733 x 3333 x
-// 2048 41.0, now 39.1; int8 48.1).
-template <bool ODD>
-__global__ __launch_bounds__(64 * Fp6Tile::NW) __attribute__((amdgpu_waves_per_eu(1, 1))) void w4a4_fp6_kernel(GemmDev p) {
-    using L = Fp6Tile;
-    constexpr int TI = L::TI, TJ = L::TJ, WM = L::WM, NST = L::NST;
+// output tile into the next.  The output leaves through LDS in 16-byte pieces, by buffer stores without branches where all rows
+// are made of such pieces.  ODD: the output's rows are not all dword-aligned and leave in halves, by a loop that only such
+// launches carry (6486 x 5705 x 256 61 us, 82 with the halves of 16-byte pieces stored one by one).
+template <class L, bool ODD>
+__global__ __launch_bounds__(64 * L::NW) __attribute__((amdgpu_waves_per_eu(L::WPE, L::WPE))) void w4a4_tiled_kernel(GemmDev p) {
+    constexpr bool FP6 = L::FP6;
+    constexpr int TI = L::TI, TJ = L::TJ, WM = L::WM, WN = L::WN, NST = L::NST;
     constexpr int NW = L::NW, TOK = L::TOK, CH = L::CH, STAGE = L::STAGE, A_TILE = TOK * GKB, NOP = TI + TJ;
     constexpr int NLA = TOK / 8 / NW, NLB = CH / 8 / NW, NL = NLA + NLB;   // load instructions per wave and iteration
-    constexpr int NKP = GKB / 32;                                   // K steps (64 codes) per iteration
+    constexpr int KS = L::KS, NKP = GKB / 32 / KS;                  // K steps (64 codes) per wave and iteration
     constexpr int LA = 2, KB = NKP - LA;                            // operands are read LA steps ahead; the steps before the barrier
-    constexpr int NQ = TI * TJ;                                     // MFMAs per step
-    constexpr int LSTEPS = 2;                                       // steps over which an iteration's loads are spread
-    static_assert(NKP == 4, "register stages below");
+    constexpr int NQ = TI * TJ * (FP6 ? 1 : 2);                     // MFMAs per step
+    constexpr int WD = FP6 ? 3 : 4;                                 // dwords of an operand register per 16 codes
+    constexpr int LSTEPS = NST == 2 || NKP == 2 ? 2 : NKP;                                       // steps over which an iteration's loads are spread
+    static_assert(NKP == 4 || NKP == 2, "register stages below");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x;
     const int l = tid & 63, c = l & 31, h = l >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = w % WM, wn = w / WM;
+    const int wm = w % WM, wn = w / WM % WN, ks = w / (WM * WN);
     const int64_t kbytes = p.n / 2;
     const int nk = p.n / (2 * GKB);
     const int ntx = (int)((p.T + TOK - 1) / TOK), nty = (p.m + CH - 1) / CH;
@@ -312,23 +151,23 @@ __global__ __launch_bounds__(64 * Fp6Tile::NW) __attribute__((amdgpu_waves_per_e
     };
 
     // ---- loads: one instruction fills 8 rows of 128 bytes; LDS slot j of row r holds the row's chunk j ^ ((r >> 1) & 7).
-    // Rows past the end re-read the last row.
+    // Rows past the end are out of the buffer's range and read as zeros.
     __amdgpu_buffer_rsrc_t abuf, bbuf;
     uint32_t aoff[NLA], boff[NLB];
+#pragma unroll
+    for (int k = 0; k < NLA; ++k) {
+        const int row = 8 * (NLA * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
+        aoff[k] = (uint32_t)row * (uint32_t)kbytes + 16 * ch;
+    }
+#pragma unroll
+    for (int k = 0; k < NLB; ++k) {
+        const int row = 8 * (NLB * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
+        boff[k] = (uint32_t)row * (uint32_t)kbytes + 16 * ch;
+    }
     auto set_source = [&](const Pos& t) {
         const int arows = (int)(p.T - t.t0 < TOK ? p.T - t.t0 : TOK), brows = p.m - t.o0 < CH ? p.m - t.o0 : CH;
         abuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.xc) + t.t0 * kbytes, 0, arows * (int)kbytes, 0x00020000);
         bbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.wc) + (int64_t)t.o0 * kbytes, 0, brows * (int)kbytes, 0x00020000);
-#pragma unroll
-        for (int k = 0; k < NLA; ++k) {
-            const int row = 8 * (NLA * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-            aoff[k] = (uint32_t)(row < arows ? row : arows - 1) * (uint32_t)kbytes + 16 * ch;
-        }
-#pragma unroll
-        for (int k = 0; k < NLB; ++k) {
-            const int row = 8 * (NLB * w + k) + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-            boff[k] = (uint32_t)(row < brows ? row : brows - 1) * (uint32_t)kbytes + 16 * ch;
-        }
     };
     typedef __attribute__((address_space(3))) void* lptr;
     // loads k0 .. k1 - 1 of the NL that bring iteration `it` (past the last one it is re-read; nobody uses it)
@@ -341,43 +180,84 @@ __global__ __launch_bounds__(64 * Fp6Tile::NW) __attribute__((amdgpu_waves_per_e
         }
     };
 
-    // ---- operands.  x < TI: tokens 32 (TI wm + x) + c; else channels 32 (TJ wn + x - TI) + c
+    // ---- operands.  x < TI: tokens 32 tok_tile(x) + c; else channels 32 ch_tile(x - TI) + c
     const int hs = h ^ ((c >> 1) & 7);   // chunk 2 kp + h of row 32 x + c sits in slot (2 kp) ^ hs
-    const int abyte = (32 * TI * wm + c) * GKB, bbyte = A_TILE + (32 * TJ * wn + c) * GKB;
+    const int atile = TI * wm, btile = TJ * wn;                     // first 32-row tiles of this wave
+    // A wave takes the tiles of its rows in an order of its own.  FP6: of the waves that read the same codes each sums a part of the
+    // rows, its first HA token and HB channel tiles; with K in two parts each wave finishes its first half of the tokens.
+    constexpr int HA = FP6 && L::WN == 2 ? (TI + 1) / 2 : TI, HB = FP6 && WM == 2 ? (TJ + 1) / 2 : TJ, IH = TI / KS;
+    const int arot = KS == 2 ? IH * ks : (TI - HA) * wn, brot = (TJ - HB) * wm;
+    constexpr int AH = KS == 2 ? IH : HA;
+    auto tok_tile = [&](int i) { return atile + (i < AH ? i + arot : i - (KS == 2 ? AH * ks : AH * wn)); };
+    auto ch_tile = [&](int j) { return btile + (j < HB ? j + brot : j - HB * wm); };
+    int lane_byte[NKP];                  // this lane's chunk of K step kp in a 32-row tile
+#pragma unroll
+    for (int kp = 0; kp < NKP; ++kp) lane_byte[kp] = c * GKB + 16 * ((2 * (NKP * ks + kp)) ^ hs);
     auto lds_chunk = [&](int stage, int kp, int x) -> u32x4 {
-        const int a = stage + (x < TI ? abyte + 32 * x * GKB : bbyte + 32 * (x - TI) * GKB) + 16 * ((2 * kp) ^ hs);
-        return *reinterpret_cast<const u32x4*>(smem + a);
+        const int a = stage + (x < TI ? 32 * GKB * tok_tile(x) : A_TILE + 32 * GKB * ch_tile(x - TI));   // scalar
+        return *reinterpret_cast<const u32x4*>(smem + a + lane_byte[kp]);
     };
     // Three register stages: while the MFMAs of step kp run on the FP6 operands W[kp & 1], the packed codes P of step kp + 1
     // are spread into W[(kp + 1) & 1], and as each operand has been spread its registers take the codes of step kp + 2 from
     // LDS.  A wave issues in order, so the vector work stands between the MFMAs, a share behind each.
-    f32x16 acc[TI][TJ];
+    typedef typename std::conditional<FP6, f32x16, i32x16>::type acc_t;
+    acc_t acc[TI][TJ];
     u32x4 P[NOP];
-    unsigned W[2][NOP][6];
-    int rsum[NOP];                       // sums of this lane's codes, per operand row
-    auto mfma = [&](int i, int j, int st) {
+    unsigned W[2][NOP][2 * WD];
+    int rsum[NOP];                       // FP6: sums of this lane's codes, of the rows that this wave sums
+    auto mfma = [&](int m, int st, bool first) {     // m-th MFMA of a step; the first step of a tile starts from zero
+        const int i = m / TJ % TI, j = m % TJ;
         const unsigned *wv = W[st][TI + j], *xv = W[st][i];
-        const i32x8 a = {(int)wv[0], (int)wv[1], (int)wv[2], (int)wv[3], (int)wv[4], (int)wv[5], 0, 0};
-        const i32x8 b = {(int)xv[0], (int)xv[1], (int)xv[2], (int)xv[3], (int)xv[4], (int)xv[5], 0, 0};
-        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i][j], 2, 2, 0, 0, 0, 0);   // FP6 E2M3 for both, no scale
+        acc_t from = acc[i][j];
+        if (first && m < TI * TJ)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) from[r] = 0;
+        if constexpr (FP6) {             // FP6 E2M3 for both, no scale
+            const i32x8 a = {(int)wv[0], (int)wv[1], (int)wv[2], (int)wv[3], (int)wv[4], (int)wv[5], 0, 0};
+            const i32x8 b = {(int)xv[0], (int)xv[1], (int)xv[2], (int)xv[3], (int)xv[4], (int)xv[5], 0, 0};
+            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, from, 2, 2, 0, 0, 0, 0);
+        } else {
+            const int s = 4 * (m / (TI * TJ));
+            const i32x4 a = {(int)wv[s], (int)wv[s + 1], (int)wv[s + 2], (int)wv[s + 3]};
+            const i32x4 b = {(int)xv[s], (int)xv[s + 1], (int)xv[s + 2], (int)xv[s + 3]};
+            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, from, 0, 0, 0);
+        }
     };
-    auto spread = [&](int st, int u) {   // half u & 1 of operand u / 2: 16 codes
-        const int x = u >> 1, s = u & 1;
+    // operands are spread in the order in which the MFMAs of a step ask for them: channels, then tokens
+    auto operand = [&](int u) { return (u >> 1) < TJ ? TI + (u >> 1) : (u >> 1) - TJ; };
+    auto spread = [&](int st, int u) {   // half u & 1 of operand(u): 16 codes
+        const int x = operand(u), s = u & 1;
         const unsigned lo = P[x][2 * s], hi = P[x][2 * s + 1];
-        spread16(lo, hi, &W[st][x][3 * s]);
-        rsum[x] = __builtin_amdgcn_sdot8((int)hi, 0x11111111, __builtin_amdgcn_sdot8((int)lo, 0x11111111, rsum[x], false), false);
+        unsigned* o = &W[st][x][WD * s];
+        if constexpr (FP6) {
+            spread16(lo, hi, o);
+        } else {
+            constexpr unsigned M = 0xF0F0F0F0u;
+            o[0] = (lo << 4) & M; o[1] = lo & M; o[2] = (hi << 4) & M; o[3] = hi & M;
+        }
+    };
+    // Row sums of the codes in P.  A dot product waits for the matrix pipe to drain (measured: 22 clocks longer than its own 4 when
+    // it follows an MFMA), so all of a step's stand in one place.
+    auto row_sums = [&]() {
+#pragma unroll
+        for (int x = 0; x < NOP; ++x)
+            if (x < TI ? x < HA : x - TI < HB)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) rsum[x] = __builtin_amdgcn_sdot8((int)P[x][k], 0x11111111, rsum[x], false);
     };
     // K step kp and a share of the loads of iteration `lit` into `stage_load`.  Steps KB .. NKP - 1 of an iteration, then
     // 0 .. KB - 1 of the next one, lie between two barriers: s is the step's place in that sequence, which the loads are
     // spread over.  `next`: there is a next step in this tile.
-    auto step = [&](int kp, int stage_ahead, int lit, int stage_load, int s, int s0, int nsteps, bool next) {
+    auto step = [&](int kp, int stage_ahead, int lit, int stage_load, int s, int s0, int nsteps, bool next, bool first) __attribute__((always_inline)) {
+        if constexpr (FP6)
+            if (next) row_sums();
 #pragma unroll
         for (int m = 0; m < NQ; ++m) {
-            mfma(m / TJ, m % TJ, kp & 1);
+            mfma(m, kp & 1, first);
 #pragma unroll
             for (int u = m * 2 * NOP / NQ; next && u < (m + 1) * 2 * NOP / NQ; ++u) {
                 spread((kp + 1) & 1, u);
-                if (u & 1) P[u >> 1] = lds_chunk(stage_ahead, (kp + LA) % NKP, u >> 1);
+                if (u & 1) P[operand(u)] = lds_chunk(stage_ahead, (kp + LA) % NKP, operand(u));
             }
             if (s >= s0 && s < s0 + nsteps) issue(lit, stage_load, ((s - s0) * NQ + m) * NL / (nsteps * NQ), ((s - s0) * NQ + m + 1) * NL / (nsteps * NQ));
             __builtin_amdgcn_sched_barrier(0);
@@ -408,119 +288,221 @@ __global__ __launch_bounds__(64 * Fp6Tile::NW) __attribute__((amdgpu_waves_per_e
     const bool flow = nk >= NST;
     while (true) {
 #pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int j = 0; j < TJ; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-#pragma unroll
         for (int x = 0; x < NOP; ++x) rsum[x] = 0;
+        if constexpr (FP6) row_sums();
 #pragma unroll
         for (int u = 0; u < 2 * NOP; ++u) spread(0, u);
+        if constexpr (FP6) {
+            // An MFMA needs wait states after the vector instructions that wrote its operands, and the compiler does not see those
+            // in spread16's block.  Inside the steps other MFMAs stand between: the operand spread last is the one read last.
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_nop 7" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
         read_step(st, 1);
         // steps 0 .. KB - 1 of iteration 0; loads of iteration NST - 1
+        if constexpr (KB == 0) issue(NST - 1, stl, 0, NL);
 #pragma unroll
-        for (int kp = 0; kp < KB; ++kp) step(kp, st, NST - 1, stl, kp, 0, LSTEPS, true);
+        for (int kp = 0; kp < KB; ++kp) step(kp, st, NST - 1, stl, kp, 0, LSTEPS < KB ? LSTEPS : KB, true, kp == 0);
         arrive();
         int lit = NST;                       // iteration to be loaded next
-        auto body = [&]() {
+        auto body = [&](bool first) __attribute__((always_inline)) {
             const int stn = advance(st);
             stl = advance(stl);
 #pragma unroll
-            for (int kp = KB; kp < NKP; ++kp) step(kp, stn, lit, stl, kp - KB, 0, LSTEPS, true);
+            for (int kp = KB; kp < NKP; ++kp) step(kp, stn, lit, stl, kp - KB, 0, LSTEPS, true, first && kp == 0);
 #pragma unroll
-            for (int kp = 0; kp < KB; ++kp) step(kp, stn, lit, stl, kp + LA, 0, LSTEPS, true);
+            for (int kp = 0; kp < KB; ++kp) step(kp, stn, lit, stl, kp + LA, 0, LSTEPS, true, false);
             arrive();
             st = stn;
             ++lit;
         };
         int it = 0;
-        for (; it < nk - 1 && lit < nk; ++it) body();
+        if constexpr (KB == 0) {
+            if (nk > NST) {
+                body(true);
+                ++it;
+            } else {
+#pragma unroll
+                for (int i = 0; i < TI; ++i)
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+            }
+        }
+        for (; it < nk - 1 && lit < nk; ++it) body(false);
         const int64_t qn = q + qstep;
         const bool more = qn < mine;
         Pos nxt = cur;
         if (more) nxt = tile_pos(qn);
         if (more && flow) { set_source(nxt); lit = 0; }
-        for (; it < nk - 1; ++it) body();
+        for (; it < nk - 1; ++it) body(false);
         // the quantization steps of this tile's rows and channels, requested ahead of the epilogue (raw bits: nothing waits here)
         const uint16_t* xs_bits = reinterpret_cast<const uint16_t*>(p.xs);
         const uint16_t* ws_bits = reinterpret_cast<const uint16_t*>(p.ws);
-        unsigned esx[TI], esw[TJ];
+        unsigned esx[IH], esw[TJ];
 #pragma unroll
-        for (int i = 0; i < TI; ++i) {
-            const int64_t t = cur.t0 + 32 * (TI * wm + i) + c;
+        for (int i = 0; i < IH; ++i) {
+            const int64_t t = cur.t0 + 32 * tok_tile(i) + c;
             esx[i] = xs_bits[t < p.T ? t : p.T - 1];
         }
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
-            const int o = cur.o0 + 32 * (TJ * wn + j) + c;
+            const int o = cur.o0 + 32 * ch_tile(j) + c;
             esw[j] = ws_bits[o < p.m ? o : p.m - 1];
         }
         // the last steps of the tile: nothing is loaded, the current stage takes the output tile
         {
             const int stn = advance(st);
 #pragma unroll
-            for (int kp = KB; kp < NKP; ++kp) step(kp, stn, 0, 0, 0, 1, 0, kp + 1 < NKP);
+            for (int kp = KB; kp < NKP; ++kp) step(kp, stn, 0, 0, 0, 1, 0, kp + 1 < NKP, false);
         }
         __builtin_amdgcn_sched_barrier(0);
 
-        // epilogue: in acc[i][j] a lane holds, for token 32 (TI wm + i) + c, the output channels 32 (TJ wn + j) + 8 (r / 4) +
+        // epilogue: in acc[i][j] a lane holds, for token 32 tok_tile(i) + c, the output channels 32 ch_tile(j) + 8 (r / 4) +
         // 4 h + r % 4.  Rounded to fp16 and turned, 32 tokens at a time, through a part of LDS that belongs to the wave
-        // alone (no barrier), from where they leave in 16-byte pieces of whole rows.  All corrections are integers below
-        // 2^24, so their fp32 sums are exact.
+        // alone (no barrier), from where they leave in 16-byte pieces of whole rows.  FP6: all corrections are integers
+        // below 2^24, so their fp32 sums are exact.  int8: every sum is a multiple of 256 (both operands carry a factor 16).
         typedef _Float16 half4 __attribute__((ext_vector_type(4)));
         constexpr int OPITCH = L::OPITCH, CPR = 4 * TJ;              // 16-byte pieces per token
         unsigned char* ot = smem + st + w * (32 * OPITCH);
-        float* wcol = reinterpret_cast<float*>(smem + NST * STAGE + w * L::WCOL);   // [32 TJ] steps, [32 TJ] corrections
+        float* wcol = reinterpret_cast<float*>(smem + NST * STAGE + w * L::WCOL);   // [32 TJ] steps of this wave's channels
+        int* sums = reinterpret_cast<int*>(smem + L::SUMS);      // FP6: sums of q + 8 of the tile's tokens, then channels, for each part of K
 #pragma unroll
-        for (int x = 0; x < NOP; ++x) rsum[x] += __shfl_xor(rsum[x], 32);
+        for (int j = 0; j < TJ; ++j) wcol[32 * j + c] = (float)__builtin_bit_cast(_Float16, (uint16_t)esw[j]); // both halves of the wave store the same
+        if constexpr (FP6) {
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-            wcol[32 * j + c] = (float)__builtin_bit_cast(_Float16, (uint16_t)esw[j]);   // both halves of the wave store the same
-            wcol[32 * TJ + 32 * j + c] = (float)(-8 * rsum[TI + j]);
+            for (int x = 0; x < HA; ++x) sums[ks * L::ROWS + 32 * tok_tile(x) + c] = rsum[x] + __shfl_xor(rsum[x], 32) + 8 / KS * p.n;
+#pragma unroll
+            for (int x = 0; x < HB; ++x) sums[ks * L::ROWS + TOK + 32 * ch_tile(x) + c] = rsum[TI + x] + __shfl_xor(rsum[TI + x], 32) + 8 / KS * p.n;
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        }
+        if constexpr (KS == 2) {
+            // The other part of K: this wave's second half of the tokens goes to its partner, whose second half is this wave's first;
+            // through the free stage, a few tiles at a time.  The sums stay exact.
+            constexpr int UPP = STAGE / NW / 4096, US = IH * TJ;     // tiles per turn, and in all
+            static_assert(UPP >= 1, "room for a tile per wave");
+            f32x4* mine_x = reinterpret_cast<f32x4*>(smem + st + w * (UPP * 4096)) + l;
+            const f32x4* theirs = reinterpret_cast<const f32x4*>(smem + st + (w ^ (WM * L::WN)) * (UPP * 4096)) + l;
+#pragma unroll
+            for (int u0 = 0; u0 < US; u0 += UPP) {
+#pragma unroll
+                for (int u = u0; u < u0 + UPP && u < US; ++u)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        const acc_t& a = acc[IH + u / TJ][u % TJ];
+                        mine_x[(u - u0) * 256 + q4 * 64] = f32x4{(float)a[4 * q4], (float)a[4 * q4 + 1], (float)a[4 * q4 + 2], (float)a[4 * q4 + 3]};
+                    }
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+                for (int u = u0; u < u0 + UPP && u < US; ++u)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        const f32x4 v = theirs[(u - u0) * 256 + q4 * 64];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[u / TJ][u % TJ][4 * q4 + e] += v[e];
+                    }
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            }
+        }
+        if constexpr (FP6) {
+            // sum q_x q_w = 64 (sum of products of (q + 8) / 8 - row sum of tokens - row sum of channels + n): one more MFMA per
+            // tile adds the last three, each sum as 64 s1 + s0 (s1 < 2^11, s0 a multiple of 1 / 8 below 64).  All partial sums are
+            // multiples of 1 / 64 below 2^18: exact.
+            half8 ax[IH], bw[TJ];
+            auto pieces = [&](int row, _Float16& s1, _Float16& s0) {
+                const int sum = sums[row] + (KS == 2 ? sums[L::ROWS + row] : 0);
+                s1 = (_Float16)(float)(sum >> 9);
+                s0 = (_Float16)((float)(sum & 511) * 0.125f);
+            };
+            const half8 none = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < IH; ++i) {
+                half8 v = {-64, -1, 0, 0, 256, 0, 0, 0};
+                _Float16 s1, s0;
+                pieces(32 * tok_tile(i) + c, s1, s0);
+                v[2] = s1; v[3] = s0;
+                ax[i] = h ? none : v;
+            }
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                half8 v = {0, 0, -64, -1, 0, 0, 0, 0};
+                _Float16 s1, s0;
+                pieces(TOK + 32 * ch_tile(j) + c, s1, s0);
+                v[0] = s1; v[1] = s0; v[4] = (_Float16)(float)(p.n / 256);
+                bw[j] = h ? none : v;
+            }
+#pragma unroll
+            for (int i = 0; i < IH; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bw[j], ax[i], acc[i][j], 0, 0, 0);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+        float4 sw[TJ][4];                                            // steps of this lane's channels
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) sw[j][g] = *reinterpret_cast<const float4*>(wcol + 32 * j + 8 * g + 4 * h);
         const uintptr_t pitch_bits = reinterpret_cast<uintptr_t>(p.out) | (uintptr_t)(2 * p.out_stride);
         const bool wide = (pitch_bits & 15) == 0, pairs = (pitch_bits & 3) == 0;   // whole pieces, dwords, or halves
+        // Whole pieces only: buffer stores from one scalar base, with an offset out of range for pieces outside the output.
+        const bool whole = !ODD && wide && p.m % 8 == 0 && p.out_stride < (1 << 20);
+        int64_t stride = p.out_stride;
+        int lane = l;
+        asm volatile("" : "+s"(stride), "+v"(lane));                 // offsets are made here, not kept (and spilled) through the main loop
+        const int pitch = (int)(2 * stride);
+        const int rows_left = (int)(p.T - cur.t0 < TOK ? p.T - cur.t0 : TOK);
+        const __amdgpu_buffer_rsrc_t obuf = __builtin_amdgcn_make_buffer_rsrc(p.out + cur.t0 * stride + cur.o0, 0, 0x40000000, 0x00020000);
+        auto scaled = [&](int i, int j, int r, float sx) {
+            float v = (float)acc[i][j][r] * sx * reinterpret_cast<const float*>(&sw[j][r >> 2])[r & 3];
+            asm("" : "+v"(v));               // rounded to fp32 as it stands, not inside a mixed-precision fma: the same bits in every form
+            return (_Float16)v;
+        };
 #pragma unroll
-        for (int i = 0; i < TI; ++i) {
-            const float sx = (float)__builtin_bit_cast(_Float16, (uint16_t)esx[i]);
-            const float cx = (float)(-8 * rsum[i] - 64 * p.n);
+        for (int i = 0; i < IH; ++i) {
+            const float sx = (float)__builtin_bit_cast(_Float16, (uint16_t)esx[i]) * (FP6 ? 64.0f : 1.0f / 256);   // the sums' unit
 #pragma unroll
             for (int j = 0; j < TJ; ++j)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const float4 sw = *reinterpret_cast<const float4*>(wcol + 32 * j + 8 * g + 4 * h);
-                    const float4 cw = *reinterpret_cast<const float4*>(wcol + 32 * TJ + 32 * j + 8 * g + 4 * h);
-                    const half4 v = {(_Float16)(fmaf(acc[i][j][4 * g], 64.0f, cx + cw.x) * sx * sw.x),
-                                     (_Float16)(fmaf(acc[i][j][4 * g + 1], 64.0f, cx + cw.y) * sx * sw.y),
-                                     (_Float16)(fmaf(acc[i][j][4 * g + 2], 64.0f, cx + cw.z) * sx * sw.z),
-                                     (_Float16)(fmaf(acc[i][j][4 * g + 3], 64.0f, cx + cw.w) * sx * sw.w)};
-                    *reinterpret_cast<half4*>(ot + c * OPITCH + 64 * j + 16 * g + 8 * h) = v;
-                }
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<half4*>(ot + c * OPITCH + 64 * j + 16 * g + 8 * h) =
+                        half4{scaled(i, j, 4 * g, sx), scaled(i, j, 4 * g + 1, sx), scaled(i, j, 4 * g + 2, sx), scaled(i, j, 4 * g + 3, sx)};
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             if constexpr (ODD) {             // 64 consecutive halves per instruction: whole lines as far as they go
-                const int64_t t = cur.t0 + 32 * (TI * wm + i);
-                const int o = cur.o0 + 32 * TJ * wn + l, rows = (int)(p.T - t < 32 ? p.T - t : 32);
-                _Float16* dst = p.out + t * p.out_stride + o;
+                const int64_t t = cur.t0 + 32 * tok_tile(i);
+                const int rows = (int)(p.T - t < 32 ? p.T - t : 32);
+                _Float16* dst = p.out + t * stride + cur.o0;
 #pragma unroll 4
-                for (int row = 0; row < rows; ++row, dst += p.out_stride)
+                for (int row = 0; row < rows; ++row, dst += stride)
 #pragma unroll
-                    for (int x = 0; x < TJ / 2; ++x) {
-                        const _Float16 v = *reinterpret_cast<const _Float16*>(ot + row * OPITCH + 2 * (l + 64 * x));
-                        if (o + 64 * x < p.m) dst[64 * x] = v;
+                    for (int x = 0; x < (TJ + 1) / 2; ++x) {
+                        const int e = lane + 64 * x, j = 2 * x + h;                    // column of the staged row, and its tile
+                        if (TJ % 2 && j >= TJ) continue;
+                        const int o = 32 * ch_tile(j) + c;
+                        const _Float16 v = *reinterpret_cast<const _Float16*>(ot + row * OPITCH + 2 * e);
+                        if (cur.o0 + o < p.m) dst[o] = v;
                     }
+            } else if (whole) {
+#pragma unroll
+                for (int k = 0; k < 32 * CPR / 64; ++k) {
+                    const int e = lane + 64 * k, ch = e % CPR, r = e / CPR;
+                    const int o = 32 * ch_tile(ch >> 2) + 8 * (ch & 3), row = 32 * tok_tile(i) + r;
+                    const int col = cur.o0 + o < p.m ? 2 * o : 0x40000000;
+                    const u32x4 v = *reinterpret_cast<const u32x4*>(ot + r * OPITCH + 16 * ch);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, obuf, row < rows_left ? row * pitch + col : 0x40000000, 0, 0);
+                }
             } else {                         // `pairs` holds (the same loop without the test measured 1 - 2 % slower)
 #pragma unroll
                 for (int k = 0; k < 32 * CPR / 64; ++k) {
-                    const int e = l + 64 * k, row = e / CPR, ch = e % CPR;
-                    const int64_t t = cur.t0 + 32 * (TI * wm + i) + row;
-                    const int o = cur.o0 + 32 * TJ * wn + 8 * ch;
+                    const int e = lane + 64 * k, row = e / CPR, ch = e % CPR, j = ch >> 2;
+                    const int64_t t = cur.t0 + 32 * tok_tile(i) + row;
+                    const int o = cur.o0 + 32 * ch_tile(j) + 8 * (ch & 3);
                     const u32x4 v = *reinterpret_cast<const u32x4*>(ot + row * OPITCH + 16 * ch);
                     if (t < p.T && o < p.m) {
-                        _Float16* dst = p.out + t * p.out_stride + o;
+                        _Float16* dst = p.out + t * stride + o;
                         if (wide && o + 8 <= p.m) {
                             *reinterpret_cast<u32x4*>(dst) = v;
                         } else if (pairs && o + 8 <= p.m) {
@@ -755,27 +737,26 @@ static hipError_t skinny_launch(const GemmDev& d, hipStream_t stream, int token_
     return hipErrorInvalidValue;
 }
 
-template <bool ODD>
-static hipError_t fp6_launch_rows(const GemmDev& d, hipStream_t stream) {
-    using L = Fp6Tile;
+template <class L, bool ODD>
+static hipError_t tiled_launch_rows(const GemmDev& d, hipStream_t stream) {
     static OccCache cache;
     int occ = 0;
-    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_fp6_kernel<ODD>), 64 * L::NW, L::LDS, cache, occ);
+    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_tiled_kernel<L, ODD>), 64 * L::NW, L::LDS, cache, occ);
     if (e != hipSuccess) return e;
     // persistent: every XCD (eight of them) gets as many workgroups as it holds at once, or as it has tiles
     const int64_t tiles = ((d.T + L::TOK - 1) / L::TOK) * ((d.m + L::CH - 1) / L::CH);
     const int64_t per_xcd = (tiles + 7) / 8, resident = (int64_t)occ * cu_count() / 8;
     const unsigned grid = 8 * (unsigned)(per_xcd < resident ? per_xcd : resident);
-    return launch(w4a4_fp6_kernel<ODD>, dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
+    return launch(w4a4_tiled_kernel<L, ODD>, dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
 }
 
-static hipError_t fp6_launch(const GemmDev& d, hipStream_t stream) {
+template <class L>
+static hipError_t tiled_launch(const GemmDev& d, hipStream_t stream) {
     const bool odd = (reinterpret_cast<uintptr_t>(d.out) | (uintptr_t)(2 * d.out_stride)) & 3;
-    return odd ? fp6_launch_rows<true>(d, stream) : fp6_launch_rows<false>(d, stream);
+    return odd ? tiled_launch_rows<L, true>(d, stream) : tiled_launch_rows<L, false>(d, stream);
 }
 
 hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
-    int unused = 0;
     GemmDev d;
     d.xc = a.x_codes; d.xs = a.x_scales; d.wc = a.w_codes; d.ws = a.w_scales; d.out = a.out;
     d.T = a.T; d.out_stride = a.out_stride; d.m = a.m; d.n = a.n;
@@ -785,57 +766,50 @@ hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
         if (a.T <= 16) return skinny_launch<2>(d, stream);
         if (a.T <= 32) return skinny_launch<4>(d, stream);
         if (a.T <= 64) return skinny_launch<8>(d, stream);
-        // More tokens: the ring kernel on tiles of 64 tokens, as long as the 128 x 128 tiles of the kernel below would
+        // More tokens: the ring kernel on tiles of 64 tokens, as long as the 128 x 128 tiles of the tiled kernel would
         // reach at most half of the CUs (measured cross-over on 1024 .. 11008 channels; FLATQUANT_GEMM_RING_MAX_T
         // replaces the rule by a token count).
-        const int64_t tiled_wgs = ((a.T + GT - 1) / GT) * ((a.m + GT - 1) / GT);
+        const int64_t tiled_wgs = ((a.T + 127) / 128) * ((a.m + 127) / 128);
         const int ring_max = env_int("FLATQUANT_GEMM_RING_MAX_T", -1);
         if (ring_max >= 0 ? a.T <= ring_max : (2 * tiled_wgs <= cu_count() && a.T <= 4096))
             return skinny_launch<8>(d, stream, (int)((a.T + 63) / 64));
     }
-    static OccCache ct, ctw;
-    // Tile form (FLATQUANT_GEMM_WIDE forces one): int8 with 128 x 128 tiles, with 256 x 128 tiles when these still give every
-    // CU a workgroup (1), or FP6 with 256 x 256 tiles (2).  A launch takes rounds of one tile per CU, measured at n = 4096: 5 + 29
-    // us per round of 256 x 128 int8 tiles, 9 + 43 us per round of FP6 tiles of twice the size, whose first pass over its
-    // code costs more.  Both parts grow with n, so their order holds from n = 1024 on.  (int8 / FP6, us: 2048 x 4096 x 4096 33.5 /
-    // 46.4, 3000 x 4096 x 4096 58.7 / 49.3, 4096 x 4096 x 4096 64.1 / 52.6, 1024 x 11008 x 4096 57.1 / 48.9, 2048 x 11008 x 4096
-    // 91.0 / 93.5, 2048 x 8192 x 14336 193 / 147, 8192 x 8192 x 1024 87.4 / 73.1, 777 x 5120 x 5120 33.2 / 49.8, 16384 x 8192 x
-    // 8192 835 - 857 / 613 - 646.  FP6 with 256 x 128 and 128 x 128 tiles is bound by the vector work and gains nothing over
-    // int8: 30.0 and 32.9 at 2048 x 4096 x 4096 with everything in the caches, but 41 against 39 for the whole layer on
-    // fresh data.)
-    // Shorter rows are one or two iterations, and output more than product: a round of FP6 tiles takes 11 us at n = 256 and 13 at
-    // n = 512, one of int8 tiles 6 and 7.5, and an int8 round on a part x of the CUs takes 0.6 + 0.4 x of that.  FP6 stays
-    // where its last round is nearly full (there the formula is not sharp enough) or comes out shorter all the same.  (int8 /
-    // FP6: 4230 x 8320 x 256, 2.2 rounds of FP6, 32.6 / 36.7; 10622 x 8576 x 256, 5.6, 64.1 / 69.1; 13407 x 8192 x 256, 6.6, 84.7 /
-    // 80.1; 4096 x 4096 x 256, 1, 16.2 / 15.2; 1429 x 8000 x 512, 0.75, 16.2 / 16.9; 9882 x 2496 x 512, 1.5, 32.3 / 29.5; 5144 x
-    // 5440 x 512, 1.8, 33.3 / 29.5.)  This is for rows of whole 128-byte lines; into others the int8 kernel's output costs
-    // more (1659 x 5716 x 256 29.7 / 20.0).
+    // Tile form (FLATQUANT_GEMM_WIDE forces one): int8 with 128 x 128 tiles, two workgroups per CU (0) or 160 x 128, one (4); FP6 with
+    // 256 x 128 tiles, K in two parts (1), or 256 x 256 (2).  A launch takes rounds of one tile per slot, and a round a fixed part
+    // and one per K iteration that grows with the share of the slots in use (the clock falls).  The constants are a fit to 110
+    // launches of 100 <= T <= 16384, 512 <= m <= 14336, 256 <= n <= 28672 (rms 5 - 6 %); what they choose is 0.2 % slower than the best
+    // form on average, 10 % at worst.  (Forms 0 / 1 / 2 / 4, us: 2048 x 4096 x 1024 11.4 / 14.3 / 16.3 / 15.5, 2048 x 4096 x 4096 28.4 / 26.7 /
+    // 36.2 / 38.5, 2048 x 4096 x 8192 52.7 / 43.7 / 62.2 / 68.8, 777 x 5120 x 5120 28.8 / 27.5 / 40.8 / 23.3, 768 x 5120 x 5120 20.6 / 27.6 / 41.7 /
+    // 24.1, 3000 x 4096 x 4096 40.9 / 44.8 / 37.0 / 54.8, 6000 x 4096 x 11008 203 / 159 / 170 / 233.)
     const int64_t cu = cu_count();
-    const int64_t wide_wgs = ((a.T + 255) / 256) * ((a.m + GT - 1) / GT), fp6_wgs = ((a.T + 255) / 256) * ((a.m + 255) / 256);
-    const int64_t int8_rounds = (wide_wgs + cu - 1) / cu, fp6_rounds = (fp6_wgs + cu - 1) / cu;
-    bool fp6 = wide_wgs >= cu && 9 + fp6_rounds * 43 < 5 + int8_rounds * 29;
-    if (fp6 && a.n <= 512 && ((reinterpret_cast<uintptr_t>(a.out) | (uintptr_t)(2 * a.out_stride)) & 127) == 0) {
-        const int64_t part = wide_wgs % cu;
-        const double int8_us = 3.2 + (wide_wgs / cu + (part ? 0.6 + 0.4 * part / cu : 0.0)) * (4.4 + 0.0061 * a.n);
-        const double fp6_us = 3.7 + fp6_rounds * (8.6 + 0.009 * a.n);
-        const bool full = 16 * fp6_wgs >= (a.n <= 256 ? 15 : 13) * fp6_rounds * cu;
-        fp6 = full || fp6_us < int8_us;
+    const double nk = a.n / 256;
+    auto round_us = [&](int tok, int ch, int64_t slots, double& part) {   // full rounds; part: how full the last one is
+        const int64_t tiles = ((a.T + tok - 1) / tok) * ((a.m + ch - 1) / ch);
+        part = (double)(tiles % slots) / (double)slots;
+        return (double)(tiles / slots);
+    };
+    double x;
+    double us[5];
+    us[0] = 3.5 + round_us(128, 128, 2 * cu, x) * (2.7 + 1.43 * nk);
+    if (x > 0.5) us[0] += 2.7 + (0.84 + 0.59 * x) * nk;              // CUs with one and with two tiles
+    else if (x > 0) us[0] += 0.5 + (0.63 + 0.28 * x) * nk;
+    us[1] = 2.8 + round_us(256, 128, cu, x) * (5.9 + 1.08 * nk);
+    if (x > 0) us[1] += 5.9 + (0.88 + 0.20 * x) * nk;
+    us[2] = 0.8 + round_us(256, 256, cu, x) * (7.7 + 1.89 * nk);
+    if (x > 0) us[2] += 7.7 + (1.57 + 0.32 * x) * nk;
+    us[4] = 1.5 + round_us(160, 128, cu, x) * (3.3 + 1.0 * nk);
+    if (x > 0) us[4] += 3.3 + (0.86 + 0.14 * x) * nk;
+    int form = 0;
+    for (int f : {1, 2, 4})
+        if (us[f] < us[form]) form = f;
+    const int asked = env_int("FLATQUANT_GEMM_WIDE", form);
+    if (asked == 0 || asked == 1 || asked == 2 || asked == 4) form = asked;
+    switch (form) {
+        case 1: return tiled_launch<Tile<true, 4, 4, 2, 1, 2, 3, 1>>(d, stream);
+        case 2: return tiled_launch<Tile<true, 4, 4, 2, 2, 1, 2, 1>>(d, stream);
+        case 4: return tiled_launch<Tile<false, 5, 1, 1, 4, 1, 3, 1>>(d, stream);
+        default: return tiled_launch<Tile<false, 2, 2, 2, 2, 1, 2, 2>>(d, stream);
     }
-    const int rule = fp6 ? 2 : wide_wgs >= cu ? 1 : 0, asked = env_int("FLATQUANT_GEMM_WIDE", rule);
-    const int wide = asked >= 0 && asked <= 2 ? asked : rule;
-    if (wide == 2) return fp6_launch(d, stream);
-    if (wide) {
-        hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_kernel<4>), 512, G_LDS_BYTES_WIDE, ctw, unused);
-        if (e != hipSuccess) return e;
-        const dim3 grid((unsigned)((a.T + 255) / 256), (unsigned)((a.m + GT - 1) / GT));
-        return launch(w4a4_kernel<4>, grid, dim3(512), G_LDS_BYTES_WIDE, stream, d);
-    }
-    {
-        hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_kernel<2>), G_NT, G_LDS_BYTES, ct, unused);
-        if (e != hipSuccess) return e;
-    }
-    const dim3 grid((unsigned)((a.T + GT - 1) / GT), (unsigned)((a.m + GT - 1) / GT));
-    return launch(w4a4_kernel<2>, grid, dim3(G_NT), G_LDS_BYTES, stream, d);
 }
 
 }  // namespace fq

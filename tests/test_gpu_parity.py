@@ -1107,6 +1107,26 @@ def test_w4a4_gemm_tiles_follow_each_other(tuning, form, T, m, n, pad):
         assert bool(torch.isnan(out[:, m:]).all())
 
 
+@pytest.mark.parametrize("form,T,m,n", [(4, 160, 128, 256), (4, 161, 129, 512), (4, 319, 300, 768), (4, 2900, 3000, 1280), (1, 256, 128, 512), (1, 257, 129, 768),
+                                        (1, 255, 300, 1024), (1, 5000, 3200, 256), (1, 5000, 3200, 1024), (1, 4353, 3105, 1536)])
+def test_w4a4_gemm_160_token_and_split_k_tiles(tuning, form, T, m, n):
+    """160 x 128 int8 tiles, and 256 x 128 FP6 tiles with K in two parts: one tile and its edges, fewer K iterations than LDS
+    stages, as many and more, several tiles per workgroup (whose partial sums are exchanged while the next tile's loads are under way).
+    Equal to the integer product, bit for bit (64 n < 2^24), twice."""
+    tuning("FLATQUANT_GEMM_TILED", 1)
+    tuning("FLATQUANT_GEMM_WIDE", form)
+    g = torch.Generator(device="cuda").manual_seed(T + m + n)
+    q = [torch.randint(-8, 8, (r, n), generator=g, device="cuda", dtype=torch.int8) for r in (T, m)]
+    packed = [((c[:, 0::2] & 15) | (c[:, 1::2] << 4)).view(torch.uint8) for c in q]
+    xs, ws = (torch.rand(r, generator=g, device="cuda").half() for r in (T, m))
+    want = ((q[0].float() @ q[1].float().t()) * xs.float()[:, None] * ws.float()[None, :]).half()
+    print(f"[case] w4a4 form={form} T={T} m={m} n={n}", flush=True)
+    for _ in range(2):
+        out = torch.full((T, m), float("nan"), dtype=torch.float16, device="cuda")
+        fq.flatquant_w4a4_gemm(packed[0], xs, packed[1], ws, T, m, n, out, m, stream=torch.cuda.current_stream())
+        assert torch.equal(out, want)
+
+
 @pytest.mark.parametrize("low", [-8, 4, 7])
 def test_w4a4_gemm_fp6_longest_rows(tuning, low):
     """The largest n: with codes of 7 throughout the offset sums reach 225 n = 14.7e6, just below 2^24, and are still exact."""
