@@ -55,6 +55,46 @@ struct KvDev {
     float clip;
 };
 
+// The grid of one group from the range of its values (always containing 0), and 8 codes on it.
+template <int QB>
+struct KvGrid {
+    static constexpr float LV = (float)((1 << QB) - 1);            // 2^b - 1 intervals
+    _Float16 step;
+    float inv, z, lim_lo, lim_hi;
+    uint32_t chain_fix;
+    static constexpr uint32_t kMagicBits = 0x4B400000u;
+    static constexpr uint32_t kFields = 1u + (1u << QB) + (1u << 2 * QB) + (1u << 3 * QB) + (QB == 4 ? 0x11110000u : (1u << 4 * QB) + (1u << 5 * QB) + (1u << 6 * QB) + (1u << 7 * QB));
+    __device__ __forceinline__ KvGrid(float mx, float mn, float clip) {
+        mx *= clip;
+        mn *= clip;
+        step = (_Float16)((mx - mn) * (1.0f / LV));                // round-to-nearest-even to fp16
+        const float s = (float)step;
+        inv = (s > 0.0f && s <= 65504.0f) ? __builtin_amdgcn_rcpf(s) : 0.0f;
+        z = __builtin_fminf(__builtin_fmaxf(__builtin_rintf(-mn * inv), 0.0f), LV);
+        // q = clamp(round(y / s) + z, 0, LV) = round(clamp(y, -z s, (LV - z) s) / s) + z: clamp, then one fma against
+        // 1.5 * 2^23 rounds y / s on its own (ties to even, as the definition has it) and leaves 0x4B400000 + round(y / s)
+        // in the register (two's complement in the low bits), so 8 results chain with shift-adds; the constant part
+        // (0x4B400000 times the sum of the shifts) comes off and the zero point (z in every field) goes on in one
+        // integer addition per 8 codes, all modulo 2^32: every field then holds its code, 0 .. LV, and nothing above.
+        const float sl = (inv != 0.0f) ? s : 0.0f;
+        lim_lo = -z * sl;
+        lim_hi = (LV - z) * sl;
+        chain_fix = (uint32_t)(int)z * kFields - kMagicBits * kFields;
+    }
+    template <typename F>
+    __device__ __forceinline__ uint32_t pack8(F&& y) const {
+        uint32_t bits[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float yc = __builtin_amdgcn_fmed3f(y(k), lim_lo, lim_hi);
+            bits[k] = __builtin_bit_cast(uint32_t, __builtin_fmaf(yc, inv, 12582912.0f));
+        }
+        const uint32_t lo4 = lshl_add(lshl_add(bits[3], QB, bits[2]), 2 * QB, lshl_add(bits[1], QB, bits[0]));
+        const uint32_t hi4 = lshl_add(lshl_add(bits[7], QB, bits[6]), 2 * QB, lshl_add(bits[5], QB, bits[4]));
+        return lshl_add(hi4, 4 * QB, lo4) + chain_fix;
+    }
+};
+
 // BITS = 2, 3, 4: asymmetric codes of that width + step + zero point per group.  BITS = 0: the transformed rows
 // themselves, rounded to fp16 (p.out_codes then points at an fp16 [T, H, D] tensor): the query side of a transformed
 // key cache.
@@ -189,40 +229,15 @@ __global__ __launch_bounds__(KV_NT) __attribute__((amdgpu_waves_per_eu(2))) void
             }
         mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32));
         mn = __builtin_fminf(mn, __shfl_xor(mn, 32));
-        mx *= clip;
-        mn *= clip;
-        constexpr int QB = BITS ? BITS : 4;                        // (the fp16-out instance never gets here)
-        constexpr float LV = (float)((1 << QB) - 1);              // 2^b - 1 intervals
-        const _Float16 sh = (_Float16)((mx - mn) * (1.0f / LV));   // round-to-nearest-even to fp16
-        const float s = (float)sh;
-        const float inv = (s > 0.0f && s <= 65504.0f) ? __builtin_amdgcn_rcpf(s) : 0.0f;
-        const float z = __builtin_fminf(__builtin_fmaxf(__builtin_rintf(-mn * inv), 0.0f), LV);
-        // q = clamp(round(y / s) + z, 0, LV) = round(clamp(y, -z s, (LV - z) s) / s) + z: clamp, then one fma against
-        // 1.5 * 2^23 rounds y / s on its own (ties to even, as the definition has it) and leaves 0x4B400000 + round(y / s)
-        // in the register (two's complement in the low bits), so 8 results chain with shift-adds; the constant part
-        // (0x4B400000 times the sum of the shifts) comes off and the zero point (z in every field) goes on in one
-        // integer addition per 8 codes, all modulo 2^32: every field then holds its code, 0 .. LV, and nothing above.
-        const float sl = (inv != 0.0f) ? s : 0.0f;
-        const float lim_lo = -z * sl, lim_hi = (LV - z) * sl;
-        constexpr float magic = 12582912.0f;
-        constexpr uint32_t kMagicBits = 0x4B400000u;
-        constexpr uint32_t kFields = 1u + (1u << QB) + (1u << 2 * QB) + (1u << 3 * QB) + (QB == 4 ? 0x11110000u : (1u << 4 * QB) + (1u << 5 * QB) + (1u << 6 * QB) + (1u << 7 * QB));
-        const uint32_t chain_fix = (uint32_t)(int)z * kFields - kMagicBits * kFields;
+        const KvGrid<BITS ? BITS : 4> g(mx, mn, clip);              // (the fp16-out instance never gets here)
+        constexpr int QB = BITS ? BITS : 4;
 
         uint8_t* srow = stage + c * KV_STAGE_PITCH;
 #pragma unroll
         for (int mt = 0; mt < KV_MT; ++mt)
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                uint32_t bits[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const float yc = __builtin_amdgcn_fmed3f(acc[mt][8 * u + k], lim_lo, lim_hi);
-                    bits[k] = __builtin_bit_cast(uint32_t, __builtin_fmaf(yc, inv, magic));
-                }
-                const uint32_t lo4 = lshl_add(lshl_add(bits[3], QB, bits[2]), 2 * QB, lshl_add(bits[1], QB, bits[0]));
-                const uint32_t hi4 = lshl_add(lshl_add(bits[7], QB, bits[6]), 2 * QB, lshl_add(bits[5], QB, bits[4]));
-                const uint32_t pk = lshl_add(hi4, 4 * QB, lo4) + chain_fix;   // 8 codes, 8 QB bits
+                const uint32_t pk = g.pack8([&](int k) { return acc[mt][8 * u + k]; });   // 8 codes, 8 QB bits
                 const int dp = 32 * mt + 16 * u + 8 * h;   // first of 8 consecutive output channels
                 if constexpr (QB == 4) {
                     *reinterpret_cast<uint32_t*>(srow + (dp >> 1)) = pk;
@@ -255,8 +270,8 @@ __global__ __launch_bounds__(KV_NT) __attribute__((amdgpu_waves_per_eu(2))) void
         }
         if (h == 0) {   // both half-waves hold the same step and zero point: one of them stores
             const size_t go = group_ofs(blk, c);
-            (p.out_scales + g0)[go] = sh;
-            (p.out_zeros + g0)[go] = (_Float16)z;
+            (p.out_scales + g0)[go] = g.step;
+            (p.out_zeros + g0)[go] = (_Float16)g.z;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();   // staged rows are consumed before the next step overwrites them
@@ -270,8 +285,107 @@ __global__ __launch_bounds__(KV_NT) __attribute__((amdgpu_waves_per_eu(2))) void
     }
 }
 
+// Few groups: a workgroup takes 32 groups, each of its four waves 32 of the 128 outputs, so that a launch is one chain of one
+// quarter of the products, with a quarter of P_h per wave (its fragments go through a part of LDS that belongs to the wave and
+// stay in registers), and four times as many CUs take part.  The groups' ranges meet in LDS.  Same arithmetic in the same
+// order as above: the same bits.  What bounds it: latency (the launch, P_h and the rows on their way, eight MFMAs in a row, the
+// exchange of the ranges).
+template <int BITS>
+__global__ __launch_bounds__(KV_NT) void kv_few_kernel(KvDev p) {
+    constexpr int QB = BITS ? BITS : 4;
+    constexpr int PITCH = 32 + 8;                                 // halves per row of a wave's 32 columns of P_h
+    __shared__ __attribute__((aligned(16))) _Float16 Pw_all[KV_WAVES * KV_D * PITCH];
+    __shared__ float2 range[KV_WAVES][KV_TOK];
+    const int tid = threadIdx.x;
+    const int l = tid & 63, c = l & 31, h = l >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int head = blockIdx.y;
+    const _Float16* Ph = p.P + (size_t)(p.Hp == 1 ? 0 : head) * KV_D * KV_D + 32 * w;
+    _Float16* Pw = Pw_all + w * KV_D * PITCH;
+    u32x4 v[8], rows[KV_KB];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const u32x4*>(Ph + (16 * k + (l >> 2)) * KV_D + 8 * (l & 3));
+    // groups past the end: the last one again, stored onto itself
+    const int64_t g0 = (int64_t)blockIdx.x * KV_TOK * p.H + head, left = p.T - 1 - (int64_t)blockIdx.x * KV_TOK;
+    const size_t gofs = (size_t)((int64_t)c < left ? c : (int)left) * p.H;
+    const u32x4* row = reinterpret_cast<const u32x4*>(p.kv + g0 * KV_D) + gofs * (KV_D / 8);
+#pragma unroll
+    for (int kb = 0; kb < KV_KB; ++kb) rows[kb] = row[2 * kb + h];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) *reinterpret_cast<u32x4*>(Pw + (16 * k + (l >> 2)) * PITCH + 8 * (l & 3)) = v[k];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    half8 a[KV_KB];
+#pragma unroll
+    for (int kb = 0; kb < KV_KB; ++kb) a[kb] = lds_column8<true>(Pw, PITCH, 16 * kb + 8 * h, 4, c & 16, l & 15);
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+    for (int kb = 0; kb < KV_KB; ++kb) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[kb], __builtin_bit_cast(half8, rows[kb]), acc, 0, 0, 0);
+    if constexpr (BITS == 0) {                                    // runs of 8 consecutive channels: 16-byte stores
+        _Float16* out = reinterpret_cast<_Float16*>(p.out_codes) + (g0 + gofs) * KV_D + 32 * w + 8 * h;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            half8 o;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) o[k] = (_Float16)acc[8 * u + k];
+            *reinterpret_cast<half8*>(out + 16 * u) = o;
+        }
+        return;
+    }
+    float mx = 0.0f, mn = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+        mx = __builtin_fmaxf(__builtin_fmaxf(mx, acc[r]), acc[r + 1]);
+        mn = __builtin_fminf(__builtin_fminf(mn, acc[r]), acc[r + 1]);
+    }
+    mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32));
+    mn = __builtin_fminf(mn, __shfl_xor(mn, 32));
+    range[w][c] = float2{mx, mn};
+    __syncthreads();
+    mx = mn = 0.0f;
+#pragma unroll
+    for (int x = 0; x < KV_WAVES; ++x) {
+        const float2 r = range[x][c];
+        mx = __builtin_fmaxf(mx, r.x);
+        mn = __builtin_fminf(mn, r.y);
+    }
+    const KvGrid<QB> g(mx, mn, p.clip);
+    uint32_t pk[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) pk[u] = g.pack8([&](int k) { return acc[8 * u + k]; });
+    // the half-waves exchange so that each lane has two consecutive runs of 8 codes: 2 QB bytes
+    const auto sw = __builtin_amdgcn_permlane32_swap(pk[0], pk[1], false, false);
+    const uint32_t p0 = sw[0], p1 = sw[1];
+    uint8_t* out = p.out_codes + (g0 + gofs) * (16 * QB) + 4 * QB * w;
+    if constexpr (QB == 4) {
+        *reinterpret_cast<uint2*>(out + 8 * h) = uint2{p0, p1};
+    } else if constexpr (QB == 2) {
+        *reinterpret_cast<uint32_t*>(out + 4 * h) = (p0 & 0xFFFFu) | (p1 << 16);
+    } else {                                                      // 6 bytes at 6 h: the dword of them that is aligned, and the rest
+        const uint32_t lo = (p0 & 0xFFFFFFu) | (p1 << 24), hi = (p1 >> 8) & 0xFFFFu;      // 48 bits
+        *reinterpret_cast<uint32_t*>(out + 8 * h) = h ? (lo >> 16) | (hi << 16) : lo;
+        *reinterpret_cast<uint16_t*>(out + 4 + 2 * h) = (uint16_t)(h ? lo : hi);
+    }
+    if (w == 0 && h == 0) {
+        (p.out_scales + g0)[gofs] = g.step;
+        (p.out_zeros + g0)[gofs] = (_Float16)g.z;
+    }
+}
+
 template <int BITS>
 static hipError_t kv_launch_mode(const KvArgs& a, hipStream_t stream) {
+    KvDev d;
+    d.kv = a.kv; d.P = a.P; d.out_codes = a.out_codes; d.out_scales = a.out_scales; d.out_zeros = a.out_zeros;
+    d.T = a.T; d.H = a.H; d.Hp = a.Hp; d.clip = a.clip;
+    const int64_t nblk = (a.T + KV_TOK - 1) / KV_TOK;
+    // Up to one workgroup per CU the few-group kernel: 64 x 32 groups 4.5 -> 3.4 us at 4 bits, 5.1 -> 3.4 at 3, 4.4 -> 3.1 as fp16 rows
+    // (1.6 us of it launch); with 320 of them both take 4.6, with 512 4.9 / 4.7, with 1024 7.3 / 4.9 (every workgroup fetches P_h).
+    // FLATQUANT_KV_FEW forces it (1) or the other one (0).
+    if (env_int("FLATQUANT_KV_FEW", nblk * a.H <= cu_count()) != 0)
+        return launch(kv_few_kernel<BITS>, dim3((unsigned)nblk, (unsigned)a.H), dim3(KV_NT), 0, stream, d);
     constexpr int LDS = BITS ? KV_LDS_BYTES : KV_OUT_LDS_BYTES;
     static OccCache occ_cache;
     int occ = 0;
@@ -285,15 +399,11 @@ static hipError_t kv_launch_mode(const KvArgs& a, hipStream_t stream) {
     // number further (0: as many as fit).
     const int cap = env_int("FLATQUANT_KV_WG_PER_CU", 1);
     if (cap > 0 && cap < occ) occ = cap;
-    const int64_t nblk = (a.T + KV_TOK - 1) / KV_TOK;
     const int64_t need = (nblk + KV_WAVES - 1) / KV_WAVES;               // workgroups per head if each wave took one step
     int64_t gx = ((int64_t)cu_count() * occ + a.H - 1) / a.H;            // resident workgroups, shared among the heads
     if (gx < 1) gx = 1;
     const int64_t rounds = (need + gx - 1) / gx;                         // same number of steps (+-1) for every workgroup
     gx = (need + rounds - 1) / rounds;
-    KvDev d;
-    d.kv = a.kv; d.P = a.P; d.out_codes = a.out_codes; d.out_scales = a.out_scales; d.out_zeros = a.out_zeros;
-    d.T = a.T; d.H = a.H; d.Hp = a.Hp; d.clip = a.clip;
     return launch(kv_kernel<BITS>, dim3((unsigned)gx, (unsigned)a.H), dim3(KV_NT), LDS, stream, d);
 }
 

@@ -517,6 +517,29 @@ def test_kv_cache_lower_bits(bits, T, H, shared):
             assert np.array_equal(c4, codes) and np.array_equal(s4.view(np.uint16), sc.view(np.uint16)) and np.array_equal(z4.view(np.uint16), zr.view(np.uint16))
 
 
+@pytest.mark.parametrize("T,H,shared", [(1, 1, True), (1, 33, True), (31, 1, False), (32, 3, False), (33, 2, False), (65, 5, True), (700, 13, True), (3000, 3, False)])
+@pytest.mark.parametrize("bits", [0, 2, 3, 4])
+def test_kv_kernels_for_few_and_many_groups_agree(tuning, bits, T, H, shared):
+    """Both KV kernels forced on launches below and above the line between them: the same bytes from both (the parity tests
+    above hold each of them against the oracle, on its own side of the line), and nothing written beside them."""
+    kv = synth.kv_cache(T=T, H=H)
+    x, P = dev(kv.k), dev(kv.P[:1] if shared else kv.P)
+    res = []
+    for few in (0, 1):
+        tuning("FLATQUANT_KV_FEW", few)
+        out = torch.full((T * H + 1, 16 * bits or 256), 0xA5, dtype=torch.uint8, device="cuda")
+        sc, zr = (torch.full((T * H + 1,), -7.0, dtype=torch.float16, device="cuda") for _ in range(2))
+        print(f"[case] kv few={few} bits={bits} T={T} H={H} shared={shared}", flush=True)
+        if bits:
+            fq.flatquant_kv_transform_quant_bits(x, P, P.shape[0], kv.clip, bits, T, H, 128, out, sc, zr, stream=torch.cuda.current_stream())
+            assert float(sc[-1]) == -7 and float(zr[-1]) == -7
+        else:
+            fq.flatquant_head_transform(x, P, P.shape[0], T, H, 128, out, stream=torch.cuda.current_stream())
+        assert bool((out[-1] == 0xA5).all())
+        res.append((out, sc.view(torch.int16), zr.view(torch.int16)))
+    assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
 def test_dequant_bits_helper():
     r = np.random.Generator(np.random.PCG64(4))
     for bits in (2, 3, 4):
