@@ -1,9 +1,13 @@
-"""ctypes binding of libflatquant.so: argument marshalling only.
+"""Binding of libflatquant.so: argument marshalling only.
 
 Functions have the names of the C entry points (see include/flatquant.h).  They
 accept raw device addresses (ints) or objects with ``data_ptr()`` (torch
-tensors); nothing is computed in Python.  There is no fallback: if the shared
+tensors); nothing is computed in Python.  There is no fallback: if a shared
 library is missing, loading raises.
+
+The entry points of a model's forward pass (``NATIVE``) are functions of the extension module ``_fqcall``
+(csrc/fq_python.cpp) with the signatures of their C counterparts, minus the types, plus ``stream=None, check=True``; they are
+loaded when the first of them is asked for.  The others call through ctypes.
 """
 from __future__ import annotations
 
@@ -23,6 +27,12 @@ EXPORTS = (
     "flatquant_weight_transform_quant", "fq_inverse_transpose", "flatquant_head_transform", "flatquant_w4a4_gemm",
     "fq_supported", "fq_choose_factors", "fq_default_design_fits", "fq_lds_bytes",
     "fq_status_string", "fq_last_hip_error", "fq_abi_version", "fq_set_tuning",
+)
+
+NATIVE = (
+    "flatquant_transform_quant", "flatquant_transform_mxfp4", "flatquant_transform_mxfp4_tiled", "flatquant_weight_transform_quant",
+    "flatquant_w4a4_gemm", "flatquant_mxfp4_gemm", "flatquant_kv_transform_quant", "flatquant_kv_transform_quant_bits",
+    "flatquant_head_transform",
 )
 
 _lib = None
@@ -110,6 +120,21 @@ def _stream(stream) -> Optional[int]:
     return int(stream.cuda_stream) or None      # torch.cuda.Stream
 
 
+def __getattr__(name):
+    """The native entry points, on first use (a module attribute from then on)."""
+    if name not in NATIVE:
+        raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
+    lib()
+    try:
+        from . import _fqcall
+    except ImportError as e:
+        raise FileNotFoundError(f"{os.path.join(_PKG, '_fqcall.so')} cannot be loaded: build it with "
+                                "`python -m paper_2410_09426_amd.build`") from e
+    _fqcall.set_error(FlatQuantError)
+    globals().update((n, getattr(_fqcall, n)) for n in NATIVE)
+    return globals()[name]
+
+
 def status_string(status: int) -> str:
     return lib().fq_status_string(int(status)).decode()
 
@@ -118,68 +143,14 @@ def last_hip_error() -> int:
     return int(lib().fq_last_hip_error())
 
 
-def flatquant_transform_quant(x, P1, P2, clip, clip_mode: int, T: int, n1: int, n2: int, x_stride: int,
-                              out_codes, out_scales, stream=None, check: bool = True) -> int:
-    st = lib().flatquant_transform_quant(_ptr(x), _ptr(P1), _ptr(P2), _ptr(clip), int(clip_mode), int(T), int(n1),
-                                         int(n2), int(x_stride), _ptr(out_codes), _ptr(out_scales), _stream(stream))
-    if check and st != FQ_OK:
-        raise FlatQuantError(st, "flatquant_transform_quant")
-    return st
-
-
-def flatquant_kv_transform_quant(kv, P, Hp: int, clip: float, T: int, H: int, D: int, out_codes, out_scales, out_zeros,
-                                 stream=None, check: bool = True) -> int:
-    st = lib().flatquant_kv_transform_quant(_ptr(kv), _ptr(P), int(Hp), float(clip), int(T), int(H), int(D),
-                                            _ptr(out_codes), _ptr(out_scales), _ptr(out_zeros), _stream(stream))
-    if check and st != FQ_OK:
-        raise FlatQuantError(st, "flatquant_kv_transform_quant")
-    return st
-
-
-def flatquant_transform_mxfp4(x, P1, P2, clip, clip_mode: int, T: int, n1: int, n2: int, x_stride: int, out_codes, out_scales,
-                              stream=None, check: bool = True) -> int:
-    st = lib().flatquant_transform_mxfp4(_ptr(x), _ptr(P1), _ptr(P2), _ptr(clip), int(clip_mode), int(T), int(n1), int(n2),
-                                         int(x_stride), _ptr(out_codes), _ptr(out_scales), _stream(stream))
-    if check and st != FQ_OK:
-        raise FlatQuantError(st, "flatquant_transform_mxfp4")
-    return st
-
-
-def flatquant_transform_mxfp4_tiled(x, P1, P2, clip, clip_mode: int, T: int, n1: int, n2: int, x_stride: int, out_codes,
-                                    out_scales, stream=None, check: bool = True) -> int:
-    st = lib().flatquant_transform_mxfp4_tiled(_ptr(x), _ptr(P1), _ptr(P2), _ptr(clip), int(clip_mode), int(T), int(n1), int(n2),
-                                               int(x_stride), _ptr(out_codes), _ptr(out_scales), _stream(stream))
-    if check and st != FQ_OK:
-        raise FlatQuantError(st, "flatquant_transform_mxfp4_tiled")
-    return st
-
-
 def fq_mxfp4_tiled_scale_bytes(rows: int, n: int) -> int:
     return int(lib().fq_mxfp4_tiled_scale_bytes(int(rows), int(n)))
-
-
-def flatquant_mxfp4_gemm(x_codes, x_scales, w_codes, w_scales, T: int, m: int, n: int, out, out_stride: int,
-                         stream=None, check: bool = True) -> int:
-    st = lib().flatquant_mxfp4_gemm(_ptr(x_codes), _ptr(x_scales), _ptr(w_codes), _ptr(w_scales), int(T), int(m), int(n),
-                                    _ptr(out), int(out_stride), _stream(stream))
-    if check and st != FQ_OK:
-        raise FlatQuantError(st, "flatquant_mxfp4_gemm")
-    return st
 
 
 def flatquant_dequant_mxfp4(codes, scales, rows: int, n: int, out, stream=None, check: bool = True) -> int:
     st = lib().flatquant_dequant_mxfp4(_ptr(codes), _ptr(scales), int(rows), int(n), _ptr(out), _stream(stream))
     if check and st != FQ_OK:
         raise FlatQuantError(st, "flatquant_dequant_mxfp4")
-    return st
-
-
-def flatquant_kv_transform_quant_bits(kv, P, Hp: int, clip: float, bits: int, T: int, H: int, D: int, out_codes, out_scales,
-                                      out_zeros, stream=None, check: bool = True) -> int:
-    st = lib().flatquant_kv_transform_quant_bits(_ptr(kv), _ptr(P), int(Hp), float(clip), int(bits), int(T), int(H), int(D),
-                                                 _ptr(out_codes), _ptr(out_scales), _ptr(out_zeros), _stream(stream))
-    if check and st != FQ_OK:
-        raise FlatQuantError(st, "flatquant_kv_transform_quant_bits")
     return st
 
 
@@ -195,31 +166,6 @@ def flatquant_dequant(codes, scales, zeros, rows: int, n: int, out, stream=None,
     st = lib().flatquant_dequant(_ptr(codes), _ptr(scales), _ptr(zeros), int(rows), int(n), _ptr(out), _stream(stream))
     if check and st != FQ_OK:
         raise FlatQuantError(st, "flatquant_dequant")
-    return st
-
-
-def flatquant_weight_transform_quant(w, A1, A2, clip, clip_mode: int, m: int, n1: int, n2: int, w_stride: int,
-                                     out_codes, out_scales, stream=None, check: bool = True) -> int:
-    st = lib().flatquant_weight_transform_quant(_ptr(w), _ptr(A1), _ptr(A2), _ptr(clip), int(clip_mode), int(m), int(n1),
-                                                int(n2), int(w_stride), _ptr(out_codes), _ptr(out_scales), _stream(stream))
-    if check and st != FQ_OK:
-        raise FlatQuantError(st, "flatquant_weight_transform_quant")
-    return st
-
-
-def flatquant_w4a4_gemm(x_codes, x_scales, w_codes, w_scales, T: int, m: int, n: int, out, out_stride: int,
-                        stream=None, check: bool = True) -> int:
-    st = lib().flatquant_w4a4_gemm(_ptr(x_codes), _ptr(x_scales), _ptr(w_codes), _ptr(w_scales), int(T), int(m), int(n),
-                                   _ptr(out), int(out_stride), _stream(stream))
-    if check and st != FQ_OK:
-        raise FlatQuantError(st, "flatquant_w4a4_gemm")
-    return st
-
-
-def flatquant_head_transform(x, P, Hp: int, T: int, H: int, D: int, out, stream=None, check: bool = True) -> int:
-    st = lib().flatquant_head_transform(_ptr(x), _ptr(P), int(Hp), int(T), int(H), int(D), _ptr(out), _stream(stream))
-    if check and st != FQ_OK:
-        raise FlatQuantError(st, "flatquant_head_transform")
     return st
 
 

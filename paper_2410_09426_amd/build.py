@@ -1,13 +1,15 @@
-"""Compile libflatquant.so (gfx950) in-tree with hipcc.  `python -m paper_2410_09426_amd.build`."""
+"""Compile libflatquant.so (gfx950) and the extension module _fqcall.so in-tree with hipcc.  `python -m paper_2410_09426_amd.build`."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libflatquant.so")
+CALLS = os.path.join(PKG, "_fqcall.so")     # CPython calls of the library's entry points (host code only)
 SOURCES = ["fq_api.hip", "fq_transform_quant.hip", "fq_tq_fast.hip", "fq_tq_wave.hip", "fq_kv.hip", "fq_dequant.hip", "fq_probe.hip", "fq_gemm.hip", "fq_gemm_mx.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          # keep hipcc from forming packed-fp32 VALU ops from scalar float code
@@ -28,6 +30,16 @@ def hipcc() -> str:
 FILE_FLAGS = {"fq_kv.hip": ["-fno-honor-nans"], "fq_tq_wave.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"]}
 
 
+def link(cmd, verbose: bool) -> None:
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link failed:\n" + r.stdout)
+    if verbose and r.stdout.strip():
+        print(r.stdout.strip())
+
+
 def build(verbose: bool = True, extra_flags=()) -> str:
     objs = []
     procs = []
@@ -45,12 +57,9 @@ def build(verbose: bool = True, extra_flags=()) -> str:
             raise RuntimeError(f"hipcc failed on {s}:\n{out}")
         if verbose and out.strip():
             print(out)
-    cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("link failed:\n" + r.stdout)
+    link([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], verbose)
+    link([hipcc(), "-x", "c++", "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "fq_python.cpp"), "-L" + PKG, "-lflatquant", "-Wl,-rpath,$ORIGIN", "-o", CALLS], verbose)
     return LIB
 
 

@@ -45,42 +45,27 @@ hipError_t kernel_occupancy(const void* fn, int threads, int lds, OccCache& cach
     return hipSuccess;
 }
 
-// Tuning overrides (kernel flavour, workgroups per CU, ...): for measurements and for the tests that must reach every
-// code path.  Each starts from the environment variable of the same name, read once per process, and can be changed
-// with fq_set_tuning; a launch only reads two atomics per override (no getenv on the launch path).
+KnobState g_knobs[(int)Knob::COUNT];
 namespace {
-struct Tunable {
-    const char* name;
-    std::atomic<int> state{0};   // 0: environment not read yet, 1: unset (callers use their default), 2: set
-    std::atomic<int> value{0};
-    explicit Tunable(const char* n) : name(n) {}
-};
-Tunable g_tunables[] = {Tunable("FLATQUANT_MODE"), Tunable("FLATQUANT_WG_PER_CU"), Tunable("FLATQUANT_FORCE_GENERIC"),
-                        Tunable("FLATQUANT_KV_WG_PER_CU"), Tunable("FLATQUANT_GEMM_TILED"),
-                        Tunable("FLATQUANT_GEMM_WIDE"), Tunable("FLATQUANT_GEMM_DEPTH"), Tunable("FLATQUANT_GEMM_WAVES"), Tunable("FLATQUANT_GEMM_ROWS"), Tunable("FLATQUANT_GEMM_RING_MAX_T"), Tunable("FLATQUANT_KV_FOLD_HEADS"), Tunable("FLATQUANT_KV_FEW"), Tunable("FLATQUANT_WAVE_TPW"), Tunable("FLATQUANT_PROBE_SHAPE")};
-Tunable* find_tunable(const char* name) {
-    for (Tunable& t : g_tunables)
-        if (std::strcmp(t.name, name) == 0) return &t;
-    return nullptr;
-}
+const char* const kKnobNames[] = {"FLATQUANT_MODE", "FLATQUANT_WG_PER_CU", "FLATQUANT_FORCE_GENERIC", "FLATQUANT_KV_WG_PER_CU", "FLATQUANT_GEMM_TILED", "FLATQUANT_GEMM_WIDE", "FLATQUANT_GEMM_DEPTH", "FLATQUANT_GEMM_WAVES", "FLATQUANT_GEMM_ROWS", "FLATQUANT_GEMM_RING_MAX_T", "FLATQUANT_KV_FOLD_HEADS", "FLATQUANT_KV_FEW", "FLATQUANT_WAVE_TPW", "FLATQUANT_PROBE_SHAPE"};
+static_assert(sizeof(kKnobNames) / sizeof(kKnobNames[0]) == (size_t)Knob::COUNT, "a name for every override");
 }  // namespace
 
-int env_int(const char* name, int dflt) {
-    Tunable* t = find_tunable(name);
-    if (!t) return dflt;
-    int st = t->state.load(std::memory_order_acquire);
+int tuned_slow(Knob k, int dflt) {
+    KnobState& t = g_knobs[(int)k];
+    int st = t.state.load(std::memory_order_acquire);
     if (st == 0) {   // first use in this process (a second thread doing the same stores the same values)
-        const char* v = std::getenv(name);
+        const char* v = std::getenv(kKnobNames[(int)k]);
         if (v && *v) {
-            t->value.store(std::atoi(v), std::memory_order_relaxed);
+            t.value.store(std::atoi(v), std::memory_order_relaxed);
             st = 2;
         } else {
             st = 1;
         }
         int expected = 0;
-        if (!t->state.compare_exchange_strong(expected, st, std::memory_order_acq_rel)) st = expected;   // fq_set_tuning came first
+        if (!t.state.compare_exchange_strong(expected, st, std::memory_order_acq_rel)) st = expected;   // fq_set_tuning came first
     }
-    return st == 2 ? t->value.load(std::memory_order_relaxed) : dflt;
+    return st == 2 ? t.value.load(std::memory_order_relaxed) : dflt;
 }
 
 static fq_status finish(hipError_t e) {
@@ -403,13 +388,15 @@ int fq_last_hip_error(void) { return fq::g_last_hip_error; }
 
 fq_status fq_set_tuning(const char* name, int value, int enable) {
     if (!name) return FQ_INVALID_ARG;
-    fq::Tunable* t = fq::find_tunable(name);
-    if (!t) return FQ_INVALID_ARG;
+    int k = 0;
+    while (k < (int)fq::Knob::COUNT && std::strcmp(fq::kKnobNames[k], name) != 0) ++k;
+    if (k == (int)fq::Knob::COUNT) return FQ_INVALID_ARG;
+    fq::KnobState& t = fq::g_knobs[k];
     if (enable) {
-        t->value.store(value, std::memory_order_relaxed);
-        t->state.store(2, std::memory_order_release);
+        t.value.store(value, std::memory_order_relaxed);
+        t.state.store(2, std::memory_order_release);
     } else {
-        t->state.store(1, std::memory_order_release);
+        t.state.store(1, std::memory_order_release);
     }
     return FQ_OK;
 }

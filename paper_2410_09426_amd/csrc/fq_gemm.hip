@@ -716,8 +716,8 @@ static hipError_t skinny_launch_rows(const GemmDev& d, hipStream_t stream, int t
     // one per CU: small workgroups (4 waves, one slot) that are all resident at once; what the second slot or the
     // other four waves would hide, the neighbouring workgroup hides.  (Measured on 4096 / 11008-wide layers.)
     const bool crowded = wgs > cu_count();
-    int nwv = env_int("FLATQUANT_GEMM_WAVES", crowded ? 4 : 8);
-    int depth = env_int("FLATQUANT_GEMM_DEPTH", crowded ? 1 : 2);
+    int nwv = tuned(Knob::GEMM_WAVES, crowded ? 4 : 8);
+    int depth = tuned(Knob::GEMM_DEPTH, crowded ? 1 : 2);
     if ((nwv != 4 && nwv != 8 && nwv != 16) || depth < 1 || depth > kRingMaxDepth) return hipErrorInvalidValue;
     if (NTD >= 8 && nwv > 8) nwv = 8;                                      // two token tiles of accumulators: compiled for at most 8 waves
     while (nwv > 4 && nwv * SLOT > kRingLdsMax) nwv >>= 1;
@@ -731,7 +731,7 @@ static hipError_t skinny_launch_rows(const GemmDev& d, hipStream_t stream, int t
 // the kernel is bound by what one CU takes in, so the channels go to as many CUs as there are.
 template <int NTD>
 static hipError_t skinny_launch(const GemmDev& d, hipStream_t stream, int token_tiles = 1) {
-    const int rows = env_int("FLATQUANT_GEMM_ROWS", (int64_t)((d.m + 15) / 16) * token_tiles <= cu_count() ? 16 : 32);
+    const int rows = tuned(Knob::GEMM_ROWS, (int64_t)((d.m + 15) / 16) * token_tiles <= cu_count() ? 16 : 32);
     if (rows == 16) return skinny_launch_rows<NTD, 16>(d, stream, token_tiles);
     if (rows == 32) return skinny_launch_rows<NTD, 32>(d, stream, token_tiles);
     return hipErrorInvalidValue;
@@ -760,7 +760,7 @@ hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
     GemmDev d;
     d.xc = a.x_codes; d.xs = a.x_scales; d.wc = a.w_codes; d.ws = a.w_scales; d.out = a.out;
     d.T = a.T; d.out_stride = a.out_stride; d.m = a.m; d.n = a.n;
-    if (env_int("FLATQUANT_GEMM_TILED", 0) == 0) {
+    if (tuned(Knob::GEMM_TILED, 0) == 0) {
         // decode and short prefill chunks: one pass over the weights, K split inside a workgroup (the ring kernel)
         if (a.T <= 8) return skinny_launch<1>(d, stream);
         if (a.T <= 16) return skinny_launch<2>(d, stream);
@@ -770,7 +770,7 @@ hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
         // reach at most half of the CUs (measured cross-over on 1024 .. 11008 channels; FLATQUANT_GEMM_RING_MAX_T
         // replaces the rule by a token count).
         const int64_t tiled_wgs = ((a.T + 127) / 128) * ((a.m + 127) / 128);
-        const int ring_max = env_int("FLATQUANT_GEMM_RING_MAX_T", -1);
+        const int ring_max = tuned(Knob::GEMM_RING_MAX_T, -1);
         if (ring_max >= 0 ? a.T <= ring_max : (2 * tiled_wgs <= cu_count() && a.T <= 4096))
             return skinny_launch<8>(d, stream, (int)((a.T + 63) / 64));
     }
@@ -802,7 +802,7 @@ hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
     int form = 0;
     for (int f : {1, 2, 4})
         if (us[f] < us[form]) form = f;
-    const int asked = env_int("FLATQUANT_GEMM_WIDE", form);
+    const int asked = tuned(Knob::GEMM_WIDE, form);
     if (asked == 0 || asked == 1 || asked == 2 || asked == 4) form = asked;
     switch (form) {
         case 1: return tiled_launch<Tile<true, 4, 4, 2, 1, 2, 3, 1>>(d, stream);

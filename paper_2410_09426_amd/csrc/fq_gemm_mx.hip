@@ -496,8 +496,8 @@ static hipError_t mx_skinny_launch_rows(const MxGemmDev& d, hipStream_t stream, 
     const int nl = d.n / 256;
     // as for the INT4 product: 8 waves and two slots when there is at most one workgroup per CU, else 4 waves and one
     const bool crowded = wgs > cu_count();
-    int nwv = env_int("FLATQUANT_GEMM_WAVES", crowded ? 4 : 8);
-    int depth = env_int("FLATQUANT_GEMM_DEPTH", crowded ? 1 : 2);
+    int nwv = tuned(Knob::GEMM_WAVES, crowded ? 4 : 8);
+    int depth = tuned(Knob::GEMM_DEPTH, crowded ? 1 : 2);
     if ((nwv != 4 && nwv != 8 && nwv != 16) || depth < 1 || depth > kRingMaxDepth) return hipErrorInvalidValue;
     if (NTD >= 8 && nwv > 8) nwv = 8;                     // two token tiles of accumulators: compiled for at most 8 waves
     while (nwv > 4 && nwv * SLOT > kRingLdsMax) nwv >>= 1;
@@ -510,7 +510,7 @@ static hipError_t mx_skinny_launch_rows(const MxGemmDev& d, hipStream_t stream, 
 // 16 channels per workgroup while that still leaves at most one workgroup per CU (FLATQUANT_GEMM_ROWS forces 16 or 32)
 template <int NTD>
 static hipError_t mx_skinny_launch(const MxGemmDev& d, hipStream_t stream, int token_tiles = 1) {
-    const int rows = env_int("FLATQUANT_GEMM_ROWS", (int64_t)((d.m + 15) / 16) * token_tiles <= cu_count() ? 16 : 32);
+    const int rows = tuned(Knob::GEMM_ROWS, (int64_t)((d.m + 15) / 16) * token_tiles <= cu_count() ? 16 : 32);
     if (rows == 16) return mx_skinny_launch_rows<NTD, 16>(d, stream, token_tiles);
     if (rows == 32) return mx_skinny_launch_rows<NTD, 32>(d, stream, token_tiles);
     return hipErrorInvalidValue;
@@ -559,7 +559,7 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
     MxGemmDev d;
     d.xc = a.x_codes; d.xe = a.x_exps; d.wc = a.w_codes; d.we = a.w_exps; d.out = a.out;
     d.T = a.T; d.out_stride = a.out_stride; d.m = a.m; d.n = a.n;
-    if (env_int("FLATQUANT_GEMM_TILED", 0) == 0) {
+    if (tuned(Knob::GEMM_TILED, 0) == 0) {
         // decode and short prefill chunks: one pass over the weights, K split inside a workgroup (the ring kernel)
         if (a.T <= 8) return mx_skinny_launch<1>(d, stream);
         if (a.T <= 16) return mx_skinny_launch<2>(d, stream);
@@ -569,7 +569,7 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
         // reach at most half of the CUs (measured cross-over on 1024 .. 11008 channels; FLATQUANT_GEMM_RING_MAX_T
         // replaces the rule by a token count).
         const int64_t tiled_wgs = ((a.T + XT - 1) / XT) * ((a.m + XT - 1) / XT);
-        const int ring_max = env_int("FLATQUANT_GEMM_RING_MAX_T", -1);
+        const int ring_max = tuned(Knob::GEMM_RING_MAX_T, -1);
         if (ring_max >= 0 ? a.T <= ring_max : (2 * tiled_wgs <= cu_count() && a.T <= 4096))
             return mx_skinny_launch<8>(d, stream, (int)((a.T + 63) / 64));
     }
@@ -577,7 +577,7 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
     // what the transform produces (n <= 32768), so there is one instance for them (1024 x 2304 x 33686272: 142.8 ms; 143.8
     // with the two-stage kernel mentioned at the top, all 64-bit addresses).
     if (d.n > kOff32MaxN) return mx_tile_launch<2, 2, 2, 2, 2, 1, uint64_t>(d, stream);
-    const int rule = mx_tile_form(d), asked = env_int("FLATQUANT_GEMM_WIDE", rule);
+    const int rule = mx_tile_form(d), asked = tuned(Knob::GEMM_WIDE, rule);
     switch (asked >= 0 && asked <= 2 ? asked : rule) {
         case 1: return mx_tile_launch<4, 2, 2, 2, 3, 2>(d, stream);
         case 2: return mx_tile_launch<4, 4, 2, 2, 2, 1>(d, stream);

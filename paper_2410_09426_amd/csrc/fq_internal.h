@@ -167,7 +167,17 @@ hipError_t kernel_occupancy(const void* fn, int threads, int lds, OccCache& cach
 
 // Number of compute units of the current device (cached per device).
 int cu_count();
-// Integer tuning override from the environment (bench / sweep aid); `dflt` if unset.
-int env_int(const char* name, int dflt);
+// Tuning overrides (kernel flavour, workgroups per CU, ...), for measurements and for the tests that must reach every code
+// path; kKnobNames (fq_api.hip) has their names in the same order.  Each starts from the environment variable of that name, read
+// once per process, and can be changed with fq_set_tuning.
+enum class Knob { MODE, WG_PER_CU, FORCE_GENERIC, KV_WG_PER_CU, GEMM_TILED, GEMM_WIDE, GEMM_DEPTH, GEMM_WAVES, GEMM_ROWS, GEMM_RING_MAX_T, KV_FOLD_HEADS, KV_FEW, WAVE_TPW, PROBE_SHAPE, COUNT };
+struct KnobState {
+    std::atomic<int> state{0};   // 0: environment not read yet, 1: unset (callers use their default), 2: set
+    std::atomic<int> value{0};
+};
+extern KnobState g_knobs[(int)Knob::COUNT];
+int tuned_slow(Knob k, int dflt);
+// The override's value, or `dflt`: on the launch path one load (by index: comparing names there took 0.3 us of a product's launch).
+inline int tuned(Knob k, int dflt) { return g_knobs[(int)k].state.load(std::memory_order_acquire) == 1 ? dflt : tuned_slow(k, dflt); }
 
 }  // namespace fq

@@ -384,7 +384,7 @@ static hipError_t kv_launch_mode(const KvArgs& a, hipStream_t stream) {
     // Up to one workgroup per CU the few-group kernel: 64 x 32 groups 4.5 -> 3.4 us at 4 bits, 5.1 -> 3.4 at 3, 4.4 -> 3.1 as fp16 rows
     // (1.6 us of it launch); with 320 of them both take 4.6, with 512 4.9 / 4.7, with 1024 7.3 / 4.9 (every workgroup fetches P_h).
     // FLATQUANT_KV_FEW forces it (1) or the other one (0).
-    if (env_int("FLATQUANT_KV_FEW", nblk * a.H <= cu_count()) != 0)
+    if (tuned(Knob::KV_FEW, nblk * a.H <= cu_count()) != 0)
         return launch(kv_few_kernel<BITS>, dim3((unsigned)nblk, (unsigned)a.H), dim3(KV_NT), 0, stream, d);
     constexpr int LDS = BITS ? KV_LDS_BYTES : KV_OUT_LDS_BYTES;
     static OccCache occ_cache;
@@ -397,7 +397,7 @@ static hipError_t kv_launch_mode(const KvArgs& a, hipStream_t stream) {
     // two halves two workgroups fit, and measured 5 - 15 % slower from T = 8192 up (twice as many fragment tables to
     // build, four steps per wave instead of eight at 32768 x 8) and the same below.  FLATQUANT_KV_WG_PER_CU caps the
     // number further (0: as many as fit).
-    const int cap = env_int("FLATQUANT_KV_WG_PER_CU", 1);
+    const int cap = tuned(Knob::KV_WG_PER_CU, 1);
     if (cap > 0 && cap < occ) occ = cap;
     const int64_t need = (nblk + KV_WAVES - 1) / KV_WAVES;               // workgroups per head if each wave took one step
     int64_t gx = ((int64_t)cu_count() * occ + a.H - 1) / a.H;            // resident workgroups, shared among the heads
@@ -412,7 +412,7 @@ hipError_t kv_launch(const KvArgs& a0, hipStream_t stream) {
     // of one head, which a wave takes 32 consecutive ones at a time (8 KB in one piece) instead of 32 rows that lie
     // H * 256 bytes apart.  Same results bit for bit; 32768 x 8 x 128: 23.2 -> 19.9 us.
     KvArgs a = a0;
-    if (a.Hp == 1 && a.H > 1 && env_int("FLATQUANT_KV_FOLD_HEADS", 1)) {
+    if (a.Hp == 1 && a.H > 1 && tuned(Knob::KV_FOLD_HEADS, 1)) {
         a.T = a.T * a.H;
         a.H = 1;
     }

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void stream_probe_rows_kernel(const u32x4* __r
 
 // shape (tuning knob FLATQUANT_PROBE_SHAPE): 0 persistent two-wave workgroups, 1 a wave per row, 2 the same with plain loads
 hipError_t stream_probe_launch(const void* x, int64_t T, int n, int64_t x_stride, uint8_t* out, hipStream_t stream) {
-    const int shape = env_int("FLATQUANT_PROBE_SHAPE", 0);
+    const int shape = tuned(Knob::PROBE_SHAPE, 0);
     if (shape == 1 || shape == 2) {
         if (T > 0x7fffffff) return hipErrorInvalidConfiguration;
         const unsigned grid = (unsigned)((T + 3) / 4);

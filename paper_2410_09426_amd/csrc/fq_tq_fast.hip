@@ -705,9 +705,9 @@ bool tq_mx_applicable(const TqDev& d) {
 hipError_t tq_mx_launch(const TqDev& d, hipStream_t stream) {
     {   // 64-wide rows: the wave-per-token kernel with the MXFP4 quantizer (modes as for INT4; the tile order of the
         // exponents needs whole K iterations of 256 channels, which 32 x 64 and 64 x 64 have)
-        const int m = env_int("FLATQUANT_MODE", -1);
+        const int m = tuned(Knob::MODE, -1);
         if ((m == -1 || m == 5 || m == 6) && tq_wave_applicable(d) && (reinterpret_cast<uintptr_t>(d.out_scales) & 7) == 0)
-            return tq_wave_launch(d, stream, env_int("FLATQUANT_WAVE_TPW", 4), m == -1 ? d.T >= 32768 : m == 6, true);
+            return tq_wave_launch(d, stream, tuned(Knob::WAVE_TPW, 4), m == -1 ? d.T >= 32768 : m == 6, true);
     }
     const int A = (d.n1 + 31) / 32, B = d.n2 / 32;
     const bool full1 = (d.n1 % 32) == 0;
@@ -722,7 +722,7 @@ hipError_t tq_mx_launch(const TqDev& d, hipStream_t stream) {
         hipError_t e = occupancy(true, occ);
         if (e != hipSuccess) return e;
         one = d.T <= (int64_t)cu_count() * occ;
-        const int force = env_int("FLATQUANT_MODE", -1);
+        const int force = tuned(Knob::MODE, -1);
         if (force == 0) one = false;
         if (force == 3) one = true;
     }
@@ -779,7 +779,7 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
         {   // wave-per-token kernel (fq_tq_wave.hip), measured against the kernels below (us per launch, cold rotation):
             // 32 x 128: T = 512 4.35 / 4.45, 2048 5.6 / 7.2, 4096 9.0 / 10.8, 8192 15.7 / 17.9, 16384 28.7 / 32.1;
             // 64 x 128: T = 2048 9.6 / 12.1, 8192 35.7 / 32.3, 16384 64.7 / 59.8.  FLATQUANT_MODE = 5 forces it.
-            const int m = env_int("FLATQUANT_MODE", -1);
+            const int m = tuned(Knob::MODE, -1);
             if ((m == 5 || (m == -1 && d.T > 256 && (d.n1 == 32 || d.T <= 4096))) && po_wave_applicable(d)) return po_wave_launch(d, stream);
         }
         const bool two = (A == 2);
@@ -796,7 +796,7 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
         hipError_t e = occ_of(1, occ1);
         if (e != hipSuccess) return e;
         int one = (d.T <= (int64_t)cu_count() * occ1) ? 1 : 0;
-        const int force = env_int("FLATQUANT_MODE", -1);
+        const int force = tuned(Knob::MODE, -1);
         if (force == 0) one = 0;
         if (force == 3 && d.T <= 0x7fffffff) one = 1;
         const Variant v = kern(one);
@@ -817,9 +817,9 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
         // 131072 285 / 254.  Up to 256 tokens the latency of a token's chain of MFMAs is what counts, and the loop-free
         // slab kernel below, which splits a token over two waves, is faster (replayed from a HIP graph, us per launch,
         // wave kernel / slab kernel: T = 64 3.87 / 3.33, 256 4.01 / 3.84, 384 4.15 / 4.60, 512 4.28 / 4.84).
-        const int m = env_int("FLATQUANT_MODE", -1);
+        const int m = tuned(Knob::MODE, -1);
         if ((m == 5 || m == 6 || (m == -1 && d.T > 256)) && tq_wave_applicable(d))
-            return tq_wave_launch(d, stream, env_int("FLATQUANT_WAVE_TPW", 4), m == -1 ? d.T >= 32768 : m == 6, false);
+            return tq_wave_launch(d, stream, tuned(Knob::WAVE_TPW, 4), m == -1 ? d.T >= 32768 : m == 6, false);
     }
     // 128-wide rows (replayed from a HIP graph up to T = 8192, cold rotation above; us per launch, loop-free / plain
     // loop / pipelined loop): 64 x 128: T = 64 4.2 / 4.4 / 4.9, 512 7.7 / 7.7 / 9.3, 1024 10.5 / 10.7 / 11.4,
@@ -840,7 +840,7 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
         // (measured at T = 3072 .. 16384: 3 - 8 % over the pipelined loop)
         else if (B == 2 && d.T < 32768) mode = 4;
     }
-    const int mode_env = env_int("FLATQUANT_MODE", -1);
+    const int mode_env = tuned(Knob::MODE, -1);
     if (mode_env == 0 || (mode_env == 1 && A <= 2 && (B == 2 || B == 4 || B == 8)) || (mode_env == 2 && A <= 2) || (mode_env == 3 && A <= 2) ||
         (mode_env == 4 && A <= 2 && B == 2)) mode = mode_env;
     const int spw = (mode == 1) ? 2 : 1;
@@ -851,7 +851,7 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
         hipError_t e = occupancy(mode, occ);
         if (e != hipSuccess) return e;
     }
-    const int cap = env_int("FLATQUANT_WG_PER_CU", 0);
+    const int cap = tuned(Knob::WG_PER_CU, 0);
     if (cap > 0 && cap < occ) occ = cap;
     // every workgroup gets the same number of tokens (+-1): grid = ceil(T / ceil(T / resident workgroups))
     const int64_t resident = (int64_t)cu_count() * occ;

@@ -471,7 +471,7 @@ hipError_t tq_launch(const TqArgs& a, hipStream_t stream) {
 
     const TqDev d = tq_dev_args(a);
     // FLATQUANT_FORCE_GENERIC=1 keeps the general kernel testable on shapes the specialised ones would take
-    if (tq_fast_applicable(d) && env_int("FLATQUANT_FORCE_GENERIC", 0) == 0) return tq_fast_launch(d, stream);
+    if (tq_fast_applicable(d) && tuned(Knob::FORCE_GENERIC, 0) == 0) return tq_fast_launch(d, stream);
 
     static OccCache occ_cache[4][8];   // per variant and device
     int occ = 0;
@@ -479,7 +479,7 @@ hipError_t tq_launch(const TqArgs& a, hipStream_t stream) {
         hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(fn), nt, (int)lds, occ_cache[A - 1][B - 1], occ);
         if (e != hipSuccess) return e;
     }
-    const int cap = env_int("FLATQUANT_WG_PER_CU", 0);
+    const int cap = tuned(Knob::WG_PER_CU, 0);
     if (cap > 0 && cap < occ) occ = cap;
     int64_t grid = (int64_t)cu_count() * occ;
     if (grid > a.T) grid = a.T;

@@ -4,6 +4,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 from paper_2410_09426_amd import binding as fq
@@ -311,3 +312,56 @@ int main(void) {
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
     r = subprocess.run([str(exe)], capture_output=True, text=True, env=env)
     assert r.returncode == 0 and "sanitized host layer ok" in r.stdout, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+class _Buffer:
+    def __init__(self, address):
+        self.address = address
+
+    def data_ptr(self):
+        return self.address
+
+
+class _Stream:
+    cuda_stream = 0
+
+
+_DIMS = {"T": 0, "m": 0, "n": 256, "n1": 16, "n2": 16, "x_stride": 256, "w_stride": 256, "out_stride": 256, "Hp": 1, "H": 2, "D": 128, "bits": 3,
+         "clip_mode": 0}
+
+
+@pytest.mark.parametrize("name", fq.NATIVE)
+def test_native_calls_marshal_like_their_signatures(name):
+    """Every launching entry point, without a launch (zero rows, or an argument the library refuses): positional and named
+    arguments, addresses, buffers, None and numpy numbers reach the C function in their places, statuses and errors come back."""
+    import inspect
+    fn = getattr(fq, name)
+    params = list(inspect.signature(fn).parameters.values())
+    names = [p.name for p in params]
+    assert names[-2:] == ["stream", "check"] and params[-2].default is None and params[-1].default is True
+    assert all(p.default is inspect.Parameter.empty for p in params[:-2])
+    good = {}
+    for k, p in enumerate(names[:-2]):
+        good[p] = _DIMS[p] if p in _DIMS else 0.5 if p == "clip" and "kv" in name else 4096 * (k + 1)
+    assert fn(*good.values()) == fq.FQ_OK and fn(**good, stream=None) == fq.FQ_OK and fn(*good.values(), _Stream(), False) == fq.FQ_OK
+    same = {p: (np.int64(v) if p in _DIMS else v if isinstance(v, float) else _Buffer(v)) for p, v in good.items()}
+    assert fn(**same, stream=_Stream(), check=True) == fq.FQ_OK
+    rows = "m" if "weight" in name else "T"
+    for p in names[:-2]:                                  # every dimension in its own place: each refused by itself
+        if p in _DIMS and p not in ("m" if rows == "T" else "", "bits"):
+            bad = {**good, p: -1}
+            assert fn(*bad.values(), check=False) != fq.FQ_OK, p
+            with pytest.raises(fq.FlatQuantError, match=name) as e:
+                fn(**bad)
+            assert e.value.status != fq.FQ_OK
+    big = {**good, rows: 1, **({"m": 8} if rows == "T" and "m" in good else {})}
+    for p in names[:-2]:                                  # every pointer in its place: None and an odd address, one at a time
+        if p not in _DIMS and not isinstance(good[p], float):
+            if p not in ("P1", "P2", "A1", "A2") or "mxfp4" in name:      # (left out, these are identities)
+                assert fn(**{**big, p: None}, check=False) == fq.FQ_INVALID_ARG, p
+            if p != "out_codes" or "mxfp4" in name or "kv" in name:        # (INT4 code rows may start anywhere)
+                assert fn(**{**big, p: _Buffer(good[p] + 1)}, check=False) == fq.FQ_MISALIGNED, p
+    for args, kw in (((), {}), (tuple(good.values())[:-1], {}), (tuple(good.values()), {"no_such": 1}), (tuple(good.values()), {names[0]: 1}),
+                     (tuple(good.values()) + (None, True, 1), {}), (tuple(good.values()), {"stream": "x"})):
+        with pytest.raises((TypeError, AttributeError)):
+            fn(*args, **kw)
