@@ -568,38 +568,52 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void w4a4_skinny_kernel(Gemm
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int o0 = blockIdx.x * ROWS;
     const int64_t t0 = (int64_t)blockIdx.y * XROWS;      // more than one token tile: launches past 64 tokens (tiles of 64)
-    const int64_t kbytes = p.n / 2;
+    const uint32_t kbytes = (uint32_t)(p.n / 2);
     const int nl = p.n / 256;                            // lines per row
     const int nwv = blockDim.x >> 6;                     // waves: 4, 8 or 16
     const int ns = (nl - w + nwv - 1) / nwv;             // this wave's steps: lines w, w + nwv, ...
     unsigned char* ring = smem + w * depth * SLOT;
 
-    const unsigned char* wsrc[NWI];
-    const unsigned char* xsrc[NTD];
+    // Row 8 k + l / 8, the chunk that belongs into slot l % 8 of it: one offset per k for both operands, from a scalar base each.
+    // Rows past the end are out of the buffers' range and read as zeros.  (With 64-bit addresses and clamped rows the first
+    // request left after some 500 instructions, 1 us.)
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.wc) + (int64_t)o0 * kbytes, 0, (p.m - o0 < ROWS ? p.m - o0 : ROWS) * (int)kbytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.xc) + t0 * kbytes, 0, (int)(p.T - t0 < XROWS ? p.T - t0 : XROWS) * (int)kbytes, 0x00020000);
+    constexpr int NV = NWI > NTD ? NWI : NTD;
+    uint32_t voff[NV];
+    {
+        const uint32_t r = l >> 3, first = r * kbytes + 128 * w, ch = (l & 7) ^ (r >> 1);
 #pragma unroll
-    for (int k = 0; k < NWI; ++k) {
-        const int row = 8 * k + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-        int orow = o0 + row;
-        if (orow >= p.m) orow = p.m - 1;
-        wsrc[k] = p.wc + (int64_t)orow * kbytes + 128 * w + 16 * ch;
+        for (int k = 0; k < NV; ++k) voff[k] = first + 16 * (k & 1 ? ch ^ 4 : ch) + 8 * k * kbytes;
     }
-#pragma unroll
-    for (int k = 0; k < NTD; ++k) {
-        const int row = 8 * k + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-        int64_t t = t0 + row;
-        if (t >= p.T) t = p.T - 1;
-        xsrc[k] = p.xc + t * kbytes + 128 * w + 16 * ch;
-    }
-    typedef const __attribute__((address_space(1))) void* gptr;
     typedef __attribute__((address_space(3))) void* lptr;
     auto issue = [&](int s, int slot) {
         unsigned char* base = ring + slot * SLOT;
-        const int64_t off = (int64_t)s * (128 * nwv);
+        const int off = s * (128 * nwv);
 #pragma unroll
-        for (int k = 0; k < NWI; ++k) __builtin_amdgcn_global_load_lds((gptr)(wsrc[k] + off), (lptr)(base + k * 1024), 16, 0, 0);
+        for (int k = 0; k < NWI; ++k) __builtin_amdgcn_raw_ptr_buffer_load_lds(wbuf, (lptr)(base + k * 1024), 16, (int)voff[k], off, 0, 0);
 #pragma unroll
-        for (int k = 0; k < NTD; ++k) __builtin_amdgcn_global_load_lds((gptr)(xsrc[k] + off), (lptr)(base + XOFF + k * 1024), 16, 0, 0);
+        for (int k = 0; k < NTD; ++k) __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (lptr)(base + XOFF + k * 1024), 16, (int)voff[k], off, 0, 0);
     };
+    // The epilogue's element e = tid + k blockDim is 4 output channels of one token: their steps are requested now, so
+    // that the kernel's tail does not wait for them (at least 256 threads: k < NK).
+    constexpr int NE = NTT * NG * 64;
+    constexpr int NK = (NE + 255) / 256;
+    unsigned esx[NK] = {}, esw[NK][4] = {};              // raw fp16 bits, converted in the epilogue: nothing waits for them here
+    const __amdgpu_buffer_rsrc_t sxbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(p.xs) + t0, 0, 2 * (int)(p.T - t0 < 32 * NTT ? p.T - t0 : 32 * NTT), 0x00020000);
+    const __amdgpu_buffer_rsrc_t swbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(p.ws) + o0, 0, 2 * (p.m - o0 < ROWS ? p.m - o0 : ROWS), 0x00020000);
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        const int e = tid + k * (int)blockDim.x;
+        const int el = e & 63, g = (e >> 6) % NG, i = (e >> 6) / NG;
+        if (e < NE) {
+            esx[k] = __builtin_amdgcn_raw_buffer_load_b16(sxbuf, 2 * (32 * i + (el & 31)), 0, 0);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) esw[k][x] = __builtin_amdgcn_raw_buffer_load_b16(swbuf, 2 * (8 * g + 4 * (el >> 5) + x), 0, 0);
+        }
+    }
+    const int npre = ns < depth ? ns : depth;
+    for (int s = 0; s < npre; ++s) issue(s, s);
     i32x16 acc[NTT];
 #pragma unroll
     for (int i = 0; i < NTT; ++i)
@@ -614,27 +628,6 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void w4a4_skinny_kernel(Gemm
         xoff[i] = XOFF + row * 128;
         xhs[i] = h ^ ((row >> 1) & 7);
     }
-    // The epilogue's element e = tid + k blockDim is 4 output channels of one token: their steps are requested now, so
-    // that the kernel's tail does not wait for them (at least 256 threads: k < NK).
-    constexpr int NE = NTT * NG * 64;
-    constexpr int NK = (NE + 255) / 256;
-    unsigned esx[NK] = {}, esw[NK][4] = {};              // raw fp16 bits, converted in the epilogue: nothing waits for them here
-    const uint16_t* xs_bits = reinterpret_cast<const uint16_t*>(p.xs);
-    const uint16_t* ws_bits = reinterpret_cast<const uint16_t*>(p.ws);
-#pragma unroll
-    for (int k = 0; k < NK; ++k) {
-        const int e = tid + k * (int)blockDim.x;
-        const int el = e & 63, g = (e >> 6) % NG, i = (e >> 6) / NG;
-        const int64_t t = t0 + 32 * i + (el & 31);
-        const int o = o0 + 8 * g + 4 * (el >> 5);
-        if (e < NE) {
-            esx[k] = xs_bits[t < p.T ? t : p.T - 1];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) esw[k][x] = ws_bits[o + x < p.m ? o + x : p.m - 1];
-        }
-    }
-    const int npre = ns < depth ? ns : depth;
-    for (int s = 0; s < npre; ++s) issue(s, s);
     int slot = 0;
     for (int s = 0; s < ns; ++s) {
         const int left = ns - 1 - s;
@@ -647,6 +640,8 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void w4a4_skinny_kernel(Gemm
 #pragma unroll
             for (int i = 0; i < NTT; ++i) xv[kp][i] = *reinterpret_cast<const u32x4*>(base + xoff[i] + 16 * ((2 * kp) ^ xhs[i]));
         }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the slot has been read: it may take the next line
+        if (s + depth < ns) issue(s + depth, slot);
 #pragma unroll
         for (int kp = 0; kp < 4; ++kp) {
             i32x4 ws0, ws1;
@@ -659,8 +654,6 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void w4a4_skinny_kernel(Gemm
                 acc[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ws1, xs1, acc[i], 0, 0, 0);
             }
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the slot has been read: it may take the next line
-        if (s + depth < ns) issue(s + depth, slot);
         slot = (slot + 1 == depth) ? 0 : slot + 1;
     }
     wait_vm_pending<0>();

@@ -359,46 +359,42 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void mxfp4_skinny_kernel(MxG
     const int nwv = blockDim.x >> 6;
     const int o0 = blockIdx.x * ROWS;
     const int64_t t0 = (int64_t)blockIdx.y * XROWS;      // more than one token tile: launches past 64 tokens (tiles of 64)
-    const int64_t kbytes = p.n / 2;
+    const uint32_t kbytes = (uint32_t)(p.n / 2);
     const int nl = p.n / 256;                            // lines per row
     const int ns = (nl - w + nwv - 1) / nwv;             // this wave's steps
     unsigned char* ring = smem + w * depth * SLOT;
 
-    const unsigned char* wsrc[NWI];
-    const unsigned char* xsrc[NTD];
-#pragma unroll
-    for (int k = 0; k < NWI; ++k) {
-        const int row = 8 * k + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-        int orow = o0 + row;
-        if (orow >= p.m) orow = p.m - 1;
-        wsrc[k] = p.wc + (int64_t)orow * kbytes + 128 * w + 16 * ch;
-    }
-#pragma unroll
-    for (int k = 0; k < NTD; ++k) {
-        const int row = 8 * k + (l >> 3), ch = (l & 7) ^ ((row >> 1) & 7);
-        int64_t t = t0 + row;
-        if (t >= p.T) t = p.T - 1;
-        xsrc[k] = p.xc + t * kbytes + 128 * w + 16 * ch;
-    }
+    // Row 8 k + l / 8, the chunk that belongs into slot l % 8 of it: one offset per k for both operands, from a scalar base each.
+    // Rows past the end are out of the buffers' range and read as zeros.
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.wc) + (int64_t)o0 * kbytes, 0, (p.m - o0 < ROWS ? p.m - o0 : ROWS) * (int)kbytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.xc) + t0 * kbytes, 0, (int)(p.T - t0 < XROWS ? p.T - t0 : XROWS) * (int)kbytes, 0x00020000);
     // exponents of line j: 1 KB per tile of 128 rows, 8 bytes per row.  The workgroup's 32 channels are 256 bytes of
     // their tile; the tokens are 32, 64 or 128 consecutive rows of one tile (the tensor is padded to whole tiles, so rows
     // past T exist).
-    const unsigned char* wesrc = p.we + (int64_t)(o0 >> 7) * nl * 1024 + 8 * (o0 & 127) + 1024 * w + 4 * (l & (2 * ROWS - 1));
-    const unsigned char* xesrc = p.xe + (t0 >> 7) * nl * 1024 + 8 * (t0 & 127) + 1024 * w + 4 * l;
-    typedef const __attribute__((address_space(1))) void* gptr;
+    const __amdgpu_buffer_rsrc_t webuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.we) + (int64_t)(o0 >> 7) * nl * 1024 + 8 * (o0 & 127), 0, nl * 1024 - 8 * (o0 & 127), 0x00020000);
+    const __amdgpu_buffer_rsrc_t xebuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.xe) + (t0 >> 7) * nl * 1024 + 8 * (t0 & 127), 0, nl * 1024 - 8 * (int)(t0 & 127), 0x00020000);
+    constexpr int NV = NWI > NTD ? NWI : NTD;
+    uint32_t voff[NV];
+    {
+        const uint32_t r = l >> 3, first = r * kbytes + 128 * w, ch = (l & 7) ^ (r >> 1);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) voff[k] = first + 16 * (k & 1 ? ch ^ 4 : ch) + 8 * k * kbytes;
+    }
+    const int wev = 1024 * w + 4 * (l & (2 * ROWS - 1)), xev = 1024 * w + 4 * l;
     typedef __attribute__((address_space(3))) void* lptr;
     auto issue = [&](int s, int slot) {
         unsigned char* base = ring + slot * SLOT;
-        const int64_t off = (int64_t)s * (128 * nwv);
-        const int64_t eoff = (int64_t)s * (1024 * nwv);
+        const int off = s * (128 * nwv), eoff = 8 * off;
 #pragma unroll
-        for (int k = 0; k < NWI; ++k) __builtin_amdgcn_global_load_lds((gptr)(wsrc[k] + off), (lptr)(base + k * 1024), 16, 0, 0);
+        for (int k = 0; k < NWI; ++k) __builtin_amdgcn_raw_ptr_buffer_load_lds(wbuf, (lptr)(base + k * 1024), 16, (int)voff[k], off, 0, 0);
 #pragma unroll
-        for (int k = 0; k < NTD; ++k) __builtin_amdgcn_global_load_lds((gptr)(xsrc[k] + off), (lptr)(base + XOFF + k * 1024), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((gptr)(wesrc + eoff), (lptr)(base + WEOFF), 4, 0, 0);
+        for (int k = 0; k < NTD; ++k) __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (lptr)(base + XOFF + k * 1024), 16, (int)voff[k], off, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(webuf, (lptr)(base + WEOFF), 4, wev, eoff, 0, 0);
 #pragma unroll
-        for (int i = 0; i < NTT; ++i) __builtin_amdgcn_global_load_lds((gptr)(xesrc + eoff + 256 * i), (lptr)(base + XEOFF + 256 * i), 4, 0, 0);
+        for (int i = 0; i < NTT; ++i) __builtin_amdgcn_raw_ptr_buffer_load_lds(xebuf, (lptr)(base + XEOFF + 256 * i), 4, xev + 256 * i, eoff, 0, 0);
     };
+    const int npre = ns < depth ? ns : depth;
+    for (int s = 0; s < npre; ++s) issue(s, s);
 
     f32x16 acc[NTT];
 #pragma unroll
@@ -414,8 +410,6 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void mxfp4_skinny_kernel(MxG
         xoff[i] = XOFF + row * 128;
         xhs[i] = h ^ ((row >> 1) & 7);
     }
-    const int npre = ns < depth ? ns : depth;
-    for (int s = 0; s < npre; ++s) issue(s, s);
     int slot = 0;
     for (int s = 0; s < ns; ++s) {
         const int left = ns - 1 - s;
@@ -437,6 +431,8 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void mxfp4_skinny_kernel(MxG
 #pragma unroll
             for (int i = 0; i < NTT; ++i) xv[kp][i] = *reinterpret_cast<const u32x4*>(base + xoff[i] + 16 * ((2 * kp) ^ xhs[i]));
         }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the slot has been read: it may take the next line
+        if (s + depth < ns) issue(s + depth, slot);
 #pragma unroll
         for (int kp = 0; kp < 4; ++kp) {
             const i32x8 a = {(int)wv[kp][0], (int)wv[kp][1], (int)wv[kp][2], (int)wv[kp][3], 0, 0, 0, 0};
@@ -447,8 +443,6 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void mxfp4_skinny_kernel(MxG
                 else acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i], 4, 4, 0, (int)ew[kp >> 1], 0, (int)ex[i][kp >> 1]);
             }
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the slot has been read: it may take the next line
-        if (s + depth < ns) issue(s + depth, slot);
         slot = (slot + 1 == depth) ? 0 : slot + 1;
     }
     wait_vm_pending<0>();
@@ -559,7 +553,7 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
     MxGemmDev d;
     d.xc = a.x_codes; d.xe = a.x_exps; d.wc = a.w_codes; d.we = a.w_exps; d.out = a.out;
     d.T = a.T; d.out_stride = a.out_stride; d.m = a.m; d.n = a.n;
-    if (tuned(Knob::GEMM_TILED, 0) == 0) {
+    if (tuned(Knob::GEMM_TILED, 0) == 0 && d.n <= kOff32MaxN) {
         // decode and short prefill chunks: one pass over the weights, K split inside a workgroup (the ring kernel)
         if (a.T <= 8) return mx_skinny_launch<1>(d, stream);
         if (a.T <= 16) return mx_skinny_launch<2>(d, stream);
