@@ -165,6 +165,41 @@ __global__ __launch_bounds__(64 * (B / SPW) * TPW) __attribute__((amdgpu_waves_p
             } else {             // only 4-byte aligned: pairs
                 copy_batched(std::integral_constant<int, 8>{}, reinterpret_cast<const uint32_t*>(p.P1), n1sq >> 1, [&](int idx, uint32_t v) { reinterpret_cast<uint32_t*>(P1flat)[idx] = v; });
             }
+        } else if constexpr (A >= 4) {
+            // Four row tiles (97 .. 127 rows): a wave takes whole rows, a lane the same pair of columns of each, so that a row costs a load, a
+            // store and hardly any arithmetic (64 tokens, against the copy below: 112 x 128 9.1 -> 8.1 us, 112 x 256 13.3 -> 12.6; with
+            // shorter rows, most of whose lanes have nothing to load, that one is as fast or faster: 86 x 128 6.3 / 6.2, 48 x 64
+            // 4.4 / 5.1).  The LDS rows have the pitch of whole row tiles, the padding is zero.  Odd rows start on odd
+            // halves (unaligned dwords); their last pair is loaded one half early, so that nothing past the matrix is read.
+            constexpr int PW = 32 * A, NWV = NTA / 64, RPW = (PW + NWV - 1) / NWV, BATCH = RPW <= 32 ? RPW : 16;
+            typedef uint32_t __attribute__((aligned(2))) pair_t;
+            const int wv = __builtin_amdgcn_readfirstlane(tida >> 6), ln = tida & 63;
+            const int q = (n1 + 1) >> 1;                               // pairs per row
+            const bool half = (n1 & 1) != 0 && ln >= q - 1;            // (the lanes past the last pair repeat it)
+            const int off = half ? n1 - 2 : 2 * (ln < q ? ln : q - 1);
+            uint32_t* dst = reinterpret_cast<uint32_t*>(P1flat);
+#pragma unroll
+            for (int base = 0; base < RPW; base += BATCH) {
+                uint32_t v[BATCH];
+#pragma unroll
+                for (int k = 0; k < BATCH; ++k) {
+                    const int row = wv + (base + k) * NWV;
+                    const _Float16* src = p.P1 + (row < n1 ? row : n1 - 1) * n1;
+                    v[k] = *reinterpret_cast<const pair_t*>(src + off);
+                }
+                if (base == 0) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    after_first_loads();
+                    queued = true;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int k = 0; k < BATCH; ++k) {
+                    const int row = wv + (base + k) * NWV;
+                    const uint32_t u = half ? v[k] >> 16 : v[k];
+                    if (row < PW && ln < PW / 2) dst[row * (PW / 2) + ln] = row < n1 && ln < q ? u : 0u;
+                }
+            }
         } else {
             // Rows re-pitched to PW = n1 rounded up to whole row tiles, the padding zero.  One short code path (these
             // launches are latency-bound and every instruction line is fetched cold; a variant that moves 16-byte
