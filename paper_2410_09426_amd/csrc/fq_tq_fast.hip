@@ -21,31 +21,6 @@
 
 namespace fq {
 
-__host__ __device__ constexpr int cmax(int a, int b) { return a > b ? a : b; }
-
-// LDS carve-up, shared by host and device.
-template <int A, int B, int NBUF = 1, bool MX = false>
-struct FastLds {
-    static constexpr int N2 = 32 * B;
-    static constexpr int PITCH = N2 + kLdsPad;                       // halves per row of the token tile
-    static constexpr int XS_BYTES = 32 * A * PITCH * 2;
-    // packed codes of one token, one row of X~ (N2 / 2 bytes) per line; 16 bytes of padding per line spread the
-    // 2-byte writes of 32 lanes (one line each) over the banks instead of piling them on two
-    static constexpr int SPITCH = N2 / 2 + 16;
-    static constexpr int STAGE_BYTES = MX ? 32 * A * SPITCH : 0;   // INT4 codes leave from registers
-    static constexpr int BODY_BYTES = NBUF * (XS_BYTES + STAGE_BYTES) + 32 * (NBUF < 2 ? 2 : NBUF);   // + one absmax float per wave and buffer
-    static constexpr int P2ROWS = (B <= 4) ? N2 : N2 / 2;            // rows of P2 staged per pass
-    static constexpr int P2PASSES = N2 / P2ROWS;
-    static constexpr int P1FLAT_BYTES = 32 * A * 32 * A * 2;
-    static constexpr int STG_BYTES = P1FLAT_BYTES + P2ROWS * N2 * 2;
-    static constexpr int R0 = (cmax(BODY_BYTES, STG_BYTES) + 15) & ~15;
-    // P1's fragments stay in registers up to three row tiles x six column slabs (86 x 128: 137 -> 130 us at T=16384,
-    // 6.7 -> 6.4 us at 64 tokens); beyond that they would spill, and are read from a table in LDS at every use
-    static constexpr bool P1LDS = (A >= 4) || (A == 3 && B >= 7);
-    static constexpr int P1S_BYTES = P1LDS ? A * 2 * A * 64 * 16 : 0;
-    static constexpr int TOTAL = R0 + P1S_BYTES;
-};
-
 // KIND 0: persistent loop, one token per step; 1: persistent loop, software-pipelined over tokens;
 // 2: one token per workgroup (small T: every token gets its own workgroup, all resident at once, 4 waves per SIMD)
 // ID2: the second factor is left out (identity): only the contraction over axis 1 runs, its operand gathered from the

@@ -23,14 +23,15 @@
 //   * Codes are staged in LDS in channel order and written with 16-byte stores.
 //   * Workgroups are persistent over tokens; the next token row is prefetched
 //     into registers while the current one is in the MFMA pipe.
+//
+// tq_kernel is that kernel for MXFP4, for rows that are only quantized and for n2 < 8; tq_any_kernel, further down, takes every
+// other INT4 call that the specialised kernels (fq_tq_fast.hip) do not.
+#include <type_traits>
+
 #include "fq_internal.h"
+#include "fq_device.h"
 
 namespace fq {
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
 
 __device__ __forceinline__ half8 split_hi(const float* z, float* resid) {
     // hi = fp16(z) rounded toward zero (never overflows to inf), resid = z - hi exactly
@@ -373,6 +374,283 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(A <= 2 ?
     }
 }
 
+// INT4, any pair of factors (n2 >= 8; either may be left out: identity): the plain loop of the specialised kernels (fq_tq_fast.hip:
+// same wave mapping, contractions, rounding and packing) for right factors that are not a multiple of 32 and rows that do not
+// start on 16 bytes.  What is different: the factors' LDS copies are padded with zeros to whole tiles; a token's row is requested in
+// flat 16-byte chunks wherever they start (dword-aligned), and a chunk that straddles two rows of X~ goes into LDS in pieces of 8
+// or 4 bytes, whichever divides n2; a lane's 8 bytes of codes are stored as far as the row goes.  Against the kernel above (2-byte
+// loads of the factors, rounding and packing in 8 instructions per value, codes staged in LDS), us:
+// 64 x 80 at 64 tokens 7.4 / 5.6, 777 11.7 / 8.9, 2048 19.1 / 13.7, 16384 103.8 / 67.6; 64 x 172 10.5 / 8.2 (64), 48.5 / 28.0 (2048), 322 / 180
+// (16384); 45 x 90 22.3 / 13.7 (2048); 97 x 98 61.3 / 35.7 (2048); 128 x 250 939 / 345 (8192); 16 x 18 7.8 / 6.3 (4096).
+template <int A, int B>
+__global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) void tq_any_kernel(TqDev p) {
+    using L = FastLds<A, B>;
+    constexpr int NT = 64 * B, N2 = 32 * B, PITCH = L::PITCH, PW = 32 * A;
+    constexpr int KB1 = 2 * A, KB2 = 2 * B, NPRE = 2 * A;
+    constexpr bool P1LDS = L::P1LDS, DEEP = NPRE <= 4;
+    typedef u32x4 __attribute__((aligned(4))) chunk_t;               // token rows start on dwords,
+    typedef u32x4 __attribute__((aligned(2))) chunk2_t;              // factors on halves
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    _Float16* Xs = reinterpret_cast<_Float16*>(smem);
+    float* red = reinterpret_cast<float*>(smem + L::XS_BYTES);
+    u32x4* P1s = reinterpret_cast<u32x4*>(smem + L::R0);
+    _Float16* P1flat = reinterpret_cast<_Float16*>(smem);
+    _Float16* P2flat = reinterpret_cast<_Float16*>(smem + L::P1FLAT_BYTES);
+    const int tid = threadIdx.x, l = tid & 63, c = l & 31, h = l >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n1 = p.n1, n2 = p.n2, n = n1 * n2;
+    const int piece = (n2 & 7) == 0 ? 8 : (n2 & 3) == 0 ? 4 : 2;     // halves that never straddle a row
+
+    // ---- token rows: chunk k of this thread starts at half e, the last one early enough to end with the row; chunks past it are
+    // the last one again (same bytes to the same place), so that nothing branches
+    auto first_half = [&](int k) { return 8 * (tid + k * NT) < n - 8 ? 8 * (tid + k * NT) : n - 8; };
+    uint32_t xput[NPRE];                         // LDS offset in halves (below 2^16), halves left in its row of X~ (16 bits up)
+#pragma unroll
+    for (int k = 0; k < NPRE; ++k) {
+        const int e = first_half(k), i = (int)__umulhi((uint32_t)e, p.n2_magic), col = e - i * n2;
+        xput[k] = (uint32_t)(i * PITCH + col) | (uint32_t)(n2 - col) << 16;
+    }
+    auto issue = [&](int64_t t, u32x4 (&pre)[NPRE]) {
+        const _Float16* row = p.x + t * p.x_stride;
+#pragma unroll
+        for (int k = 0; k < NPRE; ++k) pre[k] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(row + first_half(k)));
+    };
+    // chunks to where `where` (as above) says in a matrix of `pitch`
+    auto put = [&](_Float16* dst, int pitch, auto& where, auto& v, auto cnt) {
+        constexpr int N = decltype(cnt)::value;
+        if (piece == 8) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) *reinterpret_cast<u32x4*>(dst + (where[k] & 0xFFFFu)) = v[k];
+        } else if (piece == 4) {
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+#pragma unroll
+                for (int d = 0; d < 2; ++d)
+                    *reinterpret_cast<uint2*>(dst + (int)(where[k] & 0xFFFFu) + 4 * d + (4 * d >= (int)(where[k] >> 16) ? pitch - n2 : 0)) = uint2{v[k][2 * d], v[k][2 * d + 1]};
+        } else {
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+#pragma unroll
+                for (int d = 0; d < 4; ++d) *reinterpret_cast<uint32_t*>(dst + (int)(where[k] & 0xFFFFu) + 2 * d + (2 * d >= (int)(where[k] >> 16) ? pitch - n2 : 0)) = v[k][d];
+        }
+    };
+    auto commit = [&](const u32x4 (&pre)[NPRE]) { put(Xs, PITCH, xput, pre, std::integral_constant<int, NPRE>{}); };
+    u32x4 pre0[NPRE], pre1[DEEP ? NPRE : 1];
+    int64_t t = blockIdx.x;
+    const int64_t G = gridDim.x;
+    issue(t, pre0);
+
+    // ---- the factors: requested, then their LDS image zeroed, then put into it; fragments by transposing reads
+    half8 p2f[KB2];
+    half8 p1f[P1LDS ? 1 : A][P1LDS ? 1 : KB1];
+    constexpr int N1P = (PW * PW / 2 + NT - 1) / NT, B1 = N1P < 16 ? N1P : 16;          // pairs of P1 per thread, and in flight
+    constexpr int N2C = (L::P2ROWS * N2 / 8 + NT - 1) / NT;                            // chunks of P2 per thread and pass
+#pragma unroll
+    for (int pass = 0; pass < L::P2PASSES; ++pass) {
+        const int r0 = pass * L::P2ROWS, rows = n2 - r0 < L::P2ROWS ? n2 - r0 : L::P2ROWS;    // rows of this pass (at least one)
+        const int last2 = rows * n2 - 8;                              // a left-out factor reads the first bytes of x, for nothing
+        const _Float16* s2 = p.P2 ? p.P2 + r0 * n2 : p.x;
+        u32x4 v2[N2C];
+        int e2[N2C];
+#pragma unroll
+        for (int k = 0; k < N2C; ++k) {
+            const int q = 8 * (tid + k * NT);
+            e2[k] = q < last2 ? q : last2;
+            v2[k] = *reinterpret_cast<const chunk2_t*>(s2 + (p.P2 ? e2[k] : 0));
+        }
+        const int n1sq = n1 * n1, last1 = p.P1 && n1 > 1 ? (n1sq >> 1) - 1 : 0;
+        const _Float16* s1 = p.P1 && n1 > 1 ? p.P1 : p.x;
+        auto load1 = [&](int base, uint32_t (&v)[B1]) {
+            typedef uint32_t __attribute__((aligned(2))) pair_t;
+#pragma unroll
+            for (int k = 0; k < B1; ++k) {
+                const int u = tid + (base + k) * NT;
+                v[k] = *reinterpret_cast<const pair_t*>(s1 + 2 * (u < last1 ? u : last1));
+            }
+        };
+        uint32_t v1[B1];
+        if (pass == 0) {
+            load1(0, v1);
+            if constexpr (DEEP) issue(t + G < p.T ? t + G : p.T - 1, pre1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (pass > 0) __syncthreads();                                // previous pass fully consumed
+        for (int q = tid + (pass > 0 ? L::P1FLAT_BYTES / 16 : 0); q < L::STG_BYTES / 16; q += NT) reinterpret_cast<u32x4*>(smem)[q] = u32x4{0u, 0u, 0u, 0u};
+        __syncthreads();
+        if (p.P2) {
+            uint32_t put2[N2C];
+#pragma unroll
+            for (int k = 0; k < N2C; ++k) {
+                const int i = (int)__umulhi((uint32_t)e2[k], p.n2_magic), col = e2[k] - i * n2;
+                put2[k] = (uint32_t)(i * N2 + col) | (uint32_t)(n2 - col) << 16;
+            }
+            put(P2flat, N2, put2, v2, std::integral_constant<int, N2C>{});
+        } else {
+            for (int r = tid; r < rows; r += NT) P2flat[r * N2 + r0 + r] = (_Float16)1.0f;
+        }
+        if (pass == 0) {
+            uint16_t* d1 = reinterpret_cast<uint16_t*>(P1flat);
+            if (!p.P1) {
+                for (int r = tid; r < n1; r += NT) P1flat[r * PW + r] = (_Float16)1.0f;
+            } else {
+                if (n1 > 1) {
+#pragma unroll 1
+                    for (int base = 0; base < N1P; base += B1) {
+                        if (base > 0) load1(base, v1);
+#pragma unroll
+                        for (int k = 0; k < B1; ++k) {                // each half on its own: a pair straddles two rows when n1 is odd
+                            const int u = tid + (base + k) * NT, f = 2 * (u < last1 ? u : last1);
+                            const int row = (int)__umulhi((uint32_t)f, p.n1_magic), col = f - row * n1, a0 = row * PW + col;
+                            d1[a0] = (uint16_t)v1[k];
+                            d1[a0 + 1 + (col + 1 == n1 ? PW - n1 : 0)] = (uint16_t)(v1[k] >> 16);
+                        }
+                    }
+                }
+                if ((n1 & 1) && tid == 0) d1[(n1 - 1) * PW + n1 - 1] = reinterpret_cast<const uint16_t*>(p.P1)[n1sq - 1];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int kb = pass * (L::P2ROWS / 16); kb < (pass + 1) * (L::P2ROWS / 16); ++kb)
+            p2f[kb] = lds_column8(P2flat, N2, 16 * kb - r0 + 8 * h, 4, 32 * w + (c & 16), l & 15);
+        if (pass == 0) {
+            if constexpr (P1LDS) {
+                for (int e = tid; e < A * KB1 * 64; e += NT) {
+                    const int ln = e & 63, kk = (e >> 6) % KB1, It = (e >> 6) / KB1;
+                    const half8 f = lds_column8(P1flat, PW, 32 * (kk >> 1) + 16 * (kk & 1) + 4 * (ln >> 5), 8, 32 * It + (ln & 16), ln & 15);
+                    *reinterpret_cast<half8*>(&P1s[e]) = f;
+                }
+            } else {
+#pragma unroll
+                for (int It = 0; It < A; ++It)
+#pragma unroll
+                    for (int kk = 0; kk < KB1; ++kk) p1f[It][kk] = lds_column8(P1flat, PW, 32 * (kk >> 1) + 16 * (kk & 1) + 4 * h, 8, 32 * It + (c & 16), l & 15);
+            }
+        }
+    }
+    __syncthreads();   // the staging area becomes the token tile; what no token's row covers stays zero
+    for (int q = tid; q < L::XS_BYTES / 16; q += NT) reinterpret_cast<u32x4*>(smem)[q] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    commit(pre0);
+    __syncthreads();
+
+    auto body = [&](int64_t t, u32x4 (&pre_next)[NPRE], u32x4 (&pre_far)[NPRE]) __attribute__((always_inline)) {
+        const int64_t tf = t + (DEEP ? 2 : 1) * G;
+        issue(tf < p.T ? tf : p.T - 1, pre_far);
+        __builtin_amdgcn_sched_barrier(0);
+        const float clipv = p.clip[p.clip_mode ? t : 0];
+        f32x16 acc2[A];
+#pragma unroll
+        for (int It = 0; It < A; ++It)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc2[It][r] = 0.0f;
+#pragma unroll
+        for (int I0 = 0; I0 < A; I0 += 2) {      // row tiles in pairs, so that consecutive MFMAs are independent
+            constexpr int NI_MAX = 2;
+            const int ni = A - I0 < NI_MAX ? A - I0 : NI_MAX;
+            f32x16 acc1[NI_MAX];
+#pragma unroll
+            for (int d = 0; d < NI_MAX; ++d)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc1[d][r] = 0.0f;
+            const _Float16* arow = Xs + (32 * I0 + c) * PITCH + 8 * h;
+#pragma unroll
+            for (int kb = 0; kb < KB2; ++kb)
+#pragma unroll
+                for (int d = 0; d < NI_MAX; ++d)
+                    if (d < ni) {
+                        const half8 a = *reinterpret_cast<const half8*>(arow + d * 32 * PITCH + 16 * kb);
+                        acc1[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, p2f[kb], acc1[d], 0, 0, 0);
+                    }
+#pragma unroll
+            for (int d = 0; d < NI_MAX; ++d)
+#pragma unroll
+                for (int kq = 0; kq < 2; ++kq) {
+                    const int kk = 2 * (I0 + d) + kq;
+                    if (d < ni && (A < 4 || 16 * kk < n1)) {
+                        half8 zh, zl, b[A];
+                        split_hi_lo(acc1[d], 8 * kq, zh, zl);
+#pragma unroll
+                        for (int It = 0; It < A; ++It) {
+                            if constexpr (P1LDS) b[It] = *reinterpret_cast<const half8*>(&P1s[(It * KB1 + kk) * 64 + l]);
+                            else b[It] = p1f[It][kk];
+                        }
+#pragma unroll
+                        for (int It = 0; It < A; ++It) acc2[It] = __builtin_amdgcn_mfma_f32_32x32x16_f16(zh, b[It], acc2[It], 0, 0, 0);
+#pragma unroll
+                        for (int It = 0; It < A; ++It) acc2[It] = __builtin_amdgcn_mfma_f32_32x32x16_f16(zl, b[It], acc2[It], 0, 0, 0);
+                    }
+                }
+        }
+        float m = 0.0f;                          // padded rows and columns are exact zeros
+#pragma unroll
+        for (int It = 0; It < A; ++It)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) m = __builtin_fmaxf(m, __builtin_fabsf(acc2[It][r]));
+        m = wave_max(m);
+        if (l == 0) red[w] = m;
+        __syncthreads();                         // (A) every wave is also done reading the token tile
+#pragma unroll
+        for (int b = 0; b < B; ++b) m = __builtin_fmaxf(m, red[b]);
+        const _Float16 sh = (_Float16)(clipv * m / 7.0f);             // round-to-nearest-even to fp16
+        const float s = (float)sh;
+        const float kmul = ((s > 0.0f && s <= 65504.0f) ? 1.0f / s : 0.0f) * (4096.0f / 32767.0f);
+        constexpr float kadd = 2047.5f / 32767.0f;
+        uint8_t* row_out = p.out_codes + t * (int64_t)(n >> 1);
+        const int left = n2 - 32 * w - 16 * h;   // channels of this lane's 16 that exist
+#pragma unroll
+        for (int It = 0; It < A; ++It) {
+            uint32_t Wq[2];
+#pragma unroll
+            for (int mm = 0; mm < 2; ++mm) {     // as in the specialised kernels: clamp, round and half of the packing in one conversion
+                uint32_t D[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    D[k] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pknorm_i16(__builtin_fmaf(acc2[It][8 * mm + k], kmul, kadd),
+                                                                                       __builtin_fmaf(acc2[It][8 * mm + 4 + k], kmul, kadd)));
+                const uint32_t E = __builtin_amdgcn_perm(D[2], D[0], 0x07030501u), F = __builtin_amdgcn_perm(D[3], D[1], 0x07030501u);
+                Wq[mm] = (F & 0xF0F0F0F0u) | ((E >> 4) & 0x0F0F0F0Fu);
+            }
+            const auto sw = __builtin_amdgcn_permlane32_swap(Wq[0], Wq[1], false, false);
+            uint2 o;
+            o.x = __builtin_amdgcn_perm(sw[1], sw[0], 0x05040100u);
+            o.y = __builtin_amdgcn_perm(sw[1], sw[0], 0x07060302u);
+            const int ip = 32 * It + c;
+            if (ip < n1 && left > 0) {
+                typedef unsigned int __attribute__((ext_vector_type(2), aligned(1))) codes8_t;
+                typedef uint32_t __attribute__((aligned(1))) codes4_t;
+                uint8_t* dst = row_out + ((ip * n2 + 32 * w + 16 * h) >> 1);
+                if (left >= 16) {
+                    *reinterpret_cast<codes8_t*>(dst) = codes8_t{o.x, o.y};
+                } else {                          // 1 .. 7 bytes
+                    uint32_t r = o.x;
+                    if (left >= 8) {
+                        *reinterpret_cast<codes4_t*>(dst) = o.x;
+                        dst += 4;
+                        r = o.y;
+                    }
+                    for (int b = 0; b < (left & 7) >> 1; ++b) dst[b] = (uint8_t)(r >> (8 * b));
+                }
+            }
+        }
+        p.out_scales[t] = sh;                    // every lane writes the same two bytes
+        commit(pre_next);                        // past the end this is the re-read last row; nobody uses it
+        __syncthreads();                         // (B) the next tile is visible
+    };
+    if constexpr (DEEP) {
+        while (true) {
+            body(t, pre1, pre0);
+            t += G;
+            if (t >= p.T) break;
+            body(t, pre0, pre1);
+            t += G;
+            if (t >= p.T) break;
+        }
+    } else {
+        for (; t < p.T; t += G) body(t, pre0, pre0);
+    }
+}
+
 // ------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------
@@ -389,6 +667,32 @@ static KernelFn kernel_table(int A, int B) {
         {kernel_for<4, 1>(), kernel_for<4, 2>(), kernel_for<4, 3>(), kernel_for<4, 4>(), kernel_for<4, 5>(), kernel_for<4, 6>(), kernel_for<4, 7>(), kernel_for<4, 8>()},
     };
     return tab[A - 1][B - 1];
+}
+
+struct AnyVariant {
+    KernelFn fn;
+    int lds;
+};
+template <int A>
+static AnyVariant any_variant_a(int B) {
+    switch (B) {
+        case 1: return {&tq_any_kernel<A, 1>, FastLds<A, 1>::TOTAL};
+        case 2: return {&tq_any_kernel<A, 2>, FastLds<A, 2>::TOTAL};
+        case 3: return {&tq_any_kernel<A, 3>, FastLds<A, 3>::TOTAL};
+        case 4: return {&tq_any_kernel<A, 4>, FastLds<A, 4>::TOTAL};
+        case 5: return {&tq_any_kernel<A, 5>, FastLds<A, 5>::TOTAL};
+        case 6: return {&tq_any_kernel<A, 6>, FastLds<A, 6>::TOTAL};
+        case 7: return {&tq_any_kernel<A, 7>, FastLds<A, 7>::TOTAL};
+        default: return {&tq_any_kernel<A, 8>, FastLds<A, 8>::TOTAL};
+    }
+}
+static AnyVariant any_variant(int A, int B) {
+    switch (A) {
+        case 1: return any_variant_a<1>(B);
+        case 2: return any_variant_a<2>(B);
+        case 3: return any_variant_a<3>(B);
+        default: return any_variant_a<4>(B);
+    }
 }
 
 template <int A, int B>
@@ -417,9 +721,9 @@ static int64_t generic_lds_bytes(int n1, int n2) {
 
 int64_t tq_lds_bytes(int n1, int n2) {
     if (!tq_supported(n1, n2)) return 0;
-    const int64_t b = generic_lds_bytes(n1, n2);
+    const int64_t b = generic_lds_bytes(n1, n2), a = any_variant((n1 + 31) / 32, (n2 + 31) / 32).lds;
     const int64_t f = tq_fast_lds_bytes(n1, n2);   // the specialised kernels stage P1/P2 in LDS as well
-    return f > b ? f : b;
+    return f > b && f > a ? f : a > b ? a : b;
 }
 
 static int64_t generic_mx_lds_bytes(int n1, int n2) {
@@ -473,6 +777,21 @@ hipError_t tq_launch(const TqArgs& a, hipStream_t stream) {
     // FLATQUANT_FORCE_GENERIC=1 keeps the general kernel testable on shapes the specialised ones would take
     if (tq_fast_applicable(d) && tuned(Knob::FORCE_GENERIC, 0) == 0) return tq_fast_launch(d, stream);
 
+    // Right factors of fewer than 8 columns, and rows that are only quantized (both factors left out, where values lie exactly on the
+    // ties between two codes and the rounding above moves those by 2e-6 of a code): the kernel that rounds y / s itself.
+    // FLATQUANT_FORCE_GENERIC=2 forces it.
+    if (a.n2 >= 8 && (a.P1 || a.P2) && tuned(Knob::FORCE_GENERIC, 0) != 2) {
+        const AnyVariant v = any_variant(A, B);
+        static OccCache occ_any[4][8];
+        int occ = 0;
+        hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(v.fn), nt, v.lds, occ_any[A - 1][B - 1], occ);
+        if (e != hipSuccess) return e;
+        const int cap = tuned(Knob::WG_PER_CU, 0);
+        if (cap > 0 && cap < occ) occ = cap;
+        // every workgroup gets the same number of tokens (+-1)
+        const int64_t resident = (int64_t)cu_count() * occ, rounds = (a.T + resident - 1) / resident;
+        return launch(v.fn, dim3((unsigned)((a.T + rounds - 1) / rounds)), dim3(nt), v.lds, stream, d);
+    }
     static OccCache occ_cache[4][8];   // per variant and device
     int occ = 0;
     {

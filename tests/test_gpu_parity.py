@@ -1017,6 +1017,38 @@ def test_one_sided_shape_grid(n1, n2, T, which):
     assert rep["band_flips"] <= parity.band_flip_allowance(rep["in_band"])
 
 
+@pytest.mark.parametrize("n1,n2,T", [(1, 8, 70), (2, 10, 5), (31, 12, 300), (33, 14, 2600), (64, 30, 129), (65, 34, 600), (97, 36, 65), (128, 72, 300), (63, 100, 64),
+                                     (32, 130, 513), (1, 250, 3), (96, 172, 300), (127, 254, 40), (50, 256, 33), (3, 128, 1000), (64, 80, 2500)])
+@pytest.mark.parametrize("how", ["whole", "offsets", "P1 only", "P2 only"])
+def test_general_int4_kernels_agree(tuning, how, n1, n2, T):
+    """The two general INT4 kernels on the same call, forced: every way a chunk of a token's row can straddle rows of X~ (n2 a multiple
+    of 8, of 4, of 2), chunks that end with the row, one to four row tiles, one to eight slabs, rows of codes that start on any byte,
+    operands on their smallest alignment, a factor left out.  The sums are the same, so the steps are; codes differ where a
+    value lies within 2e-6 code units of a tie (the constants of the conversion): a share of 4e-6, allowed ten times that."""
+    c = synth.generic(41 * n1 + n2 + T, T, n1, n2, sigma=0.05)
+    n, pad = n1 * n2, 6 if how == "offsets" else 0
+    def place(a, skip):                                   # `skip` halves past an aligned address
+        buf = torch.zeros(a.numel() + 64, dtype=a.dtype, device="cuda")
+        buf[skip:skip + a.numel()] = a.flatten()
+        return buf[skip:skip + a.numel()]
+    x = torch.zeros((T, n + pad), dtype=torch.float16, device="cuda")
+    x[:, :n] = dev(c.x)
+    o = 1 if how == "offsets" else 0
+    x, P1, P2 = place(x, 2 * o), place(dev(c.P1), o), place(dev(c.P2), o)
+    res = []
+    for force in (1, 2):
+        tuning("FLATQUANT_FORCE_GENERIC", force)
+        codes = torch.full((T * n // 2 + 2,), 0xA5, dtype=torch.uint8, device="cuda")
+        steps = torch.full((T + 1,), -7.0, dtype=torch.float16, device="cuda")
+        print(f"[case] general kernels {how} {n1}x{n2} T={T} force={force}", flush=True)
+        fq.flatquant_transform_quant(x, None if how == "P2 only" else P1, None if how == "P1 only" else P2, dev(c.clip), c.clip_mode, T, n1, n2, n + pad,
+                                     codes[o:], steps, stream=torch.cuda.current_stream())
+        assert int(codes[-1]) == 0xA5 and (not o or int(codes[0]) == 0xA5) and float(steps[-1]) == -7
+        res.append((codes[o:o + T * n // 2], steps))
+    assert torch.equal(res[0][1], res[1][1])
+    assert int((res[0][0] != res[1][0]).sum()) <= 2 + 4e-5 * T * n
+
+
 @pytest.mark.parametrize("T,H,shared", [(4096, 8, False), (1, 8, False), (77, 3, False), (200, 8, True), (31, 2, True), (32, 5, False), (33, 16, True),
                                         (127, 1, False), (129, 2, True), (1000, 5, False), (3, 33, False), (4097, 3, True), (64, 40, False)])
 def test_head_transform_fp16_out(T, H, shared):
