@@ -24,7 +24,7 @@
 //   * Workgroups are persistent over tokens; the next token row is prefetched
 //     into registers while the current one is in the MFMA pipe.
 //
-// tq_kernel is that kernel for MXFP4, for rows that are only quantized and for n2 < 8; tq_any_kernel, further down, takes every
+// tq_kernel is that kernel for n2 < 8 and for INT4 rows that are only quantized; tq_any_kernel, further down, takes every
 // other INT4 call that the specialised kernels (fq_tq_fast.hip) do not.
 #include <type_traits>
 
@@ -62,6 +62,20 @@ __device__ __forceinline__ half8 to_half8_rtz(const float* z) {
 __device__ __forceinline__ uint32_t nibble(float y, float inv) {
     float u = __builtin_fminf(__builtin_fmaxf(y * inv, -8.0f), 7.0f);
     return (uint32_t)(int)__builtin_rintf(u) & 0xFu;
+}
+
+// exponent of an MXFP4 block from alpha max = m: floor(log2(m)) - 2, 0 for an all-zero block
+__device__ __forceinline__ uint32_t mx_exponent(float m) {
+    const uint32_t be = (__builtin_bit_cast(uint32_t, m) >> 23) & 0xffu;
+    return be > 2 ? be - 2 : 0;
+}
+// eight elements, converted with the stored exponent (the conversion reads the exponent field of its scale operand only, and field 0
+// means 2^-127)
+__device__ __forceinline__ uint32_t mx_codes8(float4 a, float4 b, float scale) {
+    uint32_t pk = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, a.x, a.y, scale, 0);
+    pk = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk, a.z, a.w, scale, 1);
+    pk = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk, b.x, b.y, scale, 2);
+    return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk, b.z, b.w, scale, 3);
 }
 
 // MX: MXFP4 output for the shapes the specialised kernels do not take (n2 not a multiple of 32, where a block of 32
@@ -336,28 +350,19 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(A <= 2 ?
             uint8_t* exps = reinterpret_cast<uint8_t*>(p.out_scales);
             const int nblk = n >> 5;
             for (int b = tid; b < nblk; b += NT) {
-                float y[32];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const float4 v = reinterpret_cast<const float4*>(stagef + 32 * b)[k];
-                    y[4 * k] = v.x; y[4 * k + 1] = v.y; y[4 * k + 2] = v.z; y[4 * k + 3] = v.w;
-                }
+                float4 y[8];
                 float bm = 0.0f;
 #pragma unroll
-                for (int k = 0; k < 32; ++k) bm = __builtin_fmaxf(bm, __builtin_fabsf(y[k]));
-                bm *= clipv;
-                const uint32_t be = (__builtin_bit_cast(uint32_t, bm) >> 23) & 0xffu;
-                const uint32_t e = be > 2 ? be - 2 : 0;
+                for (int k = 0; k < 8; ++k) {
+                    y[k] = reinterpret_cast<const float4*>(stagef + 32 * b)[k];
+                    bm = __builtin_fmaxf(__builtin_fmaxf(bm, __builtin_fabsf(y[k].x)), __builtin_fabsf(y[k].y));
+                    bm = __builtin_fmaxf(__builtin_fmaxf(bm, __builtin_fabsf(y[k].z)), __builtin_fabsf(y[k].w));
+                }
+                const uint32_t e = mx_exponent(bm * clipv);
                 const float scale = __builtin_bit_cast(float, e << 23);
                 u32x4 o;
 #pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    uint32_t pk = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, y[8 * d], y[8 * d + 1], scale, 0);
-                    pk = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk, y[8 * d + 2], y[8 * d + 3], scale, 1);
-                    pk = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk, y[8 * d + 4], y[8 * d + 5], scale, 2);
-                    pk = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pk, y[8 * d + 6], y[8 * d + 7], scale, 3);
-                    o[d] = pk;
-                }
+                for (int d = 0; d < 4; ++d) o[d] = mx_codes8(y[2 * d], y[2 * d + 1], scale);
                 reinterpret_cast<u32x4*>(dst)[b] = o;
                 if (p.mx_tiled) exps[((((t >> 7) * (int64_t)(n >> 8) + (b >> 3)) * 128 + (t & 127)) << 3) + (b & 7)] = (uint8_t)e;
                 else exps[t * (int64_t)nblk + b] = (uint8_t)e;
@@ -374,6 +379,12 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(A <= 2 ?
     }
 }
 
+// where P1's fragment table starts behind a token tile and the staged values of MXFP4 (or the factors, whichever is larger)
+template <int A, int B>
+__host__ __device__ constexpr int any_mx_r0(int n) {
+    return (cmax(FastLds<A, B>::STG_BYTES, FastLds<A, B>::XS_BYTES + 64 + n / 32 * 144) + 15) & ~15;
+}
+
 // INT4, any pair of factors (n2 >= 8; either may be left out: identity): the plain loop of the specialised kernels (fq_tq_fast.hip:
 // same wave mapping, contractions, rounding and packing) for right factors that are not a multiple of 32 and rows that do not
 // start on 16 bytes.  What is different: the factors' LDS copies are padded with zeros to whole tiles; a token's row is requested in
@@ -382,7 +393,11 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(A <= 2 ?
 // loads of the factors, rounding and packing in 8 instructions per value, codes staged in LDS), us:
 // 64 x 80 at 64 tokens 7.4 / 5.6, 777 11.7 / 8.9, 2048 19.1 / 13.7, 16384 103.8 / 67.6; 64 x 172 10.5 / 8.2 (64), 48.5 / 28.0 (2048), 322 / 180
 // (16384); 45 x 90 22.3 / 13.7 (2048); 97 x 98 61.3 / 35.7 (2048); 128 x 250 939 / 345 (8192); 16 x 18 7.8 / 6.3 (4096).
-template <int A, int B>
+// MX: MXFP4 output for the same shapes: Y is staged in LDS in channel order, as fp32 with 4 words of padding per block of 32 (reads of
+// consecutive blocks spread over the banks), then one thread per block forms the exponent and converts.  Same bytes as the kernel
+// above; against it, us: 64 x 80 at 64 tokens 7.6 / 5.8, 777 14.6 / 9.8, 2048 23.7 / 14.7, 16384 142 / 80; 64 x 172 10.3 / 8.6 (64), 41.5 / 29.8 (2048),
+// 142 / 96 (8192); 48 x 112 26.4 / 17.3 (2048); 96 x 90 41.6 / 25.6; 128 x 100 61.3 / 45.5; 32 x 18 5.6 / 5.3.
+template <int A, int B, bool MX>
 __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) void tq_any_kernel(TqDev p) {
     using L = FastLds<A, B>;
     constexpr int NT = 64 * B, N2 = 32 * B, PITCH = L::PITCH, PW = 32 * A;
@@ -393,7 +408,8 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     _Float16* Xs = reinterpret_cast<_Float16*>(smem);
     float* red = reinterpret_cast<float*>(smem + L::XS_BYTES);
-    u32x4* P1s = reinterpret_cast<u32x4*>(smem + L::R0);
+    u32x4* P1s = reinterpret_cast<u32x4*>(smem + (MX ? any_mx_r0<A, B>(p.n1 * p.n2) : L::R0));
+    float* stagef = reinterpret_cast<float*>(smem + L::XS_BYTES + 64);      // MX, behind the token tile
     _Float16* P1flat = reinterpret_cast<_Float16*>(smem);
     _Float16* P2flat = reinterpret_cast<_Float16*>(smem + L::P1FLAT_BYTES);
     const int tid = threadIdx.x, l = tid & 63, c = l & 31, h = l >> 5;
@@ -582,6 +598,51 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
                     }
                 }
         }
+        if constexpr (MX) {
+            __syncthreads();                     // (A) every wave is done reading the token tile, and the values staged before
+            const int pair = n2 & 2;             // runs of 4 channels stay inside a block if n2 is a multiple of 4, else runs of 2
+            int ro = c * n2 + 32 * w + 4 * h;
+            asm volatile("" : "+v"(ro));         // opaque: the 8 A offsets below are formed here, not held across the tokens (they spill)
+#pragma unroll
+            for (int It = 0; It < A; ++It) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int jp = 32 * w + 8 * g + 4 * h, e = ro + 32 * It * n2 + 8 * g;
+                    if (32 * It + c < n1 && jp < n2) {
+                        if (pair == 0) {
+                            *reinterpret_cast<float4*>(stagef + e + 4 * (e >> 5)) = float4{acc2[It][4 * g], acc2[It][4 * g + 1], acc2[It][4 * g + 2], acc2[It][4 * g + 3]};
+                        } else {
+                            *reinterpret_cast<float2*>(stagef + e + 4 * (e >> 5)) = float2{acc2[It][4 * g], acc2[It][4 * g + 1]};
+                            if (jp + 2 < n2) *reinterpret_cast<float2*>(stagef + e + 2 + 4 * ((e + 2) >> 5)) = float2{acc2[It][4 * g + 2], acc2[It][4 * g + 3]};
+                        }
+                    }
+                }
+            }
+            commit(pre_next);
+            __syncthreads();                     // (B) staged values and the next tile are visible
+            uint8_t* exps = reinterpret_cast<uint8_t*>(p.out_scales);
+            const int nblk = n >> 5;
+            for (int b = tid; b < nblk; b += NT) {
+                const float4* src = reinterpret_cast<const float4*>(stagef + 36 * b);
+                float bm = 0.0f;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const float4 v = src[k];
+                    bm = __builtin_fmaxf(__builtin_fmaxf(bm, __builtin_fabsf(v.x)), __builtin_fabsf(v.y));
+                    bm = __builtin_fmaxf(__builtin_fmaxf(bm, __builtin_fabsf(v.z)), __builtin_fabsf(v.w));
+                }
+                asm volatile("" ::: "memory");   // read again rather than held: 32 registers beside the factors' fragments spill
+                const uint32_t e = mx_exponent(bm * clipv);
+                const float scale = __builtin_bit_cast(float, e << 23);
+                u32x4 o;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) o[d] = mx_codes8(src[2 * d], src[2 * d + 1], scale);
+                reinterpret_cast<u32x4*>(p.out_codes + t * (int64_t)(n >> 1))[b] = o;
+                if (p.mx_tiled) exps[((((t >> 7) * (int64_t)(n >> 8) + (b >> 3)) * 128 + (t & 127)) << 3) + (b & 7)] = (uint8_t)e;
+                else exps[t * (int64_t)nblk + b] = (uint8_t)e;
+            }
+            return;
+        }
         float m = 0.0f;                          // padded rows and columns are exact zeros
 #pragma unroll
         for (int It = 0; It < A; ++It)
@@ -655,6 +716,7 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
 // host side
 // ------------------------------------------------------------------------------------
 using KernelFn = void (*)(TqDev);
+constexpr int kLdsMax = 160 * 1024;
 
 template <int A, int B>
 static constexpr KernelFn kernel_for() { return &tq_kernel<A, B, (A >= 3)>; }
@@ -673,26 +735,54 @@ struct AnyVariant {
     KernelFn fn;
     int lds;
 };
+template <int A, int B>
+static AnyVariant any_variant_ab(bool mx, int n) {
+    if (mx) return {&tq_any_kernel<A, B, true>, any_mx_r0<A, B>(n) + FastLds<A, B>::P1S_BYTES};
+    return {&tq_any_kernel<A, B, false>, FastLds<A, B>::TOTAL};
+}
 template <int A>
-static AnyVariant any_variant_a(int B) {
+static AnyVariant any_variant_a(int B, bool mx, int n) {
     switch (B) {
-        case 1: return {&tq_any_kernel<A, 1>, FastLds<A, 1>::TOTAL};
-        case 2: return {&tq_any_kernel<A, 2>, FastLds<A, 2>::TOTAL};
-        case 3: return {&tq_any_kernel<A, 3>, FastLds<A, 3>::TOTAL};
-        case 4: return {&tq_any_kernel<A, 4>, FastLds<A, 4>::TOTAL};
-        case 5: return {&tq_any_kernel<A, 5>, FastLds<A, 5>::TOTAL};
-        case 6: return {&tq_any_kernel<A, 6>, FastLds<A, 6>::TOTAL};
-        case 7: return {&tq_any_kernel<A, 7>, FastLds<A, 7>::TOTAL};
-        default: return {&tq_any_kernel<A, 8>, FastLds<A, 8>::TOTAL};
+        case 1: return any_variant_ab<A, 1>(mx, n);
+        case 2: return any_variant_ab<A, 2>(mx, n);
+        case 3: return any_variant_ab<A, 3>(mx, n);
+        case 4: return any_variant_ab<A, 4>(mx, n);
+        case 5: return any_variant_ab<A, 5>(mx, n);
+        case 6: return any_variant_ab<A, 6>(mx, n);
+        case 7: return any_variant_ab<A, 7>(mx, n);
+        default: return any_variant_ab<A, 8>(mx, n);
     }
 }
-static AnyVariant any_variant(int A, int B) {
+static AnyVariant any_variant(int n1, int n2, bool mx) {
+    const int A = (n1 + 31) / 32, B = (n2 + 31) / 32;
     switch (A) {
-        case 1: return any_variant_a<1>(B);
-        case 2: return any_variant_a<2>(B);
-        case 3: return any_variant_a<3>(B);
-        default: return any_variant_a<4>(B);
+        case 1: return any_variant_a<1>(B, mx, n1 * n2);
+        case 2: return any_variant_a<2>(B, mx, n1 * n2);
+        case 3: return any_variant_a<3>(B, mx, n1 * n2);
+        default: return any_variant_a<4>(B, mx, n1 * n2);
     }
+}
+// every workgroup gets the same number of tokens (+-1)
+static hipError_t any_launch(const TqDev& d, hipStream_t stream, bool mx) {
+    const int A = (d.n1 + 31) / 32, B = (d.n2 + 31) / 32;
+    const AnyVariant v = any_variant(d.n1, d.n2, mx);
+    static OccCache occ_cache[4][8];
+    int occ = 0;
+    if (!mx) {
+        hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(v.fn), 64 * B, v.lds, occ_cache[A - 1][B - 1], occ);
+        if (e != hipSuccess) return e;
+    } else {                                     // the LDS depends on n: occupancy for the most it takes, then what this launch takes
+        static OccCache occ_mx[4][8];
+        hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(v.fn), 64 * B, kLdsMax, occ_mx[A - 1][B - 1], occ);
+        if (e != hipSuccess) return e;
+        occ = kLdsMax / v.lds;
+        if (occ * B > 8) occ = 8 / B;            // two waves per SIMD
+        if (occ < 1) occ = 1;
+    }
+    const int cap = tuned(Knob::WG_PER_CU, 0);
+    if (cap > 0 && cap < occ) occ = cap;
+    const int64_t resident = (int64_t)cu_count() * occ, rounds = (d.T + resident - 1) / resident;
+    return launch(v.fn, dim3((unsigned)((d.T + rounds - 1) / rounds)), dim3(64 * B), v.lds, stream, d);
 }
 
 template <int A, int B>
@@ -721,7 +811,7 @@ static int64_t generic_lds_bytes(int n1, int n2) {
 
 int64_t tq_lds_bytes(int n1, int n2) {
     if (!tq_supported(n1, n2)) return 0;
-    const int64_t b = generic_lds_bytes(n1, n2), a = any_variant((n1 + 31) / 32, (n2 + 31) / 32).lds;
+    const int64_t b = generic_lds_bytes(n1, n2), a = any_variant(n1, n2, false).lds;
     const int64_t f = tq_fast_lds_bytes(n1, n2);   // the specialised kernels stage P1/P2 in LDS as well
     return f > b && f > a ? f : a > b ? a : b;
 }
@@ -740,6 +830,9 @@ bool tq_mx_generic_applicable(const TqDev& d) {
 
 hipError_t tq_mx_generic_launch(const TqDev& d, hipStream_t stream) {
     const int A = (d.n1 + 31) / 32, B = (d.n2 + 31) / 32;
+    // The kernel that stages unpadded values is left with right factors of fewer than 8 columns (a chunk would straddle more than two
+    // rows) and with what only fits without the padding (128 x 158).  FLATQUANT_FORCE_GENERIC=2 forces it.
+    if (d.n2 >= 8 && tuned(Knob::FORCE_GENERIC, 0) != 2 && any_variant(d.n1, d.n2, true).lds <= kLdsMax) return any_launch(d, stream, true);
     KernelFn fn = mx_kernel_table(A, B);
     const int lds = (int)generic_mx_lds_bytes(d.n1, d.n2);
     static OccCache occ_cache[4][8];
@@ -781,16 +874,7 @@ hipError_t tq_launch(const TqArgs& a, hipStream_t stream) {
     // ties between two codes and the rounding above moves those by 2e-6 of a code): the kernel that rounds y / s itself.
     // FLATQUANT_FORCE_GENERIC=2 forces it.
     if (a.n2 >= 8 && (a.P1 || a.P2) && tuned(Knob::FORCE_GENERIC, 0) != 2) {
-        const AnyVariant v = any_variant(A, B);
-        static OccCache occ_any[4][8];
-        int occ = 0;
-        hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(v.fn), nt, v.lds, occ_any[A - 1][B - 1], occ);
-        if (e != hipSuccess) return e;
-        const int cap = tuned(Knob::WG_PER_CU, 0);
-        if (cap > 0 && cap < occ) occ = cap;
-        // every workgroup gets the same number of tokens (+-1)
-        const int64_t resident = (int64_t)cu_count() * occ, rounds = (a.T + resident - 1) / resident;
-        return launch(v.fn, dim3((unsigned)((a.T + rounds - 1) / rounds)), dim3(nt), v.lds, stream, d);
+        return any_launch(d, stream, false);
     }
     static OccCache occ_cache[4][8];   // per variant and device
     int occ = 0;

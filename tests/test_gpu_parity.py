@@ -7,6 +7,8 @@ more than 1e-3 away from a rounding boundary; de-quantized values within
 """
 import os
 
+import math
+
 import numpy as np
 import pytest
 
@@ -1047,6 +1049,34 @@ def test_general_int4_kernels_agree(tuning, how, n1, n2, T):
         res.append((codes[o:o + T * n // 2], steps))
     assert torch.equal(res[0][1], res[1][1])
     assert int((res[0][0] != res[1][0]).sum()) <= 2 + 4e-5 * T * n
+
+
+@pytest.mark.parametrize("n1,n2,T", [(4, 8, 3), (64, 80, 130), (48, 112, 5), (16, 18, 129), (64, 86, 3), (96, 90, 4), (32, 250, 2), (128, 134, 3), (112, 136, 300),
+                                     (64, 172, 700), (128, 158, 2), (16, 6, 5)])
+@pytest.mark.parametrize("tiled", [False, True])
+def test_general_mxfp4_kernels_agree(tuning, tiled, n1, n2, T):
+    """The two general MXFP4 kernels: the same sums and the same conversion, so the same bytes.  Every way a run of channels can lie in a
+    block (n2 a multiple of 8, of 4, of 2), one to four row tiles, one to eight slabs, the shapes only the second takes."""
+    n = n1 * n2
+    if tiled and n % 256:
+        n1 *= 256 // math.gcd(n, 256)
+        n = n1 * n2
+        if n1 > 128 or n > 25600:
+            pytest.skip("more left rows, or more staged values, than either kernel takes")
+    c = synth.generic(43 * n1 + n2 + T, T, n1, n2, sigma=0.05)
+    x, P1, P2, clip = dev(c.x), dev(c.P1), dev(c.P2), dev(c.clip)
+    nexp = fq.fq_mxfp4_tiled_scale_bytes(T, n) if tiled else T * n // 32
+    res = []
+    for force in (0, 2):
+        tuning("FLATQUANT_FORCE_GENERIC", force)
+        codes = torch.full((T * n // 2 + 16,), 0xA5, dtype=torch.uint8, device="cuda")
+        exps = torch.full((nexp + 16,), 0x5A, dtype=torch.uint8, device="cuda")
+        print(f"[case] general MXFP4 kernels {n1}x{n2} T={T} tiled={tiled} force={force}", flush=True)
+        call = fq.flatquant_transform_mxfp4_tiled if tiled else fq.flatquant_transform_mxfp4
+        call(x, P1, P2, clip, c.clip_mode, T, n1, n2, n, codes, exps, stream=torch.cuda.current_stream())
+        assert int((codes[-16:] != 0xA5).sum()) == 0 and int((exps[-16:] != 0x5A).sum()) == 0
+        res.append((codes, exps))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
 
 
 @pytest.mark.parametrize("T,H,shared", [(4096, 8, False), (1, 8, False), (77, 3, False), (200, 8, True), (31, 2, True), (32, 5, False), (33, 16, True),
