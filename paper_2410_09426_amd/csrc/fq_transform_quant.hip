@@ -24,8 +24,8 @@
 //   * Workgroups are persistent over tokens; the next token row is prefetched
 //     into registers while the current one is in the MFMA pipe.
 //
-// tq_kernel is that kernel for n2 < 8 and for INT4 rows that are only quantized; tq_any_kernel, further down, takes every
-// other INT4 call that the specialised kernels (fq_tq_fast.hip) do not.
+// tq_kernel is that kernel for n2 < 8, for INT4 rows that are only quantized and for MXFP4 rows whose staged values only fit in LDS
+// without padding; tq_any_kernel, further down, takes every other call that the specialised kernels (fq_tq_fast.hip) do not.
 #include <type_traits>
 
 #include "fq_internal.h"
@@ -385,7 +385,7 @@ __host__ __device__ constexpr int any_mx_r0(int n) {
     return (cmax(FastLds<A, B>::STG_BYTES, FastLds<A, B>::XS_BYTES + 64 + n / 32 * 144) + 15) & ~15;
 }
 
-// INT4, any pair of factors (n2 >= 8; either may be left out: identity): the plain loop of the specialised kernels (fq_tq_fast.hip:
+// Any pair of factors (n2 >= 8; INT4: either may be left out: identity): the plain loop of the specialised kernels (fq_tq_fast.hip:
 // same wave mapping, contractions, rounding and packing) for right factors that are not a multiple of 32 and rows that do not
 // start on 16 bytes.  What is different: the factors' LDS copies are padded with zeros to whole tiles; a token's row is requested in
 // flat 16-byte chunks wherever they start (dword-aligned), and a chunk that straddles two rows of X~ goes into LDS in pieces of 8

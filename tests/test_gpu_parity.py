@@ -5,9 +5,8 @@ steps within 1e-3 relative; codes bit-exact wherever the fp64 pre-round value is
 more than 1e-3 away from a rounding boundary; de-quantized values within
 1e-2 * step outside that band.
 """
-import os
-
 import math
+import os
 
 import numpy as np
 import pytest
