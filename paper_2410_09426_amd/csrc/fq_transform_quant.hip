@@ -24,8 +24,9 @@
 //   * Workgroups are persistent over tokens; the next token row is prefetched
 //     into registers while the current one is in the MFMA pipe.
 //
-// tq_kernel is that kernel for n2 < 8, for INT4 rows that are only quantized and for MXFP4 rows whose staged values only fit in LDS
-// without padding; tq_any_kernel, further down, takes every other call that the specialised kernels (fq_tq_fast.hip) do not.
+// tq_kernel is that kernel for n2 < 8, for INT4 rows that are only quantized, for MXFP4 rows whose staged values only fit in LDS
+// without padding and where any_is_faster() says so; tq_any_kernel, further down, takes every other call that the specialised
+// kernels (fq_tq_fast.hip) do not.
 #include <type_traits>
 
 #include "fq_internal.h"
@@ -350,19 +351,21 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(A <= 2 ?
             uint8_t* exps = reinterpret_cast<uint8_t*>(p.out_scales);
             const int nblk = n >> 5;
             for (int b = tid; b < nblk; b += NT) {
-                float4 y[8];
-                float bm = 0.0f;
+                float y[32];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
-                    y[k] = reinterpret_cast<const float4*>(stagef + 32 * b)[k];
-                    bm = __builtin_fmaxf(__builtin_fmaxf(bm, __builtin_fabsf(y[k].x)), __builtin_fabsf(y[k].y));
-                    bm = __builtin_fmaxf(__builtin_fmaxf(bm, __builtin_fabsf(y[k].z)), __builtin_fabsf(y[k].w));
+                    const float4 v = reinterpret_cast<const float4*>(stagef + 32 * b)[k];
+                    y[4 * k] = v.x; y[4 * k + 1] = v.y; y[4 * k + 2] = v.z; y[4 * k + 3] = v.w;
                 }
+                float bm = 0.0f;
+#pragma unroll
+                for (int k = 0; k < 32; ++k) bm = __builtin_fmaxf(bm, __builtin_fabsf(y[k]));
                 const uint32_t e = mx_exponent(bm * clipv);
                 const float scale = __builtin_bit_cast(float, e << 23);
                 u32x4 o;
 #pragma unroll
-                for (int d = 0; d < 4; ++d) o[d] = mx_codes8(y[2 * d], y[2 * d + 1], scale);
+                for (int d = 0; d < 4; ++d)
+                    o[d] = mx_codes8(float4{y[8 * d], y[8 * d + 1], y[8 * d + 2], y[8 * d + 3]}, float4{y[8 * d + 4], y[8 * d + 5], y[8 * d + 6], y[8 * d + 7]}, scale);
                 reinterpret_cast<u32x4*>(dst)[b] = o;
                 if (p.mx_tiled) exps[((((t >> 7) * (int64_t)(n >> 8) + (b >> 3)) * 128 + (t & 127)) << 3) + (b & 7)] = (uint8_t)e;
                 else exps[t * (int64_t)nblk + b] = (uint8_t)e;
@@ -618,7 +621,7 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
                     }
                 }
             }
-            commit(pre_next);
+            if (t + G < p.T) commit(pre_next);   // (the last token does not wait for its re-read)
             __syncthreads();                     // (B) staged values and the next tile are visible
             uint8_t* exps = reinterpret_cast<uint8_t*>(p.out_scales);
             const int nblk = n >> 5;
@@ -695,7 +698,8 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
             }
         }
         p.out_scales[t] = sh;                    // every lane writes the same two bytes
-        commit(pre_next);                        // past the end this is the re-read last row; nobody uses it
+        if (t + G >= p.T) return;                // (not waiting for the re-read last row)
+        commit(pre_next);
         __syncthreads();                         // (B) the next tile is visible
     };
     if constexpr (DEEP) {
@@ -762,6 +766,29 @@ static AnyVariant any_variant(int n1, int n2, bool mx) {
         default: return any_variant_a<4>(B, mx, n1 * n2);
     }
 }
+// Whether tq_any_kernel is the faster one of the two general kernels.  With many tokens it is (up to 2.5 times: 128 x 36 MXFP4 at 8192
+// 191 / 84 us); what tq_kernel keeps is launches of few tokens whose prologue decides, and MXFP4 rows of one row tile, whose values
+// move in pieces of 8 or 16 bytes when n2 % 8 != 0.  tq_kernel / tq_any_kernel, us:
+//   one row tile, INT4: 16 x 250 8.2 / 8.5 (64 tokens), 8.9 / 9.2 (256), 11.2 / 10.8 (512); 16 x 222 8.3 / 7.8 (256);
+//   one row tile, MXFP4: 16 x 34 4.4 / 4.5 (64), 16 x 66 5.6 / 5.8 (512), 11.9 / 14.6 (4096), 16 x 250 7.7 / 8.9 (64), 14.1 / 14.5 (1024), 18.3 / 17.9 (1500),
+//     16 x 134 6.1 / 6.5 (256), 10.5 / 7.8 (512: 5 or 6 slabs, one workgroup of tq_kernel per CU), 8 x 24 4.89 / 5.09 (2048), 16 x 248 8.0 / 8.3 (256), 9.9 / 9.8
+//     (512), 16 x 152 10.6 / 7.2 (512), 16 x 40 4.4 / 4.1 (64);
+//   one slab: 64 x 12 5.6 / 6.1 (64), 6.3 / 6.4 (512), 11.0 / 10.2 (4096), 128 x 20 16.7 / 18.6 (640), 21.5 / 18.9 (1024), 96 x 20 11.6 / 9.7 (512);
+//   two slabs where a CU gets two tokens: INT4 128 x 36 13.2 / 11.5 (256), 13.8 / 14.5 (512), 19.1 / 18.5 (640), 96 x 34 11.0 / 10.3 (512);
+//     MXFP4 96 x 34 9.7 / 9.0 (256), 10.3 / 10.7 (512), 13.8 / 11.6 (640), 128 x 36 19.3 / 15.2 (512).
+static bool any_is_faster(const TqDev& d, bool mx) {
+    const int A = (d.n1 + 31) / 32, B = (d.n2 + 31) / 32;
+    if (A == 1) {
+        if (!mx) return B < 8 || d.T > 256;
+        if (d.n1 <= 8) return false;
+        if (d.n2 % 8 == 0) return B < 8 || d.T > 256;
+        return B >= 5 && d.T > (B <= 6 ? 256 : 1024);
+    }
+    if (B == 1) return d.T > 768 || (A < 4 && d.n2 >= 16);
+    if (B == 2 && A == (mx ? 3 : 4)) return d.T <= 256 || d.T > 512;
+    return true;
+}
+
 // every workgroup gets the same number of tokens (+-1)
 static hipError_t any_launch(const TqDev& d, hipStream_t stream, bool mx) {
     const int A = (d.n1 + 31) / 32, B = (d.n2 + 31) / 32;
@@ -830,9 +857,9 @@ bool tq_mx_generic_applicable(const TqDev& d) {
 
 hipError_t tq_mx_generic_launch(const TqDev& d, hipStream_t stream) {
     const int A = (d.n1 + 31) / 32, B = (d.n2 + 31) / 32;
-    // The kernel that stages unpadded values is left with right factors of fewer than 8 columns (a chunk would straddle more than two
-    // rows) and with what only fits without the padding (128 x 158).  FLATQUANT_FORCE_GENERIC=2 forces it.
-    if (d.n2 >= 8 && tuned(Knob::FORCE_GENERIC, 0) != 2 && any_variant(d.n1, d.n2, true).lds <= kLdsMax) return any_launch(d, stream, true);
+    // FLATQUANT_FORCE_GENERIC=1 / 2 forces tq_any_kernel / tq_kernel
+    const int force = tuned(Knob::FORCE_GENERIC, 0);
+    if (d.n2 >= 8 && any_variant(d.n1, d.n2, true).lds <= kLdsMax && (force == 1 || (force != 2 && any_is_faster(d, true)))) return any_launch(d, stream, true);
     KernelFn fn = mx_kernel_table(A, B);
     const int lds = (int)generic_mx_lds_bytes(d.n1, d.n2);
     static OccCache occ_cache[4][8];
@@ -871,9 +898,10 @@ hipError_t tq_launch(const TqArgs& a, hipStream_t stream) {
     if (tq_fast_applicable(d) && tuned(Knob::FORCE_GENERIC, 0) == 0) return tq_fast_launch(d, stream);
 
     // Right factors of fewer than 8 columns, and rows that are only quantized (both factors left out, where values lie exactly on the
-    // ties between two codes and the rounding above moves those by 2e-6 of a code): the kernel that rounds y / s itself.
+    // ties between two codes and the rounding above moves those by 2e-6 of a code), stay with the kernel that rounds y / s itself.
     // FLATQUANT_FORCE_GENERIC=2 forces it.
-    if (a.n2 >= 8 && (a.P1 || a.P2) && tuned(Knob::FORCE_GENERIC, 0) != 2) {
+    const int force = tuned(Knob::FORCE_GENERIC, 0);
+    if (a.n2 >= 8 && (a.P1 || a.P2) && force != 2 && (force == 1 || any_is_faster(d, false))) {
         return any_launch(d, stream, false);
     }
     static OccCache occ_cache[4][8];   // per variant and device

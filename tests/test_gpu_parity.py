@@ -1066,7 +1066,7 @@ def test_general_mxfp4_kernels_agree(tuning, tiled, n1, n2, T):
     x, P1, P2, clip = dev(c.x), dev(c.P1), dev(c.P2), dev(c.clip)
     nexp = fq.fq_mxfp4_tiled_scale_bytes(T, n) if tiled else T * n // 32
     res = []
-    for force in (0, 2):
+    for force in (1, 2):
         tuning("FLATQUANT_FORCE_GENERIC", force)
         codes = torch.full((T * n // 2 + 16,), 0xA5, dtype=torch.uint8, device="cuda")
         exps = torch.full((nexp + 16,), 0x5A, dtype=torch.uint8, device="cuda")
