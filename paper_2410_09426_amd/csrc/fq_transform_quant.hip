@@ -65,6 +65,21 @@ __device__ __forceinline__ uint32_t nibble(float y, float inv) {
     return (uint32_t)(int)__builtin_rintf(u) & 0xFu;
 }
 
+// nibble() of eight values, the first in the lowest bits.  1.5 * 2^23 is added to the clamped quotient: the sum is rounded to whole
+// numbers, ties to even, and its low bits hold 0x4B400000 + q, so the eight chain with shift-adds; the constant comes off and 8 goes on
+// in every field at once (q + 8 = 0 .. 15: nothing borrows), and q + 8 is q's two's-complement nibble with the top bit turned.
+// The clamp stands between product and sum, so that the quotient is rounded to fp32 like nibble()'s: the same code for every value.
+template <typename F>
+__device__ __forceinline__ uint32_t nibbles8(F&& y, float inv) {
+    constexpr uint32_t kFix = 0x88888888u - 0x4B400000u * 0x11111111u;
+    uint32_t b[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) b[k] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(y(k) * inv, -8.0f, 7.0f) + 12582912.0f);
+    const uint32_t lo = lshl_add(lshl_add(b[3], 4, b[2]), 8, lshl_add(b[1], 4, b[0]));
+    const uint32_t hi = lshl_add(lshl_add(b[7], 4, b[6]), 8, lshl_add(b[5], 4, b[4]));
+    return (lshl_add(hi, 16, lo) + kFix) ^ 0x88888888u;
+}
+
 // exponent of an MXFP4 block from alpha max = m: floor(log2(m)) - 2, 0 for an all-zero block
 __device__ __forceinline__ uint32_t mx_exponent(float m) {
     const uint32_t be = (__builtin_bit_cast(uint32_t, m) >> 23) & 0xffu;
@@ -389,13 +404,16 @@ __host__ __device__ constexpr int any_mx_r0(int n) {
 }
 
 // Any pair of factors (n2 >= 8; INT4: either may be left out: identity): the plain loop of the specialised kernels (fq_tq_fast.hip:
-// same wave mapping, contractions, rounding and packing) for right factors that are not a multiple of 32 and rows that do not
+// same wave mapping and contractions) for right factors that are not a multiple of 32 and rows that do not
 // start on 16 bytes.  What is different: the factors' LDS copies are padded with zeros to whole tiles; a token's row is requested in
 // flat 16-byte chunks wherever they start (dword-aligned), and a chunk that straddles two rows of X~ goes into LDS in pieces of 8
-// or 4 bytes, whichever divides n2; a lane's 8 bytes of codes are stored as far as the row goes.  Against the kernel above (2-byte
-// loads of the factors, rounding and packing in 8 instructions per value, codes staged in LDS), us:
-// 64 x 80 at 64 tokens 7.4 / 5.6, 777 11.7 / 8.9, 2048 19.1 / 13.7, 16384 103.8 / 67.6; 64 x 172 10.5 / 8.2 (64), 48.5 / 28.0 (2048), 322 / 180
-// (16384); 45 x 90 22.3 / 13.7 (2048); 97 x 98 61.3 / 35.7 (2048); 128 x 250 939 / 345 (8192); 16 x 18 7.8 / 6.3 (4096).
+// or 4 bytes, whichever divides n2; the codes are rounded as in the kernel above (the same bytes: which of the two runs must not show)
+// and a lane's 8 bytes of them are stored as far as the row goes.  Against the kernel above (2-byte loads of the factors, rounding and
+// packing in 8 instructions per value, here 4, codes staged in LDS), us:
+// 64 x 80 at 64 tokens 6.8 / 5.1, 777 11.2 / 8.6, 2048 17.3 / 13.0, 16384 97 / 74; 64 x 172 10.2 / 7.7 (64), 45 / 30 (2048), 318 / 181
+// (16384); 45 x 90 21.6 / 13.9 (2048); 97 x 98 60.9 / 36.8 (2048); 128 x 250 939 / 337 (8192); 16 x 18 7.2 / 6.1 (4096).  (Rounding by
+// v_cvt_pknorm_i16, 2 instructions per value as in the specialised kernels, moves ties and what lies within 2e-6 of one:
+// 64 x 80 12.4 at 2048, 68 at 16384.)
 // MX: MXFP4 output for the same shapes: Y is staged in LDS in channel order, as fp32 with 4 words of padding per block of 32 (reads of
 // consecutive blocks spread over the banks), then one thread per block forms the exponent and converts.  Same bytes as the kernel
 // above; against it, us: 64 x 80 at 64 tokens 7.6 / 5.8, 777 14.6 / 9.8, 2048 23.7 / 14.7, 16384 142 / 80; 64 x 172 10.3 / 8.6 (64), 41.5 / 29.8 (2048),
@@ -658,23 +676,14 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
         for (int b = 0; b < B; ++b) m = __builtin_fmaxf(m, red[b]);
         const _Float16 sh = (_Float16)(clipv * m / 7.0f);             // round-to-nearest-even to fp16
         const float s = (float)sh;
-        const float kmul = ((s > 0.0f && s <= 65504.0f) ? 1.0f / s : 0.0f) * (4096.0f / 32767.0f);
-        constexpr float kadd = 2047.5f / 32767.0f;
+        const float inv = (s > 0.0f && s <= 65504.0f) ? 1.0f / s : 0.0f;
         uint8_t* row_out = p.out_codes + t * (int64_t)(n >> 1);
         const int left = n2 - 32 * w - 16 * h;   // channels of this lane's 16 that exist
 #pragma unroll
         for (int It = 0; It < A; ++It) {
             uint32_t Wq[2];
 #pragma unroll
-            for (int mm = 0; mm < 2; ++mm) {     // as in the specialised kernels: clamp, round and half of the packing in one conversion
-                uint32_t D[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    D[k] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pknorm_i16(__builtin_fmaf(acc2[It][8 * mm + k], kmul, kadd),
-                                                                                       __builtin_fmaf(acc2[It][8 * mm + 4 + k], kmul, kadd)));
-                const uint32_t E = __builtin_amdgcn_perm(D[2], D[0], 0x07030501u), F = __builtin_amdgcn_perm(D[3], D[1], 0x07030501u);
-                Wq[mm] = (F & 0xF0F0F0F0u) | ((E >> 4) & 0x0F0F0F0Fu);
-            }
+            for (int mm = 0; mm < 2; ++mm) Wq[mm] = nibbles8([&](int k) { return acc2[It][8 * mm + k]; }, inv);
             const auto sw = __builtin_amdgcn_permlane32_swap(Wq[0], Wq[1], false, false);
             uint2 o;
             o.x = __builtin_amdgcn_perm(sw[1], sw[0], 0x05040100u);
@@ -897,9 +906,9 @@ hipError_t tq_launch(const TqArgs& a, hipStream_t stream) {
     // FLATQUANT_FORCE_GENERIC=1 keeps the general kernel testable on shapes the specialised ones would take
     if (tq_fast_applicable(d) && tuned(Knob::FORCE_GENERIC, 0) == 0) return tq_fast_launch(d, stream);
 
-    // Right factors of fewer than 8 columns, and rows that are only quantized (both factors left out, where values lie exactly on the
-    // ties between two codes and the rounding above moves those by 2e-6 of a code), stay with the kernel that rounds y / s itself.
-    // FLATQUANT_FORCE_GENERIC=2 forces it.
+    // Right factors of fewer than 8 columns stay with tq_kernel (a chunk of a row could straddle three rows of X~), and so do rows that
+    // are only quantized (both factors left out), which have not been moved: there the other one gives the same bytes in less time (64 x 80
+    // at 2048 tokens 17.9 / 12.4 us, 64 x 128 at 16384 110 / 78).  FLATQUANT_FORCE_GENERIC=2 forces it.
     const int force = tuned(Knob::FORCE_GENERIC, 0);
     if (a.n2 >= 8 && (a.P1 || a.P2) && force != 2 && (force == 1 || any_is_faster(d, false))) {
         return any_launch(d, stream, false);

@@ -1024,8 +1024,7 @@ def test_one_sided_shape_grid(n1, n2, T, which):
 def test_general_int4_kernels_agree(tuning, how, n1, n2, T):
     """The two general INT4 kernels on the same call, forced: every way a chunk of a token's row can straddle rows of X~ (n2 a multiple
     of 8, of 4, of 2), chunks that end with the row, one to four row tiles, one to eight slabs, rows of codes that start on any byte,
-    operands on their smallest alignment, a factor left out.  The sums are the same, so the steps are; codes differ where a
-    value lies within 2e-6 code units of a tie (the constants of the conversion): a share of 4e-6, allowed ten times that."""
+    operands on their smallest alignment, a factor left out.  The same sums, rounded in the same way: the same bytes."""
     c = synth.generic(41 * n1 + n2 + T, T, n1, n2, sigma=0.05)
     n, pad = n1 * n2, 6 if how == "offsets" else 0
     def place(a, skip):                                   # `skip` halves past an aligned address
@@ -1046,8 +1045,35 @@ def test_general_int4_kernels_agree(tuning, how, n1, n2, T):
                                      codes[o:], steps, stream=torch.cuda.current_stream())
         assert int(codes[-1]) == 0xA5 and (not o or int(codes[0]) == 0xA5) and float(steps[-1]) == -7
         res.append((codes[o:o + T * n // 2], steps))
-    assert torch.equal(res[0][1], res[1][1])
-    assert int((res[0][0] != res[1][0]).sum()) <= 2 + 4e-5 * T * n
+    assert torch.equal(res[0][1], res[1][1]) and torch.equal(res[0][0], res[1][0])
+
+
+@pytest.mark.parametrize("how,n1,n2", [(h, *f) for h in ("whole", "P1 only", "P2 only") for f in ((16, 250), (64, 12), (96, 20), (128, 20), (128, 36), (64, 80), (97, 98), (48, 10))]
+                         + [("P1 only", 72, 128), ("P2 only", 72, 128)])
+def test_general_int4_codes_on_ties_for_any_number_of_tokens(how, n1, n2):
+    """The library chooses between its general kernels by the number of tokens.  Signed permutations as factors and a step of one: the values
+    are halves and whole numbers exactly, and every other one is a tie.  The codes are those of rounding half to even, on both sides of
+    every line of that choice, and the same rows get the same codes."""
+    r = np.random.Generator(np.random.PCG64(97 * n1 + n2))
+    n, most = n1 * n2, 1025
+    def signed_permutation(d):
+        m = np.zeros((d, d), dtype=np.float16)
+        m[r.permutation(d), np.arange(d)] = r.choice([-1, 1], size=d)
+        return m
+    x = r.integers(-16, 17, size=(most, n)).astype(np.float16) / 2
+    x[:, 0] = 8                                           # clip 0.875 x max 8 / 7: the step
+    P1, P2 = signed_permutation(n1), signed_permutation(n2)
+    y = x.reshape(most, n1, n2).astype(np.float32)
+    if how != "P2 only": y = np.einsum("ki,tkj->tij", P1.astype(np.float32), y)
+    if how != "P1 only": y = y @ P2.astype(np.float32)
+    q = np.rint(np.clip(y.reshape(most, n), -8, 7)).astype(np.int64) & 15
+    want = dev((q[:, 0::2] | q[:, 1::2] << 4).astype(np.uint8))
+    xd, p1, p2, clip = dev(x), None if how == "P2 only" else dev(P1), None if how == "P1 only" else dev(P2), torch.full((1,), 0.875, device="cuda")
+    for T in (1, 64, 256, 257, 512, 513, 768, 769, 1024, 1025):
+        codes, steps = torch.zeros((T, n // 2), dtype=torch.uint8, device="cuda"), torch.zeros(T, dtype=torch.float16, device="cuda")
+        print(f"[case] ties {how} {n1}x{n2} T={T}", flush=True)
+        fq.flatquant_transform_quant(xd, p1, p2, clip, 0, T, n1, n2, n, codes, steps, stream=torch.cuda.current_stream())
+        assert bool((steps == 1).all()) and torch.equal(codes, want[:T])
 
 
 @pytest.mark.parametrize("n1,n2,T", [(4, 8, 3), (64, 80, 130), (48, 112, 5), (16, 18, 129), (64, 86, 3), (96, 90, 4), (32, 250, 2), (128, 134, 3), (112, 136, 300),
