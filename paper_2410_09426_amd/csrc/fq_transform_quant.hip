@@ -775,27 +775,39 @@ static AnyVariant any_variant(int n1, int n2, bool mx) {
         default: return any_variant_a<4>(B, mx, n1 * n2);
     }
 }
-// Whether tq_any_kernel is the faster one of the two general kernels.  With many tokens it is (up to 2.5 times: 128 x 36 MXFP4 at 8192
-// 191 / 84 us); what tq_kernel keeps is launches of few tokens whose prologue decides, and MXFP4 rows of one row tile, whose values
-// move in pieces of 8 or 16 bytes when n2 % 8 != 0.  tq_kernel / tq_any_kernel, us:
-//   one row tile, INT4: 16 x 250 8.2 / 8.5 (64 tokens), 8.9 / 9.2 (256), 11.2 / 10.8 (512); 16 x 222 8.3 / 7.8 (256);
-//   one row tile, MXFP4: 16 x 34 4.4 / 4.5 (64), 16 x 66 5.6 / 5.8 (512), 11.9 / 14.6 (4096), 16 x 250 7.7 / 8.9 (64), 14.1 / 14.5 (1024), 18.3 / 17.9 (1500),
-//     16 x 134 6.1 / 6.5 (256), 10.5 / 7.8 (512: 5 or 6 slabs, one workgroup of tq_kernel per CU), 8 x 24 4.89 / 5.09 (2048), 16 x 248 8.0 / 8.3 (256), 9.9 / 9.8
-//     (512), 16 x 152 10.6 / 7.2 (512), 16 x 40 4.4 / 4.1 (64);
-//   one slab: 64 x 12 5.6 / 6.1 (64), 6.3 / 6.4 (512), 11.0 / 10.2 (4096), 128 x 20 16.7 / 18.6 (640), 21.5 / 18.9 (1024), 96 x 20 11.6 / 9.7 (512);
-//   two slabs where a CU gets two tokens: INT4 128 x 36 13.2 / 11.5 (256), 13.8 / 14.5 (512), 19.1 / 18.5 (640), 96 x 34 11.0 / 10.3 (512);
-//     MXFP4 96 x 34 9.7 / 9.0 (256), 10.3 / 10.7 (512), 13.8 / 11.6 (640), 128 x 36 19.3 / 15.2 (512).
+// Whether tq_any_kernel is the faster one of the two general kernels, which give the same bytes.  tq_kernel / tq_any_kernel in us, tokens in
+// parentheses (CUs: 256); the lines are where two thousand launches per format over all (A, B) crossed, and no launch measured is more
+// than 5 % slower than with tq_kernel alone.  From two row tiles and two slabs on it is (0.5 .. 0.97 of the time), but for launches that tq_kernel, whose
+// tiles are smaller in LDS, finishes in one round of workgroups and tq_any_kernel in two:
+//   four row tiles x two slabs INT4, three x two MXFP4, two workgroups of tq_kernel per CU: 128 x 36 12.8 / 11.3 (256), 13.1 / 14.0 (512), 18.4 / 18.2 (640);
+//     96 x 34 MXFP4 9.2 / 8.5 (256), 9.6 / 10.3 (512), 13.2 / 10.9 (640);
+//   one slab x four row tiles, three workgroups (MXFP4 two): 128 x 20 15.8 / 15.9 (512), 15.9 / 18.6 (640), 20.6 / 18.7 (900); MXFP4 16.0 / 16.5 (384), 21.1 / 19.8 (640).
+// One slab x two row tiles: a row has few values, and the prologue (two staging passes through LDS) is made up for by many tokens (not with
+// n2 = 8) or, in INT4, by rows that tq_kernel loads in pairs of halves: 64 x 28 5.9 / 5.7 (64), 6.6 / 6.2 (1024); 64 x 16 5.2 / 5.5 (64), 7.1 / 7.5 (2048),
+// 23.1 / 20.7 (16384); 33 x 16 10.1 / 10.4 (4311); 48 x 8 19.1 / 19.7 (16384); MXFP4 64 x 16 4.8 / 5.4 (64), 48 x 12 9.4 / 10.3 (4192), 50 x 16 23.7 / 18.7 (13869).
+// One row tile, INT4: but for the longest prologue with one token per CU (16 x 250 8.0 / 8.3 (64), 10.5 / 10.1 (512)).
+// One row tile, MXFP4: tq_kernel has more workgroups per CU up to four slabs, and one from there on.
+//   Up to four slabs, n2 % 8 != 0 (values move in pieces of 8 or 16 bytes): 16 x 66 4.3 / 4.4 (64), 11.5 / 14.1 (4096).
+//   n2 % 8 == 0: tq_any_kernel moves and stages whole tiles, so it gains where they are filled: 32 x 80 (0.83) 5.8 / 4.7 (300), 60 / 44 (16384);
+//     24 x 80 (0.63) 48 / 41, 12 x 72 (0.28) 5.3 / 5.7 (600), 28 / 40 (16384); one slab 32 x 16 (0.5) 14.9 / 12.3; fewer tokens 24 x 72 (0.56) 8.4 / 8.2 (2048), 36 / 41 (16384),
+//     two slabs 12 x 40 6.5 / 5.6 (2048), 17 / 22 (16384).
+//   Five slabs on: 16 x 134 5.7 / 6.2 (256), 9.5 / 7.3 (300); 16 x 136 5.3 / 5.1 (64), 9.1 / 6.4 (300); 16 x 250 7.6 / 8.8 (256), 13.6 / 14.1 (1024), 17.7 / 17.5 (1500); 16 x 248 7.5 / 7.7 (256),
+//     9.4 / 9.1 (512); 8 x 248 8.6 / 8.9 (512), 12.0 / 11.8 (1024).
 static bool any_is_faster(const TqDev& d, bool mx) {
     const int A = (d.n1 + 31) / 32, B = (d.n2 + 31) / 32;
-    if (A == 1) {
-        if (!mx) return B < 8 || d.T > 256;
-        if (d.n1 <= 8) return false;
-        if (d.n2 % 8 == 0) return B < 8 || d.T > 256;
-        return B >= 5 && d.T > (B <= 6 ? 256 : 1024);
+    const int64_t cu = cu_count();
+    if (A >= 2 && B >= 2) return !(B == 2 && A == (mx ? 3 : 4)) || d.T <= cu || d.T > 2 * cu;
+    if (A == 3) return true;
+    if (A == 4) return mx ? d.T > 2 * cu : d.n2 > 8 && d.T > 3 * cu;
+    if (A == 2) return (d.n2 > 8 && d.T > (mx ? 32 : 16) * cu) || (!mx && d.n2 > 16);
+    if (!mx) return B < 8 || d.T > cu;
+    const bool chunks = d.n2 % 8 == 0;
+    if (B >= 5) {
+        if (B == 8 || !chunks) return d.T > (B <= 6 || (chunks && d.n1 > 8) ? 1 : 4) * cu;
+        return true;
     }
-    if (B == 1) return d.T > 768 || (A < 4 && d.n2 >= 16);
-    if (B == 2 && A == (mx ? 3 : 4)) return d.T <= 256 || d.T > 512;
-    return true;
+    const int filled = 100 * d.n1 * d.n2 / (32 * 32 * B);                     // percent of the tiles
+    return chunks && (filled >= (B == 1 ? 50 : 60) || (d.T <= 8 * cu && (B == 2 || filled >= 45)));
 }
 
 // every workgroup gets the same number of tokens (+-1)
