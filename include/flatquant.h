@@ -276,7 +276,9 @@ int fq_abi_version(void);
  * FLATQUANT_MODE (activation kernel flavour: 0..4 the slab kernels, 5 / 6 the wave-per-token kernel of 64-wide rows, one
  * shot / persistent; 5 also forces the wave-per-token kernel of the left-factor-only case), FLATQUANT_WAVE_TPW (2 / 4 / 8 waves per workgroup of that kernel), FLATQUANT_PROBE_SHAPE (0..2: launch
  * shape of flatquant_stream_probe), FLATQUANT_WG_PER_CU, FLATQUANT_KV_WG_PER_CU (cap on resident
- * workgroups), FLATQUANT_FORCE_GENERIC (1: general kernel on shapes the specialised ones would take, 2: the one that takes what it does not, MXFP4 too),
+ * workgroups), FLATQUANT_FORCE_GENERIC (1: general
+ * kernels on shapes the specialised INT4 kernels would take; 2 / 3: one and the other of the two
+ * general kernels, MXFP4 too, FQ_LAUNCH_FAILED where it does not exist),
  * FLATQUANT_GEMM_TILED (1: tiled product for any T), FLATQUANT_GEMM_WIDE (0 / 1 / 2: 128 x 128, 256 x 128 or 256 x 256
  * tiles, the last two on FP6 MFMA for W4A4; W4A4 only, 4: 160 x 128; any other value leaves the choice to the library),
  * FLATQUANT_GEMM_ROWS (16 / 32 output channels per workgroup), FLATQUANT_GEMM_WAVES (4 / 8 / 16) and

@@ -744,13 +744,20 @@ static KernelFn kernel_table(int A, int B) {
     return tab[A - 1][B - 1];
 }
 
+// LDS of tq_kernel with A row tiles and B slabs, and with MXFP4 output; what that does not leave room for is not supported
+__host__ __device__ constexpr int generic_lds(int A, int B) { return 32 * A * (32 * B + kLdsPad) * 2 + 512 * A * B + 32 + (A >= 3 ? A * 2 * A * 64 * 16 : 0); }
+__host__ __device__ constexpr int mx_staged_lds(int A, int B) { return generic_lds(A, B) + (4096 - 512) * A * B; }
+
 struct AnyVariant {
-    KernelFn fn;
+    KernelFn fn;                                 // null: MXFP4 rows that neither kernel has room for
     int lds;
 };
 template <int A, int B>
 static AnyVariant any_variant_ab(bool mx, int n) {
-    if (mx) return {&tq_any_kernel<A, B, true>, any_mx_r0<A, B>(n) + FastLds<A, B>::P1S_BYTES};
+    if (mx) {
+        if constexpr (mx_staged_lds(A, B) > kLdsMax) return {nullptr, kLdsMax + 1};
+        else return {&tq_any_kernel<A, B, true>, any_mx_r0<A, B>(n) + FastLds<A, B>::P1S_BYTES};
+    }
     return {&tq_any_kernel<A, B, false>, FastLds<A, B>::TOTAL};
 }
 template <int A>
@@ -833,8 +840,17 @@ static hipError_t any_launch(const TqDev& d, hipStream_t stream, bool mx) {
     return launch(v.fn, dim3((unsigned)((d.T + rounds - 1) / rounds)), dim3(64 * B), v.lds, stream, d);
 }
 
+// MXFP4 instances of tq_kernel: where any_is_faster() can say no, and four row tiles x five slabs, whose longest rows (n > 19555) tq_any_kernel's
+// padded staging has no room for.  Everywhere else there is none (null).
 template <int A, int B>
-static constexpr KernelFn mx_kernel_for() { return &tq_kernel<A, B, (A >= 3), true>; }
+static constexpr KernelFn mx_kernel_for() {
+    if constexpr (A == 1 || B == 1 || (A == 3 && B == 2) || (A == 4 && B == 5)) {
+        return &tq_kernel<A, B, (A >= 3), true>;
+    } else {
+        static_assert(mx_staged_lds(A, B) > kLdsMax || any_mx_r0<A, B>(1024 * A * B) + FastLds<A, B>::P1S_BYTES <= kLdsMax, "tq_any_kernel takes all of these rows");
+        return nullptr;
+    }
+}
 
 static KernelFn mx_kernel_table(int A, int B) {
     static const KernelFn tab[4][8] = {
@@ -850,12 +866,7 @@ bool tq_supported(int n1, int n2) {
     return n1 >= 1 && n1 <= kMaxN1 && n2 >= 2 && n2 <= kMaxN2 && (n2 % 2) == 0;
 }
 
-static int64_t generic_lds_bytes(int n1, int n2) {
-    const int A = (n1 + 31) / 32, B = (n2 + 31) / 32;
-    int64_t b = (int64_t)32 * A * (32 * B + kLdsPad) * 2 + 512 * A * B + 32;
-    if (A >= 3) b += (int64_t)A * 2 * A * 64 * 16;
-    return b;
-}
+static int64_t generic_lds_bytes(int n1, int n2) { return generic_lds((n1 + 31) / 32, (n2 + 31) / 32); }
 
 int64_t tq_lds_bytes(int n1, int n2) {
     if (!tq_supported(n1, n2)) return 0;
@@ -864,24 +875,22 @@ int64_t tq_lds_bytes(int n1, int n2) {
     return f > b && f > a ? f : a > b ? a : b;
 }
 
-static int64_t generic_mx_lds_bytes(int n1, int n2) {
-    const int A = (n1 + 31) / 32, B = (n2 + 31) / 32;
-    return generic_lds_bytes(n1, n2) + (int64_t)(4096 - 512) * A * B;
-}
+static int64_t generic_mx_lds_bytes(int n1, int n2) { return mx_staged_lds((n1 + 31) / 32, (n2 + 31) / 32); }
 
 // MXFP4 output through the general kernel: any supported (n1, n2) with whole blocks of 32 channels per row whose
 // fp32 staging fits in LDS beside the token tile (64 x 172: 74 KB), 16-byte aligned code rows.
 bool tq_mx_generic_applicable(const TqDev& d) {
     const int64_t n = (int64_t)d.n1 * d.n2;
-    return tq_supported(d.n1, d.n2) && n % 32 == 0 && d.out_vec16 && d.P1 && d.P2 && generic_mx_lds_bytes(d.n1, d.n2) <= 160 * 1024;
+    return tq_supported(d.n1, d.n2) && n % 32 == 0 && d.out_vec16 && d.P1 && d.P2 && generic_mx_lds_bytes(d.n1, d.n2) <= kLdsMax;
 }
 
 hipError_t tq_mx_generic_launch(const TqDev& d, hipStream_t stream) {
     const int A = (d.n1 + 31) / 32, B = (d.n2 + 31) / 32;
-    // FLATQUANT_FORCE_GENERIC=1 / 2 forces tq_any_kernel / tq_kernel
+    // FLATQUANT_FORCE_GENERIC = 3 / 2 forces tq_any_kernel / tq_kernel, an error where there is none; 1 tq_any_kernel where it can
     const int force = tuned(Knob::FORCE_GENERIC, 0);
-    if (d.n2 >= 8 && any_variant(d.n1, d.n2, true).lds <= kLdsMax && (force == 1 || (force != 2 && any_is_faster(d, true)))) return any_launch(d, stream, true);
+    if (d.n2 >= 8 && any_variant(d.n1, d.n2, true).lds <= kLdsMax && (force == 1 || force == 3 || (force != 2 && any_is_faster(d, true)))) return any_launch(d, stream, true);
     KernelFn fn = mx_kernel_table(A, B);
+    if (!fn || force == 3) return hipErrorInvalidValue;
     const int lds = (int)generic_mx_lds_bytes(d.n1, d.n2);
     static OccCache occ_cache[4][8];
     int occ = 0;
@@ -920,11 +929,10 @@ hipError_t tq_launch(const TqArgs& a, hipStream_t stream) {
 
     // Right factors of fewer than 8 columns stay with tq_kernel (a chunk of a row could straddle three rows of X~), and so do rows that
     // are only quantized (both factors left out), which have not been moved: there the other one gives the same bytes in less time (64 x 80
-    // at 2048 tokens 17.9 / 12.4 us, 64 x 128 at 16384 110 / 78).  FLATQUANT_FORCE_GENERIC=2 forces it.
+    // at 2048 tokens 17.9 / 12.4 us, 64 x 128 at 16384 110 / 78).  FLATQUANT_FORCE_GENERIC as for MXFP4.
     const int force = tuned(Knob::FORCE_GENERIC, 0);
-    if (a.n2 >= 8 && (a.P1 || a.P2) && force != 2 && (force == 1 || any_is_faster(d, false))) {
-        return any_launch(d, stream, false);
-    }
+    if (a.n2 >= 8 && (a.P1 || a.P2) && force != 2 && (force == 1 || force == 3 || any_is_faster(d, false))) return any_launch(d, stream, false);
+    if (force == 3) return hipErrorInvalidValue;
     static OccCache occ_cache[4][8];   // per variant and device
     int occ = 0;
     {

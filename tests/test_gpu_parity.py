@@ -350,7 +350,9 @@ def test_mxfp4_wave_per_token_kernel(tuning, mode, tpw):
         test_mxfp4_tiled_exponents_equal_row_major(n1, 64, T)
 
 
-@pytest.mark.parametrize("n1,n2,T", [(64, 172, 70), (64, 172, 2049), (10, 48, 33), (3, 32, 7), (64, 34, 300), (86, 16, 129), (128, 130, 40), (1, 32, 5)])
+@pytest.mark.parametrize("n1,n2,T", [(64, 172, 70), (64, 172, 2049), (10, 48, 33), (3, 32, 7), (64, 34, 300), (86, 16, 129), (128, 130, 40), (1, 32, 5),
+                                     (64, 80, 130), (48, 112, 5), (64, 86, 3), (96, 90, 4), (64, 172, 700), (128, 158, 2), (16, 6, 5), (60, 216, 3), (96, 108, 70), (64, 252, 9),
+                                     (96, 208, 3), (128, 40, 300), (112, 88, 6), (128, 104, 5)])
 def test_mxfp4_output_general_kernel(n1, n2, T):
     """Right factors that are not a multiple of 32 (a block of 32 channels then straddles rows of X~; 64 x 172 is the
     paper's other factorization of 11008), and rows of fewer than 128 channels: the general kernel stages Y in LDS and
@@ -1036,7 +1038,7 @@ def test_general_int4_kernels_agree(tuning, how, n1, n2, T):
     o = 1 if how == "offsets" else 0
     x, P1, P2 = place(x, 2 * o), place(dev(c.P1), o), place(dev(c.P2), o)
     res = []
-    for force in (1, 2):
+    for force in (3, 2):
         tuning("FLATQUANT_FORCE_GENERIC", force)
         codes = torch.full((T * n // 2 + 2,), 0xA5, dtype=torch.uint8, device="cuda")
         steps = torch.full((T + 1,), -7.0, dtype=torch.float16, device="cuda")
@@ -1076,12 +1078,13 @@ def test_general_int4_codes_on_ties_for_any_number_of_tokens(how, n1, n2):
         assert bool((steps == 1).all()) and torch.equal(codes, want[:T])
 
 
-@pytest.mark.parametrize("n1,n2,T", [(4, 8, 3), (64, 80, 130), (48, 112, 5), (16, 18, 129), (64, 86, 3), (96, 90, 4), (32, 250, 2), (128, 134, 3), (112, 136, 300),
-                                     (64, 172, 700), (128, 158, 2), (16, 6, 5)])
+@pytest.mark.parametrize("n1,n2,T", [(4, 8, 3), (16, 18, 129), (16, 48, 70), (32, 88, 5), (32, 104, 600), (32, 134, 3), (16, 184, 300), (32, 202, 70), (32, 250, 2), (64, 24, 9), (48, 14, 300),
+                                     (96, 24, 70), (96, 56, 4), (80, 48, 600), (80, 34, 3), (128, 14, 5), (128, 134, 3), (112, 136, 300)])
 @pytest.mark.parametrize("tiled", [False, True])
 def test_general_mxfp4_kernels_agree(tuning, tiled, n1, n2, T):
-    """The two general MXFP4 kernels: the same sums and the same conversion, so the same bytes.  Every way a run of channels can lie in a
-    block (n2 a multiple of 8, of 4, of 2), one to four row tiles, one to eight slabs, the shapes only the second takes."""
+    """The two general MXFP4 kernels where there are both: the same sums and the same conversion, so the same bytes.  Every way a run of
+    channels can lie in a block (n2 a multiple of 8, of 4, of 2), one to four row tiles, one to eight slabs.  (A forced kernel that a shape does not
+    have is an error, so none is compared with itself.)"""
     n = n1 * n2
     if tiled and n % 256:
         n1 *= 256 // math.gcd(n, 256)
@@ -1092,7 +1095,7 @@ def test_general_mxfp4_kernels_agree(tuning, tiled, n1, n2, T):
     x, P1, P2, clip = dev(c.x), dev(c.P1), dev(c.P2), dev(c.clip)
     nexp = fq.fq_mxfp4_tiled_scale_bytes(T, n) if tiled else T * n // 32
     res = []
-    for force in (1, 2):
+    for force in (3, 2):
         tuning("FLATQUANT_FORCE_GENERIC", force)
         codes = torch.full((T * n // 2 + 16,), 0xA5, dtype=torch.uint8, device="cuda")
         exps = torch.full((nexp + 16,), 0x5A, dtype=torch.uint8, device="cuda")
@@ -1102,6 +1105,16 @@ def test_general_mxfp4_kernels_agree(tuning, tiled, n1, n2, T):
         assert int((codes[-16:] != 0xA5).sum()) == 0 and int((exps[-16:] != 0x5A).sum()) == 0
         res.append((codes, exps))
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
+@pytest.mark.parametrize("n1,n2,force", [(64, 80, 2), (96, 90, 2), (128, 40, 2), (16, 6, 3), (128, 158, 3)])
+def test_a_forced_general_mxfp4_kernel_that_is_not_there_is_refused(tuning, n1, n2, force):
+    c = synth.generic(5, 3, n1, n2)
+    x, P1, P2, clip = dev(c.x), dev(c.P1), dev(c.P2), dev(c.clip)
+    codes, exps = (torch.full((3 * n1 * n2,), 0xA5, dtype=torch.uint8, device="cuda") for _ in range(2))
+    tuning("FLATQUANT_FORCE_GENERIC", force)
+    assert fq.flatquant_transform_mxfp4(x, P1, P2, clip, c.clip_mode, 3, n1, n2, n1 * n2, codes, exps, check=False) == fq.FQ_LAUNCH_FAILED
+    assert bool((codes == 0xA5).all()) and bool((exps == 0xA5).all())
 
 
 @pytest.mark.parametrize("T,H,shared", [(4096, 8, False), (1, 8, False), (77, 3, False), (200, 8, True), (31, 2, True), (32, 5, False), (33, 16, True),
