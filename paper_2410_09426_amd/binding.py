@@ -7,11 +7,12 @@ library is missing, loading raises.
 
 The entry points of a model's forward pass (``NATIVE``) are functions of the extension module ``_fqcall``
 (csrc/fq_python.cpp) with the signatures of their C counterparts, minus the types, plus ``stream=None, check=True``; they are
-loaded when the first of them is asked for.  The others call through ctypes.
+loaded when the first of them is asked for, and call the library that ``lib()`` has loaded.  The others call through ctypes.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 from typing import Optional
 
@@ -36,6 +37,7 @@ NATIVE = (
 )
 
 _lib = None
+_fqcall = None
 
 
 class FlatQuantError(RuntimeError):
@@ -101,6 +103,8 @@ def lib() -> ctypes.CDLL:
         L.fq_abi_version.argtypes = []
         L.fq_abi_version.restype = i32
         _lib = L
+        if _fqcall:
+            _fqcall.bind({n: ctypes.cast(getattr(L, n), vp).value for n in NATIVE})
     return _lib
 
 
@@ -122,15 +126,17 @@ def _stream(stream) -> Optional[int]:
 
 def __getattr__(name):
     """The native entry points, on first use (a module attribute from then on)."""
+    global _fqcall, _lib
     if name not in NATIVE:
         raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
-    lib()
     try:
-        from . import _fqcall
+        _fqcall = importlib.import_module(__package__ + "._fqcall")
     except ImportError as e:
         raise FileNotFoundError(f"{os.path.join(_PKG, '_fqcall.so')} cannot be loaded: build it with "
                                 "`python -m paper_2410_09426_amd.build`") from e
-    _fqcall.set_error(FlatQuantError)
+    _fqcall.connect(lib, FlatQuantError)
+    _lib = None                                 # bound when it is loaded (again)
+    lib()
     globals().update((n, getattr(_fqcall, n)) for n in NATIVE)
     return globals()[name]
 

@@ -2,6 +2,9 @@
 // binding.py's other functions in native code.  What bounds a decode step is the host: 2.6 us per launch in the HIP runtime, and
 // 1.0 us of interpreter and 0.5 us of ctypes on top of it through a Python function; from here 0.3 us.
 //
+// Nothing of the library is linked here: binding.py hands over the addresses of the entry points when it loads libflatquant.so, so
+// both halves of the binding always talk to the same one, and importing this module loads nothing.
+//
 // A pointer argument is None, an address, or an object with data_ptr(); a stream is None, a handle, or an object with
 // cuda_stream.  Numbers go through int() / float() as they did there, and into the C types like ctypes does it (low bits of an
 // integer).  The interpreter lock is released around the call.
@@ -14,7 +17,10 @@
 
 namespace {
 
+enum Entry { TRANSFORM, MX, MX_TILED, WEIGHT, W4A4, MX_GEMM, KV, KV_BITS, HEAD, COUNT };
+void* g_entry[COUNT];                 // addresses in the loaded library; null until then
 PyObject* g_error = nullptr;          // binding.FlatQuantError(status, where)
+PyObject* g_load = nullptr;           // binding.lib: loads the library and binds its addresses, or raises
 PyObject *g_data_ptr, *g_cuda_stream; // attribute names
 
 struct Reader {                       // reads arguments in order; after a failure everything reads as 0
@@ -74,11 +80,28 @@ constexpr int kMaxArgs = 16;
 
 // Positional and keyword arguments into out[0 .. n - 1] by the names of a signature whose last two are optional: stream, check.
 struct Signature {
+    Entry entry;
     const char* name;
     const char* names[kMaxArgs];
     int n = 0;
     PyObject* keys[kMaxArgs] = {};
 };
+
+// The entry point's address: on the first call the library is loaded.
+template <typename Fn>
+bool entry(Entry e, Fn& fn) {
+    if (!g_entry[e]) {
+        PyObject* r = g_load ? PyObject_CallNoArgs(g_load) : nullptr;
+        if (!r && g_load) return false;
+        Py_XDECREF(r);
+        if (!g_entry[e]) {
+            PyErr_SetString(PyExc_RuntimeError, "libflatquant is not bound");
+            return false;
+        }
+    }
+    fn = reinterpret_cast<Fn>(g_entry[e]);
+    return true;
+}
 
 bool collect(const Signature& s, PyObject* const* args, Py_ssize_t nargs, PyObject* kw, PyObject** out) {
     if (nargs > s.n) {
@@ -129,10 +152,11 @@ PyObject* finish(const Signature& s, fq_status st, PyObject* check) {
     return PyLong_FromLong((long)st);
 }
 
-// activation and weight transforms
-using TransformFn = fq_status (*)(const void*, const void*, const void*, const float*, int, int64_t, int, int, int64_t, uint8_t*, void*, void*);
-PyObject* transform(const Signature& s, TransformFn fn, PyObject* const* args, Py_ssize_t nargs, PyObject* kw) {
+// activation and weight transforms: the same arguments, but for the type of the scales
+template <typename Scales, typename Fn>
+PyObject* transform(const Signature& s, PyObject* const* args, Py_ssize_t nargs, PyObject* kw) {
     PyObject* v[kMaxArgs];
+    Fn fn;
     if (!collect(s, args, nargs, kw, v)) return nullptr;
     Reader r{v};
     const void *x = r.ptr(), *P1 = r.ptr(), *P2 = r.ptr(), *clip = r.ptr();
@@ -141,24 +165,19 @@ PyObject* transform(const Signature& s, TransformFn fn, PyObject* const* args, P
     const int n1 = r.i32(), n2 = r.i32();
     const int64_t stride = r.i64();
     void *codes = r.ptr(), *scales = r.ptr(), *stream = r.stream();
-    if (!r.ok) return nullptr;
+    if (!r.ok || !entry(s.entry, fn)) return nullptr;
     fq_status st;
     Py_BEGIN_ALLOW_THREADS
-    st = fn(x, P1, P2, (const float*)clip, mode, T, n1, n2, stride, (uint8_t*)codes, scales, stream);
+    st = fn(x, P1, P2, (const float*)clip, mode, T, n1, n2, stride, (uint8_t*)codes, (Scales*)scales, stream);
     Py_END_ALLOW_THREADS
     return finish(s, st, v[s.n - 1]);
 }
-fq_status mx(const void* x, const void* P1, const void* P2, const float* clip, int mode, int64_t T, int n1, int n2, int64_t stride, uint8_t* codes, void* scales, void* stream) {
-    return flatquant_transform_mxfp4(x, P1, P2, clip, mode, T, n1, n2, stride, codes, (uint8_t*)scales, stream);
-}
-fq_status mx_tiled(const void* x, const void* P1, const void* P2, const float* clip, int mode, int64_t T, int n1, int n2, int64_t stride, uint8_t* codes, void* scales, void* stream) {
-    return flatquant_transform_mxfp4_tiled(x, P1, P2, clip, mode, T, n1, n2, stride, codes, (uint8_t*)scales, stream);
-}
 
 // matrix products
-using ProductFn = fq_status (*)(const uint8_t*, const void*, const uint8_t*, const void*, int64_t, int, int, void*, int64_t, void*);
-PyObject* product(const Signature& s, ProductFn fn, PyObject* const* args, Py_ssize_t nargs, PyObject* kw) {
+template <typename Scales, typename Fn>
+PyObject* product(const Signature& s, PyObject* const* args, Py_ssize_t nargs, PyObject* kw) {
     PyObject* v[kMaxArgs];
+    Fn fn;
     if (!collect(s, args, nargs, kw, v)) return nullptr;
     Reader r{v};
     const void *xc = r.ptr(), *xs = r.ptr(), *wc = r.ptr(), *ws = r.ptr();
@@ -167,61 +186,61 @@ PyObject* product(const Signature& s, ProductFn fn, PyObject* const* args, Py_ss
     void* out = r.ptr();
     const int64_t stride = r.i64();
     void* stream = r.stream();
-    if (!r.ok) return nullptr;
+    if (!r.ok || !entry(s.entry, fn)) return nullptr;
     fq_status st;
     Py_BEGIN_ALLOW_THREADS
-    st = fn((const uint8_t*)xc, xs, (const uint8_t*)wc, ws, T, m, n, out, stride, stream);
-    Py_END_ALLOW_THREADS
-    return finish(s, st, v[s.n - 1]);
-}
-fq_status mx_product(const uint8_t* xc, const void* xs, const uint8_t* wc, const void* ws, int64_t T, int m, int n, void* out, int64_t stride, void* stream) {
-    return flatquant_mxfp4_gemm(xc, (const uint8_t*)xs, wc, (const uint8_t*)ws, T, m, n, out, stride, stream);
-}
-
-// KV cache; `bits` is an argument of one of the two
-PyObject* kv(const Signature& s, bool has_bits, PyObject* const* args, Py_ssize_t nargs, PyObject* kw) {
-    PyObject* v[kMaxArgs];
-    if (!collect(s, args, nargs, kw, v)) return nullptr;
-    Reader r{v};
-    const void *x = r.ptr(), *P = r.ptr();
-    const int Hp = r.i32();
-    const float clip = r.f32();
-    const int bits = has_bits ? r.i32() : 4;
-    const int64_t T = r.i64();
-    const int H = r.i32(), D = r.i32();
-    void *codes = r.ptr(), *scales = r.ptr(), *zeros = r.ptr(), *stream = r.stream();
-    if (!r.ok) return nullptr;
-    fq_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = flatquant_kv_transform_quant_bits(x, P, Hp, clip, bits, T, H, D, (uint8_t*)codes, scales, zeros, stream);
+    st = fn((const uint8_t*)xc, (const Scales*)xs, (const uint8_t*)wc, (const Scales*)ws, T, m, n, out, stride, stream);
     Py_END_ALLOW_THREADS
     return finish(s, st, v[s.n - 1]);
 }
 
 #define ACT() "x", "P1", "P2", "clip", "clip_mode", "T", "n1", "n2", "x_stride", "out_codes", "out_scales", "stream", "check"
-Signature kTransform{"flatquant_transform_quant", {ACT()}};
-Signature kMx{"flatquant_transform_mxfp4", {ACT()}};
-Signature kMxTiled{"flatquant_transform_mxfp4_tiled", {ACT()}};
-Signature kWeight{"flatquant_weight_transform_quant", {"w", "A1", "A2", "clip", "clip_mode", "m", "n1", "n2", "w_stride", "out_codes", "out_scales", "stream", "check"}};
+Signature kTransform{TRANSFORM, "flatquant_transform_quant", {ACT()}};
+Signature kMx{MX, "flatquant_transform_mxfp4", {ACT()}};
+Signature kMxTiled{MX_TILED, "flatquant_transform_mxfp4_tiled", {ACT()}};
+Signature kWeight{WEIGHT, "flatquant_weight_transform_quant", {"w", "A1", "A2", "clip", "clip_mode", "m", "n1", "n2", "w_stride", "out_codes", "out_scales", "stream", "check"}};
 #define GEMM() "x_codes", "x_scales", "w_codes", "w_scales", "T", "m", "n", "out", "out_stride", "stream", "check"
-Signature kW4a4{"flatquant_w4a4_gemm", {GEMM()}};
-Signature kMxGemm{"flatquant_mxfp4_gemm", {GEMM()}};
-Signature kKv{"flatquant_kv_transform_quant", {"kv", "P", "Hp", "clip", "T", "H", "D", "out_codes", "out_scales", "out_zeros", "stream", "check"}};
-Signature kKvBits{"flatquant_kv_transform_quant_bits", {"kv", "P", "Hp", "clip", "bits", "T", "H", "D", "out_codes", "out_scales", "out_zeros", "stream", "check"}};
-Signature kHead{"flatquant_head_transform", {"x", "P", "Hp", "T", "H", "D", "out", "stream", "check"}};
-Signature* const kAll[] = {&kTransform, &kMx, &kMxTiled, &kWeight, &kW4a4, &kMxGemm, &kKv, &kKvBits, &kHead};
+Signature kW4a4{W4A4, "flatquant_w4a4_gemm", {GEMM()}};
+Signature kMxGemm{MX_GEMM, "flatquant_mxfp4_gemm", {GEMM()}};
+Signature kKv{KV, "flatquant_kv_transform_quant", {"kv", "P", "Hp", "clip", "T", "H", "D", "out_codes", "out_scales", "out_zeros", "stream", "check"}};
+Signature kKvBits{KV_BITS, "flatquant_kv_transform_quant_bits", {"kv", "P", "Hp", "clip", "bits", "T", "H", "D", "out_codes", "out_scales", "out_zeros", "stream", "check"}};
+Signature kHead{HEAD, "flatquant_head_transform", {"x", "P", "Hp", "T", "H", "D", "out", "stream", "check"}};
+Signature* const kAll[COUNT] = {&kTransform, &kMx, &kMxTiled, &kWeight, &kW4a4, &kMxGemm, &kKv, &kKvBits, &kHead};
 
 #define ARGS PyObject*, PyObject *const *a, Py_ssize_t n, PyObject *kw
-PyObject* py_transform(ARGS) { return transform(kTransform, flatquant_transform_quant, a, n, kw); }
-PyObject* py_mx(ARGS) { return transform(kMx, mx, a, n, kw); }
-PyObject* py_mx_tiled(ARGS) { return transform(kMxTiled, mx_tiled, a, n, kw); }
-PyObject* py_weight(ARGS) { return transform(kWeight, flatquant_weight_transform_quant, a, n, kw); }
-PyObject* py_w4a4(ARGS) { return product(kW4a4, flatquant_w4a4_gemm, a, n, kw); }
-PyObject* py_mx_gemm(ARGS) { return product(kMxGemm, mx_product, a, n, kw); }
-PyObject* py_kv(ARGS) { return kv(kKv, false, a, n, kw); }
-PyObject* py_kv_bits(ARGS) { return kv(kKvBits, true, a, n, kw); }
+#define TYPE(entry) decltype(&entry)
+PyObject* py_transform(ARGS) { return transform<void, TYPE(flatquant_transform_quant)>(kTransform, a, n, kw); }
+PyObject* py_mx(ARGS) { return transform<uint8_t, TYPE(flatquant_transform_mxfp4)>(kMx, a, n, kw); }
+PyObject* py_mx_tiled(ARGS) { return transform<uint8_t, TYPE(flatquant_transform_mxfp4_tiled)>(kMxTiled, a, n, kw); }
+PyObject* py_weight(ARGS) { return transform<void, TYPE(flatquant_weight_transform_quant)>(kWeight, a, n, kw); }
+PyObject* py_w4a4(ARGS) { return product<void, TYPE(flatquant_w4a4_gemm)>(kW4a4, a, n, kw); }
+PyObject* py_mx_gemm(ARGS) { return product<uint8_t, TYPE(flatquant_mxfp4_gemm)>(kMxGemm, a, n, kw); }
+// KV cache; the code width is an argument of one of the two
+template <bool BITS>
+PyObject* kv(const Signature& s, PyObject* const* args, Py_ssize_t nargs, PyObject* kw) {
+    PyObject* v[kMaxArgs];
+    TYPE(flatquant_kv_transform_quant_bits) fn;
+    if (!collect(s, args, nargs, kw, v)) return nullptr;
+    Reader r{v};
+    const void *x = r.ptr(), *P = r.ptr();
+    const int Hp = r.i32();
+    const float clip = r.f32();
+    const int bits = BITS ? r.i32() : 4;
+    const int64_t T = r.i64();
+    const int H = r.i32(), D = r.i32();
+    void *codes = r.ptr(), *scales = r.ptr(), *zeros = r.ptr(), *stream = r.stream();
+    if (!r.ok || !entry(KV_BITS, fn)) return nullptr;
+    fq_status st;
+    Py_BEGIN_ALLOW_THREADS
+    st = fn(x, P, Hp, clip, bits, T, H, D, (uint8_t*)codes, scales, zeros, stream);
+    Py_END_ALLOW_THREADS
+    return finish(s, st, v[s.n - 1]);
+}
+PyObject* py_kv(ARGS) { return kv<false>(kKv, a, n, kw); }
+PyObject* py_kv_bits(ARGS) { return kv<true>(kKvBits, a, n, kw); }
 PyObject* py_head(ARGS) {
     PyObject* v[kMaxArgs];
+    TYPE(flatquant_head_transform) fn;
     if (!collect(kHead, a, n, kw, v)) return nullptr;
     Reader r{v};
     const void *x = r.ptr(), *P = r.ptr();
@@ -229,15 +248,35 @@ PyObject* py_head(ARGS) {
     const int64_t T = r.i64();
     const int H = r.i32(), D = r.i32();
     void *out = r.ptr(), *stream = r.stream();
-    if (!r.ok) return nullptr;
+    if (!r.ok || !entry(kHead.entry, fn)) return nullptr;
     fq_status st;
     Py_BEGIN_ALLOW_THREADS
-    st = flatquant_head_transform(x, P, Hp, T, H, D, out, stream);
+    st = fn(x, P, Hp, T, H, D, out, stream);
     Py_END_ALLOW_THREADS
     return finish(kHead, st, v[kHead.n - 1]);
 }
-PyObject* py_set_error(PyObject*, PyObject* cls) {
-    Py_XSETREF(g_error, Py_NewRef(cls));
+// connect(load, error): `load` is called when an entry point is needed whose address is not known; `error` is what is raised
+PyObject* py_connect(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (n != 2) {
+        PyErr_SetString(PyExc_TypeError, "connect(load, error)");
+        return nullptr;
+    }
+    Py_XSETREF(g_load, Py_NewRef(a[0]));
+    Py_XSETREF(g_error, Py_NewRef(a[1]));
+    for (void*& e : g_entry) e = nullptr;
+    Py_RETURN_NONE;
+}
+// bind({name: address}): the entry points of the library just loaded
+PyObject* py_bind(PyObject*, PyObject* addresses) {
+    void* found[COUNT];
+    for (Signature* s : kAll) {
+        PyObject* o = PyMapping_GetItemString(addresses, s->name);
+        if (!o) return nullptr;
+        found[s->entry] = PyLong_AsVoidPtr(o);
+        Py_DECREF(o);
+        if (PyErr_Occurred()) return nullptr;
+    }
+    for (int e = 0; e < COUNT; ++e) g_entry[e] = found[e];
     Py_RETURN_NONE;
 }
 
@@ -254,7 +293,8 @@ PyMethodDef kMethods[] = {
     FN("flatquant_kv_transform_quant", py_kv, "(kv, P, Hp, clip, T, H, D, out_codes, out_scales, out_zeros, stream=None, check=True)"),
     FN("flatquant_kv_transform_quant_bits", py_kv_bits, "(kv, P, Hp, clip, bits, T, H, D, out_codes, out_scales, out_zeros, stream=None, check=True)"),
     FN("flatquant_head_transform", py_head, "(x, P, Hp, T, H, D, out, stream=None, check=True)"),
-    {"set_error", py_set_error, METH_O, nullptr},
+    {"connect", (PyCFunction)(void (*)(void))py_connect, METH_FASTCALL, nullptr},
+    {"bind", py_bind, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_fqcall", "Native calls of libflatquant's launching entry points (see binding.py).", -1, kMethods, nullptr, nullptr, nullptr, nullptr};
 

@@ -365,3 +365,19 @@ def test_native_calls_marshal_like_their_signatures(name):
                      (tuple(good.values()) + (None, True, 1), {}), (tuple(good.values()), {"stream": "x"})):
         with pytest.raises((TypeError, AttributeError)):
             fn(*args, **kw)
+
+
+def test_native_calls_and_ctypes_use_one_library(tmp_path):
+    """A library at another place (LIB_PATH): all entry points run in it, and no second one is loaded."""
+    import shutil
+    import subprocess
+    import sys
+    other = str(tmp_path / "libflatquant.so")
+    shutil.copy(fq.LIB_PATH, other)
+    code = (f"from paper_2410_09426_amd import binding as fq\nfq.LIB_PATH = {other!r}\n"
+            "assert fq.flatquant_w4a4_gemm(4096, 8192, 12288, 16384, 0, 8, 256, 20480, 8) == fq.FQ_OK\n"
+            "assert fq.fq_choose_factors(8192) == (64, 128)\n"
+            "print(sorted({l.split()[-1] for l in open('/proc/self/maps') if l.rstrip().endswith('/libflatquant.so')}))\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert r.stdout.strip() == str([other])
