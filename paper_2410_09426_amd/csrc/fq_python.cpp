@@ -219,20 +219,21 @@ PyObject* py_mx_gemm(ARGS) { return product<uint8_t, TYPE(flatquant_mxfp4_gemm)>
 template <bool BITS>
 PyObject* kv(const Signature& s, PyObject* const* args, Py_ssize_t nargs, PyObject* kw) {
     PyObject* v[kMaxArgs];
+    TYPE(flatquant_kv_transform_quant) fn4;
     TYPE(flatquant_kv_transform_quant_bits) fn;
     if (!collect(s, args, nargs, kw, v)) return nullptr;
     Reader r{v};
     const void *x = r.ptr(), *P = r.ptr();
     const int Hp = r.i32();
     const float clip = r.f32();
-    const int bits = BITS ? r.i32() : 4;
+    const int bits = BITS ? r.i32() : 0;
     const int64_t T = r.i64();
     const int H = r.i32(), D = r.i32();
     void *codes = r.ptr(), *scales = r.ptr(), *zeros = r.ptr(), *stream = r.stream();
-    if (!r.ok || !entry(KV_BITS, fn)) return nullptr;
+    if (!r.ok || !(BITS ? entry(s.entry, fn) : entry(s.entry, fn4))) return nullptr;
     fq_status st;
     Py_BEGIN_ALLOW_THREADS
-    st = fn(x, P, Hp, clip, bits, T, H, D, (uint8_t*)codes, scales, zeros, stream);
+    st = BITS ? fn(x, P, Hp, clip, bits, T, H, D, (uint8_t*)codes, scales, zeros, stream) : fn4(x, P, Hp, clip, T, H, D, (uint8_t*)codes, scales, zeros, stream);
     Py_END_ALLOW_THREADS
     return finish(s, st, v[s.n - 1]);
 }

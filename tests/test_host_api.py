@@ -1,6 +1,7 @@
 """Host-side checks that need no GPU: the library loads, exports what the header
 declares, and rejects bad arguments before touching a device."""
 import ctypes
+import importlib
 import os
 import re
 
@@ -381,3 +382,26 @@ def test_native_calls_and_ctypes_use_one_library(tmp_path):
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
     assert r.returncode == 0, r.stderr[-2000:]
     assert r.stdout.strip() == str([other])
+
+
+def test_native_calls_reach_the_c_function_of_their_name():
+    """Every launching entry point with a recording function in the place of each C function: the call arrives at the one of its name,
+    every argument in its place and in its C type."""
+    fq.flatquant_head_transform                            # loads the extension
+    calls = importlib.import_module("paper_2410_09426_amd._fqcall")
+    seen, keep, addresses = [], [], {}
+    for name in fq.NATIVE:
+        c = getattr(fq.lib(), name)
+        f = ctypes.CFUNCTYPE(c.restype, *c.argtypes)(lambda *a, name=name: seen.append((name, *a)) or fq.FQ_OK)
+        keep.append(f)
+        addresses[name] = ctypes.cast(f, ctypes.c_void_p).value
+    real = {n: ctypes.cast(getattr(fq.lib(), n), ctypes.c_void_p).value for n in fq.NATIVE}
+    calls.bind(addresses)
+    try:
+        for name in fq.NATIVE:
+            types = getattr(fq.lib(), name).argtypes[:-1]                     # without the stream
+            args = [0.25 if t is ctypes.c_float else 2 ** 40 + k if t is ctypes.c_int64 else 100 + k if t is ctypes.c_int else 2 ** 45 + k for k, t in enumerate(types)]
+            assert getattr(fq, name)(*args, 2 ** 44) == fq.FQ_OK
+            assert seen.pop() == (name, *args, 2 ** 44) and not seen
+    finally:
+        calls.bind(real)
