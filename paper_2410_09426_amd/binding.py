@@ -2,12 +2,13 @@
 
 Functions have the names of the C entry points (see include/flatquant.h).  They
 accept raw device addresses (ints) or objects with ``data_ptr()`` (torch
-tensors); nothing is computed in Python.  There is no fallback: if a shared
-library is missing, loading raises.
+tensors); nothing is computed in Python.  There is no fallback for the
+kernels: if the library is missing, loading raises.
 
-The entry points of a model's forward pass (``NATIVE``) are functions of the extension module ``_fqcall``
-(csrc/fq_python.cpp) with the signatures of their C counterparts, minus the types, plus ``stream=None, check=True``; they are
-loaded when the first of them is asked for, and call the library that ``lib()`` has loaded.  The others call through ctypes.
+All entry points have the parameters of their C counterparts, plus ``stream=None, check=True`` where they launch.  Those of a model's
+forward pass (``NATIVE``) are functions of the extension module ``_fqcall`` (csrc/fq_python.cpp), which calls the library that
+``lib()`` has loaded.  The module is compiled for one interpreter; under another one, or where it has not been built, the same functions
+call through ctypes like the rest (2.6 us of host time for a product's arguments instead of 0.5).
 """
 from __future__ import annotations
 
@@ -30,11 +31,21 @@ EXPORTS = (
     "fq_status_string", "fq_last_hip_error", "fq_abi_version", "fq_set_tuning",
 )
 
-NATIVE = (
-    "flatquant_transform_quant", "flatquant_transform_mxfp4", "flatquant_transform_mxfp4_tiled", "flatquant_weight_transform_quant",
-    "flatquant_w4a4_gemm", "flatquant_mxfp4_gemm", "flatquant_kv_transform_quant", "flatquant_kv_transform_quant_bits",
-    "flatquant_head_transform",
-)
+# parameters of the launching entry points without the stream, and their C types: pointer, int, long (int64_t), float
+_ACT = ("P1 P2 clip clip_mode T n1 n2 x_stride out_codes out_scales", "ppppiliilpp")
+_GEMM = ("x_codes x_scales w_codes w_scales T m n out out_stride", "ppppliipl")
+_NATIVE_PARAMS = {
+    "flatquant_transform_quant": ("x " + _ACT[0], _ACT[1]),
+    "flatquant_transform_mxfp4": ("x " + _ACT[0], _ACT[1]),
+    "flatquant_transform_mxfp4_tiled": ("x " + _ACT[0], _ACT[1]),
+    "flatquant_weight_transform_quant": ("w A1 A2 clip clip_mode m n1 n2 w_stride out_codes out_scales", _ACT[1]),
+    "flatquant_w4a4_gemm": _GEMM,
+    "flatquant_mxfp4_gemm": _GEMM,
+    "flatquant_kv_transform_quant": ("kv P Hp clip T H D out_codes out_scales out_zeros", "ppifliippp"),
+    "flatquant_kv_transform_quant_bits": ("kv P Hp clip bits T H D out_codes out_scales out_zeros", "ppifiliippp"),
+    "flatquant_head_transform": ("x P Hp T H D out", "ppiliip"),
+}
+NATIVE = tuple(_NATIVE_PARAMS)
 
 _lib = None
 _fqcall = None
@@ -56,32 +67,17 @@ def lib() -> ctypes.CDLL:
                 "(there is no CPU fallback for the FlatQuant kernels)")
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_float
-        L.flatquant_transform_quant.argtypes = [vp, vp, vp, vp, i32, i64, i32, i32, i64, vp, vp, vp]
-        L.flatquant_transform_quant.restype = i32
-        L.flatquant_transform_mxfp4.argtypes = L.flatquant_transform_quant.argtypes
-        L.flatquant_transform_mxfp4.restype = i32
-        L.flatquant_transform_mxfp4_tiled.argtypes = L.flatquant_transform_quant.argtypes
-        L.flatquant_transform_mxfp4_tiled.restype = i32
+        for name, (params, types) in _NATIVE_PARAMS.items():
+            getattr(L, name).argtypes = [{"p": vp, "i": i32, "l": i64, "f": f32}[t] for t in types] + [vp]
+            getattr(L, name).restype = i32
         L.fq_mxfp4_tiled_scale_bytes.argtypes = [i64, i64]
         L.fq_mxfp4_tiled_scale_bytes.restype = i64
-        L.flatquant_mxfp4_gemm.argtypes = [vp, vp, vp, vp, i64, i32, i32, vp, i64, vp]
-        L.flatquant_mxfp4_gemm.restype = i32
         L.flatquant_dequant_mxfp4.argtypes = [vp, vp, i64, i32, vp, vp]
         L.flatquant_dequant_mxfp4.restype = i32
-        L.flatquant_kv_transform_quant.argtypes = [vp, vp, i32, f32, i64, i32, i32, vp, vp, vp, vp]
-        L.flatquant_kv_transform_quant.restype = i32
         L.flatquant_dequant.argtypes = [vp, vp, vp, i64, i32, vp, vp]
         L.flatquant_dequant.restype = i32
-        L.flatquant_kv_transform_quant_bits.argtypes = [vp, vp, i32, f32, i32, i64, i32, i32, vp, vp, vp, vp]
-        L.flatquant_kv_transform_quant_bits.restype = i32
         L.flatquant_dequant_bits.argtypes = [vp, vp, vp, i64, i32, i32, vp, vp]
         L.flatquant_dequant_bits.restype = i32
-        L.flatquant_weight_transform_quant.argtypes = L.flatquant_transform_quant.argtypes
-        L.flatquant_weight_transform_quant.restype = i32
-        L.flatquant_w4a4_gemm.argtypes = [vp, vp, vp, vp, i64, i32, i32, vp, i64, vp]
-        L.flatquant_w4a4_gemm.restype = i32
-        L.flatquant_head_transform.argtypes = [vp, vp, i32, i64, i32, i32, vp, vp]
-        L.flatquant_head_transform.restype = i32
         L.fq_inverse_transpose.argtypes = [vp, i32, vp, ctypes.POINTER(ctypes.c_double)]
         L.fq_inverse_transpose.restype = i32
         L.flatquant_stream_probe.argtypes = [vp, i64, i32, i64, vp, vp]
@@ -124,21 +120,28 @@ def _stream(stream) -> Optional[int]:
     return int(stream.cuda_stream) or None      # torch.cuda.Stream
 
 
-def __getattr__(name):
-    """The native entry points, on first use (a module attribute from then on)."""
-    global _fqcall, _lib
-    if name not in NATIVE:
-        raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
-    try:
-        _fqcall = importlib.import_module(__package__ + "._fqcall")
-    except ImportError as e:
-        raise FileNotFoundError(f"{os.path.join(_PKG, '_fqcall.so')} cannot be loaded: build it with "
-                                "`python -m paper_2410_09426_amd.build`") from e
+def _ctypes_call(name: str):
+    """A launching entry point through ctypes, written out from its parameters."""
+    params, types = _NATIVE_PARAMS[name]
+    convert = {"p": "_ptr", "i": "int", "l": "int", "f": "float"}
+    values = ", ".join(f"{convert[t]}({p})" for p, t in zip(params.split(), types))
+    scope = {}
+    exec(f"def {name}({', '.join(params.split())}, stream=None, check=True):\n"
+         "    'See include/flatquant.h; returns the status, raises FlatQuantError if check.'\n"
+         f"    st = lib().{name}({values}, _stream(stream))\n"
+         "    if check and st != FQ_OK:\n"
+         f"        raise FlatQuantError(st, {name!r})\n"
+         "    return st\n", globals(), scope)
+    return scope[name]
+
+
+try:
+    _fqcall = importlib.import_module(__package__ + "._fqcall")
+except ModuleNotFoundError:                     # not built, or built for another interpreter
+    globals().update((n, _ctypes_call(n)) for n in NATIVE)
+else:
     _fqcall.connect(lib, FlatQuantError)
-    _lib = None                                 # bound when it is loaded (again)
-    lib()
     globals().update((n, getattr(_fqcall, n)) for n in NATIVE)
-    return globals()[name]
 
 
 def status_string(status: int) -> str:

@@ -9,7 +9,8 @@ import sysconfig
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libflatquant.so")
-CALLS = os.path.join(PKG, "_fqcall.so")     # CPython calls of the library's entry points (host code that links nothing)
+# CPython calls of the library's entry points: host code that links nothing, for the interpreter that builds it (its name says which)
+CALLS = os.path.join(PKG, "_fqcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["fq_api.hip", "fq_transform_quant.hip", "fq_tq_fast.hip", "fq_tq_wave.hip", "fq_kv.hip", "fq_dequant.hip", "fq_probe.hip", "fq_gemm.hip", "fq_gemm_mx.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          # keep hipcc from forming packed-fp32 VALU ops from scalar float code
@@ -58,6 +59,9 @@ def build(verbose: bool = True, extra_flags=()) -> str:
         if verbose and out.strip():
             print(out)
     link([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], verbose)
+    untagged = os.path.join(PKG, "_fqcall.so")   # of an earlier build: any interpreter would take it
+    if os.path.exists(untagged):
+        os.remove(untagged)
     link([hipcc(), "-x", "c++", "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-no-hip-rt", "-I" + sysconfig.get_paths()["include"],
           os.path.join(CSRC, "fq_python.cpp"), "-o", CALLS], verbose)
     return LIB

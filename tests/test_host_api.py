@@ -331,12 +331,15 @@ _DIMS = {"T": 0, "m": 0, "n": 256, "n1": 16, "n2": 16, "x_stride": 256, "w_strid
          "clip_mode": 0}
 
 
+@pytest.mark.parametrize("through", ["extension", "ctypes"])
 @pytest.mark.parametrize("name", fq.NATIVE)
-def test_native_calls_marshal_like_their_signatures(name):
+def test_native_calls_marshal_like_their_signatures(name, through):
     """Every launching entry point, without a launch (zero rows, or an argument the library refuses): positional and named
-    arguments, addresses, buffers, None and numpy numbers reach the C function in their places, statuses and errors come back."""
+    arguments, addresses, buffers, None and numpy numbers reach the C function in their places, statuses and errors come back.
+    Through the extension and, as under an interpreter that it was not built for, through ctypes."""
     import inspect
-    fn = getattr(fq, name)
+    fn = getattr(fq, name) if through == "extension" else fq._ctypes_call(name)
+    assert type(getattr(fq, name)) is type(len), "the extension is not built"
     params = list(inspect.signature(fn).parameters.values())
     names = [p.name for p in params]
     assert names[-2:] == ["stream", "check"] and params[-2].default is None and params[-1].default is True
@@ -387,7 +390,6 @@ def test_native_calls_and_ctypes_use_one_library(tmp_path):
 def test_native_calls_reach_the_c_function_of_their_name():
     """Every launching entry point with a recording function in the place of each C function: the call arrives at the one of its name,
     every argument in its place and in its C type."""
-    fq.flatquant_head_transform                            # loads the extension
     calls = importlib.import_module("paper_2410_09426_amd._fqcall")
     seen, keep, addresses = [], [], {}
     for name in fq.NATIVE:
@@ -405,3 +407,39 @@ def test_native_calls_reach_the_c_function_of_their_name():
             assert seen.pop() == (name, *args, 2 ** 44) and not seen
     finally:
         calls.bind(real)
+
+
+@pytest.mark.parametrize("built", ["nothing", "the extension alone", "without the extension", "for another interpreter", "a broken extension"])
+def test_module_surface_whatever_is_built(tmp_path, built):
+    """The package copied without its library, without its extension, without both, with one whose name says another interpreter, and with one that is no
+    library: every name is in the module, tests for it answer, and calls do what is possible."""
+    import shutil
+    import subprocess
+    import sys
+    pkg = tmp_path / "paper_2410_09426_amd"
+    src = os.path.dirname(fq.LIB_PATH)
+    pkg.mkdir()
+    for f in ("__init__.py", "binding.py", "synth.py"):
+        shutil.copy(os.path.join(src, f), pkg / f)
+    if built == "the extension alone":
+        ext = fq._fqcall.__file__
+        shutil.copy(ext, pkg / os.path.basename(ext))
+    elif built != "nothing":
+        shutil.copy(fq.LIB_PATH, pkg / "libflatquant.so")
+    if built == "for another interpreter":
+        (pkg / "_fqcall.cpython-399-x86_64-linux-gnu.so").write_bytes(b"not for this one")
+    if built == "a broken extension":
+        import sysconfig
+        (pkg / ("_fqcall" + sysconfig.get_config_var("EXT_SUFFIX"))).write_bytes(b"no library")
+    code = ("from paper_2410_09426_amd import binding as fq\n"
+            "from paper_2410_09426_amd.binding import *\n"
+            "names = [n for n in fq.EXPORTS if n.startswith('flatquant_')]\n"
+            "assert all(n in vars(fq) and n in dir(fq) and hasattr(fq, n) and n in globals() for n in names)\n"
+            "try:\n    print('status', flatquant_w4a4_gemm(4096, 8192, 12288, 16384, 0, 8, 256, 20480, 8))\n"
+            "except FileNotFoundError as e:\n    print('missing', 'libflatquant.so is missing: build it' in str(e))\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=tmp_path)
+    if built == "a broken extension":                      # what is wrong with it is what is reported
+        assert r.returncode != 0 and "ImportError" in r.stderr and "_fqcall" in r.stderr and "build it" not in r.stderr
+    else:
+        assert r.returncode == 0, r.stderr[-2000:]
+        assert r.stdout.split() == (["missing", "True"] if built in ("nothing", "the extension alone") else ["status", "0"])
