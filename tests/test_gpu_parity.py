@@ -1205,9 +1205,11 @@ def test_w4a4_gemm_tiles_are_exact(tuning, form, T, m, n):
 
 
 @pytest.mark.parametrize("form,T,m,n,pad", [(2, 4400, 4500, 512, 0), (2, 4353, 4105, 768, 7), (2, 4353, 4105, 1024, 1), (2, 4353, 4105, 1280, 0),
-                                            (0, 4353, 4105, 768, 7), (1, 4353, 4105, 768, 7), (None, 8000, 8100, 2304, 4)])
+                                            (0, 4353, 4105, 768, 7), (1, 4353, 4105, 768, 7), (None, 8000, 8100, 2304, 4),
+                                            (1, 4353, 3105, 1536, 2), (1, 5000, 3201, 256, 7), (1, 5000, 3105, 1024, 1),
+                                            (4, 4353, 4105, 768, 7), (4, 2900, 3000, 1280, 1), (4, 2900, 3001, 256, 1), (4, 5000, 4096, 512, 8)])
 def test_w4a4_gemm_tiles_follow_each_other(tuning, form, T, m, n, pad):
-    """More 256 x 256 tiles than workgroups are resident (306 and more for 256) and at least two K iterations: the loads of a
+    """More tiles of a form than workgroups are resident (306 and more 256 x 256 tiles for 256), with one K iteration and more: the loads of a
     tile's last iteration belong to the next tile, its output leaves through a stage that then takes loads again, and the
     row sums start over.  Ragged on both sides; the output leaves in 16-byte pieces (row strides 4112 and 8104), dwords
     (4500 and 4106) and halves (4105); the last case goes through the library's own choice of form.
@@ -1250,12 +1252,14 @@ def test_w4a4_gemm_160_token_and_split_k_tiles(tuning, form, T, m, n):
         assert torch.equal(out, want)
 
 
+@pytest.mark.parametrize("form", [2, 1, 0, 4])
 @pytest.mark.parametrize("low", [-8, 4, 7])
-def test_w4a4_gemm_fp6_longest_rows(tuning, low):
-    """The largest n: with codes of 7 throughout the offset sums reach 225 n = 14.7e6, just below 2^24, and are still exact."""
+def test_w4a4_gemm_fp6_longest_rows(tuning, low, form):
+    """The largest n: with codes of 7 throughout the offset sums of the FP6 forms reach 225 n = 14.7e6, just below 2^24, and are still exact,
+    in one part of K or in two that meet in LDS; the int8 forms' sums, of products that carry a factor 256, reach 2^29.6."""
     T, m, n = 70, 130, 65536
     tuning("FLATQUANT_GEMM_TILED", 1)
-    tuning("FLATQUANT_GEMM_WIDE", 2)
+    tuning("FLATQUANT_GEMM_WIDE", form)
     g = torch.Generator(device="cuda")
     g.manual_seed(low + 8)
     q = [torch.randint(low, 8, (r, n), generator=g, device="cuda", dtype=torch.int8) for r in (T, m)]
