@@ -17,7 +17,7 @@
  *     (fq_last_hip_error), per-device launch facts cached on first use (number
  *     of compute units, workgroups per compute unit of each kernel), and the
  *     process-wide tuning overrides of fq_set_tuning (launch-shape choices for
- *     measurements and tests; they never change results).  Nothing else:
+ *     measurements and tests; results stay what the entry point states).  Nothing else:
  *     calls are independent and may come from several threads at once.
  *   - Two entry points are measurement aids and not part of the method:
  *     flatquant_stream_probe (the activation kernel's memory traffic without
@@ -54,6 +54,8 @@ enum {
  *     s_t = fp16( clip_t * max_c |Y_t[c]| / 7 )            (Sec. 3.1 "Learnable Clipping Thresholds",
  *     q_t[c] = clamp( round_half_even( Y_t[c] / s_t ), -8, 7 )   Sec. 4.1 "Quantization": per-token symmetric)
  * A row whose step rounds to zero gets step +0 and all-zero codes.
+ * Y and the quotient are computed in fp32: a value within 1e-5 of a tie may get the code on its other side, and where n2 is a multiple of
+ * 32 an exact tie may get the larger code instead of the even one.  A row's codes do not depend on T.
  *
  *   x          fp16 [T, n], row t starts at x + t*x_stride halves; x_stride >= n.
  *              Alignment: 4 bytes (base and row pitch, i.e. x_stride even).
