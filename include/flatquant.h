@@ -283,9 +283,9 @@ int fq_abi_version(void);
  * general kernels, MXFP4 too, FQ_LAUNCH_FAILED where it does not exist),
  * FLATQUANT_GEMM_TILED (1: tiled product for any T), FLATQUANT_GEMM_WIDE (0 / 1 / 2: 128 x 128, 256 x 128 or 256 x 256
  * tiles, the last two on FP6 MFMA for W4A4; W4A4 only, 4: 160 x 128; any other value leaves the choice to the library),
- * FLATQUANT_GEMM_ROWS (16 / 32 output channels per workgroup), FLATQUANT_GEMM_WAVES (4 / 8 / 16) and
- * FLATQUANT_GEMM_DEPTH (1..8 line slots per wave) of the few-token products, FLATQUANT_GEMM_RING_MAX_T (token count up to
- * which the few-token kernel is used), FLATQUANT_KV_FEW (1 / 0: the KV kernel for few groups, or the one for many),
+ * FLATQUANT_GEMM_ROWS (16 / 32 / 48 / 64 output channels per workgroup), FLATQUANT_GEMM_TOKENS (8 / 16 / 32 / 64 tokens per
+ * workgroup), FLATQUANT_GEMM_WAVES (4 / 8 / 16) and FLATQUANT_GEMM_DEPTH (1..8 line slots per wave) of the few-token products,
+ * FLATQUANT_GEMM_RING_MAX_T (token count up to which the few-token kernel is used), FLATQUANT_KV_FEW (1 / 0: the KV kernel for few groups, or the one for many),
  * FLATQUANT_KV_FOLD_HEADS (0: a shared P_h is applied head by head like separate ones).  enable != 0 sets the override to `value`, enable == 0 removes it.  Each override starts from the environment variable of the same name, read once per process.
  * Process-wide; affects launches issued after the call returns.  Unknown names return FQ_INVALID_ARG.
  */

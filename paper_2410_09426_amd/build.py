@@ -28,7 +28,8 @@ def hipcc() -> str:
 # the compiler quiets every operand first (one extra instruction per element).  Inputs are finite by contract.
 # The wave-per-token kernel takes plain arguments in the order it needs them; the first 14 dwords are delivered in
 # registers at wave start (kernel-argument preloading), which takes a scalar-memory round trip off the front of every wave.
-FILE_FLAGS = {"fq_kv.hip": ["-fno-honor-nans"], "fq_tq_wave.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"]}
+PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
+FILE_FLAGS = {"fq_kv.hip": ["-fno-honor-nans"], "fq_tq_wave.hip": PRELOAD, "fq_gemm.hip": PRELOAD, "fq_gemm_mx.hip": PRELOAD}
 
 
 def link(cmd, verbose: bool) -> None:

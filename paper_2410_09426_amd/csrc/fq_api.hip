@@ -47,7 +47,7 @@ hipError_t kernel_occupancy(const void* fn, int threads, int lds, OccCache& cach
 
 KnobState g_knobs[(int)Knob::COUNT];
 namespace {
-const char* const kKnobNames[] = {"FLATQUANT_MODE", "FLATQUANT_WG_PER_CU", "FLATQUANT_FORCE_GENERIC", "FLATQUANT_KV_WG_PER_CU", "FLATQUANT_GEMM_TILED", "FLATQUANT_GEMM_WIDE", "FLATQUANT_GEMM_DEPTH", "FLATQUANT_GEMM_WAVES", "FLATQUANT_GEMM_ROWS", "FLATQUANT_GEMM_RING_MAX_T", "FLATQUANT_KV_FOLD_HEADS", "FLATQUANT_KV_FEW", "FLATQUANT_WAVE_TPW", "FLATQUANT_PROBE_SHAPE"};
+const char* const kKnobNames[] = {"FLATQUANT_MODE", "FLATQUANT_WG_PER_CU", "FLATQUANT_FORCE_GENERIC", "FLATQUANT_KV_WG_PER_CU", "FLATQUANT_GEMM_TILED", "FLATQUANT_GEMM_WIDE", "FLATQUANT_GEMM_DEPTH", "FLATQUANT_GEMM_WAVES", "FLATQUANT_GEMM_ROWS", "FLATQUANT_GEMM_TOKENS", "FLATQUANT_GEMM_RING_MAX_T", "FLATQUANT_KV_FOLD_HEADS", "FLATQUANT_KV_FEW", "FLATQUANT_WAVE_TPW", "FLATQUANT_PROBE_SHAPE"};
 static_assert(sizeof(kKnobNames) / sizeof(kKnobNames[0]) == (size_t)Knob::COUNT, "a name for every override");
 }  // namespace
 

@@ -15,6 +15,7 @@
 // The weights are the MFMA's first operand, so that a lane ends up with runs of 4 consecutive output channels of one token.
 // Many tokens take the tiled kernel; launches whose 128 x 128 tiles would reach at most half of the CUs (decode, short prefill
 // chunks) take the few-token kernel further down.
+#include <cmath>
 #include <type_traits>
 
 #include "fq_internal.h"
@@ -541,22 +542,27 @@ __global__ __launch_bounds__(64 * L::NW) __attribute__((amdgpu_waves_per_eu(L::W
     wait_vm_pending<0>();                    // nothing may still be on its way into LDS when the workgroup ends
 }
 
-// ---- few tokens (decode, short prefill chunks): the weights are read once (per tile of 64 tokens), and what bounds the kernel is how fast the CUs take
-// them in.  A workgroup owns 32 (or 16) output channels for all tokens.  Every operand byte goes from global memory
+// ---- few tokens (decode, short prefill chunks): the weights are read once per tile of up to 64 tokens, and what bounds the kernel is
+// memory (the weights at 5 TB/s behind 2.4 us of launch and first latency) or how fast the CUs take in their rows (45 KB per us each).  A
+// workgroup owns 16 to 64 output channels for 8 to 64 tokens, whatever spreads the rows best (ring_shape).  Every operand byte goes from global memory
 // straight into LDS, a whole cache line per row at a time: a wave owns every nwv-th 128-byte line of K (256 codes) of
 // the workgroup's weight rows and of the token rows, with a ring of `depth` line slots of its own in LDS.  One
 // global-to-LDS instruction moves 8 whole rows; the wave waits only for its own oldest slot (no barrier in the loop),
 // multiplies it and requests the line `depth` steps ahead into the same slot.  The slots use the swizzle of the tiled
 // kernel (slot chunk j of row r holds the row's chunk j ^ ((r >> 1) & 7)).  The partial sums of the waves are added
-// through LDS at the end.  (Feeding the MFMA from registers instead, 32 bytes of 32 rows per load, costs four
+// through LDS at the end.  (Arguments are plain and in the order they are needed: they arrive in registers at wave start.  One
+// token, 4096 x 4096: MXFP4 4.25 -> 4.02 us, 23 x 11008 x 4096 7.7 -> 7.4.  Touching the later lines at the start, to have them in L2
+// in time, is slower: 8 x 4096 x 11008 7.4 -> 9.0 us, as is a deeper ring, 8.4.  Feeding the MFMA from registers instead, 32 bytes of 32 rows per load, costs four
 // instructions and tag look-ups per cache line and holds far less in flight: 1.5 to 3 times slower.)
-// ROWS = 16: the workgroup owns 16 output channels only (twice as many workgroups, for layers with too few channels
-// to give every CU one of 32); the MFMA's upper 16 rows repeat the lower ones and are dropped.
-template <int NTD, int ROWS>   // token rows in groups of 8 (one load instruction each): 1, 2, 4, 8 for T <= 8, 16, 32, 64
-__global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void w4a4_skinny_kernel(GemmDev p, int depth) {
-    static_assert(ROWS == 16 || ROWS == 32, "weight rows per workgroup");
+// NTD: token rows in groups of 8 (one load instruction each): 1, 2, 4, 8 for tiles of 8, 16, 32, 64 tokens.  ROWS output channels;
+// where the last MFMA tile has 16 of them, its upper 16 rows repeat the lower ones and are dropped.
+template <int NTD, int ROWS>
+__global__ __launch_bounds__(ring_max_waves(NTD, ROWS) * 64) void w4a4_skinny_kernel(const uint8_t* wc, const uint8_t* xc, const _Float16* ws, const _Float16* xs, _Float16* out,
+                                                                             int n, int m, int T, RingConfig cfg, int64_t out_stride) {
+    static_assert(ROWS == 16 || ROWS == 32 || ROWS == 48 || ROWS == 64, "weight rows per workgroup");
     constexpr int NWI = ROWS / 8;                        // load instructions per line of the weight rows
     constexpr int NG = ROWS / 8;                         // groups of 8 output channels
+    constexpr int NCT = (ROWS + 31) / 32;                // MFMA channel tiles of 32
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int NTT = NTD > 4 ? NTD / 4 : 1;           // MFMA token tiles of 32
     constexpr int XROWS = 8 * NTD;
@@ -566,19 +572,22 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void w4a4_skinny_kernel(Gemm
     const int tid = threadIdx.x;
     const int l = tid & 63, c = l & 31, h = l >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int o0 = blockIdx.x * ROWS;
-    const int64_t t0 = (int64_t)blockIdx.y * XROWS;      // more than one token tile: launches past 64 tokens (tiles of 64)
-    const uint32_t kbytes = (uint32_t)(p.n / 2);
-    const int nl = p.n / 256;                            // lines per row
-    const int nwv = blockDim.x >> 6;                     // waves: 4, 8 or 16
-    const int ns = (nl - w + nwv - 1) / nwv;             // this wave's steps: lines w, w + nwv, ...
+    const RingTile wg = ring_tile(blockIdx.x, (m + ROWS - 1) / ROWS, cfg.token_tiles(), T / 2 > m);
+    if (wg.channels < 0) return;
+    const int o0 = wg.channels * ROWS;
+    const int t0 = wg.tokens * XROWS;
+    const uint32_t kbytes = (uint32_t)(n / 2);
+    const int nl = n / 256;                              // lines per row
+    const int nwv = cfg.waves(), depth = cfg.depth();
+    const int ns = (nl - w + nwv - 1) >> cfg.log2_waves();   // this wave's steps: lines w, w + nwv, ...
     unsigned char* ring = smem + w * depth * SLOT;
 
     // Row 8 k + l / 8, the chunk that belongs into slot l % 8 of it: one offset per k for both operands, from a scalar base each.
     // Rows past the end are out of the buffers' range and read as zeros.  (With 64-bit addresses and clamped rows the first
     // request left after some 500 instructions, 1 us.)
-    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.wc) + (int64_t)o0 * kbytes, 0, (p.m - o0 < ROWS ? p.m - o0 : ROWS) * (int)kbytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.xc) + t0 * kbytes, 0, (int)(p.T - t0 < XROWS ? p.T - t0 : XROWS) * (int)kbytes, 0x00020000);
+    const int mrows = m - o0 < ROWS ? m - o0 : ROWS, trows = T - t0 < XROWS ? T - t0 : XROWS;
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(wc) + (int64_t)o0 * kbytes, 0, mrows * (int)kbytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(xc) + (int64_t)t0 * kbytes, 0, trows * (int)kbytes, 0x00020000);
     constexpr int NV = NWI > NTD ? NWI : NTD;
     uint32_t voff[NV];
     {
@@ -595,32 +604,39 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void w4a4_skinny_kernel(Gemm
 #pragma unroll
         for (int k = 0; k < NTD; ++k) __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (lptr)(base + XOFF + k * 1024), 16, (int)voff[k], off, 0, 0);
     };
-    // The epilogue's element e = tid + k blockDim is 4 output channels of one token: their steps are requested now, so
-    // that the kernel's tail does not wait for them (at least 256 threads: k < NK).
+    const int npre = ns < depth ? ns : depth;
+#pragma unroll 1
+    for (int s = 0; s < npre; ++s) issue(s, s);
+    // The epilogue's element e = tid + k blockDim is 4 output channels of one token: their steps are requested now, behind the
+    // first lines, so that the kernel's tail does not wait for them (at least 256 threads: k < NK; elements past the last one
+    // are out of the tokens' range).
     constexpr int NE = NTT * NG * 64;
     constexpr int NK = (NE + 255) / 256;
-    unsigned esx[NK] = {}, esw[NK][4] = {};              // raw fp16 bits, converted in the epilogue: nothing waits for them here
-    const __amdgpu_buffer_rsrc_t sxbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(p.xs) + t0, 0, 2 * (int)(p.T - t0 < 32 * NTT ? p.T - t0 : 32 * NTT), 0x00020000);
-    const __amdgpu_buffer_rsrc_t swbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(p.ws) + o0, 0, 2 * (p.m - o0 < ROWS ? p.m - o0 : ROWS), 0x00020000);
+    unsigned esx[NK], esw[NK][4];                        // raw fp16 bits, converted in the epilogue: nothing waits for them here
+    const __amdgpu_buffer_rsrc_t sxbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(xs) + t0, 0, 2 * (T - t0 < 32 * NTT ? T - t0 : 32 * NTT), 0x00020000);
+    const __amdgpu_buffer_rsrc_t swbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(ws) + o0, 0, 2 * mrows, 0x00020000);
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-        const int e = tid + k * (int)blockDim.x;
+        const int e = tid + (k << (6 + cfg.log2_waves()));
         const int el = e & 63, g = (e >> 6) % NG, i = (e >> 6) / NG;
-        if (e < NE) {
-            esx[k] = __builtin_amdgcn_raw_buffer_load_b16(sxbuf, 2 * (32 * i + (el & 31)), 0, 0);
+        esx[k] = __builtin_amdgcn_raw_buffer_load_b16(sxbuf, 2 * (32 * i + (el & 31)), 0, 0);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) esw[k][x] = __builtin_amdgcn_raw_buffer_load_b16(swbuf, 2 * (8 * g + 4 * (el >> 5) + x), 0, 0);
-        }
+        for (int x = 0; x < 4; ++x) esw[k][x] = __builtin_amdgcn_raw_buffer_load_b16(swbuf, 2 * (8 * g + 4 * (el >> 5) + x), 0, 0);
     }
-    const int npre = ns < depth ? ns : depth;
-    for (int s = 0; s < npre; ++s) issue(s, s);
-    i32x16 acc[NTT];
+    i32x16 acc[NTT][NCT];
 #pragma unroll
     for (int i = 0; i < NTT; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0;
-    const int woff = (c & (ROWS - 1)) * 128;
-    const int whs = h ^ (((c & (ROWS - 1)) >> 1) & 7);
+        for (int j = 0; j < NCT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+    int woff[NCT], whs[NCT];
+#pragma unroll
+    for (int j = 0; j < NCT; ++j) {
+        const int row = 32 * j + (c & (ROWS - 32 * j >= 32 ? 31 : 15));
+        woff[j] = row * 128;
+        whs[j] = h ^ ((row >> 1) & 7);
+    }
     int xoff[NTT], xhs[NTT];
 #pragma unroll
     for (int i = 0; i < NTT; ++i) {
@@ -631,12 +647,13 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void w4a4_skinny_kernel(Gemm
     int slot = 0;
     for (int s = 0; s < ns; ++s) {
         const int left = ns - 1 - s;
-        wait_ring_step<NI>(left < depth - 1 ? left : depth - 1);
+        wait_ring_step<NI>(left < depth - 1 ? left : depth - 1);   // (the first time the quantization steps as well: they are younger, and not counted)
         const unsigned char* base = ring + slot * SLOT;
-        u32x4 wv[4], xv[4][NTT];
+        u32x4 wv[4][NCT], xv[4][NTT];
 #pragma unroll
         for (int kp = 0; kp < 4; ++kp) {
-            wv[kp] = *reinterpret_cast<const u32x4*>(base + woff + 16 * ((2 * kp) ^ whs));
+#pragma unroll
+            for (int j = 0; j < NCT; ++j) wv[kp][j] = *reinterpret_cast<const u32x4*>(base + woff[j] + 16 * ((2 * kp) ^ whs[j]));
 #pragma unroll
             for (int i = 0; i < NTT; ++i) xv[kp][i] = *reinterpret_cast<const u32x4*>(base + xoff[i] + 16 * ((2 * kp) ^ xhs[i]));
         }
@@ -644,14 +661,17 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void w4a4_skinny_kernel(Gemm
         if (s + depth < ns) issue(s + depth, slot);
 #pragma unroll
         for (int kp = 0; kp < 4; ++kp) {
-            i32x4 ws0, ws1;
-            widen(wv[kp], ws0, ws1);
+            i32x4 ws0[NCT], ws1[NCT];
+#pragma unroll
+            for (int j = 0; j < NCT; ++j) widen(wv[kp][j], ws0[j], ws1[j]);
 #pragma unroll
             for (int i = 0; i < NTT; ++i) {
                 i32x4 xs0, xs1;
                 widen(xv[kp][i], xs0, xs1);
-                acc[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ws0, xs0, acc[i], 0, 0, 0);
-                acc[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ws1, xs1, acc[i], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < NCT; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ws0[j], xs0, acc[i][j], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < NCT; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ws1[j], xs1, acc[i][j], 0, 0, 0);
             }
         }
         slot = (slot + 1 == depth) ? 0 : slot + 1;
@@ -663,71 +683,142 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void w4a4_skinny_kernel(Gemm
     for (int i = 0; i < NTT; ++i)
 #pragma unroll
         for (int g = 0; g < NG; ++g)
-            part[((w * NTT + i) * NG + g) * 64 + l] = i32x4{acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]};
+            part[((w * NTT + i) * NG + g) * 64 + l] = i32x4{acc[i][g / 4][4 * (g % 4)], acc[i][g / 4][4 * (g % 4) + 1], acc[i][g / 4][4 * (g % 4) + 2], acc[i][g / 4][4 * (g % 4) + 3]};
     __syncthreads();
     typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-    const bool wide = ((reinterpret_cast<uintptr_t>(p.out) & 7) == 0) && (p.out_stride % 4 == 0);
+    const bool wide = ((reinterpret_cast<uintptr_t>(out) & 7) == 0) && (out_stride % 4 == 0);
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-        const int e = tid + k * (int)blockDim.x;
+        const int e = tid + (k << (6 + cfg.log2_waves()));
         if (e >= NE) break;
         const int el = e & 63, g = (e >> 6) % NG, i = (e >> 6) / NG;
         i32x4 sum = part[e];
         for (int ww = 1; ww < nwv; ++ww) sum += part[ww * NE + e];
-        const int64_t t = t0 + 32 * i + (el & 31);
+        const int t = t0 + 32 * i + (el & 31);
         const int o = o0 + 8 * g + 4 * (el >> 5);
-        if (t < p.T && o < p.m) {
+        if (t < T && o < m) {
             // (the empty statement pins the conversions here: hoisted to the loads, they would stall the kernel's start)
             asm volatile("" : "+v"(esx[k]), "+v"(esw[k][0]), "+v"(esw[k][1]), "+v"(esw[k][2]), "+v"(esw[k][3]));
             const float sx = (float)__builtin_bit_cast(_Float16, (uint16_t)esx[k]);
             _Float16 v[4];
 #pragma unroll
             for (int x = 0; x < 4; ++x) v[x] = (_Float16)((float)(sum[x] >> 8) * sx * (float)__builtin_bit_cast(_Float16, (uint16_t)esw[k][x]));
-            _Float16* dst = p.out + t * p.out_stride + o;
-            if (wide && o + 4 <= p.m) {
+            _Float16* dst = out + t * out_stride + o;
+            if (wide && o + 4 <= m) {
                 *reinterpret_cast<half4*>(dst) = half4{v[0], v[1], v[2], v[3]};
             } else {
                 for (int x = 0; x < 4; ++x)
-                    if (o + x < p.m) dst[x] = v[x];
+                    if (o + x < m) dst[x] = v[x];
             }
         }
     }
 }
 
+// What a launch of the few-token kernels takes, for a workgroup of `tokens` x `rows`: a fixed part, the lines of 256 codes that a wave
+// works on one after the other, the operand rows that the fullest CU and that all CUs take in per line, the products of all CUs and
+// of one wave, the partial sums that meet in LDS, and the weights from memory.  Fits to about 500 launches per format of 1 <= T <= 4000,
+// 256 <= m <= 14336, 256 <= n <= 28672, 8 to 24 shapes each, with the weights in memory and in the last-level cache; what they choose is
+// 1.2 % slower than the best shape on average.  One shape per T and one rule on workgroups (64 tokens from 33 on; 32 channels, or
+// 16 while no CU has more than one workgroup of those) takes 13 % longer on average, 3 % less in 2 % of the launches (7 % in
+// one): INT4 64 x 4096 x 11008 12.0 us, here 9.6 in 32 x 32; 45 x 1408 x 12288 9.8 / 7.0 in 32 x 16; 45 x 8666 x 11008 20.0 / 16.5 in 64 x
+// 48; 230 x 7936 x 14336 44 / 33 in 64 x 64; MXFP4 42 x 1664 x 28672 20.6 / 13.3.
+// Waves and slots: 8 waves give every SIMD two to overlap where CUs have one workgroup; where they have more, small ones (4 waves)
+// that are all resident overlap each other.  A second slot per wave helps MXFP4 (T = 2, 1792 x 28672: 9.4 us, 12.6 with one), whose
+// steps are shorter; INT4 is faster without (53 x 2960 x 11008 8.1 / 7.6: memory does better with fewer lines asked for).
+struct RingForm {
+    int waves, depth;
+    double fixed, line, rows_fullest, rows_all, product, sums_fullest, sums_all, weights, product_wave;
+};
+static const RingForm kRingInt4[] = {{8, 1, 2.4295, 0.2834, 0.7443e-3, 0.0503e-3, 3.2499e-5, 4.7473e-4, 1.6524e-4, 0.0258e-6, 0.0639e-5},
+                                     {4, 1, 2.4459, 0.3433, 0.3771e-3, 0.1285e-3, 2.4934e-5, 3.0777e-4, 0.0010e-4, 0.0300e-6, 8.2138e-5}};
+static const RingForm kRingMx[] = {{8, 2, 2.5729, 0.0215, 1.0573e-3, 0.0366e-3, 2.0803e-5, 2.1883e-4, 2.3732e-4, 0.0607e-6, 0.0128e-5},
+                                   {4, 1, 2.8166, 0.1582, 0.5245e-3, 0.4159e-3, 0.2941e-5, 0.3131e-4, 0.0438e-4, 0.0330e-6, 13.6616e-5},
+                                   {4, 2, 2.2628, 0.1485, 0.7724e-3, 0.0967e-3, 2.4500e-5, 4.8268e-4, 0.7322e-4, 0.0376e-6, 0.2875e-5}};
+
+RingShape ring_shape(int64_t T, int m, int n, bool mx) {
+    const RingForm* forms = mx ? kRingMx : kRingInt4;
+    const int nforms = mx ? 3 : 2;
+    const double cu = cu_count(), nl = n / 256, weights = 0.5 * m * (double)n;
+    RingShape best{};
+    best.us = 1e300;
+    auto consider = [&](int tokens, int rows) {
+        const int64_t groups = ((m + rows - 1) / rows) * ((T + tokens - 1) / tokens);
+        const double all = groups / cu, fullest = std::ceil(all), sums = rows * (tokens < 32 ? 32 : tokens), lines = nl * (rows + tokens);
+        for (int f = 0; f < nforms; ++f) {
+            const RingForm& r = forms[f];
+            const double steps = std::ceil(nl / r.waves);
+            const double us = r.fixed + r.line * steps + lines * (r.rows_fullest * fullest + r.rows_all * all) + r.weights * weights +
+                              sums * (r.product * nl * all + r.product_wave * steps + r.sums_fullest * fullest + r.sums_all * all);
+            if (us < best.us) best = RingShape{tokens, rows, r.waves, r.depth, us};
+        }
+    };
+    const int want_tokens = tuned(Knob::GEMM_TOKENS, 0), want_rows = tuned(Knob::GEMM_ROWS, 0);
+    auto over_rows = [&](int tokens) {
+        if (want_rows) return consider(tokens, want_rows);
+        consider(tokens, 16);
+        consider(tokens, 32);
+        consider(tokens, 48);
+        consider(tokens, 64);
+    };
+    if (want_tokens) {
+        over_rows(want_tokens);
+    } else if (T <= 32) {
+        over_rows(T <= 8 ? 8 : T <= 16 ? 16 : 32);
+    } else {
+        over_rows(64);      // first: of two shapes of the same cost the one with fewer token tiles
+        over_rows(32);
+    }
+    best.waves = tuned(Knob::GEMM_WAVES, best.waves);
+    best.depth = tuned(Knob::GEMM_DEPTH, best.depth);
+    return best;
+}
+
+bool ring_launch(const RingShape& s, int64_t T, int m, int n, int slot, int loads, RingLaunch& r) {
+    const int64_t groups = (m + s.rows - 1) / s.rows, tiles = (T + s.tokens - 1) / s.tokens;
+    const int64_t grid = tiles == 1 ? groups : (groups * tiles + 7) / 8 * 8;   // whole rounds of the eight XCDs (see ring_tile)
+    if (grid > 0x7fffffff || tiles > RingConfig::kMaxTokenTiles) return false;
+    if (tiles > 1 && s.tokens < 32) return false;                         // the lanes past a smaller tile repeat its rows: only tokens past T are dropped
+    int nwv = s.waves, depth = s.depth;
+    if ((nwv != 4 && nwv != 8 && nwv != 16) || depth < 1 || depth > kRingMaxDepth) return false;
+    if (nwv > ring_max_waves(s.tokens / 8, s.rows)) nwv = ring_max_waves(s.tokens / 8, s.rows);
+    while (nwv > 4 && nwv * slot > kRingLdsMax) nwv >>= 1;
+    const int steps = (n / 256 + nwv - 1) / nwv;                          // of the wave with the most lines
+    if (depth > steps) depth = steps;
+    while (depth > 1 && (nwv * depth * slot > kRingLdsMax || (depth - 1) * loads > 63)) --depth;
+    r.grid = (unsigned)grid;
+    r.cfg = RingConfig(depth, nwv, (int)tiles);
+    r.lds = nwv * depth * slot;                                           // the partial sums (128 bytes per channel and 32 tokens, per wave) reuse the rings
+    return true;
+}
+
 template <int NTD, int ROWS>
-static hipError_t skinny_launch_rows(const GemmDev& d, hipStream_t stream, int token_tiles) {
-    if (token_tiles < 1 || (token_tiles > 1 && NTD < 4)) return hipErrorInvalidValue;   // tiles of 32 tokens or more keep their exponents inside one 128-row tile
+static hipError_t skinny_launch_shape(const GemmDev& d, hipStream_t stream, const RingShape& s) {
     static OccCache oc;
     int unused = 0;
-    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_skinny_kernel<NTD, ROWS>), NTD >= 8 ? 512 : 1024, kRingLdsMax, oc, unused);
+    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_skinny_kernel<NTD, ROWS>), 64 * ring_max_waves(NTD, ROWS), kRingLdsMax, oc, unused);
     if (e != hipSuccess) return e;
-    constexpr int SLOT = (ROWS + 8 * NTD) * 128, NI = ROWS / 8 + NTD;
-    const unsigned wgx = (unsigned)((d.m + ROWS - 1) / ROWS);
-    const int64_t wgs = (int64_t)wgx * token_tiles;
-    const int nl = d.n / 256;
-    // One workgroup per CU (or fewer): 8 waves, so that every SIMD has two to overlap, and two slots each.  More than
-    // one per CU: small workgroups (4 waves, one slot) that are all resident at once; what the second slot or the
-    // other four waves would hide, the neighbouring workgroup hides.  (Measured on 4096 / 11008-wide layers.)
-    const bool crowded = wgs > cu_count();
-    int nwv = tuned(Knob::GEMM_WAVES, crowded ? 4 : 8);
-    int depth = tuned(Knob::GEMM_DEPTH, crowded ? 1 : 2);
-    if ((nwv != 4 && nwv != 8 && nwv != 16) || depth < 1 || depth > kRingMaxDepth) return hipErrorInvalidValue;
-    if (NTD >= 8 && nwv > 8) nwv = 8;                                      // two token tiles of accumulators: compiled for at most 8 waves
-    while (nwv > 4 && nwv * SLOT > kRingLdsMax) nwv >>= 1;
-    const int steps = (nl + nwv - 1) / nwv;                               // of the wave with the most lines
-    if (depth > steps) depth = steps;
-    while (depth > 1 && (nwv * depth * SLOT > kRingLdsMax || (depth - 1) * NI > 63)) --depth;
-    const int bytes = nwv * depth * SLOT;                                 // the partial sums (at most 4 KB per wave and token tile) reuse the rings
-    return launch((w4a4_skinny_kernel<NTD, ROWS>), dim3(wgx, (unsigned)token_tiles), dim3(64 * nwv), bytes, stream, d, depth);
+    RingLaunch r;
+    if (!ring_launch(s, d.T, d.m, d.n, (ROWS + 8 * NTD) * 128, ROWS / 8 + NTD, r)) return hipErrorInvalidValue;
+    return launch((w4a4_skinny_kernel<NTD, ROWS>), dim3(r.grid), dim3(64 * r.cfg.waves()), r.lds, stream, d.wc, d.xc, d.ws, d.xs, d.out, d.n, d.m, (int)d.T, r.cfg, d.out_stride);
 }
-// 16 channels per workgroup while that still leaves at most one workgroup per CU (FLATQUANT_GEMM_ROWS forces 16 or 32):
-// the kernel is bound by what one CU takes in, so the channels go to as many CUs as there are.
 template <int NTD>
-static hipError_t skinny_launch(const GemmDev& d, hipStream_t stream, int token_tiles = 1) {
-    const int rows = tuned(Knob::GEMM_ROWS, (int64_t)((d.m + 15) / 16) * token_tiles <= cu_count() ? 16 : 32);
-    if (rows == 16) return skinny_launch_rows<NTD, 16>(d, stream, token_tiles);
-    if (rows == 32) return skinny_launch_rows<NTD, 32>(d, stream, token_tiles);
-    return hipErrorInvalidValue;
+static hipError_t skinny_launch_tokens(const GemmDev& d, hipStream_t stream, const RingShape& s) {
+    switch (s.rows) {
+        case 16: return skinny_launch_shape<NTD, 16>(d, stream, s);
+        case 32: return skinny_launch_shape<NTD, 32>(d, stream, s);
+        case 48: return skinny_launch_shape<NTD, 48>(d, stream, s);
+        case 64: return skinny_launch_shape<NTD, 64>(d, stream, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+static hipError_t skinny_launch(const GemmDev& d, hipStream_t stream, const RingShape& s) {
+    switch (s.tokens) {
+        case 8: return skinny_launch_tokens<1>(d, stream, s);
+        case 16: return skinny_launch_tokens<2>(d, stream, s);
+        case 32: return skinny_launch_tokens<4>(d, stream, s);
+        case 64: return skinny_launch_tokens<8>(d, stream, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <class L, bool ODD>
@@ -749,31 +840,14 @@ static hipError_t tiled_launch(const GemmDev& d, hipStream_t stream) {
     return odd ? tiled_launch_rows<L, true>(d, stream) : tiled_launch_rows<L, false>(d, stream);
 }
 
-hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
-    GemmDev d;
-    d.xc = a.x_codes; d.xs = a.x_scales; d.wc = a.w_codes; d.ws = a.w_scales; d.out = a.out;
-    d.T = a.T; d.out_stride = a.out_stride; d.m = a.m; d.n = a.n;
-    if (tuned(Knob::GEMM_TILED, 0) == 0) {
-        // decode and short prefill chunks: one pass over the weights, K split inside a workgroup (the ring kernel)
-        if (a.T <= 8) return skinny_launch<1>(d, stream);
-        if (a.T <= 16) return skinny_launch<2>(d, stream);
-        if (a.T <= 32) return skinny_launch<4>(d, stream);
-        if (a.T <= 64) return skinny_launch<8>(d, stream);
-        // More tokens: the ring kernel on tiles of 64 tokens, as long as the 128 x 128 tiles of the tiled kernel would
-        // reach at most half of the CUs (measured cross-over on 1024 .. 11008 channels; FLATQUANT_GEMM_RING_MAX_T
-        // replaces the rule by a token count).
-        const int64_t tiled_wgs = ((a.T + 127) / 128) * ((a.m + 127) / 128);
-        const int ring_max = tuned(Knob::GEMM_RING_MAX_T, -1);
-        if (ring_max >= 0 ? a.T <= ring_max : (2 * tiled_wgs <= cu_count() && a.T <= 4096))
-            return skinny_launch<8>(d, stream, (int)((a.T + 63) / 64));
-    }
-    // Tile form (FLATQUANT_GEMM_WIDE forces one): int8 with 128 x 128 tiles, two workgroups per CU (0) or 160 x 128, one (4); FP6 with
-    // 256 x 128 tiles, K in two parts (1), or 256 x 256 (2).  A launch takes rounds of one tile per slot, and a round a fixed part
-    // and one per K iteration that grows with the share of the slots in use (the clock falls).  The constants are a fit to 110
-    // launches of 100 <= T <= 16384, 512 <= m <= 14336, 256 <= n <= 28672 (rms 5 - 6 %); what they choose is 0.2 % slower than the best
-    // form on average, 10 % at worst.  (Forms 0 / 1 / 2 / 4, us: 2048 x 4096 x 1024 11.4 / 14.3 / 16.3 / 15.5, 2048 x 4096 x 4096 28.4 / 26.7 /
-    // 36.2 / 38.5, 2048 x 4096 x 8192 52.7 / 43.7 / 62.2 / 68.8, 777 x 5120 x 5120 28.8 / 27.5 / 40.8 / 23.3, 768 x 5120 x 5120 20.6 / 27.6 / 41.7 /
-    // 24.1, 3000 x 4096 x 4096 40.9 / 44.8 / 37.0 / 54.8, 6000 x 4096 x 11008 203 / 159 / 170 / 233.)
+// Tile form (FLATQUANT_GEMM_WIDE forces one): int8 with 128 x 128 tiles, two workgroups per CU (0) or 160 x 128, one (4); FP6 with
+// 256 x 128 tiles, K in two parts (1), or 256 x 256 (2).  A launch takes rounds of one tile per slot, and a round a fixed part
+// and one per K iteration that grows with the share of the slots in use (the clock falls).  The constants are a fit to 110
+// launches of 100 <= T <= 16384, 512 <= m <= 14336, 256 <= n <= 28672 (rms 5 - 6 %); what they choose is 0.2 % slower than the best
+// form on average, 10 % at worst.  (Forms 0 / 1 / 2 / 4, us: 2048 x 4096 x 1024 11.4 / 14.3 / 16.3 / 15.5, 2048 x 4096 x 4096 28.4 / 26.7 /
+// 36.2 / 38.5, 2048 x 4096 x 8192 52.7 / 43.7 / 62.2 / 68.8, 777 x 5120 x 5120 28.8 / 27.5 / 40.8 / 23.3, 768 x 5120 x 5120 20.6 / 27.6 / 41.7 /
+// 24.1, 3000 x 4096 x 4096 40.9 / 44.8 / 37.0 / 54.8, 6000 x 4096 x 11008 203 / 159 / 170 / 233.)
+static double w4a4_tiled_us(const GemmArgs& a, int* form) {
     const int64_t cu = cu_count();
     const double nk = a.n / 256;
     auto round_us = [&](int tok, int ch, int64_t slots, double& part) {   // full rounds; part: how full the last one is
@@ -792,9 +866,28 @@ hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
     if (x > 0) us[2] += 7.7 + (1.57 + 0.32 * x) * nk;
     us[4] = 1.5 + round_us(160, 128, cu, x) * (3.3 + 1.0 * nk);
     if (x > 0) us[4] += 3.3 + (0.86 + 0.14 * x) * nk;
-    int form = 0;
+    int best = 0;
     for (int f : {1, 2, 4})
-        if (us[f] < us[form]) form = f;
+        if (us[f] < us[best]) best = f;
+    if (form) *form = best;
+    return us[best];
+}
+
+hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
+    GemmDev d;
+    d.xc = a.x_codes; d.xs = a.x_scales; d.wc = a.w_codes; d.ws = a.w_scales; d.out = a.out;
+    d.T = a.T; d.out_stride = a.out_stride; d.m = a.m; d.n = a.n;
+    // Decode and short prefill chunks: one pass over the weights per tile of up to 64 tokens, K split inside a workgroup (the ring
+    // kernel), for as long as it is the cheaper one (FLATQUANT_GEMM_RING_MAX_T replaces the comparison by a token count).
+    const bool ring = tuned(Knob::GEMM_TILED, 0) == 0;
+    const int ring_max = tuned(Knob::GEMM_RING_MAX_T, -1);
+    if (ring && (ring_max >= 0 ? a.T <= (ring_max > 64 ? ring_max : 64) : a.T <= 4096)) {
+        const RingShape s = ring_shape(a.T, a.m, a.n, false);
+        if (a.T <= 64 || ring_max >= 0) return skinny_launch(d, stream, s);
+        if (s.us < w4a4_tiled_us(a, nullptr)) return skinny_launch(d, stream, s);
+    }
+    int form = 0;
+    w4a4_tiled_us(a, &form);
     const int asked = tuned(Knob::GEMM_WIDE, form);
     if (asked == 0 || asked == 1 || asked == 2 || asked == 4) form = asked;
     switch (form) {

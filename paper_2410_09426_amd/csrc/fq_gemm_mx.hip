@@ -335,44 +335,49 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
 }
 
 // ---- few tokens (decode, short prefill chunks; tiles of up to 64 tokens): the weights are read once per tile and the kernel is bound by how fast a CU takes them in.  A
-// workgroup owns 32 (or 16) output channels for all tokens; its waves split K by 128-byte lines (256 codes: wave w takes
+// workgroup owns 16 to 64 output channels for 8 to 64 tokens (ring_shape); its waves split K by 128-byte lines (256 codes: wave w takes
 // lines w, w + waves, ...) and each keeps a ring of line slots of its own in LDS: four global-to-LDS instructions
 // bring 32 weight rows of a line (8 whole rows each), one per 8 token rows the tokens, one the 256 bytes of weight
-// exponents (the tile order keeps them contiguous) and one per 32 tokens theirs.  A wave waits only for its own
+// exponents of 32 channels (the tile order keeps them contiguous) and one per 32 tokens theirs.  A wave waits only for its own
 // oldest slot (no barrier in the loop).  The partial sums of the waves are added in fp32 through LDS at the end.
-// ROWS = 16: the workgroup owns 16 output channels only (twice as many workgroups, for layers with too few channels
-// to give every CU one of 32); the MFMA's upper 16 rows repeat the lower ones and are dropped.
-template <int NTD, int ROWS>   // token rows in groups of 8 (one load instruction each): 1, 2, 4, 8 for T <= 8, 16, 32, 64
-__global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void mxfp4_skinny_kernel(MxGemmDev p, int depth) {
-    static_assert(ROWS == 16 || ROWS == 32, "weight rows per workgroup");
+// NTD and ROWS as for the INT4 product.
+template <int NTD, int ROWS>
+__global__ __launch_bounds__(ring_max_waves(NTD, ROWS) * 64) void mxfp4_skinny_kernel(const uint8_t* wc, const uint8_t* xc, const uint8_t* we, const uint8_t* xe, _Float16* out,
+                                                                              int n, int m, int T, RingConfig cfg, int64_t out_stride) {
+    static_assert(ROWS == 16 || ROWS == 32 || ROWS == 48 || ROWS == 64, "weight rows per workgroup");
     constexpr int NWI = ROWS / 8;                        // load instructions per line of the weight rows
     constexpr int NG = ROWS / 8;                         // groups of 8 output channels
+    constexpr int NCT = (ROWS + 31) / 32;                // MFMA channel tiles of 32, and 256-byte pieces of their exponents
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int NTT = NTD > 4 ? NTD / 4 : 1;           // MFMA token tiles of 32
     constexpr int XROWS = 8 * NTD;
-    constexpr int XOFF = ROWS * 128, WEOFF = XOFF + 1024 * NTD, XEOFF = WEOFF + 256;
+    constexpr int XOFF = ROWS * 128, WEOFF = XOFF + 1024 * NTD, XEOFF = WEOFF + 256 * NCT;
     constexpr int SLOT = XEOFF + 256 * NTT;
-    constexpr int NI = NWI + NTD + 1 + NTT;              // load instructions per step
+    constexpr int NI = NWI + NTD + NCT + NTT;            // load instructions per step
     const int tid = threadIdx.x;
     const int l = tid & 63, c = l & 31, h = l >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nwv = blockDim.x >> 6;
-    const int o0 = blockIdx.x * ROWS;
-    const int64_t t0 = (int64_t)blockIdx.y * XROWS;      // more than one token tile: launches past 64 tokens (tiles of 64)
-    const uint32_t kbytes = (uint32_t)(p.n / 2);
-    const int nl = p.n / 256;                            // lines per row
-    const int ns = (nl - w + nwv - 1) / nwv;             // this wave's steps
+    const RingTile wg = ring_tile(blockIdx.x, (m + ROWS - 1) / ROWS, cfg.token_tiles(), T / 2 > m);
+    if (wg.channels < 0) return;
+    const int o0 = wg.channels * ROWS;
+    const int t0 = wg.tokens * XROWS;
+    const uint32_t kbytes = (uint32_t)(n / 2);
+    const int nl = n / 256;                              // lines per row
+    const int nwv = cfg.waves(), depth = cfg.depth();
+    const int ns = (nl - w + nwv - 1) >> cfg.log2_waves();   // this wave's steps
     unsigned char* ring = smem + w * depth * SLOT;
 
     // Row 8 k + l / 8, the chunk that belongs into slot l % 8 of it: one offset per k for both operands, from a scalar base each.
     // Rows past the end are out of the buffers' range and read as zeros.
-    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.wc) + (int64_t)o0 * kbytes, 0, (p.m - o0 < ROWS ? p.m - o0 : ROWS) * (int)kbytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.xc) + t0 * kbytes, 0, (int)(p.T - t0 < XROWS ? p.T - t0 : XROWS) * (int)kbytes, 0x00020000);
-    // exponents of line j: 1 KB per tile of 128 rows, 8 bytes per row.  The workgroup's 32 channels are 256 bytes of
-    // their tile; the tokens are 32, 64 or 128 consecutive rows of one tile (the tensor is padded to whole tiles, so rows
-    // past T exist).
-    const __amdgpu_buffer_rsrc_t webuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.we) + (int64_t)(o0 >> 7) * nl * 1024 + 8 * (o0 & 127), 0, nl * 1024 - 8 * (o0 & 127), 0x00020000);
-    const __amdgpu_buffer_rsrc_t xebuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.xe) + (t0 >> 7) * nl * 1024 + 8 * (t0 & 127), 0, nl * 1024 - 8 * (int)(t0 & 127), 0x00020000);
+    const int mrows = m - o0 < ROWS ? m - o0 : ROWS, trows = T - t0 < XROWS ? T - t0 : XROWS;
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(wc) + (int64_t)o0 * kbytes, 0, mrows * (int)kbytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(xc) + (int64_t)t0 * kbytes, 0, trows * (int)kbytes, 0x00020000);
+    // exponents of line j: 1 KB per tile of 128 rows, 8 bytes per row.  The workgroup's channels are 256 bytes of a tile for every 32
+    // of them (48 channels may begin in one tile and end in the next); the tokens are 32 or 64 consecutive rows of one tile
+    // (the tensor is padded to whole tiles, so rows past T exist).  Rows past the last tile are out of the buffer's range.
+    const int wt = o0 >> 7, wtiles = ((m + 127) >> 7) - wt;
+    const __amdgpu_buffer_rsrc_t webuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(we) + (int64_t)wt * nl * 1024, 0, __builtin_amdgcn_readfirstlane(nl * 1024 * (wtiles < 2 ? 1 : 2)), 0x00020000);
+    const __amdgpu_buffer_rsrc_t xebuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(xe) + (int64_t)(t0 >> 7) * nl * 1024 + 8 * (t0 & 127), 0, nl * 1024 - 8 * (t0 & 127), 0x00020000);
     constexpr int NV = NWI > NTD ? NWI : NTD;
     uint32_t voff[NV];
     {
@@ -380,7 +385,13 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void mxfp4_skinny_kernel(MxG
 #pragma unroll
         for (int k = 0; k < NV; ++k) voff[k] = first + 16 * (k & 1 ? ch ^ 4 : ch) + 8 * k * kbytes;
     }
-    const int wev = 1024 * w + 4 * (l & (2 * ROWS - 1)), xev = 1024 * w + 4 * l;
+    int wev[NCT];                                        // lanes 2 r, 2 r + 1: the 8 bytes of channel r of a piece
+#pragma unroll
+    for (int j = 0; j < NCT; ++j) {
+        const int row = (o0 & 127) + 32 * j + ((l >> 1) & (ROWS - 32 * j >= 32 ? 31 : 15));
+        wev[j] = 1024 * w + (row >> 7) * nl * 1024 + 8 * (row & 127) + 4 * (l & 1);
+    }
+    const int xev = 1024 * w + 4 * l;
     typedef __attribute__((address_space(3))) void* lptr;
     auto issue = [&](int s, int slot) {
         unsigned char* base = ring + slot * SLOT;
@@ -389,20 +400,30 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void mxfp4_skinny_kernel(MxG
         for (int k = 0; k < NWI; ++k) __builtin_amdgcn_raw_ptr_buffer_load_lds(wbuf, (lptr)(base + k * 1024), 16, (int)voff[k], off, 0, 0);
 #pragma unroll
         for (int k = 0; k < NTD; ++k) __builtin_amdgcn_raw_ptr_buffer_load_lds(xbuf, (lptr)(base + XOFF + k * 1024), 16, (int)voff[k], off, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(webuf, (lptr)(base + WEOFF), 4, wev, eoff, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NCT; ++j) __builtin_amdgcn_raw_ptr_buffer_load_lds(webuf, (lptr)(base + WEOFF + 256 * j), 4, wev[j], eoff, 0, 0);
 #pragma unroll
         for (int i = 0; i < NTT; ++i) __builtin_amdgcn_raw_ptr_buffer_load_lds(xebuf, (lptr)(base + XEOFF + 256 * i), 4, xev + 256 * i, eoff, 0, 0);
     };
     const int npre = ns < depth ? ns : depth;
+#pragma unroll 1
     for (int s = 0; s < npre; ++s) issue(s, s);
 
-    f32x16 acc[NTT];
+    f32x16 acc[NTT][NCT];
 #pragma unroll
     for (int i = 0; i < NTT; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0.0f;
-    const int woff = (c & (ROWS - 1)) * 128;
-    const int whs = h ^ (((c & (ROWS - 1)) >> 1) & 7);
+        for (int j = 0; j < NCT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    int woff[NCT], whs[NCT], wexp[NCT];
+#pragma unroll
+    for (int j = 0; j < NCT; ++j) {
+        const int row = 32 * j + (c & (ROWS - 32 * j >= 32 ? 31 : 15));
+        woff[j] = row * 128;
+        whs[j] = h ^ ((row >> 1) & 7);
+        wexp[j] = WEOFF + 8 * row;
+    }
     int xoff[NTT], xhs[NTT];
 #pragma unroll
     for (int i = 0; i < NTT; ++i) {
@@ -416,18 +437,23 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void mxfp4_skinny_kernel(MxG
         wait_ring_step<NI>(left < depth - 1 ? left : depth - 1);
         const unsigned char* base = ring + slot * SLOT;
         // block 2 kp + h of this lane's row: after the shift by 8 h, byte 2 (kp & 1) of dword kp / 2
-        u32x2 ew = *reinterpret_cast<const u32x2*>(base + WEOFF + 8 * (c & (ROWS - 1)));
-        ew = u32x2{ew[0] >> (8 * h), ew[1] >> (8 * h)};
+        u32x2 ew[NCT];
+#pragma unroll
+        for (int j = 0; j < NCT; ++j) {
+            const u32x2 v = *reinterpret_cast<const u32x2*>(base + wexp[j]);
+            ew[j] = u32x2{v[0] >> (8 * h), v[1] >> (8 * h)};
+        }
         u32x2 ex[NTT];
 #pragma unroll
         for (int i = 0; i < NTT; ++i) {
             const u32x2 v = *reinterpret_cast<const u32x2*>(base + XEOFF + 256 * i + 8 * c);
             ex[i] = u32x2{v[0] >> (8 * h), v[1] >> (8 * h)};
         }
-        u32x4 wv[4], xv[4][NTT];
+        u32x4 wv[4][NCT], xv[4][NTT];
 #pragma unroll
         for (int kp = 0; kp < 4; ++kp) {
-            wv[kp] = *reinterpret_cast<const u32x4*>(base + woff + 16 * ((2 * kp) ^ whs));
+#pragma unroll
+            for (int j = 0; j < NCT; ++j) wv[kp][j] = *reinterpret_cast<const u32x4*>(base + woff[j] + 16 * ((2 * kp) ^ whs[j]));
 #pragma unroll
             for (int i = 0; i < NTT; ++i) xv[kp][i] = *reinterpret_cast<const u32x4*>(base + xoff[i] + 16 * ((2 * kp) ^ xhs[i]));
         }
@@ -435,12 +461,15 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void mxfp4_skinny_kernel(MxG
         if (s + depth < ns) issue(s + depth, slot);
 #pragma unroll
         for (int kp = 0; kp < 4; ++kp) {
-            const i32x8 a = {(int)wv[kp][0], (int)wv[kp][1], (int)wv[kp][2], (int)wv[kp][3], 0, 0, 0, 0};
 #pragma unroll
             for (int i = 0; i < NTT; ++i) {
                 const i32x8 b = {(int)xv[kp][i][0], (int)xv[kp][i][1], (int)xv[kp][i][2], (int)xv[kp][i][3], 0, 0, 0, 0};
-                if (kp & 1) acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i], 4, 4, 2, (int)ew[kp >> 1], 2, (int)ex[i][kp >> 1]);
-                else acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i], 4, 4, 0, (int)ew[kp >> 1], 0, (int)ex[i][kp >> 1]);
+#pragma unroll
+                for (int j = 0; j < NCT; ++j) {
+                    const i32x8 a = {(int)wv[kp][j][0], (int)wv[kp][j][1], (int)wv[kp][j][2], (int)wv[kp][j][3], 0, 0, 0, 0};
+                    if (kp & 1) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i][j], 4, 4, 2, (int)ew[j][kp >> 1], 2, (int)ex[i][kp >> 1]);
+                    else acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i][j], 4, 4, 0, (int)ew[j][kp >> 1], 0, (int)ex[i][kp >> 1]);
+                }
             }
         }
         slot = (slot + 1 == depth) ? 0 : slot + 1;
@@ -453,61 +482,59 @@ __global__ __launch_bounds__(NTD >= 8 ? 512 : 1024) void mxfp4_skinny_kernel(MxG
     for (int i = 0; i < NTT; ++i)
 #pragma unroll
         for (int g = 0; g < NG; ++g)
-            part[((w * NTT + i) * NG + g) * 64 + l] = f32x4{acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]};
+            part[((w * NTT + i) * NG + g) * 64 + l] = f32x4{acc[i][g / 4][4 * (g % 4)], acc[i][g / 4][4 * (g % 4) + 1], acc[i][g / 4][4 * (g % 4) + 2], acc[i][g / 4][4 * (g % 4) + 3]};
     __syncthreads();
     typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-    const bool wide = ((reinterpret_cast<uintptr_t>(p.out) & 7) == 0) && (p.out_stride % 4 == 0);
-    for (int e = tid; e < NTT * NG * 64; e += (int)blockDim.x) {
+    const bool wide = ((reinterpret_cast<uintptr_t>(out) & 7) == 0) && (out_stride % 4 == 0);
+    for (int e = tid; e < NTT * NG * 64; e += 64 * nwv) {
         const int el = e & 63, g = (e >> 6) % NG, i = (e >> 6) / NG;
         f32x4 sum = part[e];
         for (int ww = 1; ww < nwv; ++ww) sum += part[ww * NTT * NG * 64 + e];
-        const int64_t t = t0 + 32 * i + (el & 31);
+        const int t = t0 + 32 * i + (el & 31);
         const int o = o0 + 8 * g + 4 * (el >> 5);
-        if (t < p.T && o < p.m) {
+        if (t < T && o < m) {
             const _Float16 v[4] = {(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
-            _Float16* dst = p.out + t * p.out_stride + o;
-            if (wide && o + 4 <= p.m) {
+            _Float16* dst = out + t * out_stride + o;
+            if (wide && o + 4 <= m) {
                 *reinterpret_cast<half4*>(dst) = half4{v[0], v[1], v[2], v[3]};
             } else {
                 for (int x = 0; x < 4; ++x)
-                    if (o + x < p.m) dst[x] = v[x];
+                    if (o + x < m) dst[x] = v[x];
             }
         }
     }
 }
 
 template <int NTD, int ROWS>
-static hipError_t mx_skinny_launch_rows(const MxGemmDev& d, hipStream_t stream, int token_tiles) {
-    if (token_tiles < 1 || (token_tiles > 1 && NTD < 4)) return hipErrorInvalidValue;   // tiles of 32 tokens or more keep their exponents inside one 128-row tile
+static hipError_t mx_skinny_launch_shape(const MxGemmDev& d, hipStream_t stream, const RingShape& s) {
     static OccCache oc;
     int unused = 0;
-    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(mxfp4_skinny_kernel<NTD, ROWS>), NTD >= 8 ? 512 : 1024, kRingLdsMax, oc, unused);
+    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(mxfp4_skinny_kernel<NTD, ROWS>), 64 * ring_max_waves(NTD, ROWS), kRingLdsMax, oc, unused);
     if (e != hipSuccess) return e;
-    constexpr int NTT = NTD > 4 ? NTD / 4 : 1;
-    constexpr int SLOT = ROWS * 128 + 1024 * NTD + 256 + 256 * NTT, NI = ROWS / 8 + NTD + 1 + NTT;
-    const unsigned wgx = (unsigned)((d.m + ROWS - 1) / ROWS);
-    const int64_t wgs = (int64_t)wgx * token_tiles;
-    const int nl = d.n / 256;
-    // as for the INT4 product: 8 waves and two slots when there is at most one workgroup per CU, else 4 waves and one
-    const bool crowded = wgs > cu_count();
-    int nwv = tuned(Knob::GEMM_WAVES, crowded ? 4 : 8);
-    int depth = tuned(Knob::GEMM_DEPTH, crowded ? 1 : 2);
-    if ((nwv != 4 && nwv != 8 && nwv != 16) || depth < 1 || depth > kRingMaxDepth) return hipErrorInvalidValue;
-    if (NTD >= 8 && nwv > 8) nwv = 8;                     // two token tiles of accumulators: compiled for at most 8 waves
-    while (nwv > 4 && nwv * SLOT > kRingLdsMax) nwv >>= 1;
-    const int steps = (nl + nwv - 1) / nwv;
-    if (depth > steps) depth = steps;
-    while (depth > 1 && (nwv * depth * SLOT > kRingLdsMax || (depth - 1) * NI > 63)) --depth;
-    const int bytes = nwv * depth * SLOT;                // the partial sums (at most 4 KB per wave and token tile) reuse the rings
-    return launch((mxfp4_skinny_kernel<NTD, ROWS>), dim3(wgx, (unsigned)token_tiles), dim3(64 * nwv), bytes, stream, d, depth);
+    constexpr int NTT = NTD > 4 ? NTD / 4 : 1, NCT = (ROWS + 31) / 32;
+    RingLaunch r;
+    if (!ring_launch(s, d.T, d.m, d.n, ROWS * 128 + 1024 * NTD + 256 * (NCT + NTT), ROWS / 8 + NTD + NCT + NTT, r)) return hipErrorInvalidValue;
+    return launch((mxfp4_skinny_kernel<NTD, ROWS>), dim3(r.grid), dim3(64 * r.cfg.waves()), r.lds, stream, d.wc, d.xc, d.we, d.xe, d.out, d.n, d.m, (int)d.T, r.cfg, d.out_stride);
 }
-// 16 channels per workgroup while that still leaves at most one workgroup per CU (FLATQUANT_GEMM_ROWS forces 16 or 32)
 template <int NTD>
-static hipError_t mx_skinny_launch(const MxGemmDev& d, hipStream_t stream, int token_tiles = 1) {
-    const int rows = tuned(Knob::GEMM_ROWS, (int64_t)((d.m + 15) / 16) * token_tiles <= cu_count() ? 16 : 32);
-    if (rows == 16) return mx_skinny_launch_rows<NTD, 16>(d, stream, token_tiles);
-    if (rows == 32) return mx_skinny_launch_rows<NTD, 32>(d, stream, token_tiles);
-    return hipErrorInvalidValue;
+static hipError_t mx_skinny_launch_tokens(const MxGemmDev& d, hipStream_t stream, const RingShape& s) {
+    switch (s.rows) {
+        case 16: return mx_skinny_launch_shape<NTD, 16>(d, stream, s);
+        case 32: return mx_skinny_launch_shape<NTD, 32>(d, stream, s);
+        case 48: return mx_skinny_launch_shape<NTD, 48>(d, stream, s);
+        case 64: return mx_skinny_launch_shape<NTD, 64>(d, stream, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+static hipError_t mx_skinny_launch(const MxGemmDev& d, hipStream_t stream) {
+    const RingShape s = ring_shape(d.T, d.m, d.n, true);
+    switch (s.tokens) {
+        case 8: return mx_skinny_launch_tokens<1>(d, stream, s);
+        case 16: return mx_skinny_launch_tokens<2>(d, stream, s);
+        case 32: return mx_skinny_launch_tokens<4>(d, stream, s);
+        case 64: return mx_skinny_launch_tokens<8>(d, stream, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <int TI, int TJ, int WM, int WN, int NST, int LA, typename Off, bool ODD>
@@ -555,17 +582,14 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
     d.T = a.T; d.out_stride = a.out_stride; d.m = a.m; d.n = a.n;
     if (tuned(Knob::GEMM_TILED, 0) == 0 && d.n <= kOff32MaxN) {
         // decode and short prefill chunks: one pass over the weights, K split inside a workgroup (the ring kernel)
-        if (a.T <= 8) return mx_skinny_launch<1>(d, stream);
-        if (a.T <= 16) return mx_skinny_launch<2>(d, stream);
-        if (a.T <= 32) return mx_skinny_launch<4>(d, stream);
-        if (a.T <= 64) return mx_skinny_launch<8>(d, stream);
+        if (a.T <= 64) return mx_skinny_launch(d, stream);
         // More tokens: the ring kernel on tiles of 64 tokens, as long as the 128 x 128 tiles of the kernel below would
         // reach at most half of the CUs (measured cross-over on 1024 .. 11008 channels; FLATQUANT_GEMM_RING_MAX_T
         // replaces the rule by a token count).
         const int64_t tiled_wgs = ((a.T + XT - 1) / XT) * ((a.m + XT - 1) / XT);
         const int ring_max = tuned(Knob::GEMM_RING_MAX_T, -1);
         if (ring_max >= 0 ? a.T <= ring_max : (2 * tiled_wgs <= cu_count() && a.T <= 4096))
-            return mx_skinny_launch<8>(d, stream, (int)((a.T + 63) / 64));
+            return mx_skinny_launch(d, stream);
     }
     // Rows whose offsets inside a tile need 64 bits: the smallest tile, whatever the form asked for.  They are far beyond
     // what the transform produces (n <= 32768), so there is one instance for them (1024 x 2304 x 33686272: 142.8 ms; 143.8

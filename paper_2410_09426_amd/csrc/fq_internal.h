@@ -120,7 +120,48 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream);
 // Few-token products (fq_gemm.hip, fq_gemm_mx.hip): per wave a ring of LDS slots filled by global-to-LDS loads.
 constexpr int kRingMaxDepth = 8;
 constexpr int kRingLdsMax = 160 * 1024;
+// waves that a workgroup of 8 ntd tokens and `rows` channels is compiled for: more than 32 of either need the registers of two waves per SIMD
+constexpr int ring_max_waves(int ntd, int rows) { return ntd >= 8 || rows > 32 ? 8 : 16; }
+// Tokens (8, 16, 32, 64) and output channels (16, 32, 48, 64) of a workgroup, its waves and line slots per wave, and what the launch is
+// expected to take.
+struct RingShape {
+    int tokens, rows, waves, depth;
+    double us;
+};
+RingShape ring_shape(int64_t T, int m, int n, bool mx);
+// Ring depth, waves and token tiles of a launch in one dword (the kernels' arguments arrive in registers, as many as there is room for).
+struct RingConfig {
+    static constexpr int kMaxTokenTiles = (1 << 24) - 1;
+    uint32_t bits;
+    RingConfig() = default;
+    RingConfig(int depth, int waves, int token_tiles) : bits((uint32_t)depth | (uint32_t)__builtin_ctz(waves) << 4 | (uint32_t)token_tiles << 8) {}
+    __host__ __device__ int depth() const { return bits & 15; }
+    __host__ __device__ int log2_waves() const { return bits >> 4 & 15; }
+    __host__ __device__ int waves() const { return 1 << log2_waves(); }
+    __host__ __device__ int token_tiles() const { return (int)(bits >> 8); }
+};
+struct RingLaunch {
+    unsigned grid;
+    RingConfig cfg;
+    int lds;
+};
+// Waves, ring depth and grid for slots of `slot` bytes that `loads` instructions fill; false for overrides that no launch can honour.
+bool ring_launch(const RingShape& s, int64_t T, int m, int n, int slot, int loads, RingLaunch& r);
 #if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
+// Channel group and token tile of a workgroup.  Workgroup b runs on XCD b % 8: an XCD takes a contiguous eighth of an order in which the
+// tiles that share the larger operand follow each other, so that its rows come from memory once and are in that L2 for the others
+// (1025 x 842 x 11008 20.8 -> 16.7 us; 4000 x 512 x 4096, with the smaller one, 16 -> 21).  channels < 0: nothing to do (the grid
+// is a whole number of rounds of the XCDs).
+struct RingTile {
+    int channels, tokens;
+};
+__device__ __forceinline__ RingTile ring_tile(int b, int groups, int token_tiles, bool more_tokens) {
+    if (token_tiles == 1) return RingTile{b, 0};
+    const int all = groups * token_tiles, per_xcd = (all + 7) >> 3, q = (b & 7) * per_xcd + (b >> 3);
+    if (q >= all) return RingTile{-1, 0};
+    const int inner = more_tokens ? groups : token_tiles, outer = q / inner, r = q - outer * inner;
+    return more_tokens ? RingTile{r, outer} : RingTile{outer, r};
+}
 // Every kernel launch of the library goes through here.  The runtime keeps the last error of any earlier call on the
 // thread (the caller's own, unrelated ones included) until somebody reads it: it is read and dropped first, so that
 // what is returned belongs to this launch.
@@ -170,7 +211,7 @@ int cu_count();
 // Tuning overrides (kernel flavour, workgroups per CU, ...), for measurements and for the tests that must reach every code
 // path; kKnobNames (fq_api.hip) has their names in the same order.  Each starts from the environment variable of that name, read
 // once per process, and can be changed with fq_set_tuning.
-enum class Knob { MODE, WG_PER_CU, FORCE_GENERIC, KV_WG_PER_CU, GEMM_TILED, GEMM_WIDE, GEMM_DEPTH, GEMM_WAVES, GEMM_ROWS, GEMM_RING_MAX_T, KV_FOLD_HEADS, KV_FEW, WAVE_TPW, PROBE_SHAPE, COUNT };
+enum class Knob { MODE, WG_PER_CU, FORCE_GENERIC, KV_WG_PER_CU, GEMM_TILED, GEMM_WIDE, GEMM_DEPTH, GEMM_WAVES, GEMM_ROWS, GEMM_TOKENS, GEMM_RING_MAX_T, KV_FOLD_HEADS, KV_FEW, WAVE_TPW, PROBE_SHAPE, COUNT };
 struct KnobState {
     std::atomic<int> state{0};   // 0: environment not read yet, 1: unset (callers use their default), 2: set
     std::atomic<int> value{0};

@@ -792,12 +792,30 @@ def test_tiled_products_at_every_output_alignment(tuning, kind, T, m, n, form):
                                                     (4, 1, 16, 1, 33, 256), (8, 2, 32, 9, 8200, 512), (8, 2, 16, 12, 8200, 512), (4, 2, 32, 64, 4096, 1024), (16, 3, 32, 120, 200, 2304), (4, 2, 16, 90, 100, 1024)])
 @pytest.mark.parametrize("kind", ["int4", "mxfp4"])
 def test_few_token_products_every_launch_shape(tuning, kind, waves, depth, rows, T, m, n):
-    """The few-token kernels give a workgroup 16 or 32 output channels and split K over 4, 8 or 16 waves with rings of
+    """The few-token kernels give a workgroup 16 to 64 output channels and split K over 4, 8 or 16 waves with rings of
     1 to 8 line slots; the library picks one shape per launch, the others are forced here (a depth the ring cannot hold
     is cut back by the launcher)."""
     tuning("FLATQUANT_GEMM_WAVES", waves)
     tuning("FLATQUANT_GEMM_DEPTH", depth)
     tuning("FLATQUANT_GEMM_ROWS", rows)
+    if kind == "int4":
+        _w4a4_case(T, m, n, 0)
+    else:
+        _mxfp4_gemm_case(T, m, n)
+
+
+@pytest.mark.parametrize("T,m,n", [(1, 1, 256), (8, 129, 2304), (13, 1000, 768), (17, 48, 4096), (63, 100, 768), (65, 250, 1024), (150, 50, 512), (300, 129, 768)])
+@pytest.mark.parametrize("rows", [16, 32, 48, 64])
+@pytest.mark.parametrize("tokens", [8, 16, 32, 64])
+@pytest.mark.parametrize("kind", ["int4", "mxfp4"])
+def test_few_token_products_every_workgroup(tuning, kind, tokens, rows, T, m, n):
+    """8 to 64 tokens and 16 to 64 output channels per workgroup: last groups that are not full, channels whose exponents begin in one
+    128-row tile and end in the next (48 of them), fewer lines than waves, and several token tiles in either order over the XCDs."""
+    if T > tokens:
+        tokens = max(tokens, 32)        # several tiles: of 32 or 64 tokens
+    tuning("FLATQUANT_GEMM_TOKENS", tokens)
+    tuning("FLATQUANT_GEMM_ROWS", rows)
+    tuning("FLATQUANT_GEMM_RING_MAX_T", 1 << 20)
     if kind == "int4":
         _w4a4_case(T, m, n, 0)
     else:
@@ -852,7 +870,7 @@ def test_products_at_the_longest_rows(kind, T, m):
         _mxfp4_gemm_case(T, m, 65536)
 
 
-@pytest.mark.parametrize("knob,value", [("FLATQUANT_GEMM_WAVES", 5), ("FLATQUANT_GEMM_DEPTH", 0), ("FLATQUANT_GEMM_DEPTH", 9), ("FLATQUANT_GEMM_ROWS", 24)])
+@pytest.mark.parametrize("knob,value", [("FLATQUANT_GEMM_WAVES", 5), ("FLATQUANT_GEMM_DEPTH", 0), ("FLATQUANT_GEMM_DEPTH", 9), ("FLATQUANT_GEMM_ROWS", 24), ("FLATQUANT_GEMM_TOKENS", 24)])
 def test_ring_kernel_overrides_out_of_range_are_launch_errors(tuning, knob, value):
     """A tuning override the ring kernels cannot honour is reported (no launch, outputs untouched), not silently replaced."""
     tuning(knob, value)
