@@ -108,11 +108,11 @@ struct Tile {
 // Every operand byte goes from global memory straight into LDS (global-to-LDS loads, unpadded 128-byte rows, 16-byte chunks
 // swizzled), NST iterations of 256 codes deep, one barrier per iteration; persistent workgroups whose loads run on from one
 // output tile into the next.  The output leaves through LDS in 16-byte pieces, by buffer stores without branches where all rows
-// are made of such pieces.  ODD: the output's rows are not all dword-aligned and leave in halves, by a loop that only such
-// launches carry (6486 x 5705 x 256 61 us, 82 with the halves of 16-byte pieces stored one by one).
-template <class L, bool ODD>
+// are made of such pieces.  OUT: how it leaves (tiled_output).  odd: the output's rows are not all dword-aligned and leave in
+// halves, by a loop that only such launches carry (6486 x 5705 x 256 61 us, 82 with the halves of 16-byte pieces stored one by one).
+template <class L, Out OUT>
 __global__ __launch_bounds__(64 * L::NW) __attribute__((amdgpu_waves_per_eu(L::WPE, L::WPE))) void w4a4_tiled_kernel(GemmDev p) {
-    constexpr bool FP6 = L::FP6;
+    constexpr bool FP6 = L::FP6, ODD = OUT == Out::odd;
     constexpr int TI = L::TI, TJ = L::TJ, WM = L::WM, WN = L::WN, NST = L::NST;
     constexpr int NW = L::NW, TOK = L::TOK, CH = L::CH, STAGE = L::STAGE, A_TILE = TOK * GKB, NOP = TI + TJ;
     constexpr int NLA = TOK / 8 / NW, NLB = CH / 8 / NW, NL = NLA + NLB;   // load instructions per wave and iteration
@@ -493,7 +493,7 @@ __global__ __launch_bounds__(64 * L::NW) __attribute__((amdgpu_waves_per_eu(L::W
                     const int o = 32 * ch_tile(ch >> 2) + 8 * (ch & 3), row = 32 * tok_tile(i) + r;
                     const int col = cur.o0 + o < p.m ? 2 * o : 0x40000000;
                     const u32x4 v = *reinterpret_cast<const u32x4*>(ot + r * OPITCH + 16 * ch);
-                    __builtin_amdgcn_raw_buffer_store_b128(v, obuf, row < rows_left ? row * pitch + col : 0x40000000, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, obuf, row < rows_left ? row * pitch + col : 0x40000000, 0, OUT == Out::streamed ? 2 : 0);   // 2: nt
                 }
             } else {                         // `pairs` holds (the same loop without the test measured 1 - 2 % slower)
 #pragma unroll
@@ -821,23 +821,38 @@ static hipError_t skinny_launch(const GemmDev& d, hipStream_t stream, const Ring
     }
 }
 
-template <class L, bool ODD>
+// What is dirty in the L2s (32 MB) when a kernel ends is written back before the next one starts, 1.5 us for a whole tile per CU, so
+// outputs about as large as that go past them (non-temporal stores): us cached / streamed, INT4 2048 x 4096 x 4096 27.1 / 25.6, 777 x 5120 x
+// 5120 23.5 / 22.6, 6142 x 640 x 5120 23.4 / 19.4; MXFP4 2048 x 4096 x 11008 50.2 / 47.5, 2048 x 4104 x 7168 49.9 / 40.9, 3458 x 3584 x 4096 33.2 /
+// 29.1.  Larger ones leave L2 while the kernel runs and gain nothing, and rows that are not whole 128-byte lines lose: their ends
+// are merged in L2 or are writes of their own (INT4 7395 x 1592 x 2048, 24 MB, 26.2 / 26.6; 4461 x 8944 x 5120, 80 MB, 130 / 138; 8192 x 8200 x
+// 512 49 / 69; whole lines: MXFP4 12382 x 2176 x 5120, 54 MB, 83 / 76, 8192 x 8192 x 512, 134 MB, 35.7 / 39.6).
+Out tiled_output(int64_t T, int m, const void* out, int64_t out_stride) {
+    const uintptr_t rows = reinterpret_cast<uintptr_t>(out) | (uintptr_t)(2 * out_stride);
+    if (rows & 3) return Out::odd;
+    return 2 * T * m <= (rows & 127 ? 20 << 20 : 64 << 20) ? Out::streamed : Out::cached;
+}
+
+template <class L, Out OUT>
 static hipError_t tiled_launch_rows(const GemmDev& d, hipStream_t stream) {
     static OccCache cache;
     int occ = 0;
-    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_tiled_kernel<L, ODD>), 64 * L::NW, L::LDS, cache, occ);
+    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(w4a4_tiled_kernel<L, OUT>), 64 * L::NW, L::LDS, cache, occ);
     if (e != hipSuccess) return e;
     // persistent: every XCD (eight of them) gets as many workgroups as it holds at once, or as it has tiles
     const int64_t tiles = ((d.T + L::TOK - 1) / L::TOK) * ((d.m + L::CH - 1) / L::CH);
     const int64_t per_xcd = (tiles + 7) / 8, resident = (int64_t)occ * cu_count() / 8;
     const unsigned grid = 8 * (unsigned)(per_xcd < resident ? per_xcd : resident);
-    return launch(w4a4_tiled_kernel<L, ODD>, dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
+    return launch(w4a4_tiled_kernel<L, OUT>, dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
 }
 
 template <class L>
 static hipError_t tiled_launch(const GemmDev& d, hipStream_t stream) {
-    const bool odd = (reinterpret_cast<uintptr_t>(d.out) | (uintptr_t)(2 * d.out_stride)) & 3;
-    return odd ? tiled_launch_rows<L, true>(d, stream) : tiled_launch_rows<L, false>(d, stream);
+    switch (tiled_output(d.T, d.m, d.out, d.out_stride)) {
+        case Out::odd: return tiled_launch_rows<L, Out::odd>(d, stream);
+        case Out::streamed: return tiled_launch_rows<L, Out::streamed>(d, stream);
+        default: return tiled_launch_rows<L, Out::cached>(d, stream);
+    }
 }
 
 // Tile form (FLATQUANT_GEMM_WIDE forces one): int8 with 128 x 128 tiles, two workgroups per CU (0) or 160 x 128, one (4); FP6 with

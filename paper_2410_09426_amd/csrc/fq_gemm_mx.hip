@@ -42,9 +42,9 @@ struct MxGemmDev {
 
 // TI x TJ: MFMA tiles per wave (tokens x channels), WM x WN: waves, NST: LDS stages, LA: K steps that an operand is read
 // from LDS ahead of its MFMAs.  Off: offsets of a tile's rows from its first one.  32 bits hold 256 rows of n / 2 bytes up
-// to n = 2^25 (kOff32MaxN); longer rows take 64.  ODD: the output's rows are not all dword-aligned and leave in halves, by
-// a loop that only such launches carry (beside the other one it costs the aligned rows 1 - 2 %).  With the halves of 16-byte
-// pieces stored one by one, eight rows to an instruction, 520 x 12609 x 2048 took 25.5 us, now 16.6; 1538 x 10027 x 4096 77.9,
+// to n = 2^25 (kOff32MaxN); longer rows take 64.  OUT: how the output leaves (tiled_output); odd: its rows are not
+// all dword-aligned and leave in halves, by a loop that only such launches carry (beside the other one it costs the aligned rows
+// 1 - 2 %).  With the halves of 16-byte pieces stored one by one, eight rows to an instruction, 520 x 12609 x 2048 took 25.5 us, now 16.6; 1538 x 10027 x 4096 77.9,
 // now 66.9; 1223 x 1819 x 2048 13.4, now 12.3 with two stages.
 constexpr int kOff32MaxN = 1 << 25;
 template <int TI, int TJ, int WM, int WN, int NST>
@@ -58,9 +58,10 @@ struct MxTile {
     static_assert(NW * 32 * OPITCH <= STAGE && LDS <= 160 * 1024 && NST >= 2, "LDS budget");
 };
 
-template <int TI, int TJ, int WM, int WN, int NST, int LA, typename Off, bool ODD>
+template <int TI, int TJ, int WM, int WN, int NST, int LA, typename Off, Out OUT>
 __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI * TJ > 4 ? 1 : 2, TI * TJ > 4 ? 1 : 2))) void mxfp4_gemm_kernel(MxGemmDev p) {
     using L = MxTile<TI, TJ, WM, WN, NST>;
+    constexpr bool ODD = OUT == Out::odd;
     constexpr int NW = L::NW, TOK = L::TOK, CH = L::CH, STAGE = L::STAGE, A_TILE = TOK * XKB, NOP = TI + TJ;
     constexpr int NLA = TOK / 8 / NW, NLB = CH / 8 / NW, NL = 1 + NLA + NLB;   // load instructions per wave and iteration
     constexpr int NPC = L::ROWS / 128;                              // 1 KB pieces of exponents per iteration
@@ -293,7 +294,8 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
                     if (t < p.T && o < p.m) {
                         _Float16* dst = p.out + t * p.out_stride + o;
                         if (wide && o + 8 <= p.m) {
-                            *reinterpret_cast<u32x4*>(dst) = v;
+                            if constexpr (OUT == Out::streamed) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
+                            else *reinterpret_cast<u32x4*>(dst) = v;
                         } else if (pairs && o + 8 <= p.m) {
                             for (int x = 0; x < 4; ++x) reinterpret_cast<uint32_t*>(dst)[x] = v[x];
                         } else {
@@ -537,25 +539,27 @@ static hipError_t mx_skinny_launch(const MxGemmDev& d, hipStream_t stream) {
     }
 }
 
-template <int TI, int TJ, int WM, int WN, int NST, int LA, typename Off, bool ODD>
+template <int TI, int TJ, int WM, int WN, int NST, int LA, typename Off, Out OUT>
 static hipError_t mx_tile_launch_rows(const MxGemmDev& d, hipStream_t stream) {
     using L = MxTile<TI, TJ, WM, WN, NST>;
     static OccCache cache;
     int occ = 0;
-    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA, Off, ODD>), 64 * L::NW, L::LDS, cache, occ);
+    hipError_t e = kernel_occupancy(reinterpret_cast<const void*>(mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA, Off, OUT>), 64 * L::NW, L::LDS, cache, occ);
     if (e != hipSuccess) return e;
     // persistent: every XCD (eight of them) gets as many workgroups as it holds at once, or as it has tiles
     const int64_t tiles = ((d.T + L::TOK - 1) / L::TOK) * ((d.m + L::CH - 1) / L::CH);
     const int64_t per_xcd = (tiles + 7) / 8, resident = (int64_t)occ * cu_count() / 8;
     const unsigned grid = 8 * (unsigned)(per_xcd < resident ? per_xcd : resident);
-    return launch((mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA, Off, ODD>), dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
+    return launch((mxfp4_gemm_kernel<TI, TJ, WM, WN, NST, LA, Off, OUT>), dim3(grid), dim3(64 * L::NW), L::LDS, stream, d);
 }
 
 template <int TI, int TJ, int WM, int WN, int NST, int LA, typename Off = uint32_t>
 static hipError_t mx_tile_launch(const MxGemmDev& d, hipStream_t stream) {
-    const bool odd = (reinterpret_cast<uintptr_t>(d.out) | (uintptr_t)(2 * d.out_stride)) & 3;
-    return odd ? mx_tile_launch_rows<TI, TJ, WM, WN, NST, LA, Off, true>(d, stream)
-               : mx_tile_launch_rows<TI, TJ, WM, WN, NST, LA, Off, false>(d, stream);
+    switch (tiled_output(d.T, d.m, d.out, d.out_stride)) {
+        case Out::odd: return mx_tile_launch_rows<TI, TJ, WM, WN, NST, LA, Off, Out::odd>(d, stream);
+        case Out::streamed: return mx_tile_launch_rows<TI, TJ, WM, WN, NST, LA, Off, Out::streamed>(d, stream);
+        default: return mx_tile_launch_rows<TI, TJ, WM, WN, NST, LA, Off, Out::cached>(d, stream);
+    }
 }
 
 // Tile form: 0 = 128 x 128 (two workgroups per CU, or one with three stages), 1 = 256 x 128, 2 = 256 x 256 (one per CU).  The
