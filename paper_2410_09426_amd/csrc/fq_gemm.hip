@@ -493,7 +493,7 @@ __global__ __launch_bounds__(64 * L::NW) __attribute__((amdgpu_waves_per_eu(L::W
                     const int o = 32 * ch_tile(ch >> 2) + 8 * (ch & 3), row = 32 * tok_tile(i) + r;
                     const int col = cur.o0 + o < p.m ? 2 * o : 0x40000000;
                     const u32x4 v = *reinterpret_cast<const u32x4*>(ot + r * OPITCH + 16 * ch);
-                    __builtin_amdgcn_raw_buffer_store_b128(v, obuf, row < rows_left ? row * pitch + col : 0x40000000, 0, OUT == Out::streamed ? 2 : 0);   // 2: nt
+                    __builtin_amdgcn_raw_buffer_store_b128(v, obuf, row < rows_left ? row * pitch + col : 0x40000000, 0, OUT == Out::through ? 16 : 0);   // 16: sc1
                 }
             } else {                         // `pairs` holds (the same loop without the test measured 1 - 2 % slower)
 #pragma unroll
@@ -821,16 +821,15 @@ static hipError_t skinny_launch(const GemmDev& d, hipStream_t stream, const Ring
     }
 }
 
-// What is dirty in the L2s (32 MB) when a kernel ends is written back before the next one starts, 1.5 us for a whole tile per CU, so
-// outputs about as large as that go past them (non-temporal stores): us cached / streamed, INT4 2048 x 4096 x 4096 27.1 / 25.6, 777 x 5120 x
-// 5120 23.5 / 22.6, 6142 x 640 x 5120 23.4 / 19.4; MXFP4 2048 x 4096 x 11008 50.2 / 47.5, 2048 x 4104 x 7168 49.9 / 40.9, 3458 x 3584 x 4096 33.2 /
-// 29.1.  Larger ones leave L2 while the kernel runs and gain nothing, and rows that are not whole 128-byte lines lose: their ends
-// are merged in L2 or are writes of their own (INT4 7395 x 1592 x 2048, 24 MB, 26.2 / 26.6; 4461 x 8944 x 5120, 80 MB, 130 / 138; 8192 x 8200 x
-// 512 49 / 69; whole lines: MXFP4 12382 x 2176 x 5120, 54 MB, 83 / 76, 8192 x 8192 x 512, 134 MB, 35.7 / 39.6).
-Out tiled_output(int64_t T, int m, const void* out, int64_t out_stride) {
+// What is dirty in L2 when a kernel ends is written back before the next one starts, about 1.5 us for a whole tile per CU.  So rows of
+// whole cache lines are written through, while the other tiles are still at work: us cached / through, INT4 2048 x 4096 x 4096 27.5 / 26.8,
+// 777 x 5120 x 5120 24.0 / 22.8, 16384 x 8192 x 1024 115.3 / 110.6; MXFP4 2048 x 4096 x 11008 51.8 / 49.4, 1139 x 7296 x 4096 30.7 / 29.7,
+// 2508 x 2944 x 4096 21.8 / 20.2; 46 such launches of 7 to 268 MB 0.976 on average, 0.976 also together with a kernel that reads the output.
+// (Non-temporal stores save more, 0.94, but the reader pays it back: 0.99 together.)  The ends of other rows are merged in L2, written through
+// they are writes of their own: 8192 x 8200 x 512 50 / 64, MXFP4 2580 x 10328 x 2048 37.5 / 39.3.
+Out tiled_output(const void* out, int64_t out_stride) {
     const uintptr_t rows = reinterpret_cast<uintptr_t>(out) | (uintptr_t)(2 * out_stride);
-    if (rows & 3) return Out::odd;
-    return 2 * T * m <= (rows & 127 ? 20 << 20 : 64 << 20) ? Out::streamed : Out::cached;
+    return rows & 3 ? Out::odd : rows & 127 ? Out::cached : Out::through;
 }
 
 template <class L, Out OUT>
@@ -848,9 +847,9 @@ static hipError_t tiled_launch_rows(const GemmDev& d, hipStream_t stream) {
 
 template <class L>
 static hipError_t tiled_launch(const GemmDev& d, hipStream_t stream) {
-    switch (tiled_output(d.T, d.m, d.out, d.out_stride)) {
+    switch (tiled_output(d.out, d.out_stride)) {
         case Out::odd: return tiled_launch_rows<L, Out::odd>(d, stream);
-        case Out::streamed: return tiled_launch_rows<L, Out::streamed>(d, stream);
+        case Out::through: return tiled_launch_rows<L, Out::through>(d, stream);
         default: return tiled_launch_rows<L, Out::cached>(d, stream);
     }
 }

@@ -294,7 +294,9 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(TI
                     if (t < p.T && o < p.m) {
                         _Float16* dst = p.out + t * p.out_stride + o;
                         if (wide && o + 8 <= p.m) {
-                            if constexpr (OUT == Out::streamed) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
+                            // (in asm: there is no builtin for it with a 64-bit address.  The s_nop is what a store of more than 8 bytes needs before its
+                            // data registers are written again)
+                            if constexpr (OUT == Out::through) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(dst), "v"(v) : "memory");
                             else *reinterpret_cast<u32x4*>(dst) = v;
                         } else if (pairs && o + 8 <= p.m) {
                             for (int x = 0; x < 4; ++x) reinterpret_cast<uint32_t*>(dst)[x] = v[x];
@@ -555,9 +557,9 @@ static hipError_t mx_tile_launch_rows(const MxGemmDev& d, hipStream_t stream) {
 
 template <int TI, int TJ, int WM, int WN, int NST, int LA, typename Off = uint32_t>
 static hipError_t mx_tile_launch(const MxGemmDev& d, hipStream_t stream) {
-    switch (tiled_output(d.T, d.m, d.out, d.out_stride)) {
+    switch (tiled_output(d.out, d.out_stride)) {
         case Out::odd: return mx_tile_launch_rows<TI, TJ, WM, WN, NST, LA, Off, Out::odd>(d, stream);
-        case Out::streamed: return mx_tile_launch_rows<TI, TJ, WM, WN, NST, LA, Off, Out::streamed>(d, stream);
+        case Out::through: return mx_tile_launch_rows<TI, TJ, WM, WN, NST, LA, Off, Out::through>(d, stream);
         default: return mx_tile_launch_rows<TI, TJ, WM, WN, NST, LA, Off, Out::cached>(d, stream);
     }
 }

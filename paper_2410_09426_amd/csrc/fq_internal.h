@@ -117,10 +117,10 @@ struct MxGemmArgs {
 };
 hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream);
 
-// How the tiled products' output leaves: in halves (rows that are not all dword-aligned), or in 16-byte pieces where it can, through L2
-// or past it.
-enum class Out { odd, cached, streamed };
-Out tiled_output(int64_t T, int m, const void* out, int64_t out_stride);
+// How the tiled products' output leaves: in halves (rows that are not all dword-aligned), or in 16-byte pieces where it can, which
+// stay in L2 or are written through it.
+enum class Out { odd, cached, through };
+Out tiled_output(const void* out, int64_t out_stride);
 // Few-token products (fq_gemm.hip, fq_gemm_mx.hip): per wave a ring of LDS slots filled by global-to-LDS loads.
 constexpr int kRingMaxDepth = 8;
 constexpr int kRingLdsMax = 160 * 1024;

@@ -789,36 +789,32 @@ def test_tiled_products_at_every_output_alignment(tuning, kind, T, m, n, form):
 
 
 @pytest.mark.parametrize("form", [0, 1, 2, 4])
-@pytest.mark.parametrize("T,m", [(2200, 5000), (16500, 2048)])
+@pytest.mark.parametrize("T,m,n", [(300, 456, 256), (777, 1000, 1280)])
 @pytest.mark.parametrize("kind", ["int4", "mxfp4"])
-def test_tiled_products_with_large_and_small_outputs(tuning, kind, T, m, form):
-    """Outputs past 20 MB (rows that are not whole cache lines) or 64 MB leave through L2, smaller ones past it: the same bits, and nothing
-    beside the rows."""
+def test_tiled_products_write_through_whole_lines_only(tuning, kind, T, m, n, form):
+    """Rows of whole cache lines are written through L2, others stay in it: the same bits, and nothing beside the rows."""
     if kind == "mxfp4" and form == 4:
         pytest.skip("W4A4 only")
     tuning("FLATQUANT_GEMM_TILED", 1)
     tuning("FLATQUANT_GEMM_WIDE", form)
-    n = 256
     g = torch.Generator(device="cuda").manual_seed(T + m + form)
     codes = [torch.randint(0, 256, (r, n // 2), generator=g, device="cuda", dtype=torch.uint8) for r in (T, m)]
-    half = T // 256 * 128                 # whole 128-row tiles of exponents
     if kind == "int4":
         product = fq.flatquant_w4a4_gemm
         steps = [torch.rand(r, generator=g, device="cuda").half() * 0.1 for r in (T, m)]
-        tail = steps[0][half:]
     else:
         product = fq.flatquant_mxfp4_gemm
         steps = [torch.randint(118, 126, (fq.fq_mxfp4_tiled_scale_bytes(r, n),), generator=g, device="cuda", dtype=torch.uint8) for r in (T, m)]
-        tail = steps[0][fq.fq_mxfp4_tiled_scale_bytes(half, n):]
-    stride = m + 64
-    out = [torch.full((T, stride), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2)]
-    st = torch.cuda.current_stream()
-    print(f"[case] large output {kind} form={form} T={T} m={m}", flush=True)
-    product(codes[0], steps[0], codes[1], steps[1], T, m, n, out[0], stride, stream=st)
-    product(codes[0], steps[0], codes[1], steps[1], half, m, n, out[1], stride, stream=st)
-    product(codes[0][half:], tail, codes[1], steps[1], T - half, m, n, out[1][half:], stride, stream=st)
-    assert bool(torch.isfinite(out[0][:, :m]).all()) and bool(torch.isnan(out[0][:, m:]).all())
-    assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
+    got = []
+    for offset, stride in ((0, 64 * (m // 64 + 2)), (8, 64 * (m // 64 + 2)), (0, 64 * (m // 64 + 2) + 8)):
+        buf = torch.full((T * stride + 64,), float("nan"), dtype=torch.float16, device="cuda")
+        print(f"[case] whole lines {kind} form={form} T={T} m={m} offset={offset} stride={stride}", flush=True)
+        product(codes[0], steps[0], codes[1], steps[1], T, m, n, buf[offset:], stride, stream=torch.cuda.current_stream())
+        rows = buf[offset:offset + T * stride].view(T, stride)
+        assert bool(torch.isfinite(rows[:, :m]).all()) and bool(torch.isnan(rows[:, m:]).all())
+        assert bool(torch.isnan(buf[:offset]).all()) and bool(torch.isnan(buf[offset + T * stride:]).all())
+        got.append(rows[:, :m].contiguous().view(torch.int16))
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
 
 
 @pytest.mark.parametrize("waves,depth,rows,T,m,n", [(16, 1, 32, 5, 100, 4096), (16, 2, 16, 64, 70, 2304), (4, 3, 32, 20, 330, 11008), (8, 8, 16, 40, 64, 4096),
