@@ -99,12 +99,15 @@ struct FastLds {
     static constexpr int P2PASSES = N2 / P2ROWS;
     static constexpr int P1FLAT_BYTES = 32 * A * 32 * A * 2;
     static constexpr int STG_BYTES = P1FLAT_BYTES + P2ROWS * N2 * 2;
-    static constexpr int R0 = (cmax(BODY_BYTES, STG_BYTES) + 15) & ~15;
     // P1's fragments stay in registers up to three row tiles x six column slabs (86 x 128: 137 -> 130 us at T=16384,
-    // 6.7 -> 6.4 us at 64 tokens); beyond that they would spill, and are read from a table in LDS at every use
+    // 6.7 -> 6.4 us at 64 tokens); beyond that they would spill, and are read from a table in LDS at every use.  The table lies
+    // behind the loop's buffers and over the staging area, which its bytes leave by way of registers: with a place of its own behind
+    // both, four row tiles had one workgroup per CU at three and four slabs (now two) and two at one and two (now three).  us before /
+    // after: 112 x 128 16384 tokens 228 / 209, 64 tokens 8.0 / 7.6; 128 x 96 192 / 173 (16384); 104 x 64 124 / 105; 97 x 98 125 / 105 (8192)
     static constexpr bool P1LDS = (A >= 4) || (A == 3 && B >= 7);
     static constexpr int P1S_BYTES = P1LDS ? A * 2 * A * 64 * 16 : 0;
-    static constexpr int TOTAL = R0 + P1S_BYTES;
+    static constexpr int R0 = (BODY_BYTES + 15) & ~15;
+    static constexpr int TOTAL = (cmax(R0 + P1S_BYTES, STG_BYTES) + 15) & ~15;
 };
 
 }  // namespace fq

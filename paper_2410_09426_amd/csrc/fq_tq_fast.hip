@@ -200,6 +200,8 @@ __global__ __launch_bounds__(64 * (B / SPW) * TPW) __attribute__((amdgpu_waves_p
     };
     half8 p2f[ID2 ? 1 : SPW][ID2 ? 1 : KB2];
     half8 p1f[P1LDS ? 1 : A][P1LDS ? 1 : KB1];
+    constexpr int NP1S = P1LDS ? (A * KB1 * 64 + NT - 1) / NT : 1;
+    half8 p1s[NP1S];                     // on their way from the staging area into the table
 #pragma unroll
     for (int pass = 0; pass < (ID2 ? 1 : L::P2PASSES); ++pass) {
         constexpr int CH = L::P2ROWS * N2 / 8;
@@ -237,11 +239,12 @@ __global__ __launch_bounds__(64 * (B / SPW) * TPW) __attribute__((amdgpu_waves_p
             // K block kk, slot s, half-wave h  <->  i = 32(kk/2) + 8(2(kk%2) + s/4) + 4h + s%4.  The LDS copy is padded with
             // zeros to whole row tiles, so ragged factors take the same transposing reads as full ones.
             if constexpr (P1LDS) {
-                for (int e = tid; e < A * KB1 * 64; e += NT) {   // e % 64 is the lane: whole 16-lane blocks cooperate in the reads
-                    const int ln = e & 63, kk = (e >> 6) % KB1, It = (e >> 6) / KB1;
+#pragma unroll
+                for (int k = 0; k < NP1S; ++k) {   // e % 64 is the lane: whole 16-lane blocks cooperate in the reads
+                    const int e = tid + k * NT < A * KB1 * 64 ? tid + k * NT : 0;
+                    const int ln = tid & 63, kk = (e >> 6) % KB1, It = (e >> 6) / KB1;
                     const int cc = ln & 31, hh = ln >> 5;
-                    const half8 f = lds_column8(P1flat, 32 * A, 32 * (kk >> 1) + 16 * (kk & 1) + 4 * hh, 8, 32 * It + (cc & 16), ln & 15);
-                    *reinterpret_cast<half8*>(&P1s[e]) = f;
+                    p1s[k] = lds_column8(P1flat, 32 * A, 32 * (kk >> 1) + 16 * (kk & 1) + 4 * hh, 8, 32 * It + (cc & 16), ln & 15);
                 }
             } else {
 #pragma unroll
@@ -263,6 +266,11 @@ __global__ __launch_bounds__(64 * (B / SPW) * TPW) __attribute__((amdgpu_waves_p
             __syncthreads();
         }
     };
+    if constexpr (P1LDS) {
+#pragma unroll
+        for (int k = 0; k < NP1S; ++k)
+            if (tid + k * NT < A * KB1 * 64) *reinterpret_cast<half8*>(&P1s[tid + k * NT]) = p1s[k];
+    }
     commit(pre0, ts);
     token_sync();
 

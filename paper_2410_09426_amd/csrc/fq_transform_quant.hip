@@ -397,10 +397,14 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(A <= 2 ?
     }
 }
 
-// where P1's fragment table starts behind a token tile and the staged values of MXFP4 (or the factors, whichever is larger)
+// where P1's fragment table starts behind a token tile and the staged values of MXFP4, and the bytes in all (the factors' may be more)
 template <int A, int B>
 __host__ __device__ constexpr int any_mx_r0(int n) {
-    return (cmax(FastLds<A, B>::STG_BYTES, FastLds<A, B>::XS_BYTES + 64 + n / 32 * 144) + 15) & ~15;
+    return (FastLds<A, B>::XS_BYTES + 64 + n / 32 * 144 + 15) & ~15;
+}
+template <int A, int B>
+constexpr int any_mx_lds(int n) {
+    return (cmax(any_mx_r0<A, B>(n) + FastLds<A, B>::P1S_BYTES, FastLds<A, B>::STG_BYTES) + 15) & ~15;
 }
 
 // Any pair of factors (n2 >= 8; INT4: either may be left out: identity): the plain loop of the specialised kernels (fq_tq_fast.hip:
@@ -480,6 +484,8 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
     // ---- the factors: requested, then their LDS image zeroed, then put into it; fragments by transposing reads
     half8 p2f[KB2];
     half8 p1f[P1LDS ? 1 : A][P1LDS ? 1 : KB1];
+    constexpr int NP1S = P1LDS ? (A * KB1 * 64 + NT - 1) / NT : 1;
+    half8 p1s[NP1S];                             // on their way from the staging area into the table
     constexpr int N1P = (PW * PW / 2 + NT - 1) / NT, B1 = N1P < 16 ? N1P : 16;          // pairs of P1 per thread, and in flight
     constexpr int N2C = (L::P2ROWS * N2 / 8 + NT - 1) / NT;                            // chunks of P2 per thread and pass
 #pragma unroll
@@ -552,10 +558,11 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
             p2f[kb] = lds_column8(P2flat, N2, 16 * kb - r0 + 8 * h, 4, 32 * w + (c & 16), l & 15);
         if (pass == 0) {
             if constexpr (P1LDS) {
-                for (int e = tid; e < A * KB1 * 64; e += NT) {
-                    const int ln = e & 63, kk = (e >> 6) % KB1, It = (e >> 6) / KB1;
-                    const half8 f = lds_column8(P1flat, PW, 32 * (kk >> 1) + 16 * (kk & 1) + 4 * (ln >> 5), 8, 32 * It + (ln & 16), ln & 15);
-                    *reinterpret_cast<half8*>(&P1s[e]) = f;
+#pragma unroll
+                for (int k = 0; k < NP1S; ++k) {
+                    const int e = tid + k * NT < A * KB1 * 64 ? tid + k * NT : 0;
+                    const int kk = (e >> 6) % KB1, It = (e >> 6) / KB1;
+                    p1s[k] = lds_column8(P1flat, PW, 32 * (kk >> 1) + 16 * (kk & 1) + 4 * h, 8, 32 * It + (c & 16), l & 15);
                 }
             } else {
 #pragma unroll
@@ -567,6 +574,11 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
     }
     __syncthreads();   // the staging area becomes the token tile; what no token's row covers stays zero
     for (int q = tid; q < L::XS_BYTES / 16; q += NT) reinterpret_cast<u32x4*>(smem)[q] = u32x4{0u, 0u, 0u, 0u};
+    if constexpr (P1LDS) {
+#pragma unroll
+        for (int k = 0; k < NP1S; ++k)
+            if (tid + k * NT < A * KB1 * 64) *reinterpret_cast<half8*>(&P1s[tid + k * NT]) = p1s[k];
+    }
     __syncthreads();
     commit(pre0);
     __syncthreads();
@@ -756,7 +768,7 @@ template <int A, int B>
 static AnyVariant any_variant_ab(bool mx, int n) {
     if (mx) {
         if constexpr (mx_staged_lds(A, B) > kLdsMax) return {nullptr, kLdsMax + 1};
-        else return {&tq_any_kernel<A, B, true>, any_mx_r0<A, B>(n) + FastLds<A, B>::P1S_BYTES};
+        else return {&tq_any_kernel<A, B, true>, any_mx_lds<A, B>(n)};
     }
     return {&tq_any_kernel<A, B, false>, FastLds<A, B>::TOTAL};
 }
@@ -847,7 +859,7 @@ static constexpr KernelFn mx_kernel_for() {
     if constexpr (A == 1 || B == 1 || (A == 3 && B == 2) || (A == 4 && B == 5)) {
         return &tq_kernel<A, B, (A >= 3), true>;
     } else {
-        static_assert(mx_staged_lds(A, B) > kLdsMax || any_mx_r0<A, B>(1024 * A * B) + FastLds<A, B>::P1S_BYTES <= kLdsMax, "tq_any_kernel takes all of these rows");
+        static_assert(mx_staged_lds(A, B) > kLdsMax || any_mx_lds<A, B>(1024 * A * B) <= kLdsMax, "tq_any_kernel takes all of these rows");
         return nullptr;
     }
 }
