@@ -11,7 +11,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libflatquant.so")
 # CPython calls of the library's entry points: host code that links nothing, for the interpreter that builds it (its name says which)
 CALLS = os.path.join(PKG, "_fqcall" + sysconfig.get_config_var("EXT_SUFFIX"))
-SOURCES = ["fq_api.hip", "fq_transform_quant.hip", "fq_tq_fast.hip", "fq_tq_wave.hip", "fq_kv.hip", "fq_dequant.hip", "fq_probe.hip", "fq_gemm.hip", "fq_gemm_mx.hip"]
+SOURCES = ["fq_api.hip", "fq_transform_quant.hip", "fq_tq_fast.hip", "fq_tq_wave.hip", "fq_tq_rows.hip", "fq_kv.hip", "fq_dequant.hip", "fq_probe.hip", "fq_gemm.hip", "fq_gemm_mx.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          # keep hipcc from forming packed-fp32 VALU ops from scalar float code
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

@@ -632,28 +632,29 @@ struct Variant {
 // mode 3: one slab per wave, one token per workgroup (only when every token can have a resident workgroup);
 // mode 4 (n2 = 64): one wave per token, kTokensPerWg tokens per workgroup sharing the staged transforms, no loop
 constexpr int kTokensPerWg = 4;
+// an instance, if any left factor of these row tiles gets here (rows_kernel_takes)
+template <int A, int B, int SPW, bool FULL1, int KIND, int TPW, bool MX>
+static Variant slab() {
+    constexpr int NBUF = KIND == 1 ? 2 : TPW;
+    if constexpr (slab_kernel_reached(A, B, FULL1, MX)) return {&tq_fast_kernel<A, B, SPW, FULL1, KIND, false, TPW, MX>, FastLds<A, B, NBUF, MX>::TOTAL + (MX ? 32 * A * B : 0)};
+    else return {nullptr, 0};
+}
+template <int A, int B, int SPW, int KIND, int TPW = 1, bool MX = false>
+static Variant slab_of(bool full1) { return full1 ? slab<A, B, SPW, true, KIND, TPW, MX>() : slab<A, B, SPW, false, KIND, TPW, MX>(); }
+
 template <int A, int B>
 static Variant variant_ab(bool full1, int mode) {
     if constexpr (A <= 2 && (B == 2 || B == 4 || B == 8)) {
-        if (mode == 1)
-            return full1 ? Variant{&tq_fast_kernel<A, B, 2, true, 0>, FastLds<A, B>::TOTAL}
-                         : Variant{&tq_fast_kernel<A, B, 2, false, 0>, FastLds<A, B>::TOTAL};
+        if (mode == 1) return slab_of<A, B, 2, 0>(full1);
     }
     if constexpr (A <= 2 && B == 2) {
-        if (mode == 4)
-            return full1 ? Variant{&tq_fast_kernel<A, B, 2, true, 2, false, kTokensPerWg>, FastLds<A, B, kTokensPerWg>::TOTAL}
-                         : Variant{&tq_fast_kernel<A, B, 2, false, 2, false, kTokensPerWg>, FastLds<A, B, kTokensPerWg>::TOTAL};
+        if (mode == 4) return slab_of<A, B, 2, 2, kTokensPerWg>(full1);
     }
     if constexpr (A <= 2) {
-        if (mode == 2)
-            return full1 ? Variant{&tq_fast_kernel<A, B, 1, true, 1>, FastLds<A, B, 2>::TOTAL}
-                         : Variant{&tq_fast_kernel<A, B, 1, false, 1>, FastLds<A, B, 2>::TOTAL};
-        if (mode == 3)
-            return full1 ? Variant{&tq_fast_kernel<A, B, 1, true, 2>, FastLds<A, B>::TOTAL}
-                         : Variant{&tq_fast_kernel<A, B, 1, false, 2>, FastLds<A, B>::TOTAL};
+        if (mode == 2) return slab_of<A, B, 1, 1>(full1);
+        if (mode == 3) return slab_of<A, B, 1, 2>(full1);
     }
-    return full1 ? Variant{&tq_fast_kernel<A, B, 1, true, 0>, FastLds<A, B>::TOTAL}
-                 : Variant{&tq_fast_kernel<A, B, 1, false, 0>, FastLds<A, B>::TOTAL};
+    return slab_of<A, B, 1, 0>(full1);
 }
 
 template <int A>
@@ -684,10 +685,9 @@ static Variant variant(int A, int B, bool full1, int mode) {
 template <int A, int B>
 static Variant variant_mx_ab(bool full1, bool one) {
     if constexpr (A <= 2 && B == 2) {
-        if (one && full1) return Variant{&tq_fast_kernel<A, B, 1, true, 2, false, 1, true>, FastLds<A, B, 1, true>::TOTAL + 32 * A * B};
+        if (one && full1) return slab<A, B, 1, true, 2, 1, true>();
     }
-    return full1 ? Variant{&tq_fast_kernel<A, B, 1, true, 0, false, 1, true>, FastLds<A, B, 1, true>::TOTAL + 32 * A * B}
-                 : Variant{&tq_fast_kernel<A, B, 1, false, 0, false, 1, true>, FastLds<A, B, 1, true>::TOTAL + 32 * A * B};
+    return slab_of<A, B, 1, 0, 1, true>(full1);
 }
 
 template <int A>
@@ -727,6 +727,7 @@ hipError_t tq_mx_launch(const TqDev& d, hipStream_t stream) {
         if ((m == -1 || m == 5 || m == 6) && tq_wave_applicable(d) && (reinterpret_cast<uintptr_t>(d.out_scales) & 7) == 0)
             return tq_wave_launch(d, stream, tuned(Knob::WAVE_TPW, 4), m == -1 ? d.T >= 32768 : m == 6, true);
     }
+    if (rows_kernel_takes(d.n1, d.n2 / 32, true)) return tq_rows_launch(d, stream, true);
     const int A = (d.n1 + 31) / 32, B = d.n2 / 32;
     const bool full1 = (d.n1 % 32) == 0;
     static OccCache occ_cache[4][8][2][2];
@@ -774,6 +775,7 @@ bool tq_fast_applicable(const TqDev& d) {
 int64_t tq_fast_lds_bytes(int n1, int n2) {
     if (n1 < 1 || n1 > kMaxN1 || n2 < 32 || n2 > kMaxN2 || n2 % 32) return 0;
     const int A = (n1 + 31) / 32;
+    if (rows_kernel_takes(n1, n2 / 32, false)) return tq_rows_lds_bytes(n1, n2);
     const int a = variant(A, n2 / 32, n1 % 32 == 0, 0).lds, b = variant(A, n2 / 32, n1 % 32 == 0, 2).lds;
     return a > b ? a : b;
 }
@@ -828,6 +830,7 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
         }
         return launch(v.fn, dim3((unsigned)grid), dim3(256), v.lds, stream, d, d.clip);
     }
+    if (rows_kernel_takes(d.n1, B, false)) return tq_rows_launch(d, stream, false);
     {   // 64-wide rows (n1 = 32 or 64): the wave-per-token kernel (fq_tq_wave.hip).  Mode 5: one token per wave, the
         // hardware hands out workgroups as earlier ones retire; mode 6: persistent workgroups.  Measured on MI355X
         // (64 x 64, same run, us per launch; loop-free / persistent):

@@ -309,6 +309,20 @@ def test_mxfp4_output_shape_grid(n1, n2, T):
     run_mx(c, rows=None if T <= 300 else subset_rows(T, 100, n1, must=(0, 1, 2047, 2048, T - 2)))
 
 
+@pytest.mark.parametrize("n1,n2", [(32, 160), (33, 96), (48, 64), (63, 192), (64, 128), (65, 256), (80, 160), (81, 128), (96, 256), (97, 64), (111, 128), (112, 256),
+                                   (112, 224), (113, 224), (127, 160)])
+@pytest.mark.parametrize("T", [1, 600, 1027])
+def test_row_tiles_of_16(n1, n2, T):
+    """The kernel with row tiles of 16: odd and even numbers of them, full and ragged, P1 as whole tiles, by pairs and through registers
+    (odd lengths), one token per workgroup and several, both formats."""
+    print(f"[case] row tiles of 16 {n1}x{n2} T={T}", flush=True)
+    c = synth.generic(1000 + 7 * n1 + n2 + T, T, n1, n2, clip_mode=T % 2)
+    rows = None if T == 1 else subset_rows(T, 60, n1, must=(0, 255, 256, 511, 512, T - 1))
+    check_case(c, rows=rows, with_dequant=False, label=f"row tiles {n1}x{n2}")
+    if n1 * n2 % 128 == 0:
+        run_mx(c, rows=rows)
+
+
 @pytest.mark.parametrize("mode", ["-1", "0", "3"])
 def test_mxfp4_output(tuning, mode):
     if mode != "-1":
