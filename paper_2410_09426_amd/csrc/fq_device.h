@@ -103,7 +103,7 @@ struct FastLds {
     // 6.7 -> 6.4 us at 64 tokens); beyond that they would spill, and are read from a table in LDS at every use.  The table lies
     // behind the loop's buffers and over the staging area, which its bytes leave by way of registers: with a place of its own behind
     // both, four row tiles had one workgroup per CU at three and four slabs (now two) and two at one and two (now three).  us before /
-    // after: 112 x 128 16384 tokens 228 / 209, 64 tokens 8.0 / 7.6; 128 x 96 192 / 173 (16384); 104 x 64 124 / 105; 97 x 98 125 / 105 (8192)
+    // after: 128 x 128 16384 tokens 239 / 220, 64 tokens 6.6 / 6.4; 128 x 96 192 / 173 (16384); tq_any_kernel 97 x 98 125 / 105 (8192), 120 x 28 63 / 49
     static constexpr bool P1LDS = (A >= 4) || (A == 3 && B >= 7);
     static constexpr int P1S_BYTES = P1LDS ? A * 2 * A * 64 * 16 : 0;
     static constexpr int R0 = (BODY_BYTES + 15) & ~15;

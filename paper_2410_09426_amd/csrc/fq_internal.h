@@ -61,27 +61,29 @@ int64_t tq_rows_lds_bytes(int n1, int n2);
 hipError_t tq_rows_launch(const TqDev& d, hipStream_t stream, bool mx);
 // Whether a left factor of n1 rows and a right factor of 32 B columns go to tq_rows_kernel rather than to tq_fast_kernel; both give the same
 // bytes.  tq_fast_kernel / tq_rows_kernel in us, tokens in parentheses: row tiles that are not full gain most, by the 16 rows that are no longer
-// padding and by the prologue: 48 x 64 4.2 / 3.4 (64), 43 / 34 (16384); 72 x 128 5.9 / 5.1, 136 / 122; 86 x 128 6.0 / 4.9, 143 / 141; 104 x 64 8.5 / 5.2,
-// 127 / 89; 112 x 128 7.8 / 6.0, 122 / 99 (8192); 112 x 256 11.9 / 10.8, 493 / 447 (16384); MXFP4 112 x 224 13.5 / 8.6, 302 / 203 (8192).  Full ones gain by one
+// padding and by the prologue: 48 x 64 4.2 / 3.3 (64), 44 / 29 (16384); 72 x 128 5.9 / 5.0, 135 / 111; 86 x 128 6.0 / 4.9, 142 / 136; 104 x 64 8.5 / 5.2,
+// 127 / 89; 112 x 128 7.8 / 6.0, 122 / 99 (8192); 112 x 256 11.7 / 10.7, 490 / 425 (16384); MXFP4 112 x 224 13.5 / 8.6, 302 / 203 (8192).  Full ones gain by one
 // barrier less per token and by tokens that arrive straight in LDS: 32 x 160 7.8 / 4.8 (512), 87 / 68 (16384); 64 x 96 5.5 / 4.5, 71 / 67; 64 x 128 4.2 / 4.0 (64),
 // 14.6 / 13.2 (2048); 96 x 256 9.6 / 8.2 (64), 55 / 52 (2048); 128 x 224 10.3 / 9.2, 69 / 66, MXFP4 13.2 / 9.1, 87 / 64.
 // Not taken: 32- and 64-wide rows of full tiles (wave-per-token kernel); five slabs of 49 .. 64 rows, which tq_fast_kernel has two workgroups
 // per CU for (12.4 / 14.0 at 1024); eight slabs of 64 rows; 113 rows on with up to four slabs (128 x 128 113 / 124 at 8192) and with eight, whose two
-// tiles LDS has no room for; MXFP4 at 32 rows with an even number of slabs (32 x 128 39 / 43 at 16384).
-constexpr bool rows_kernel_takes(int n1, int B, bool mx) {
+// tiles LDS has no room for; MXFP4 at 32 rows with an even number of slabs (32 x 128 39 / 43 at 16384) and long launches of 49 .. 63 x 64 (56 x 64
+// 8.4 / 7.4 at 2048, 37 / 38 at 16384).
+constexpr bool rows_kernel_takes(int n1, int B, bool mx, int64_t T) {
     if (B < 2 || B > 8) return false;
     switch ((n1 + 15) / 16) {
         case 2: return n1 == 32 && B >= 3 && (!mx || B % 2 == 1);
-        case 4: return n1 == 64 ? B >= 3 && B != 5 && B != 8 : B != 5;
+        case 4: return n1 == 64 ? B >= 3 && B != 5 && B != 8 : B != 5 && !(B == 2 && mx && T > 8192);
         case 8: return B >= 5 && B <= 7;
         default: return n1 > 16;
     }
 }
-// whether any left factor of A row tiles of 32, full or not, is left to tq_fast_kernel
+// whether any left factor of A row tiles of 32, full or not, is left to tq_fast_kernel (by many tokens, if not by all)
 constexpr bool slab_kernel_reached(int A, int B, bool full, bool mx) {
-    if (full) return !rows_kernel_takes(32 * A, B, mx);
+    constexpr int64_t many = INT64_MAX;
+    if (full) return !rows_kernel_takes(32 * A, B, mx, many);
     for (int n1 = 32 * A - 31; n1 < 32 * A; ++n1)
-        if (!rows_kernel_takes(n1, B, mx)) return true;
+        if (!rows_kernel_takes(n1, B, mx, many)) return true;
     return false;
 }
 // MXFP4 output variant of the specialised kernels (d.out_scales points at the u8 [T, n/32] shared exponents).

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(64 * (B / SPW) * TPW) __attribute__((amdgpu_waves_p
             }
         } else if constexpr (A >= 4) {
             // Four row tiles (97 .. 127 rows): a wave takes whole rows, a lane the same pair of columns of each, so that a row costs a load, a
-            // store and hardly any arithmetic (64 tokens, against the copy below: 112 x 128 9.1 -> 8.1 us, 112 x 256 13.3 -> 12.6; with
+            // store and hardly any arithmetic (64 tokens, against the copy below, on factors that tq_rows_kernel has taken since: 112 x 128 9.1 -> 8.1 us, 112 x 256 13.3 -> 12.6; with
             // shorter rows, most of whose lanes have nothing to load, that one is as fast or faster: 86 x 128 6.3 / 6.2, 48 x 64
             // 4.4 / 5.1).  The LDS rows have the pitch of whole row tiles, the padding is zero.  Odd rows start on odd
             // halves (unaligned dwords); their last pair is loaded one half early, so that nothing past the matrix is read.
@@ -727,7 +727,7 @@ hipError_t tq_mx_launch(const TqDev& d, hipStream_t stream) {
         if ((m == -1 || m == 5 || m == 6) && tq_wave_applicable(d) && (reinterpret_cast<uintptr_t>(d.out_scales) & 7) == 0)
             return tq_wave_launch(d, stream, tuned(Knob::WAVE_TPW, 4), m == -1 ? d.T >= 32768 : m == 6, true);
     }
-    if (rows_kernel_takes(d.n1, d.n2 / 32, true)) return tq_rows_launch(d, stream, true);
+    if (rows_kernel_takes(d.n1, d.n2 / 32, true, d.T)) return tq_rows_launch(d, stream, true);
     const int A = (d.n1 + 31) / 32, B = d.n2 / 32;
     const bool full1 = (d.n1 % 32) == 0;
     static OccCache occ_cache[4][8][2][2];
@@ -775,7 +775,7 @@ bool tq_fast_applicable(const TqDev& d) {
 int64_t tq_fast_lds_bytes(int n1, int n2) {
     if (n1 < 1 || n1 > kMaxN1 || n2 < 32 || n2 > kMaxN2 || n2 % 32) return 0;
     const int A = (n1 + 31) / 32;
-    if (rows_kernel_takes(n1, n2 / 32, false)) return tq_rows_lds_bytes(n1, n2);
+    if (rows_kernel_takes(n1, n2 / 32, false, 1)) return tq_rows_lds_bytes(n1, n2);
     const int a = variant(A, n2 / 32, n1 % 32 == 0, 0).lds, b = variant(A, n2 / 32, n1 % 32 == 0, 2).lds;
     return a > b ? a : b;
 }
@@ -784,9 +784,9 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
     const int A = (d.n1 + 31) / 32, B = d.n2 / 32;
     const bool full1 = (d.n1 % 32) == 0;
     // Kernel flavour (see variant_ab), from measurements on MI355X (tables below): 64-wide rows belong to the
-    // wave-per-token kernel except for the smallest launches; when every token can have its own resident workgroup the
-    // loop-free kernel wins; of the two persistent loops the pipelined one wins for 32 x 128 from 16384 tokens on and
-    // for the other shapes with at most two row tiles, the plain one for 64 x 128 and for three or four row tiles.
+    // wave-per-token kernel except for the smallest launches; most other factors to tq_rows_kernel (rows_kernel_takes).  Of
+    // what is left: when every token can have its own resident workgroup the loop-free kernel wins; of the two persistent
+    // loops the pipelined one wins with at most two row tiles, the plain one for 64 x 256 and for four row tiles.
     // What the loop-free kernel pays per workgroup is the staging of P1 and P2.  FLATQUANT_MODE overrides the choice
     // for tuning and tests.
     static OccCache occ_cache[4][8][2][5];   // per variant and device
@@ -830,7 +830,7 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
         }
         return launch(v.fn, dim3((unsigned)grid), dim3(256), v.lds, stream, d, d.clip);
     }
-    if (rows_kernel_takes(d.n1, B, false)) return tq_rows_launch(d, stream, false);
+    if (rows_kernel_takes(d.n1, B, false, d.T)) return tq_rows_launch(d, stream, false);
     {   // 64-wide rows (n1 = 32 or 64): the wave-per-token kernel (fq_tq_wave.hip).  Mode 5: one token per wave, the
         // hardware hands out workgroups as earlier ones retire; mode 6: persistent workgroups.  Measured on MI355X
         // (64 x 64, same run, us per launch; loop-free / persistent):
@@ -842,20 +842,18 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
         if ((m == 5 || m == 6 || (m == -1 && d.T > 256)) && tq_wave_applicable(d))
             return tq_wave_launch(d, stream, tuned(Knob::WAVE_TPW, 4), m == -1 ? d.T >= 32768 : m == 6, false);
     }
-    // 128-wide rows (replayed from a HIP graph up to T = 8192, cold rotation above; us per launch, loop-free / plain
-    // loop / pipelined loop): 64 x 128: T = 64 4.2 / 4.4 / 4.9, 512 7.7 / 7.7 / 9.3, 1024 10.5 / 10.7 / 11.4,
-    // 2048 17.0 / 15.7 / 16.6, 4096 29.5 / 25.6 / 27.2, 8192 53.5 / 45.2 / 46.7, 16384 - / 75 / 94, 32768 - / 162 / 189;
-    // 32 x 128: T = 512 5.4 / 5.4 / 6.6, 1536 10.6 / 8.7 / 9.4, 4096 20.5 / 14.3 / 15.6, 8192 35.8 / 24.5 / 25.6,
-    // 16384 - / 41.4 / 38.0.
+    // 128-wide rows of one row tile (here n1 < 32; measured on 32 x 128; replayed from a HIP graph up to T = 8192, cold rotation
+    // above; us per launch, loop-free / plain loop / pipelined loop): T = 512 5.4 / 5.4 / 6.6, 1536 10.6 / 8.7 / 9.4,
+    // 4096 20.5 / 14.3 / 15.6, 8192 35.8 / 24.5 / 25.6, 16384 - / 41.4 / 38.0.
     int mode = (A <= 2) ? 2 : 0;
-    if (A == 2 && (B == 4 || B >= 7)) mode = 0;   // (64 x 256, T = 16384: 226 against 290 us)
+    if (A == 2 && B == 8) mode = 0;   // (64 x 256, T = 16384: 226 against 290 us)
     if (A == 1 && B == 4 && d.T <= 8192) mode = 0;
     if (A <= 2 && B == 2 && d.T >= 32768) mode = 1;
     if (A <= 2 && (B <= 2 || B == 4)) {
         int occ3 = 0;
         hipError_t e = occupancy(3, occ3);
         if (e != hipSuccess) return e;
-        if (B == 4 ? d.T <= (A == 2 ? 1024 : 512) : d.T <= (int64_t)cu_count() * occ3) mode = 3;
+        if (B == 4 ? d.T <= 512 : d.T <= (int64_t)cu_count() * occ3) mode = 3;
         // past that, and up to where the wave-per-token loop takes over, 64-wide rows do best without a loop as well:
         // workgroups of kTokensPerWg single-wave tokens, handed out by the hardware as earlier ones retire
         // (measured at T = 3072 .. 16384: 3 - 8 % over the pipelined loop)

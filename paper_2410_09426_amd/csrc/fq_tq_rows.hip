@@ -6,9 +6,9 @@
 // group, one after the other: v_mfma_f32_16x16x32_f16 gives the bits of two v_mfma_f32_32x32x16_f16).  Large launches are bound by the power that fp16
 // MFMAs draw (112 x 256 at 16384 tokens, tq_fast_kernel: 490 us, 361 on all-zero rows) and small ones by the prologue's chain of latencies, so
 // what counts is work not done:
-//   * 112 rows are seven tiles of 16, not four of 32, in both contractions (112 x 256 at 16384 tokens 493 -> 447 us).  With an odd number of row
+//   * 112 rows are seven tiles of 16, not four of 32, in both contractions (112 x 256 at 16384 tokens 490 -> 425 us).  With an odd number of row
 //     tiles the first one goes by MFMAs of 16 rows, and Z's accumulators (four rows of a column per lane) become the second one's operand by
-//     exchanges between lane groups; the last 16 columns of Y take hi and lo parts in one MFMA.  Even numbers go by tiles of 32.
+//     exchanges between lane groups (v_permlane16_swap, v_permlane32_swap).  Even numbers go by tiles of 32.
 //   * Two tiles of LDS per workgroup, filled by global-to-LDS loads with the 16-byte chunks swizzled: no registers and no LDS writes by the
 //     waves, and one barrier per token (the absmax exchange, which also hands the tiles over), so that a wave rounds and stores its codes
 //     while others are in the next token's MFMAs (64 x 128 at 2048 tokens 14.6 -> 13.2, 96 x 256 55 -> 52).
@@ -25,14 +25,20 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // staging lies over all of it.
 template <int R, int B, bool MX>
 struct RowsLds {
-    static constexpr int N2 = 32 * B, PW = 16 * R, NF = R * ((R + 1) / 2);   // NF: fragments of P1
-    static constexpr bool P1REG = R <= 6 || (R == 7 && B <= 4);    // P1's fragments beside P2's in registers
+    static constexpr int N2 = 32 * B, PW = 16 * R;
+    // Odd numbers of row tiles: all of Y by tiles of 16 columns, whose hi and lo parts share an MFMA: fewer exchanges, less power, twice the
+    // fragments of P1.  us with tiles of 32 and a last one of 16 / of 16: 72 x 128 at 16384 tokens 122 / 111, 48 x 128 77 / 68, 48 x 64 32 / 29, 112 x 256 at 8192
+    // 246 / 231.  Not where only the former's fragments fit in registers (112 x 128 187 / 212), nor for even numbers (86 x 128 136 / 144).
+    static constexpr bool T16 = R % 2 == 1 && (R <= 5 || B > 4);
+    static constexpr int E = T16 ? 0 : R / 2, NT16 = R - 2 * E, EN = E + NT16, NF = R * EN;   // tiles of 32 and of 16 columns of Y, fragments of P1
+    static constexpr int FRAG = T16 ? 512 : 1024;                  // both half-waves have the same fragment for tiles of 16
+    static constexpr bool P1REG = T16 ? R <= 5 : R <= 6 || (R == 7 && B <= 4);    // P1's fragments beside P2's in registers
     static constexpr int TILE = 16 * R * N2 * 2;
     static constexpr int P1FLAT_BYTES = PW * PW * 2, STG_BYTES = P1FLAT_BYTES + N2 * N2 * 2;
     // the second tile lies behind the staging area, where that leaves room for two waves per SIMD (two slabs: four): its token is requested at once
     static constexpr bool EARLY = P1REG && STG_BYTES + TILE + 64 + (MX ? 32 * R * B : 0) <= 160 * 1024 / (B >= 5 ? 1 : B >= 3 ? 2 : 8);
     static constexpr int TILE1 = EARLY ? STG_BYTES : TILE;
-    static constexpr int P1S = TILE1 + TILE, P1S_BYTES = P1REG ? 0 : NF * 1024;
+    static constexpr int P1S = TILE1 + TILE, P1S_BYTES = P1REG ? 0 : NF * FRAG;
     static constexpr int RED = P1S + P1S_BYTES, EXPS = RED + 64, EXPS_BYTES = 16 * R * B;
     static constexpr int TOTAL = (cmax(EXPS + (MX ? 2 * EXPS_BYTES : 0), STG_BYTES) + 15) & ~15;
 };
@@ -40,13 +46,12 @@ struct RowsLds {
 template <int R, int B, bool MX>
 __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) void tq_rows_kernel(TqDev p, const float* __restrict__ clip) {
     using L = RowsLds<R, B, MX>;
-    constexpr int N2 = L::N2, PW = L::PW, NF = L::NF, NT = 64 * B, E = R / 2, EN = (R + 1) / 2;   // E: row tiles of 32, EN: and the last 16
-    constexpr bool ODD = R % 2 != 0;
+    constexpr int N2 = L::N2, PW = L::PW, NF = L::NF, NT = 64 * B, E = L::E, NT16 = L::NT16, EN = L::EN;
+    constexpr bool ODD = NT16 > 0;             // MFMAs of 16 rows in the first contraction
     constexpr bool P1REG = L::P1REG;
     constexpr int SW = B % 4 == 0 ? 15 : B % 2 == 0 ? 7 : 3, SWS = B % 4 == 0 ? 0 : B % 2 == 0 ? 1 : 2;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     float* red = reinterpret_cast<float*>(smem + L::RED);
-    u32x4* P1s = reinterpret_cast<u32x4*>(smem + L::P1S);
     _Float16* P1flat = reinterpret_cast<_Float16*>(smem);
     _Float16* P2flat = reinterpret_cast<_Float16*>(smem + L::P1FLAT_BYTES);
     typedef __attribute__((address_space(3))) void* lptr;
@@ -146,14 +151,14 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll
     for (int k = 0; k < NP1; ++k) {
         const int e = P1REG ? k : w + B * k < NF ? w + B * k : 0, kk = e / EN, It = e % EN;
-        const bool last = ODD && It == E;
-        p1f[k] = lds_column8(P1flat, PW, 16 * kk + 4 * (last ? q & 1 : h), 8, 32 * It + (last ? 0 : c32 & 16), c);
+        const bool last = It >= E;
+        p1f[k] = lds_column8(P1flat, PW, 16 * kk + 4 * (last ? q & 1 : h), 8, last ? 32 * E + 16 * (It - E) : 32 * It + (c32 & 16), c);
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the staging area is free
     if constexpr (!P1REG) {
 #pragma unroll
         for (int k = 0; k < NP1; ++k)
-            if (w + B * k < NF) *reinterpret_cast<half8*>(&P1s[(w + B * k) * 64 + l]) = p1f[k];
+            if (w + B * k < NF && (L::FRAG == 1024 || h == 0)) *reinterpret_cast<half8*>(smem + L::P1S + (w + B * k) * L::FRAG + 16 * (L::FRAG == 1024 ? l : c32)) = p1f[k];
     }
 #pragma unroll
     for (int k = 0; k < R; ++k) *reinterpret_cast<u32x4*>(smem + (w + B * k) * 1024 + 16 * l) = pre[k];
@@ -180,14 +185,16 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
 #pragma unroll 1
     for (int buf = 0;; buf ^= 1, t += G) {
         const float clipv = clip[p.clip_mode ? t : 0];
-        f32x16 acc[E];
-        f32x4 tail[2];                                             // ODD: columns n1 - 16 .. of Y, 16 channels each
+        f32x16 acc[E > 0 ? E : 1];
+        f32x4 tail[NT16 > 0 ? NT16 : 1][2];                        // columns 32 E + 16 j .. of Y, 16 channels each
 #pragma unroll
         for (int It = 0; It < E; ++It)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[It][r] = 0.0f;
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) tail[ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j = 0; j < NT16; ++j)
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct) tail[j][ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         constexpr int NX = ODD ? 4 : 8, STEP = ODD ? 4 : 2;        // operands of 256 bytes of a row, chunks from one to the next
         const unsigned char* xb[NX];
 #pragma unroll
@@ -195,9 +202,9 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
         auto operand = [&](int m, int tile) {                      // tile: of 32 rows, ODD: 16
             return *reinterpret_cast<const half8*>(xb[m % NX] + (m / NX) * 256 + tile * (ODD ? 16 : 32) * 64 * B);
         };
-        auto p1 = [&](int e) { return P1REG ? p1f[P1REG ? e : 0] : *reinterpret_cast<const half8*>(&P1s[e * 64 + l]); };
+        auto p1 = [&](int e) { return P1REG ? p1f[P1REG ? e : 0] : *reinterpret_cast<const half8*>(smem + L::P1S + e * L::FRAG + 16 * (L::FRAG == 1024 ? l : c32)); };
         auto second = [&](int kk, half8 zh, half8 zl) {            // Y^T += Z^T P1 over row tile kk
-            half8 b[E];
+            half8 b[E > 0 ? E : 1];
 #pragma unroll
             for (int It = 0; It < E; ++It) b[It] = p1(kk * EN + It);
 #pragma unroll
@@ -239,7 +246,7 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
             }
         } else {
 #pragma unroll
-            for (int s = 0; s < EN; ++s) {                         // row tiles of 16 in pairs
+            for (int s = 0; s < (R + 1) / 2; ++s) {                // row tiles of 16 in pairs
                 const bool two = 2 * s + 1 < R;
                 f32x4 z[2][2];
 #pragma unroll
@@ -289,8 +296,8 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
                             return __builtin_bit_cast(half8, o);
                         };
                         const int kk = 2 * s + d;
-                        second(kk, columns32(hi), columns32(lo));
-                        const half8 b = p1(kk * EN + E);
+                        if constexpr (E > 0) second(kk, columns32(hi), columns32(lo));
+                        half8 z16[2];
 #pragma unroll
                         for (int ct = 0; ct < 2; ++ct) {
                             u32x4 o;
@@ -300,7 +307,13 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
                                 o[k] = s32[0];
                                 o[2 + k] = s32[1];
                             }
-                            tail[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, o), b, tail[ct], 0, 0, 0);
+                            z16[ct] = __builtin_bit_cast(half8, o);
+                        }
+#pragma unroll
+                        for (int j = 0; j < NT16; ++j) {
+                            const half8 b = p1(kk * EN + E + j);
+#pragma unroll
+                            for (int ct = 0; ct < 2; ++ct) tail[j][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(z16[ct], b, tail[j][ct], 0, 0, 0);
                         }
                     }
             }
@@ -311,9 +324,10 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
             for (int It = 0; It < E; ++It)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) m = __builtin_fmaxf(m, __builtin_fabsf(acc[It][r]));
-            if constexpr (ODD)
 #pragma unroll
-                for (int r = 0; r < 8; ++r) m = __builtin_fmaxf(m, __builtin_fabsf(tail[r >> 2][r & 3]));
+            for (int j = 0; j < NT16; ++j)
+#pragma unroll
+                for (int r = 0; r < 8; ++r) m = __builtin_fmaxf(m, __builtin_fabsf(tail[j][r >> 2][r & 3]));
             m = wave_max(m);
             if (l == 0) red[buf * 8 + w] = m;
         }
@@ -367,6 +381,7 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
             const int be = (int)((__builtin_bit_cast(uint32_t, m) >> 23) & 0xffu);   // biased exponent of alpha * max
             return be > 2 ? be - 2 : 0;
         };
+        uint2 first8 = {0u, 0u};
 #pragma unroll
         for (int It = 0; It < E; ++It) {
             const int row = 32 * It + c32;
@@ -382,27 +397,45 @@ __global__ __launch_bounds__(64 * B) __attribute__((amdgpu_waves_per_eu(2))) voi
             // channels 8 g + 4 h .. of the slab in registers 4 g ..: afterwards half-wave 0 has the groups g = 0, 1 of both, half-wave 1 the others
             const auto sw = __builtin_amdgcn_permlane32_swap(codes8(acc[It], 0, acc[It], 4, scale), codes8(acc[It], 8, acc[It], 12, scale), false, false);
             const uint2 o = {__builtin_amdgcn_perm(sw[1], sw[0], 0x05040100u), __builtin_amdgcn_perm(sw[1], sw[0], 0x07060302u)};
-            if (row < n1) *reinterpret_cast<uint2*>(dst + row * (N2 / 2) + 8 * h) = o;
-        }
-        if constexpr (ODD) {
-            const int row = 32 * E + c;
-            float scale = 0.0f;
-            if constexpr (MX) {
-                float m = 0.0f;
-#pragma unroll
-                for (int r = 0; r < 8; ++r) m = __builtin_fmaxf(m, __builtin_fabsf(tail[r >> 2][r & 3]));
-                const int e = exponent(m, true);
-                scale = __builtin_bit_cast(float, (uint32_t)e << 23);
-                if (q == 0) smem[L::EXPS + buf * L::EXPS_BYTES + row * B + w] = (uint8_t)e;
+            if (It % 2 == 0 && It + 1 < E) {                       // with the next row tile: half-wave h stores 16 bytes of row tile It + h
+                first8 = o;
+            } else if (It % 2 == 0) {
+                if (row < n1) *reinterpret_cast<uint2*>(dst + row * (N2 / 2) + 8 * h) = o;
+            } else {
+                const auto x = __builtin_amdgcn_permlane32_swap(first8.x, o.x, false, false);
+                const auto y = __builtin_amdgcn_permlane32_swap(first8.y, o.y, false, false);
+                const int row2 = 32 * (It - 1 + h) + c32;
+                if (row2 < n1) *reinterpret_cast<u32x4*>(dst + row2 * (N2 / 2)) = u32x4{x[0], y[0], x[1], y[1]};
             }
-            // channels 4 q .. and 16 + 4 q ..: afterwards the lower half-wave's even group has 8 bytes of the first 16 channels, the other one of the last 16
-            const uint32_t d = codes8(tail[0], 0, tail[1], 0, scale);
-            const auto s32 = __builtin_amdgcn_permlane32_swap(d, d, false, false);                     // q = 0, 1 | q = 2, 3 in both half-waves
-            const auto a16 = __builtin_amdgcn_permlane16_swap((uint32_t)s32[0], (uint32_t)s32[0], false, false);   // q = 0 | q = 1
-            const auto b16 = __builtin_amdgcn_permlane16_swap((uint32_t)s32[1], (uint32_t)s32[1], false, false);   // q = 2 | q = 3
-            const uint32_t sel = h == 0 ? 0x05040100u : 0x07060302u;
-            const uint2 o = {__builtin_amdgcn_perm((uint32_t)a16[1], (uint32_t)a16[0], sel), __builtin_amdgcn_perm((uint32_t)b16[1], (uint32_t)b16[0], sel)};
-            if ((q & 1) == 0 && row < n1) *reinterpret_cast<uint2*>(dst + row * (N2 / 2) + 8 * h) = o;
+        }
+#pragma unroll
+        for (int g = 0; g < (NT16 + 3) / 4; ++g) {                 // tiles of 16, four at a time
+            uint32_t d[4];                                         // of tile 4 g + k: channels 4 q .. and 16 + 4 q .. of row c
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int j = 4 * g + k;
+                d[k] = 0;
+                if (j >= NT16) continue;
+                float scale = 0.0f;
+                if constexpr (MX) {
+                    float m = 0.0f;
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) m = __builtin_fmaxf(m, __builtin_fabsf(tail[j][r >> 2][r & 3]));
+                    const int e = exponent(m, true);
+                    scale = __builtin_bit_cast(float, (uint32_t)e << 23);
+                    if (q == 0) smem[L::EXPS + buf * L::EXPS_BYTES + (32 * E + 16 * j + c) * B + w] = (uint8_t)e;
+                }
+                d[k] = codes8(tail[j][0], 0, tail[j][1], 0, scale);
+            }
+            // 4 x 4 between the lane groups and the tiles: afterwards lane group q has all 32 channels of tile 4 g + q
+            const auto e0 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
+            const auto e1 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
+            const auto f0 = __builtin_amdgcn_permlane16_swap(e0[0], e1[0], false, false);
+            const auto f1 = __builtin_amdgcn_permlane16_swap(e0[1], e1[1], false, false);
+            const u32x4 o = {__builtin_amdgcn_perm(f0[1], f0[0], 0x05040100u), __builtin_amdgcn_perm(f1[1], f1[0], 0x05040100u),
+                             __builtin_amdgcn_perm(f0[1], f0[0], 0x07060302u), __builtin_amdgcn_perm(f1[1], f1[0], 0x07060302u)};
+            const int j = 4 * g + q, row = 32 * E + 16 * j + c;
+            if (j < NT16 && row < n1) *reinterpret_cast<u32x4*>(dst + row * (N2 / 2)) = o;
         }
         if (t + G >= p.T) {
             if constexpr (MX) {
@@ -422,7 +455,7 @@ struct RowsVariant {
 // an instance, if any left factor of these row tiles gets here
 template <int R, int B, bool MX>
 static RowsVariant rows_instance() {
-    if constexpr (rows_kernel_takes(16 * R, B, MX) || rows_kernel_takes(16 * R - 1, B, MX)) return {&tq_rows_kernel<R, B, MX>, RowsLds<R, B, MX>::TOTAL};
+    if constexpr (rows_kernel_takes(16 * R, B, MX, 1) || rows_kernel_takes(16 * R - 1, B, MX, 1)) return {&tq_rows_kernel<R, B, MX>, RowsLds<R, B, MX>::TOTAL};
     else return {nullptr, 0};
 }
 template <int R>
