@@ -323,6 +323,21 @@ def test_row_tiles_of_16(n1, n2, T):
         run_mx(c, rows=rows)
 
 
+@pytest.mark.parametrize("n1,n2", [(33, 64), (50, 128), (70, 96), (82, 128), (98, 256), (113, 160)])
+def test_row_tiles_of_16_read_nothing_past_a_row_or_a_factor(n1, n2):
+    """Tile rows past n1 are zeros, not what lies behind a token's row or behind P1: both are followed by NaN here."""
+    print(f"[case] nothing past a row {n1}x{n2}", flush=True)
+    c = synth.generic(77 + n1, 5, n1, n2)
+    n, stride = n1 * n2, n1 * n2 + 16 * n2
+    want = run_tq(dev(c.x), dev(c.P1), dev(c.P2), dev(c.clip), c.clip_mode, n1, n2)
+    x = torch.full((5, stride), float("nan"), dtype=torch.float16, device="cuda")
+    x[:, :n] = dev(c.x)
+    P1 = torch.full((n1 * n1 + 16 * 128,), float("nan"), dtype=torch.float16, device="cuda")
+    P1[:n1 * n1] = dev(c.P1).reshape(-1)
+    got = run_tq(x, P1, dev(c.P2), dev(c.clip), c.clip_mode, n1, n2, x_stride=stride)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1].view(np.uint16), want[1].view(np.uint16))
+
+
 @pytest.mark.parametrize("mode", ["-1", "0", "3"])
 def test_mxfp4_output(tuning, mode):
     if mode != "-1":
