@@ -702,7 +702,11 @@ __global__ __launch_bounds__(ring_max_waves(NTD, ROWS) * 64) void w4a4_skinny_ke
             const float sx = (float)__builtin_bit_cast(_Float16, (uint16_t)esx[k]);
             _Float16 v[4];
 #pragma unroll
-            for (int x = 0; x < 4; ++x) v[x] = (_Float16)((float)(sum[x] >> 8) * sx * (float)__builtin_bit_cast(_Float16, (uint16_t)esw[k][x]));
+            for (int x = 0; x < 4; ++x) {
+                float y = (float)(sum[x] >> 8) * sx * (float)__builtin_bit_cast(_Float16, (uint16_t)esw[k][x]);
+                asm("" : "+v"(y));           // rounded to fp32 as it stands, as in the tiled kernel: the same bits whichever of the two runs
+                v[x] = (_Float16)y;
+            }
             _Float16* dst = out + t * out_stride + o;
             if (wide && o + 4 <= m) {
                 *reinterpret_cast<half4*>(dst) = half4{v[0], v[1], v[2], v[3]};

@@ -1355,3 +1355,22 @@ def test_w4a4_gemm_every_form(tuning, knob, value, T, m, n):
     tiles on a large one, the tiled product for few tokens."""
     tuning(knob, value)
     _w4a4_case(T, m, n, 0)
+
+
+@pytest.mark.parametrize("T,m,n", [(1, 20000, 4096), (16, 16384, 768), (40, 8191, 1024), (512, 4096, 256), (300, 2050, 512)])
+def test_w4a4_gemm_rounds_alike_in_every_kernel(tuning, T, m, n):
+    """The exact sum, two fp32 multiplications, one rounding to fp16, in the few-token kernel and in every form of the tiled one: a row's
+    bits do not depend on how many tokens it is multiplied with."""
+    g = torch.Generator(device="cuda").manual_seed(T + m + n)
+    q = [torch.randint(-8, 8, (r, n), generator=g, device="cuda", dtype=torch.int8) for r in (T, m)]
+    packed = [((c[:, 0::2] & 15) | (c[:, 1::2] << 4)).view(torch.uint8) for c in q]
+    xs, ws = (torch.rand(r, generator=g, device="cuda").half() * 0.1 for r in (T, m))
+    want = ((q[0].float() @ q[1].float().t()) * xs.float()[:, None] * ws.float()[None, :]).half()   # integers below 2^24
+    for knob, value in (("FLATQUANT_GEMM_RING_MAX_T", 1 << 20), ("FLATQUANT_GEMM_TILED", 1)):
+        for form in (0, 1, 2, 4) if knob == "FLATQUANT_GEMM_TILED" else (-1,):
+            print(f"[case] w4a4 rounding {knob} form={form} T={T} m={m} n={n}", flush=True)
+            tuning(knob, value)
+            tuning("FLATQUANT_GEMM_WIDE", form)
+            out = torch.full((T, m), float("nan"), dtype=torch.float16, device="cuda")
+            fq.flatquant_w4a4_gemm(packed[0], xs, packed[1], ws, T, m, n, out, m, stream=torch.cuda.current_stream())
+            assert torch.equal(out, want), int((out != want).sum())
