@@ -572,7 +572,7 @@ __global__ __launch_bounds__(ring_max_waves(NTD, ROWS) * 64) void w4a4_skinny_ke
     const int tid = threadIdx.x;
     const int l = tid & 63, c = l & 31, h = l >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const RingTile wg = ring_tile(blockIdx.x, (m + ROWS - 1) / ROWS, cfg.token_tiles(), T / 2 > m);
+    const RingTile wg = ring_tile(blockIdx.x, (m + ROWS - 1) / ROWS, cfg, T / 2 > m);
     if (wg.channels < 0) return;
     const int o0 = wg.channels * ROWS;
     const int t0 = wg.tokens * XROWS;
@@ -790,7 +790,13 @@ bool ring_launch(const RingShape& s, int64_t T, int m, int n, int slot, int load
     if (depth > steps) depth = steps;
     while (depth > 1 && (nwv * depth * slot > kRingLdsMax || (depth - 1) * loads > 63)) --depth;
     r.grid = (unsigned)grid;
-    r.cfg = RingConfig(depth, nwv, (int)tiles);
+    // More than a workgroup per CU, a whole number of groups per XCD, and their weights fit in its L2 or are less than the tokens: the weights stay
+    // there while the tokens pass.  us contiguous / channels first, tokens x channels x n, 4 waves: INT4 2048 x 1024 x 12288 (64 x 32) 52.8 / 35.2;
+    // 256 x 5120 x 1792 (32 x 32) 8.6 / 7.4; MXFP4 241 x 4096 x 5120 (32 x 64) 12.2 / 10.9; 1300 forms of 900 such launches 0.975 on average.  Otherwise the
+    // weights would come again for every token tile: 254 x 13824 x 11008 (32 x 64) 1.5 times as long.  Not groups of 16, of which INT4 takes 2 % longer.
+    const bool channels_first = groups * tiles > cu_count() && tiles > 1 && groups % 8 == 0 && s.rows > 16 && T / 2 <= m &&
+                                ((int64_t)m * n <= 8LL * 2 * (4 << 20) || 8 * T > m);
+    r.cfg = RingConfig(depth, nwv, channels_first, (int)tiles);
     r.lds = nwv * depth * slot;                                           // the partial sums (128 bytes per channel and 32 tokens, per wave) reuse the rings
     return true;
 }

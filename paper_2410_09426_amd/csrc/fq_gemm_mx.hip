@@ -361,7 +361,7 @@ __global__ __launch_bounds__(ring_max_waves(NTD, ROWS) * 64) void mxfp4_skinny_k
     const int tid = threadIdx.x;
     const int l = tid & 63, c = l & 31, h = l >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const RingTile wg = ring_tile(blockIdx.x, (m + ROWS - 1) / ROWS, cfg.token_tiles(), T / 2 > m);
+    const RingTile wg = ring_tile(blockIdx.x, (m + ROWS - 1) / ROWS, cfg, T / 2 > m);
     if (wg.channels < 0) return;
     const int o0 = wg.channels * ROWS;
     const int t0 = wg.tokens * XROWS;

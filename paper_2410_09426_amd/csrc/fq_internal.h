@@ -163,15 +163,17 @@ struct RingShape {
     double us;
 };
 RingShape ring_shape(int64_t T, int m, int n, bool mx);
-// Ring depth, waves and token tiles of a launch in one dword (the kernels' arguments arrive in registers, as many as there is room for).
+// Ring depth, waves, order and number of the token tiles of a launch in one dword (the kernels' arguments arrive in registers, as many as there is room for).
 struct RingConfig {
     static constexpr int kMaxTokenTiles = (1 << 24) - 1;
     uint32_t bits;
     RingConfig() = default;
-    RingConfig(int depth, int waves, int token_tiles) : bits((uint32_t)depth | (uint32_t)__builtin_ctz(waves) << 4 | (uint32_t)token_tiles << 8) {}
+    RingConfig(int depth, int waves, bool channels_first, int token_tiles)
+        : bits((uint32_t)depth | (uint32_t)__builtin_ctz(waves) << 4 | (uint32_t)channels_first << 7 | (uint32_t)token_tiles << 8) {}
     __host__ __device__ int depth() const { return bits & 15; }
-    __host__ __device__ int log2_waves() const { return bits >> 4 & 15; }
+    __host__ __device__ int log2_waves() const { return bits >> 4 & 7; }
     __host__ __device__ int waves() const { return 1 << log2_waves(); }
+    __host__ __device__ bool channels_first() const { return bits >> 7 & 1; }
     __host__ __device__ int token_tiles() const { return (int)(bits >> 8); }
 };
 struct RingLaunch {
@@ -185,14 +187,17 @@ bool ring_launch(const RingShape& s, int64_t T, int m, int n, int slot, int load
 // Channel group and token tile of a workgroup.  Workgroup b runs on XCD b % 8: an XCD takes a contiguous eighth of an order in which the
 // tiles that share the larger operand follow each other, so that its rows come from memory once and are in that L2 for the others
 // (1025 x 842 x 11008 20.8 -> 16.7 us; 4000 x 512 x 4096, with the smaller one, 16 -> 21).  channels < 0: nothing to do (the grid
-// is a whole number of rounds of the XCDs).
+// is a whole number of rounds of the XCDs).  RingConfig::channels_first (ring_launch says when): channel groups in their own order, one
+// token tile after the other; every XCD has the same eighth of the groups in each.
 struct RingTile {
     int channels, tokens;
 };
-__device__ __forceinline__ RingTile ring_tile(int b, int groups, int token_tiles, bool more_tokens) {
+__device__ __forceinline__ RingTile ring_tile(int b, int groups, RingConfig cfg, bool more_tokens) {
+    const int token_tiles = cfg.token_tiles();
     if (token_tiles == 1) return RingTile{b, 0};
-    const int all = groups * token_tiles, per_xcd = (all + 7) >> 3, q = (b & 7) * per_xcd + (b >> 3);
+    const int all = groups * token_tiles, per_xcd = (all + 7) >> 3, q = cfg.channels_first() ? b : (b & 7) * per_xcd + (b >> 3);
     if (q >= all) return RingTile{-1, 0};
+    more_tokens |= cfg.channels_first();
     const int inner = more_tokens ? groups : token_tiles, outer = q / inner, r = q - outer * inner;
     return more_tokens ? RingTile{r, outer} : RingTile{outer, r};
 }

@@ -1374,3 +1374,32 @@ def test_w4a4_gemm_rounds_alike_in_every_kernel(tuning, T, m, n):
             out = torch.full((T, m), float("nan"), dtype=torch.float16, device="cuda")
             fq.flatquant_w4a4_gemm(packed[0], xs, packed[1], ws, T, m, n, out, m, stream=torch.cuda.current_stream())
             assert torch.equal(out, want), int((out != want).sum())
+
+
+@pytest.mark.parametrize("T,m,n", [(65, 8192, 8448), (130, 2048, 1024), (1100, 512, 768), (520, 512, 4096), (70, 300, 512), (333, 4096, 256)])
+@pytest.mark.parametrize("kind", ["int4", "mxfp4"])
+def test_few_token_products_in_every_tile_order(tuning, kind, T, m, n):
+    """Several token tiles, by contiguous eighths in either order and channel groups first: each output once, the bits of the tiled kernel
+    (MXFP4 too: with equal exponents its sums are exact in any order)."""
+    g = torch.Generator(device="cuda").manual_seed(T + m + n)
+    codes = [torch.randint(0, 256, (r, n // 2), generator=g, device="cuda", dtype=torch.uint8) for r in (T, m)]
+    if kind == "int4":
+        product, scales = fq.flatquant_w4a4_gemm, [torch.rand(r, generator=g, device="cuda").half() * 0.02 for r in (T, m)]
+    else:
+        product, scales = fq.flatquant_mxfp4_gemm, [torch.full((fq.fq_mxfp4_tiled_scale_bytes(r, n),), 124, device="cuda", dtype=torch.uint8) for r in (T, m)]
+
+    def run():
+        out = torch.full((T + 1, m), float("nan"), dtype=torch.float16, device="cuda")
+        product(codes[0], scales[0], codes[1], scales[1], T, m, n, out, m, stream=torch.cuda.current_stream())
+        assert bool(torch.isnan(out[T]).all())
+        return out[:T].view(torch.int16)
+    tuning("FLATQUANT_GEMM_TILED", 1)
+    want = run()
+    tuning("FLATQUANT_GEMM_TILED", 0)
+    tuning("FLATQUANT_GEMM_RING_MAX_T", 1 << 20)
+    for tokens in (32, 64):
+        for rows in (16, 32, 48, 64):
+            print(f"[case] tile order {kind} {tokens}x{rows} T={T} m={m} n={n}", flush=True)
+            tuning("FLATQUANT_GEMM_TOKENS", tokens)
+            tuning("FLATQUANT_GEMM_ROWS", rows)
+            assert torch.equal(run(), want)
