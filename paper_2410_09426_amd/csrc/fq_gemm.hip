@@ -871,7 +871,7 @@ static hipError_t tiled_launch(const GemmDev& d, hipStream_t stream) {
 // form on average, 10 % at worst.  (Forms 0 / 1 / 2 / 4, us: 2048 x 4096 x 1024 11.4 / 14.3 / 16.3 / 15.5, 2048 x 4096 x 4096 28.4 / 26.7 /
 // 36.2 / 38.5, 2048 x 4096 x 8192 52.7 / 43.7 / 62.2 / 68.8, 777 x 5120 x 5120 28.8 / 27.5 / 40.8 / 23.3, 768 x 5120 x 5120 20.6 / 27.6 / 41.7 /
 // 24.1, 3000 x 4096 x 4096 40.9 / 44.8 / 37.0 / 54.8, 6000 x 4096 x 11008 203 / 159 / 170 / 233.)
-static double w4a4_tiled_us(const GemmArgs& a, int* form) {
+static double w4a4_tiled_us(const GemmArgs& a, int& form) {
     const int64_t cu = cu_count();
     const double nk = a.n / 256;
     auto round_us = [&](int tok, int ch, int64_t slots, double& part) {   // full rounds; part: how full the last one is
@@ -893,7 +893,7 @@ static double w4a4_tiled_us(const GemmArgs& a, int* form) {
     int best = 0;
     for (int f : {1, 2, 4})
         if (us[f] < us[best]) best = f;
-    if (form) *form = best;
+    form = best;
     return us[best];
 }
 
@@ -902,16 +902,19 @@ hipError_t w4a4_launch(const GemmArgs& a, hipStream_t stream) {
     d.xc = a.x_codes; d.xs = a.x_scales; d.wc = a.w_codes; d.ws = a.w_scales; d.out = a.out;
     d.T = a.T; d.out_stride = a.out_stride; d.m = a.m; d.n = a.n;
     // Decode and short prefill chunks: one pass over the weights per tile of up to 64 tokens, K split inside a workgroup (the ring
-    // kernel), for as long as it is the cheaper one (FLATQUANT_GEMM_RING_MAX_T replaces the comparison by a token count).
+    // kernel), for as long as it is the cheaper one (FLATQUANT_GEMM_RING_MAX_T replaces the comparison by a token count).  Beyond one
+    // 128 x 128 tile per CU it has to promise a quarter less: the tiled kernel's estimate holds there (3 % too low), the ring kernel's is 10 to 30 %
+    // too low (tiled / ring, us: 2048 x 8200 x 11008 164 / 227, 384 x 11008 x 8192 39 / 49, 777 x 5120 x 28672 113 / 148; 192 x 8200 x 65536 232 / 125).
     const bool ring = tuned(Knob::GEMM_TILED, 0) == 0;
-    const int ring_max = tuned(Knob::GEMM_RING_MAX_T, -1);
-    if (ring && (ring_max >= 0 ? a.T <= (ring_max > 64 ? ring_max : 64) : a.T <= 4096)) {
-        const RingShape s = ring_shape(a.T, a.m, a.n, false);
-        if (a.T <= 64 || ring_max >= 0) return skinny_launch(d, stream, s);
-        if (s.us < w4a4_tiled_us(a, nullptr)) return skinny_launch(d, stream, s);
-    }
+    if (ring && a.T <= 64) return skinny_launch(d, stream, ring_shape(a.T, a.m, a.n, false));
     int form = 0;
-    w4a4_tiled_us(a, &form);
+    const double tiled_us = w4a4_tiled_us(a, form);
+    const int ring_max = tuned(Knob::GEMM_RING_MAX_T, -1);
+    if (ring && a.T <= (ring_max >= 0 ? ring_max : 4096)) {
+        const RingShape s = ring_shape(a.T, a.m, a.n, false);
+        const bool tile_per_cu = ((a.T + 127) / 128) * ((a.m + 127) / 128) <= cu_count();
+        if (ring_max >= 0 || s.us * (tile_per_cu ? 1.0 : 1.25) < tiled_us) return skinny_launch(d, stream, s);
+    }
     const int asked = tuned(Knob::GEMM_WIDE, form);
     if (asked == 0 || asked == 1 || asked == 2 || asked == 4) form = asked;
     switch (form) {

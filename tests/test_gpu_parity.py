@@ -1403,3 +1403,47 @@ def test_few_token_products_in_every_tile_order(tuning, kind, T, m, n):
             tuning("FLATQUANT_GEMM_TOKENS", tokens)
             tuning("FLATQUANT_GEMM_ROWS", rows)
             assert torch.equal(run(), want)
+
+
+def graph_us(launch, launches=20, replays=9):
+    """Replays a graph of `launches` calls; the time of one in us (the least of the replays)."""
+    launch()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(launches):
+            launch()
+    ends = [[torch.cuda.Event(enable_timing=True) for _ in range(2)] for _ in range(replays)]
+    graph.replay()
+    for a, b in ends:
+        a.record()
+        graph.replay()
+        b.record()
+    torch.cuda.synchronize()
+    return min(a.elapsed_time(b) for a, b in ends) * 1e3 / launches
+
+
+def w4a4_us(tuning, T, m, n, **overrides):
+    """Time of the INT4 product on arbitrary codes under tuning overrides (without FLATQUANT_GEMM_), and without them."""
+    g = torch.Generator(device="cuda").manual_seed(T + m + n)
+    codes = [torch.randint(0, 256, (r, n // 2), generator=g, device="cuda", dtype=torch.uint8) for r in (T, m)]
+    steps = [torch.rand(r, generator=g, device="cuda").half() * 0.01 for r in (T, m)]
+    out = torch.empty((T, m), dtype=torch.float16, device="cuda")
+
+    def launch():
+        fq.flatquant_w4a4_gemm(codes[0], steps[0], codes[1], steps[1], T, m, n, out, m, stream=torch.cuda.current_stream())
+    chosen = graph_us(launch)
+    for name, value in overrides.items():
+        tuning("FLATQUANT_GEMM_" + name, value)
+    forced = graph_us(launch)
+    for name in overrides:
+        fq.fq_set_tuning("FLATQUANT_GEMM_" + name, None)
+    print(f"[us] w4a4 T={T} m={m} n={n}: chosen {chosen:.2f}, {overrides} {forced:.2f}", flush=True)
+    return chosen, forced
+
+
+@pytest.mark.parametrize("T,m,n", [(2048, 8200, 11008), (384, 11008, 8192), (777, 5120, 28672), (512, 8704, 8448), (2012, 2176, 21504)])
+def test_w4a4_gemm_takes_the_tiled_kernel_where_it_is_faster(tuning, T, m, n):
+    """More tiles than CUs, up to 4096 tokens: the choice is at most 12 % slower than the tiled kernel (the few-token one takes 1.25 to 1.4 times as long)."""
+    chosen, tiled = w4a4_us(tuning, T, m, n, TILED=1)
+    assert chosen <= 1.12 * tiled
