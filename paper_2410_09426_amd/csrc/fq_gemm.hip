@@ -720,15 +720,20 @@ __global__ __launch_bounds__(ring_max_waves(NTD, ROWS) * 64) void w4a4_skinny_ke
 
 // What a launch of the few-token kernels takes, for a workgroup of `tokens` x `rows`: a fixed part, the lines of 256 codes that a wave
 // works on one after the other, the operand rows that the fullest CU and that all CUs take in per line, the products of all CUs and
-// of one wave, the partial sums that meet in LDS, and the weights from memory.  Fits to about 500 launches per format of 1 <= T <= 4000,
-// 256 <= m <= 14336, 256 <= n <= 28672, 8 to 24 shapes each, with the weights in memory and in the last-level cache; what they choose is
-// 1.2 % slower than the best shape on average.  One shape per T and one rule on workgroups (64 tokens from 33 on; 32 channels, or
-// 16 while no CU has more than one workgroup of those) takes 13 % longer on average, 3 % less in 2 % of the launches (7 % in
-// one): INT4 64 x 4096 x 11008 12.0 us, here 9.6 in 32 x 32; 45 x 1408 x 12288 9.8 / 7.0 in 32 x 16; 45 x 8666 x 11008 20.0 / 16.5 in 64 x
-// 48; 230 x 7936 x 14336 44 / 33 in 64 x 64; MXFP4 42 x 1664 x 28672 20.6 / 13.3.
+// of one wave, the partial sums that meet in LDS, and the weights.  Fits to about 500 launches per format of 1 <= T <= 4000,
+// 256 <= m <= 14336, 256 <= n <= 28672, 8 to 24 shapes each, with the weights in memory and in the last-level cache (so the weights' term is no
+// memory rate: 16 to 39 TB/s).  Against a single shape per T and one rule on workgroups (64 tokens from 33 on; 32 channels, or 16 while no
+// CU has more than one workgroup of those; 8 waves while none has more than one, else 4), us: INT4 64 x 4096 x 11008 12.0, here 9.6 in 32 x 32;
+// 45 x 1408 x 12288 9.8 / 7.0 in 32 x 16; 45 x 8666 x 11008 20.0 / 16.5 in 64 x 48; 230 x 7936 x 14336 44 / 33 in 64 x 64; MXFP4 42 x 1664 x 28672 20.6 / 13.3.
+// The estimates are off by 6 % (more than two workgroups per CU: 10 to 30 % too low), so up to 32 tokens, where that rule's tokens and channels
+// are rarely far from the best, other channels have to promise 5 % (INT4 2 x 14336 x 2048 4.9 -> 4.1, 13824 x 3072 6.1 -> 4.7); and 16 channels in 4
+// waves are not taken for more tokens and workgroups than CUs (INT4 213 x 4096 x 256 4.6 -> 3.7, 1638 x 512 x 1280 6.4 -> 5.1).  4000 launches per
+// format against that rule: 5 % faster up to 32 tokens (MXFP4 6), 16 up to 64, 11 up to 256, 7 beyond (MXFP4 9); 3 % of them more than 3 % slower
+// up to 32 tokens, 5 % beyond (MXFP4 none and 3).
 // Waves and slots: 8 waves give every SIMD two to overlap where CUs have one workgroup; where they have more, small ones (4 waves)
 // that are all resident overlap each other.  A second slot per wave helps MXFP4 (T = 2, 1792 x 28672: 9.4 us, 12.6 with one), whose
-// steps are shorter; INT4 is faster without (53 x 2960 x 11008 8.1 / 7.6: memory does better with fewer lines asked for).
+// steps are shorter; INT4 is faster without (53 x 2960 x 11008 8.1 / 7.6: memory does better with fewer lines asked for) unless few tokens leave
+// it 16 lines per wave or more (1 x 2250 x 65536 26.6 / 23.8, 4 x 14336 x 65536 107 / 89).
 struct RingForm {
     int waves, depth;
     double fixed, line, rows_fullest, rows_all, product, sums_fullest, sums_all, weights, product_wave;
@@ -743,26 +748,32 @@ RingShape ring_shape(int64_t T, int m, int n, bool mx) {
     const RingForm* forms = mx ? kRingMx : kRingInt4;
     const int nforms = mx ? 3 : 2;
     const double cu = cu_count(), nl = n / 256, weights = 0.5 * m * (double)n;
+    const int want_tokens = tuned(Knob::GEMM_TOKENS, 0), want_rows = tuned(Knob::GEMM_ROWS, 0);
     RingShape best{};
-    best.us = 1e300;
+    double limit = 1e300;
     auto consider = [&](int tokens, int rows) {
         const int64_t groups = ((m + rows - 1) / rows) * ((T + tokens - 1) / tokens);
         const double all = groups / cu, fullest = std::ceil(all), sums = rows * (tokens < 32 ? 32 : tokens), lines = nl * (rows + tokens);
         for (int f = 0; f < nforms; ++f) {
             const RingForm& r = forms[f];
+            if (T > 32 && rows == 16 && r.waves == 4 && all > 1 && !want_rows) continue;
             const double steps = std::ceil(nl / r.waves);
             const double us = r.fixed + r.line * steps + lines * (r.rows_fullest * fullest + r.rows_all * all) + r.weights * weights +
                               sums * (r.product * nl * all + r.product_wave * steps + r.sums_fullest * fullest + r.sums_all * all);
-            if (us < best.us) best = RingShape{tokens, rows, r.waves, r.depth, us};
+            if (us >= limit) continue;
+            best = RingShape{tokens, rows, r.waves, !mx && T <= 32 && r.waves == 8 && steps >= 16 ? 2 : r.depth, us};
+            limit = us;
         }
     };
-    const int want_tokens = tuned(Knob::GEMM_TOKENS, 0), want_rows = tuned(Knob::GEMM_ROWS, 0);
     auto over_rows = [&](int tokens) {
         if (want_rows) return consider(tokens, want_rows);
-        consider(tokens, 16);
-        consider(tokens, 32);
-        consider(tokens, 48);
-        consider(tokens, 64);
+        const int plain = T > 32 ? 0 : (m + 15) / 16 <= cu ? 16 : 32;
+        if (plain) {
+            consider(tokens, plain);
+            limit *= 0.95;
+        }
+        for (int rows = 16; rows <= 64; rows += 16)
+            if (rows != plain) consider(tokens, rows);
     };
     if (want_tokens) {
         over_rows(want_tokens);

@@ -1447,3 +1447,11 @@ def test_w4a4_gemm_takes_the_tiled_kernel_where_it_is_faster(tuning, T, m, n):
     """More tiles than CUs, up to 4096 tokens: the choice is at most 12 % slower than the tiled kernel (the few-token one takes 1.25 to 1.4 times as long)."""
     chosen, tiled = w4a4_us(tuning, T, m, n, TILED=1)
     assert chosen <= 1.12 * tiled
+
+
+@pytest.mark.parametrize("T,m,n,tokens,waves,depth", [(2, 14336, 2048, 8, 4, 1), (2, 13824, 3072, 8, 4, 1), (1, 28672, 2560, 8, 4, 1), (1, 13824, 65536, 8, 8, 2),
+                                                      (4, 14336, 65536, 8, 8, 2), (213, 4096, 256, 32, 4, 1), (1638, 512, 1280, 32, 4, 1)])
+def test_few_token_products_take_a_shape_that_is_not_much_slower(tuning, T, m, n, tokens, waves, depth):
+    """32 channels per workgroup where other shapes take 1.2 to 1.3 times as long: the choice is at most 12 % slower."""
+    chosen, forced = w4a4_us(tuning, T, m, n, TOKENS=tokens, ROWS=32, WAVES=waves, DEPTH=depth, RING_MAX_T=1 << 20)
+    assert chosen <= 1.12 * forced
