@@ -68,9 +68,11 @@ hipError_t tq_rows_launch(const TqDev& d, hipStream_t stream, bool mx);
 // Not taken: 32- and 64-wide rows of full tiles (wave-per-token kernel); five slabs of 49 .. 64 rows, which tq_fast_kernel has two workgroups
 // per CU for (12.4 / 14.0 at 1024); eight slabs of 64 rows; 113 rows on with up to four slabs (128 x 128 113 / 124 at 8192) and with eight, whose two
 // tiles LDS has no room for; MXFP4 at 32 rows with an even number of slabs (32 x 128 39 / 43 at 16384) and long launches of 49 .. 63 x 64 (56 x 64
-// 8.4 / 7.4 at 2048, 37 / 38 at 16384).
+// 8.4 / 7.4 at 2048, 37 / 38 at 16384); 64-wide rows of an odd P1, whose staging goes through registers, before the loop has made up for it (49 x 64
+// 3.8 / 4.1 (1), 4.8 / 5.4 (300), 14.3 / 14.8 (4096), 25.1 / 22.8 (8192); 33 x 64 4.5 / 4.8 (300), 7.9 / 8.1 (2048), 9.7 / 8.5 (2500)).
 constexpr bool rows_kernel_takes(int n1, int B, bool mx, int64_t T) {
     if (B < 2 || B > 8) return false;
+    if (B == 2 && n1 % 2 == 1 && n1 > 32 && n1 < 64 && T <= (n1 < 48 ? 2048 : 5632)) return false;
     switch ((n1 + 15) / 16) {
         case 2: return n1 == 32 && B >= 3 && (!mx || B % 2 == 1);
         case 4: return n1 == 64 ? B >= 3 && B != 5 && B != 8 : B != 5 && !(B == 2 && mx && T > 8192);
@@ -78,12 +80,16 @@ constexpr bool rows_kernel_takes(int n1, int B, bool mx, int64_t T) {
         default: return n1 > 16;
     }
 }
-// whether any left factor of A row tiles of 32, full or not, is left to tq_fast_kernel (by many tokens, if not by all)
+// whether any left factor of R row tiles of 16 goes to tq_rows_kernel, by few tokens or many
+constexpr bool rows_kernel_reached(int R, int B, bool mx) {
+    for (int n1 = 16 * R - 15; n1 <= 16 * R; ++n1)
+        if (rows_kernel_takes(n1, B, mx, 1) || rows_kernel_takes(n1, B, mx, INT64_MAX)) return true;
+    return false;
+}
+// whether any left factor of A row tiles of 32, full or not, is left to tq_fast_kernel, by few tokens or many
 constexpr bool slab_kernel_reached(int A, int B, bool full, bool mx) {
-    constexpr int64_t many = INT64_MAX;
-    if (full) return !rows_kernel_takes(32 * A, B, mx, many);
-    for (int n1 = 32 * A - 31; n1 < 32 * A; ++n1)
-        if (!rows_kernel_takes(n1, B, mx, many)) return true;
+    for (int n1 = full ? 32 * A : 32 * A - 31; n1 < 32 * A + full; ++n1)
+        if (!rows_kernel_takes(n1, B, mx, 1) || !rows_kernel_takes(n1, B, mx, INT64_MAX)) return true;
     return false;
 }
 // MXFP4 output variant of the specialised kernels (d.out_scales points at the u8 [T, n/32] shared exponents).

@@ -14,6 +14,7 @@
 //   * A wave may own SPW adjacent slabs (template parameter).  With SPW = n2/32 a
 //     token belongs to a single wave: no workgroup barrier partner to wait for,
 //     and the token tile is read from LDS once instead of once per slab.
+#include <algorithm>
 #include <type_traits>
 
 #include "fq_internal.h"
@@ -775,9 +776,12 @@ bool tq_fast_applicable(const TqDev& d) {
 int64_t tq_fast_lds_bytes(int n1, int n2) {
     if (n1 < 1 || n1 > kMaxN1 || n2 < 32 || n2 > kMaxN2 || n2 % 32) return 0;
     const int A = (n1 + 31) / 32;
-    if (rows_kernel_takes(n1, n2 / 32, false, 1)) return tq_rows_lds_bytes(n1, n2);
-    const int a = variant(A, n2 / 32, n1 % 32 == 0, 0).lds, b = variant(A, n2 / 32, n1 % 32 == 0, 2).lds;
-    return a > b ? a : b;
+    // few tokens and many may go to different kernels: the larger of them
+    const bool few = rows_kernel_takes(n1, n2 / 32, false, 1), many = rows_kernel_takes(n1, n2 / 32, false, INT64_MAX);
+    int64_t bytes = few || many ? tq_rows_lds_bytes(n1, n2) : 0;
+    if (!few || !many)
+        for (int mode : {0, 2}) bytes = std::max<int64_t>(bytes, variant(A, n2 / 32, n1 % 32 == 0, mode).lds);
+    return bytes;
 }
 
 hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {

@@ -455,7 +455,7 @@ struct RowsVariant {
 // an instance, if any left factor of these row tiles gets here
 template <int R, int B, bool MX>
 static RowsVariant rows_instance() {
-    if constexpr (rows_kernel_takes(16 * R, B, MX, 1) || rows_kernel_takes(16 * R - 1, B, MX, 1)) return {&tq_rows_kernel<R, B, MX>, RowsLds<R, B, MX>::TOTAL};
+    if constexpr (rows_kernel_reached(R, B, MX)) return {&tq_rows_kernel<R, B, MX>, RowsLds<R, B, MX>::TOTAL};
     else return {nullptr, 0};
 }
 template <int R>

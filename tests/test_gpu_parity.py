@@ -1455,3 +1455,15 @@ def test_few_token_products_take_a_shape_that_is_not_much_slower(tuning, T, m, n
     """32 channels per workgroup where other shapes take 1.2 to 1.3 times as long: the choice is at most 12 % slower."""
     chosen, forced = w4a4_us(tuning, T, m, n, TOKENS=tokens, ROWS=32, WAVES=waves, DEPTH=depth, RING_MAX_T=1 << 20)
     assert chosen <= 1.12 * forced
+
+
+@pytest.mark.parametrize("n1,T", [(33, 2048), (47, 2048), (49, 5632), (63, 5632)])
+def test_odd_left_factors_of_64_wide_rows_on_both_sides_of_the_kernel_change(n1, T):
+    """64-wide rows of an odd left factor change kernels with the number of tokens: both match the oracle, and a token's bytes do not depend on it."""
+    print(f"[case] kernel change {n1}x64 T={T}", flush=True)
+    c = synth.generic(2000 + n1, T + 1, n1, 64, clip_mode=1)
+    check_case(c, rows=subset_rows(T + 1, 60, n1, must=(0, T - 1, T)), with_dequant=False, label=f"{n1}x64 T={T + 1}")
+    x, P1, P2, clip = dev(c.x), dev(c.P1), dev(c.P2), dev(c.clip)
+    more = run_tq(x, P1, P2, clip, 1, n1, 64)
+    few = run_tq(x[:T], P1, P2, clip, 1, n1, 64)
+    assert np.array_equal(more[0][:T], few[0]) and np.array_equal(more[1][:T].view(np.uint16), few[1].view(np.uint16))
