@@ -59,6 +59,27 @@ hipError_t po_wave_launch(const TqDev& d, hipStream_t stream);
 // Row tiles of 16, one barrier per token (fq_tq_rows.hip): for the factors that rows_kernel_takes() names.
 int64_t tq_rows_lds_bytes(int n1, int n2);
 hipError_t tq_rows_launch(const TqDev& d, hipStream_t stream, bool mx);
+// Grid of a persistent loop over the tokens with room for occ workgroups per CU: every workgroup gets the same number of tokens (+-1).
+// Four row tiles with three or four slabs have room for two.  Both stage the factors, and a round of tokens takes the two 1.6 times as long as
+// one alone (tq_any_kernel 1.35 times), so few tokens per CU, and numbers of them that leave the second workgroup a round short, are faster with one:
+// r1 and r2 are the rounds with one and with two.  us with one / two: 128 x 128 9.8 / 10.8 (300 tokens), 13.2 / 15.4 (640), 18.3 / 19.0 (1024), 20.6 / 21.8
+// (1100), 25.8 / 25.6 (1536), 33.0 / 31.9 (2048), 114 / 100 (8192); 113 x 96 10.5 / 11.0, 13.5 / 15.3, 16.7 / 16.3, 19.0 / 19.6, 21.4 (1300) / 20.0; MXFP4 128 x 96 12.8 / 14.4 (640),
+// 16.2 / 15.5 (1024); tq_any_kernel 112 x 80 13.0 / 13.4 (300), 16.7 / 18.4 (768), 22.9 / 22.6 (1100).
+inline unsigned token_loop_grid(int64_t T, int64_t cu, int occ, bool one) {
+    if (one && occ == 2) occ = 1;
+    const int64_t rounds = (T + cu * occ - 1) / (cu * occ);
+    return (unsigned)((T + rounds - 1) / rounds);
+}
+inline bool slab_loop_alone(int64_t T, int64_t cu, int A, int B, bool full) {
+    const int64_t r1 = (T + cu - 1) / cu, r2 = (r1 + 1) / 2;
+    // (four slabs, two tokens for nearly every CU: as fast or slower alone, 128 x 128 at 512 tokens 11.0 / 11.9 on one machine and 15.8 / 13.1 on another)
+    if (B == 4 && r1 == 2 && 4 * T > 7 * cu) return false;
+    return A == 4 && (B == 3 || B == 4) && 5 * r1 <= 8 * r2 + (full && B == 4 ? 4 : 2);
+}
+inline bool any_loop_alone(int64_t T, int64_t cu, int A, int B) {
+    const int64_t r1 = (T + cu - 1) / cu, r2 = (r1 + 1) / 2;
+    return A == 4 && (B == 3 || B == 4) && 3 * r1 <= 4 * r2 + 2;
+}
 // Whether a left factor of n1 rows and a right factor of 32 B columns go to tq_rows_kernel rather than to tq_fast_kernel; both give the same
 // bytes.  tq_fast_kernel / tq_rows_kernel in us, tokens in parentheses: row tiles that are not full gain most, by the 16 rows that are no longer
 // padding and by the prologue: 48 x 64 4.2 / 3.3 (64), 44 / 29 (16384); 72 x 128 5.9 / 5.0, 135 / 111; 86 x 128 6.0 / 4.9, 142 / 136; 104 x 64 8.5 / 5.2,

@@ -752,11 +752,7 @@ hipError_t tq_mx_launch(const TqDev& d, hipStream_t stream) {
     }
     const Variant v = variant_mx(A, B, full1, one);
     int64_t grid = d.T;
-    if (!one) {
-        const int64_t resident = (int64_t)cu_count() * occ;
-        const int64_t rounds = (d.T + resident - 1) / resident;
-        grid = (d.T + rounds - 1) / rounds;
-    }
+    if (!one) grid = token_loop_grid(d.T, cu_count(), occ, slab_loop_alone(d.T, cu_count(), A, B, full1));
     return launch(v.fn, dim3((unsigned)grid), dim3(64 * B), v.lds, stream, d, d.clip);
 }
 
@@ -876,10 +872,7 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
     }
     const int cap = tuned(Knob::WG_PER_CU, 0);
     if (cap > 0 && cap < occ) occ = cap;
-    // every workgroup gets the same number of tokens (+-1): grid = ceil(T / ceil(T / resident workgroups))
-    const int64_t resident = (int64_t)cu_count() * occ;
-    const int64_t rounds = (d.T + resident - 1) / resident;
-    int64_t grid = (d.T + rounds - 1) / rounds;
+    int64_t grid = token_loop_grid(d.T, cu_count(), occ, slab_loop_alone(d.T, cu_count(), A, B, full1));
     if (mode >= 3) {
         if (d.T > 0x7fffffff) return hipErrorInvalidConfiguration;   // only reachable through the tuning overrides
         grid = mode == 4 ? (d.T + kTokensPerWg - 1) / kTokensPerWg : d.T;

@@ -829,7 +829,6 @@ static bool any_is_faster(const TqDev& d, bool mx) {
     return chunks && (filled >= (B == 1 ? 50 : 60) || (d.T <= 8 * cu && (B == 2 || filled >= 45)));
 }
 
-// every workgroup gets the same number of tokens (+-1)
 static hipError_t any_launch(const TqDev& d, hipStream_t stream, bool mx) {
     const int A = (d.n1 + 31) / 32, B = (d.n2 + 31) / 32;
     const AnyVariant v = any_variant(d.n1, d.n2, mx);
@@ -848,8 +847,7 @@ static hipError_t any_launch(const TqDev& d, hipStream_t stream, bool mx) {
     }
     const int cap = tuned(Knob::WG_PER_CU, 0);
     if (cap > 0 && cap < occ) occ = cap;
-    const int64_t resident = (int64_t)cu_count() * occ, rounds = (d.T + resident - 1) / resident;
-    return launch(v.fn, dim3((unsigned)((d.T + rounds - 1) / rounds)), dim3(64 * B), v.lds, stream, d);
+    return launch(v.fn, dim3(token_loop_grid(d.T, cu_count(), occ, any_loop_alone(d.T, cu_count(), A, B))), dim3(64 * B), v.lds, stream, d);
 }
 
 // MXFP4 instances of tq_kernel: where any_is_faster() can say no, and four row tiles x five slabs, whose longest rows (n > 19555) tq_any_kernel's

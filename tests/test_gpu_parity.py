@@ -1438,6 +1438,7 @@ def w4a4_us(tuning, T, m, n, **overrides):
     forced = graph_us(launch)
     for name in overrides:
         fq.fq_set_tuning("FLATQUANT_GEMM_" + name, None)
+    chosen = min(chosen, graph_us(launch))
     print(f"[us] w4a4 T={T} m={m} n={n}: chosen {chosen:.2f}, {overrides} {forced:.2f}", flush=True)
     return chosen, forced
 
@@ -1467,3 +1468,33 @@ def test_odd_left_factors_of_64_wide_rows_on_both_sides_of_the_kernel_change(n1,
     more = run_tq(x, P1, P2, clip, 1, n1, 64)
     few = run_tq(x[:T], P1, P2, clip, 1, n1, 64)
     assert np.array_equal(more[0][:T], few[0]) and np.array_equal(more[1][:T].view(np.uint16), few[1].view(np.uint16))
+
+
+@pytest.mark.parametrize("n1,n2,T", [(128, 128, 640), (128, 96, 640), (113, 128, 640), (128, 128, 1024), (112, 80, 700)])
+def test_four_row_tiles_run_one_workgroup_per_cu_for_few_tokens(tuning, n1, n2, T):
+    """Two workgroups per CU stage the factors twice, for one or two tokens each (1.1 to 1.2 times as long): the choice is at most 6 % slower than one."""
+    c = synth.generic(3000 + n1 + n2, T, n1, n2)
+    x, P1, P2, clip = dev(c.x), dev(c.P1), dev(c.P2), dev(c.clip)
+    codes, steps = torch.empty((T, n1 * n2 // 2), dtype=torch.uint8, device="cuda"), torch.empty((T,), dtype=torch.float16, device="cuda")
+
+    def launch():
+        fq.flatquant_transform_quant(x, P1, P2, clip, c.clip_mode, T, n1, n2, n1 * n2, codes, steps, stream=torch.cuda.current_stream())
+    chosen = graph_us(launch)
+    tuning("FLATQUANT_WG_PER_CU", 1)
+    one = graph_us(launch)
+    fq.fq_set_tuning("FLATQUANT_WG_PER_CU", None)
+    chosen = min(chosen, graph_us(launch))
+    print(f"[us] transform {n1}x{n2} T={T}: chosen {chosen:.2f}, one workgroup per CU {one:.2f}", flush=True)
+    assert chosen <= 1.06 * one
+
+
+@pytest.mark.parametrize("n1,n2", [(128, 128), (113, 96), (112, 80), (97, 98)])
+@pytest.mark.parametrize("T", [257, 1023, 2049])
+def test_four_row_tiles_with_one_and_two_workgroups_per_cu(n1, n2, T):
+    """Few and many tokens per CU, both formats, against the oracle."""
+    print(f"[case] four row tiles {n1}x{n2} T={T}", flush=True)
+    c = synth.generic(3100 + n1 + n2 + T, T, n1, n2, clip_mode=1)
+    rows = subset_rows(T, 50, n1, must=(0, 255, 256, T - 1))
+    check_case(c, rows=rows, with_dequant=False, label=f"four row tiles {n1}x{n2}")
+    if n1 * n2 % 128 == 0:
+        run_mx(c, rows=rows)
