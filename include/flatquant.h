@@ -275,8 +275,11 @@ int fq_abi_version(void);
 
 /*
  * Tuning overrides, for measurements and tests (the defaults are what the library measures best).  `name` is one of
- * FLATQUANT_MODE (activation kernel flavour: 0..4 the slab kernels, 5 / 6 the wave-per-token kernel of 64-wide rows, one
- * shot / persistent; 5 also forces the wave-per-token kernel of the left-factor-only case), FLATQUANT_WAVE_TPW (2 / 4 / 8 waves per workgroup of that kernel), FLATQUANT_PROBE_SHAPE (0..2: launch
+ * FLATQUANT_MODE (activation kernel flavour of the factors that the slab kernels take: 0 one slab per wave, 1 two (n2 = 64), 2 pipelined over
+ * tokens, 3 a token per workgroup, 4 a token per wave (n2 = 64), 1..4 INT4 and n1 <= 64 only, MXFP4 0 and 3 with 64-wide rows;
+ * 5 / 6 the wave-per-token kernel of 64-wide rows, one shot / persistent; 5 also forces the wave-per-token kernel of the
+ * left-factor-only case.  A flavour that the factors have no kernel for leaves the choice to the library; so do all of them for factors that go to the
+ * kernel with row tiles of 16, which has one), FLATQUANT_WAVE_TPW (2 / 4 / 8 waves per workgroup of that kernel), FLATQUANT_PROBE_SHAPE (0..2: launch
  * shape of flatquant_stream_probe), FLATQUANT_WG_PER_CU, FLATQUANT_KV_WG_PER_CU (cap on resident
  * workgroups), FLATQUANT_FORCE_GENERIC (1: general
  * kernels on shapes the specialised INT4 kernels would take; 2 / 3: one and the other of the two

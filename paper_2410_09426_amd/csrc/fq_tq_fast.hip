@@ -629,7 +629,7 @@ struct Variant {
     int lds;
 };
 
-// mode 0: one slab per wave; mode 1: two slabs per wave; mode 2: one slab per wave, software-pipelined over tokens;
+// mode 0: one slab per wave; mode 1 (n2 = 64): two slabs per wave; mode 2: one slab per wave, software-pipelined over tokens;
 // mode 3: one slab per wave, one token per workgroup (only when every token can have a resident workgroup);
 // mode 4 (n2 = 64): one wave per token, kTokensPerWg tokens per workgroup sharing the staged transforms, no loop
 constexpr int kTokensPerWg = 4;
@@ -645,10 +645,8 @@ static Variant slab_of(bool full1) { return full1 ? slab<A, B, SPW, true, KIND, 
 
 template <int A, int B>
 static Variant variant_ab(bool full1, int mode) {
-    if constexpr (A <= 2 && (B == 2 || B == 4 || B == 8)) {
-        if (mode == 1) return slab_of<A, B, 2, 0>(full1);
-    }
     if constexpr (A <= 2 && B == 2) {
+        if (mode == 1) return slab_of<A, B, 2, 0>(full1);
         if (mode == 4) return slab_of<A, B, 2, 2, kTokensPerWg>(full1);
     }
     if constexpr (A <= 2) {
@@ -860,7 +858,7 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
         else if (B == 2 && d.T < 32768) mode = 4;
     }
     const int mode_env = tuned(Knob::MODE, -1);
-    if (mode_env == 0 || (mode_env == 1 && A <= 2 && (B == 2 || B == 4 || B == 8)) || (mode_env == 2 && A <= 2) || (mode_env == 3 && A <= 2) ||
+    if (mode_env == 0 || (mode_env == 1 && A <= 2 && B == 2) || (mode_env == 2 && A <= 2) || (mode_env == 3 && A <= 2) ||
         (mode_env == 4 && A <= 2 && B == 2)) mode = mode_env;
     const int spw = (mode == 1) ? 2 : 1;
     const Variant v = variant(A, B, full1, mode);

@@ -1498,3 +1498,24 @@ def test_four_row_tiles_with_one_and_two_workgroups_per_cu(n1, n2, T):
     check_case(c, rows=rows, with_dequant=False, label=f"four row tiles {n1}x{n2}")
     if n1 * n2 % 128 == 0:
         run_mx(c, rows=rows)
+
+
+@pytest.mark.parametrize("mode", ["0", "1", "2", "3", "4"])
+@pytest.mark.parametrize("n1,n2", [(5, 64), (32, 64), (49, 64), (17, 128), (31, 256), (64, 256), (56, 160), (128, 96)])
+def test_every_slab_kernel_flavour(tuning, mode, n1, n2):
+    """On factors that the slab kernel takes; a flavour that they do not have leaves the choice to the library."""
+    tuning("FLATQUANT_MODE", mode)
+    for T in (3, 600):
+        print(f"[case] slab kernel {n1}x{n2} mode={mode} T={T}", flush=True)
+        c = synth.generic(4000 + n1 + n2 + T + int(mode), T, n1, n2, clip_mode=1)
+        check_case(c, rows=None if T == 3 else subset_rows(T, 50, n1), with_dequant=False, label=f"slab kernel {n1}x{n2} mode {mode}")
+
+
+@pytest.mark.parametrize("mode", ["0", "3"])
+@pytest.mark.parametrize("n1,n2", [(64, 64), (32, 64), (32, 128), (20, 128), (64, 160), (128, 128)])
+def test_every_slab_kernel_flavour_mxfp4(tuning, mode, n1, n2):
+    tuning("FLATQUANT_MODE", mode)
+    for T in (3, 600):
+        print(f"[case] MXFP4 slab kernel {n1}x{n2} mode={mode} T={T}", flush=True)
+        c = synth.generic(4500 + n1 + n2 + T + int(mode), T, n1, n2, clip_mode=1)
+        run_mx(c, rows=None if T == 3 else subset_rows(T, 50, n1))
