@@ -1519,3 +1519,76 @@ def test_every_slab_kernel_flavour_mxfp4(tuning, mode, n1, n2):
         print(f"[case] MXFP4 slab kernel {n1}x{n2} mode={mode} T={T}", flush=True)
         c = synth.generic(4500 + n1 + n2 + T + int(mode), T, n1, n2, clip_mode=1)
         run_mx(c, rows=None if T == 3 else subset_rows(T, 50, n1))
+
+
+@pytest.mark.parametrize("kind", ["int4", "mxfp4"])
+@pytest.mark.parametrize("n1,n2", [(34, 64), (50, 128), (70, 96), (82, 128), (98, 256), (115, 160), (126, 192)])
+def test_row_tiles_of_16_read_nothing_past_any_row(tuning, kind, n1, n2):
+    """Every workgroup walks several tokens, whose rows go straight into LDS: what lies behind each of them, and behind P1, is NaN."""
+    if n1 * n2 % 128 and kind == "mxfp4":
+        pytest.skip("no MXFP4 rows of this length")
+    T = 1027
+    tuning("FLATQUANT_WG_PER_CU", 1)
+    print(f"[case] nothing past any row {kind} {n1}x{n2}", flush=True)
+    c = synth.generic(5000 + n1 + n2, T, n1, n2, clip_mode=1)
+    n, stride = n1 * n2, n1 * n2 + 16 * n2
+    x = torch.full((T, stride), float("nan"), dtype=torch.float16, device="cuda")
+    x[:, :n] = dev(c.x)
+    P1 = torch.full((n1 * n1 + 16 * 128,), float("nan"), dtype=torch.float16, device="cuda")
+    P1[:n1 * n1] = dev(c.P1).reshape(-1)
+    P2, clip = dev(c.P2), dev(c.clip)
+    got = []
+    for xs, p1, pitch in ((x, P1, stride), (dev(c.x), dev(c.P1), n)):
+        codes = torch.full((T, n // 2), 0xCD, dtype=torch.uint8, device="cuda")
+        scales = torch.full((T, 2 if kind == "int4" else n // 32), 0xCD, dtype=torch.uint8, device="cuda")
+        entry = fq.flatquant_transform_quant if kind == "int4" else fq.flatquant_transform_mxfp4
+        entry(xs, p1, P2, clip, 1, T, n1, n2, pitch, codes, scales, stream=torch.cuda.current_stream())
+        got.append((codes, scales))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    if kind == "int4":
+        check_case(c, rows=subset_rows(T, 40, n1, must=(0, 256, 512, T - 1)), with_dequant=False, label=f"several tokens {n1}x{n2}")
+    else:
+        run_mx(c, rows=subset_rows(T, 40, n1, must=(0, 256, 512, T - 1)))
+
+
+@pytest.mark.parametrize("n1,n2", [(48, 64), (64, 128), (80, 96), (96, 256), (112, 256), (128, 160), (50, 128)])
+def test_row_tiles_of_16_with_a_left_factor_on_dwords(n1, n2):
+    """P1 four bytes past a multiple of sixteen: whole row tiles are staged by pairs then, to the same bytes."""
+    print(f"[case] P1 on dwords {n1}x{n2}", flush=True)
+    c = synth.generic(5200 + n1 + n2, 300, n1, n2)
+    P1 = torch.full((n1 * n1 + 10,), float("nan"), dtype=torch.float16, device="cuda")
+    P1[2:2 + n1 * n1] = dev(c.P1).reshape(-1)
+    want = run_tq(dev(c.x), dev(c.P1), dev(c.P2), dev(c.clip), c.clip_mode, n1, n2)
+    got = run_tq(dev(c.x), P1[2:], dev(c.P2), dev(c.clip), c.clip_mode, n1, n2)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1].view(np.uint16), want[1].view(np.uint16))
+
+
+@pytest.mark.parametrize("tiled", [False, True])
+@pytest.mark.parametrize("n1", [50, 56, 60])
+def test_mxfp4_of_64_wide_rows_on_both_sides_of_the_kernel_change(n1, tiled):
+    """MXFP4 with 49 .. 63 x 64 changes kernels past 8192 tokens: both match the oracle, and a token's codes and exponents do not depend on it."""
+    T = 8192
+    print(f"[case] MXFP4 kernel change {n1}x64 tiled={tiled}", flush=True)
+    if tiled and n1 * 64 % 256:
+        pytest.skip("the tile order needs whole groups of 256 channels")
+    c = synth.generic(5400 + n1, T + 200, n1, 64, clip_mode=1)
+    n = n1 * 64
+    x, P1, P2, clip = dev(c.x), dev(c.P1), dev(c.P2), dev(c.clip)
+    if not tiled:
+        run_mx(c, rows=subset_rows(c.T, 60, n1, must=(0, T - 1, T, c.T - 1)))
+    got = []
+    for tokens in (T, c.T):
+        codes = torch.full((tokens, n // 2), 0xCD, dtype=torch.uint8, device="cuda")
+        exps = torch.full((fq.fq_mxfp4_tiled_scale_bytes(tokens, n) if tiled else tokens * n // 32,), 0xCD, dtype=torch.uint8, device="cuda")
+        entry = fq.flatquant_transform_mxfp4_tiled if tiled else fq.flatquant_transform_mxfp4
+        entry(x[:tokens], P1, P2, clip, 1, tokens, n1, 64, n, codes, exps, stream=torch.cuda.current_stream())
+        got.append((codes[:T], exps[:T * n // 32]))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("form,T,m,n", [(1, 300, 260, 768), (1, 513, 129, 256), (2, 300, 260, 768), (4, 513, 129, 256)])
+def test_w4a4_gemm_forms_on_small_launches(tuning, form, T, m, n):
+    """Tile forms that the few-token kernel would otherwise take the launch from."""
+    tuning("FLATQUANT_GEMM_TILED", 1)
+    tuning("FLATQUANT_GEMM_WIDE", form)
+    _w4a4_case(T, m, n, 0)
