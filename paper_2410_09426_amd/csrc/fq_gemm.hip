@@ -612,16 +612,16 @@ __global__ __launch_bounds__(ring_max_waves(NTD, ROWS) * 64) void w4a4_skinny_ke
     // are out of the tokens' range).
     constexpr int NE = NTT * NG * 64;
     constexpr int NK = (NE + 255) / 256;
-    unsigned esx[NK], esw[NK][4];                        // raw fp16 bits, converted in the epilogue: nothing waits for them here
+    _Float16 esx[NK], esw[NK][4];                        // converted in the epilogue: nothing waits for them here
     const __amdgpu_buffer_rsrc_t sxbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(xs) + t0, 0, 2 * (T - t0 < 32 * NTT ? T - t0 : 32 * NTT), 0x00020000);
     const __amdgpu_buffer_rsrc_t swbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(ws) + o0, 0, 2 * mrows, 0x00020000);
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
         const int e = tid + (k << (6 + cfg.log2_waves()));
         const int el = e & 63, g = (e >> 6) % NG, i = (e >> 6) / NG;
-        esx[k] = __builtin_amdgcn_raw_buffer_load_b16(sxbuf, 2 * (32 * i + (el & 31)), 0, 0);
+        esx[k] = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(sxbuf, 2 * (32 * i + (el & 31)), 0, 0));
 #pragma unroll
-        for (int x = 0; x < 4; ++x) esw[k][x] = __builtin_amdgcn_raw_buffer_load_b16(swbuf, 2 * (8 * g + 4 * (el >> 5) + x), 0, 0);
+        for (int x = 0; x < 4; ++x) esw[k][x] = __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(swbuf, 2 * (8 * g + 4 * (el >> 5) + x), 0, 0));
     }
     i32x16 acc[NTT][NCT];
 #pragma unroll
@@ -699,12 +699,12 @@ __global__ __launch_bounds__(ring_max_waves(NTD, ROWS) * 64) void w4a4_skinny_ke
         if (t < T && o < m) {
             // (the empty statement pins the conversions here: hoisted to the loads, they would stall the kernel's start)
             asm volatile("" : "+v"(esx[k]), "+v"(esw[k][0]), "+v"(esw[k][1]), "+v"(esw[k][2]), "+v"(esw[k][3]));
-            const float sx = (float)__builtin_bit_cast(_Float16, (uint16_t)esx[k]);
+            const float sx = (float)esx[k];
             _Float16 v[4];
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
-                float y = (float)(sum[x] >> 8) * sx * (float)__builtin_bit_cast(_Float16, (uint16_t)esw[k][x]);
-                asm("" : "+v"(y));           // rounded to fp32 as it stands, as in the tiled kernel: the same bits whichever of the two runs
+                float y = __builtin_fmaf((float)(sum[x] >> 8) * sx, (float)esw[k][x], 0.0f);
+                asm("" : "+v"(y));           // rounded to fp32 as it stands, as in the tiled kernel: the same bits whichever of the two runs (the fma takes the step as fp16)
                 v[x] = (_Float16)y;
             }
             _Float16* dst = out + t * out_stride + o;

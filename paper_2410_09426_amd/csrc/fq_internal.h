@@ -221,7 +221,7 @@ struct RingTile {
 };
 __device__ __forceinline__ RingTile ring_tile(int b, int groups, RingConfig cfg, bool more_tokens) {
     const int token_tiles = cfg.token_tiles();
-    if (token_tiles == 1) return RingTile{b, 0};
+    if (__builtin_expect(token_tiles == 1, true)) return RingTile{b, 0};   // decode: the rest is out of its way
     const int all = groups * token_tiles, per_xcd = (all + 7) >> 3, q = cfg.channels_first() ? b : (b & 7) * per_xcd + (b >> 3);
     if (q >= all) return RingTile{-1, 0};
     more_tokens |= cfg.channels_first();
