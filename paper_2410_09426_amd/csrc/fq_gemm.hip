@@ -805,8 +805,8 @@ bool ring_launch(const RingShape& s, int64_t T, int m, int n, int slot, int load
     // there while the tokens pass.  us contiguous / channels first, tokens x channels x n, 4 waves: INT4 2048 x 1024 x 12288 (64 x 32) 52.8 / 35.2;
     // 256 x 5120 x 1792 (32 x 32) 8.6 / 7.4; MXFP4 241 x 4096 x 5120 (32 x 64) 12.2 / 10.9; 1300 forms of 900 such launches 0.975 on average.  Otherwise the
     // weights would come again for every token tile: 254 x 13824 x 11008 (32 x 64) 1.5 times as long.  Not groups of 16, of which INT4 takes 2 % longer.
-    const bool channels_first = groups * tiles > cu_count() && tiles > 1 && groups % 8 == 0 && s.rows > 16 && T / 2 <= m &&
-                                ((int64_t)m * n <= 8LL * 2 * (4 << 20) || 8 * T > m);
+    const bool channels_first = tiles > 1 && groups % 8 == 0 && s.rows > 16 && T / 2 <= m && ((int64_t)m * n <= 8LL * 2 * (4 << 20) || 8 * T > m) &&
+                                groups * tiles > cu_count();
     r.cfg = RingConfig(depth, nwv, channels_first, (int)tiles);
     r.lds = nwv * depth * slot;                                           // the partial sums (128 bytes per channel and 32 tokens, per wave) reuse the rings
     return true;

@@ -71,14 +71,16 @@ inline unsigned token_loop_grid(int64_t T, int64_t cu, int occ, bool one) {
     return (unsigned)((T + rounds - 1) / rounds);
 }
 inline bool slab_loop_alone(int64_t T, int64_t cu, int A, int B, bool full) {
+    if (A != 4 || (B != 3 && B != 4)) return false;
     const int64_t r1 = (T + cu - 1) / cu, r2 = (r1 + 1) / 2;
     // (four slabs, two tokens for nearly every CU: as fast or slower alone, 128 x 128 at 512 tokens 11.0 / 11.9 on one machine and 15.8 / 13.1 on another)
     if (B == 4 && r1 == 2 && 4 * T > 7 * cu) return false;
-    return A == 4 && (B == 3 || B == 4) && 5 * r1 <= 8 * r2 + (full && B == 4 ? 4 : 2);
+    return 5 * r1 <= 8 * r2 + (full && B == 4 ? 4 : 2);
 }
 inline bool any_loop_alone(int64_t T, int64_t cu, int A, int B) {
+    if (A != 4 || (B != 3 && B != 4)) return false;
     const int64_t r1 = (T + cu - 1) / cu, r2 = (r1 + 1) / 2;
-    return A == 4 && (B == 3 || B == 4) && 3 * r1 <= 4 * r2 + 2;
+    return 3 * r1 <= 4 * r2 + 2;
 }
 // Whether a left factor of n1 rows and a right factor of 32 B columns go to tq_rows_kernel rather than to tq_fast_kernel; both give the same
 // bytes.  tq_fast_kernel / tq_rows_kernel in us, tokens in parentheses: row tiles that are not full gain most, by the 16 rows that are no longer

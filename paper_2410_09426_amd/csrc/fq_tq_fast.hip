@@ -750,7 +750,10 @@ hipError_t tq_mx_launch(const TqDev& d, hipStream_t stream) {
     }
     const Variant v = variant_mx(A, B, full1, one);
     int64_t grid = d.T;
-    if (!one) grid = token_loop_grid(d.T, cu_count(), occ, slab_loop_alone(d.T, cu_count(), A, B, full1));
+    if (!one) {
+        const int64_t cu = cu_count();
+        grid = token_loop_grid(d.T, cu, occ, slab_loop_alone(d.T, cu, A, B, full1));
+    }
     return launch(v.fn, dim3((unsigned)grid), dim3(64 * B), v.lds, stream, d, d.clip);
 }
 
@@ -870,10 +873,13 @@ hipError_t tq_fast_launch(const TqDev& d, hipStream_t stream) {
     }
     const int cap = tuned(Knob::WG_PER_CU, 0);
     if (cap > 0 && cap < occ) occ = cap;
-    int64_t grid = token_loop_grid(d.T, cu_count(), occ, slab_loop_alone(d.T, cu_count(), A, B, full1));
+    int64_t grid = 0;
     if (mode >= 3) {
         if (d.T > 0x7fffffff) return hipErrorInvalidConfiguration;   // only reachable through the tuning overrides
         grid = mode == 4 ? (d.T + kTokensPerWg - 1) / kTokensPerWg : d.T;
+    } else {
+        const int64_t cu = cu_count();
+        grid = token_loop_grid(d.T, cu, occ, slab_loop_alone(d.T, cu, A, B, full1));
     }
     return launch(v.fn, dim3((unsigned)grid), dim3(nt), v.lds, stream, d, d.clip);
 }

@@ -847,7 +847,8 @@ static hipError_t any_launch(const TqDev& d, hipStream_t stream, bool mx) {
     }
     const int cap = tuned(Knob::WG_PER_CU, 0);
     if (cap > 0 && cap < occ) occ = cap;
-    return launch(v.fn, dim3(token_loop_grid(d.T, cu_count(), occ, any_loop_alone(d.T, cu_count(), A, B))), dim3(64 * B), v.lds, stream, d);
+    const int64_t cu = cu_count();
+    return launch(v.fn, dim3(token_loop_grid(d.T, cu, occ, any_loop_alone(d.T, cu, A, B))), dim3(64 * B), v.lds, stream, d);
 }
 
 // MXFP4 instances of tq_kernel: where any_is_faster() can say no, and four row tiles x five slabs, whose longest rows (n > 19555) tq_any_kernel's
