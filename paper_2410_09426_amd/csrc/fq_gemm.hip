@@ -13,8 +13,8 @@
 //    and the total at most 225 n / 64, which fits 24 bits.  The offset leaves in the epilogue, with the row sums of the codes (one
 //    v_dot8 per dword) taken on the way.
 // The weights are the MFMA's first operand, so that a lane ends up with runs of 4 consecutive output channels of one token.
-// Many tokens take the tiled kernel; launches whose 128 x 128 tiles would reach at most half of the CUs (decode, short prefill
-// chunks) take the few-token kernel further down.
+// Many tokens take the tiled kernel, up to 64 (decode) the few-token kernel further down, and in between the one that w4a4_launch estimates to
+// be faster (short prefill chunks, few output channels).
 #include <cmath>
 #include <type_traits>
 

@@ -589,9 +589,11 @@ hipError_t mxfp4_gemm_launch(const MxGemmArgs& a, hipStream_t stream) {
     if (tuned(Knob::GEMM_TILED, 0) == 0 && d.n <= kOff32MaxN) {
         // decode and short prefill chunks: one pass over the weights, K split inside a workgroup (the ring kernel)
         if (a.T <= 64) return mx_skinny_launch(d, stream);
-        // More tokens: the ring kernel on tiles of 64 tokens, as long as the 128 x 128 tiles of the kernel below would
-        // reach at most half of the CUs (measured cross-over on 1024 .. 11008 channels; FLATQUANT_GEMM_RING_MAX_T
-        // replaces the rule by a token count).
+        // More tokens: the ring kernel on tiles of 32 or 64 tokens, as long as the 128 x 128 tiles of the kernel below would
+        // reach at most half of the CUs (FLATQUANT_GEMM_RING_MAX_T replaces the rule by a token count).  Tiled / ring, us, weights from
+        // memory, the number of those tiles in front: 32 128 x 4096 x 4096 13.5 / 6.8, 32 512 x 1024 x 4096 10.8 / 5.9, 64 256 x 4096 x 11008
+        // 29.9 / 16.5, 64 1024 x 1024 x 4096 10.9 / 8.0, 80 640 x 2048 x 8192 21.1 / 17.7, 112 128 x 14336 x 4096 14.5 / 15.1, 128 512 x 4096 x 4096 13.1 / 12.6,
+        // 128 256 x 8192 x 8192 23.3 / 23.0, 128 2048 x 1024 x 4096 11.3 / 12.9, 172 256 x 11008 x 4096 13.8 / 19.2, 192 768 x 4096 x 4096 13.1 / 17.9.
         const int64_t tiled_wgs = ((a.T + XT - 1) / XT) * ((a.m + XT - 1) / XT);
         const int ring_max = tuned(Knob::GEMM_RING_MAX_T, -1);
         if (ring_max >= 0 ? a.T <= ring_max : (2 * tiled_wgs <= cu_count() && a.T <= 4096))

@@ -10,10 +10,12 @@
 //   * P1 and P2 are fetched with coalesced 16-byte loads into LDS once per
 //     workgroup and the strided MFMA fragments are gathered from LDS, not HBM/L2.
 //   * The loop body has no shape conditionals, the wave reduction uses DPP, and
-//     rounding + nibble extraction is one fused multiply-add against 1.5 * 2^23.
-//   * A wave may own SPW adjacent slabs (template parameter).  With SPW = n2/32 a
-//     token belongs to a single wave: no workgroup barrier partner to wait for,
-//     and the token tile is read from LDS once instead of once per slab.
+//     rounding + nibble extraction is one fused multiply-add and a packed conversion.
+//   * For 64-wide rows a wave may own both slabs (SPW = 2): the token belongs to a single
+//     wave, so that no wave waits for another one, and its tile is read from LDS once.
+// The kernels here get what rows_kernel_takes() and the wave-per-token kernel leave: left factors of up to 31 rows, n2 = 32, few
+// tokens of 32 x 64, 64 x 64 and 33 .. 63 (odd) x 64, 49 .. 64 x 160, 64 x 256, 113 .. 128 rows with up to four slabs or with
+// eight; of MXFP4 also 32 rows with an even number of slabs and many tokens of 49 .. 63 x 64.
 #include <algorithm>
 #include <type_traits>
 
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(64 * (B / SPW) * TPW) __attribute__((amdgpu_waves_p
                 copy_batched(std::integral_constant<int, 8>{}, reinterpret_cast<const uint32_t*>(p.P1), n1sq >> 1, [&](int idx, uint32_t v) { reinterpret_cast<uint32_t*>(P1flat)[idx] = v; });
             }
         } else if constexpr (A >= 4) {
-            // Four row tiles (97 .. 127 rows): a wave takes whole rows, a lane the same pair of columns of each, so that a row costs a load, a
+            // Four row tiles that are not full (here 113 .. 127 rows, and 97 .. 112 with one slab): a wave takes whole rows, a lane the same pair of columns of each, so that a row costs a load, a
             // store and hardly any arithmetic (64 tokens, against the copy below, on factors that tq_rows_kernel has taken since: 112 x 128 9.1 -> 8.1 us, 112 x 256 13.3 -> 12.6; with
             // shorter rows, most of whose lanes have nothing to load, that one is as fast or faster: 86 x 128 6.3 / 6.2, 48 x 64
             // 4.4 / 5.1).  The LDS rows have the pitch of whole row tiles, the padding is zero.  Odd rows start on odd
